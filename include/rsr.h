@@ -211,8 +211,8 @@ typedef struct rsr_info_t {
   int32_t last_block_width; /* cols - (nblocks-1)*k, in 1..k */
   int32_t lo_bits, hi_bits; /* how the k value bits are split for the two-level fold */
   int64_t stored_rows;      /* row indices stored over all blocks and parts (value-0 rows left out) */
-  int64_t segments;         /* stored groups of equal rows (long groups are cut into several) */
-  int64_t work_units;       /* scheduling units (part of the segments of 512 consecutive row values) */
+  int64_t segments;         /* stored groups of equal rows */
+  int64_t work_units;       /* scheduling units (a few thousand rows of one block each) */
   int64_t index_bytes;      /* row indices of the packed permutation, padding included */
   int64_t segment_bytes;    /* value ids of the segments, padding included */
   int64_t schedule_bytes;   /* unit descriptors and per-block unit ranges */

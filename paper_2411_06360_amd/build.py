@@ -13,12 +13,12 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librsr.so")
-SOURCES = ["rsr_lib.hip", "rsr_dense.hip", "rsr_prep.hip", "rsr_pack.cpp", "rsr_qbit.cpp"]
+SOURCES = ["rsr_lib.hip", "rsr_dense.hip", "rsr_prep.hip", "rsr_pack.cpp", "rsr_export.cpp", "rsr_qbit.cpp"]
 ARCH = "gfx950"
 
 # -packed-fp32-ops off: the compiler must not form packed fp32 instructions from the float adds.
 FLAGS = [
-    "-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-shared", "-fno-strict-aliasing",
+    "-O3", "-std=c++20", f"--offload-arch={ARCH}", "-fPIC", "-shared", "-fno-strict-aliasing",
     "-fno-gpu-rdc", "-Wall", "-Wno-unused-command-line-argument",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]

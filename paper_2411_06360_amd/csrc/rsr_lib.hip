@@ -1,32 +1,26 @@
 // C ABI (include/rsr.h) and the gfx950 kernels of the RSR++ vector x binary/ternary-matrix product.
 //
-// Kernel structure (one launch per product):
-//   * A workgroup stages one activation vector in LDS (plus a zero behind it for the null row
-//     index) and owns a contiguous range of column blocks, i.e. a contiguous byte range of the
-//     index streams.  Column blocks are independent (the paper's parallelisation I, Appendix C.1).
-//   * Its wavefronts take work units (one window of 2^kw row values of one block and part, see
-//     rsr_format.h) from an LDS counter.  For a unit a wavefront
-//       1. reads the unit's stream with 16-byte buffer loads (the next unit's loads go out while
-//          the current one is summed) and walks its positions: every lane owns a run of
-//          consecutive sorted rows and gathers v[sigma(p)] from LDS into its running sum - the
-//          segmented sums of Eq. SS2 - and where a row's flag says that a new value starts it
-//          first drops the sum into the current slot of its private window of u in LDS and moves
-//          to the next slot (plain stores: a slot is stored by the lane in which its segment
-//          ends; the part of a segment that a lane is left with at the end of its run is added
-//          to the slot afterwards);
-//       2. reads the window back in value order;
-//       3. takes the low kw levels of the RSR++ fold (Section 4.3, Algorithm 3): "sum the
-//          odd-indexed entries, then add neighbours" - three levels inside a lane's 8 consecutive
-//          values, the next six across the 64 lanes - and leaves kw sums plus the window total
-//          in a per-unit record.
-//   * The wavefront that completes the last unit of a block adds the records up: low bits sum
-//     over windows, the k-kw high levels of the fold see only window totals; the two parts of a
-//     ternary matrix are reduced separately and subtracted once (Proposition 2.1); k outputs are
-//     stored.
+// Kernel structure (one launch per product; rsr_layout.h describes the index it reads):
+//   * A workgroup stages the activations of one, two or four vectors in LDS (with a zero behind them for the null row
+//     index) and owns a contiguous range of column blocks, i.e. a contiguous byte range of the index streams.
+//     Column blocks are independent (the paper's parallelisation I, Appendix C.1).
+//   * Its wavefronts take units (whole groups of 64 segments, one segment per lane) from an LDS counter.  For a unit a
+//     wavefront
+//       1. reads the unit's stream with 16-byte buffer loads (the next unit's loads go out while the current one is
+//          summed) and walks its positions: every lane gathers the activations of its segment's rows from LDS into
+//          running sums - the segmented sums of Eq. SS2 - and at a group's end, the same position for all lanes,
+//          stores them to the slot of its segment's value in the panel's part of LDS (u of Algorithm 2);
+//       2. counts itself off.  The wavefront that completes a panel reads its sums back in value order and takes the
+//          RSR++ fold (Section 4.3, Algorithm 3), "sum the odd-indexed entries, then add neighbours": the upper value
+//          bits inside a lane, the lower six across the 64 lanes.
+//   * A block whose values are one panel (both parts of a ternary matrix are subtracted slot by slot, Proposition 2.1)
+//     is then stored; otherwise the panels leave records, and the wavefront that completes the block's last panel adds
+//     them up: bits inside a panel sum over panels, bits above it see only panel totals.
 // All float additions happen in a fixed order (no floating-point atomics), so results are
 // reproducible from run to run.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -39,6 +33,7 @@
 #include "../../include/rsr.h"
 #include "rsr_format.h"
 #include "rsr_internal.h"
+#include "rsr_layout.h"
 #include "rsr_pack.h"
 
 namespace {
@@ -75,12 +70,17 @@ constexpr uint64_t kMagic = 0x5253522b2b763031ull;  // "RSR++v01"
 // One row tile of the index on the device (a matrix of up to rsr::kTileRows rows has one).
 struct DeviceTile {
   int64_t rows = 0, row0 = 0;
+  rsr::Shape shape{};
+  int extra_stride = 0, max_extras = 0;  // entries per panel in d_extras; extra slots of a panel at most
+  bool fill = false;  // absent values are stored as zeros: a panel's slots need no clearing
   uint32_t max_units_per_block = 0;
   int64_t nunits = 0;
-  size_t stream_bytes = 0, unit_bytes = 0, blk_bytes = 0;
+  size_t stream_bytes = 0, unit_bytes = 0, blk_bytes = 0, extra_bytes = 0;
+  void* d_tables = nullptr;  // the allocation that holds them all
   void* d_stream = nullptr;
   void* d_units = nullptr;
   void* d_blk_unit = nullptr;
+  void* d_extras = nullptr;  // slots of the pieces of segments that were cut (null if there are none)
 };
 
 struct rsr_handle {
@@ -89,14 +89,16 @@ struct rsr_handle {
   size_t lds_max = 0;
   // shape
   int64_t rows = 0, cols = 0, nblocks = 0;
-  int k = 0, kw = 0, parts = 0, last_width = 0;
+  int k = 0, parts = 0, last_width = 0;
+  bool qbit = false;      // the parts are bit planes: part i weighs 2^(first_plane + i), negative_part its negative
+  int first_plane = 0, negative_part = -1;
   int64_t stored_rows = 0, segments = 0, nunits = 0;
-  int64_t flag_bytes = 0, stream_bytes = 0, schedule_bytes = 0;
+  int64_t head_bytes = 0, stream_bytes = 0, schedule_bytes = 0;
   std::vector<DeviceTile> tiles;
   int waves = 16;  // wavefronts per workgroup at most
   bool step2_plain = false;  // rsr_set_step2
   // host copy of the device tables, fetched on the first rsr_export_block
-  std::unique_ptr<rsr::Index> downloaded;
+  std::vector<rsr_internal::TileTables> downloaded;
 };
 
 struct rsr_host_index {
@@ -133,19 +135,41 @@ bool valid(const rsr_handle* h) { return h && h->magic == kMagic; }
 // device code
 // ---------------------------------------------------------------------------------------------
 struct KArgs {
-  int rows, cols, k, kw, parts, nblocks, last_width, batch;
+  int rows, cols, k, nblocks, last_width, batch;
   int vstride;   // elements between the activation vectors of consecutive batch lanes (the matrix's row count)
   int row0;      // first row of this row tile
   int accumulate;  // add to `out` instead of overwriting it (second and later row tiles, rsr_matvec_acc)
   int scaled;      // multiply the product by `scale` first (rsr_matvec_acc)
   uint32_t scale;  // bits of a float (float activations) or of an int (int8 activations)
-  int g1;        // workgroups per batch lane
-  int waves;     // wavefronts that take units (the LDS layout has a window for each)
-  int ucap;      // unit records per round
-  int nslot;     // block completion counters per round
+  int kc, both, pslots, panels;  // panels of a block (rsr_layout.h)
+  int fill, extra_stride;        // absent values are stored as zeros; entries per panel in the list of extra slots
+  // a part's weight: 1 << (part * wshift + wfirst), negative for part `wneg` (-1: none)
+  int wshift, wfirst, wneg;
+  int g1;        // workgroups per set of vectors
+  int waves;     // wavefronts that take units
   int nunits;    // unit descriptors in the index
-  uint32_t off_win, off_rec, off_done, off_ctr, off_bu;  // LDS byte offsets
+  int nbuf;      // panels in flight per workgroup
+  int nrec;      // blocks whose panel records are kept (panels > 1)
+  uint32_t buf_magic, rec_magic;  // x / nbuf and x / nrec as high halves of products
+  uint32_t ubytes;  // bytes of a panel's sums in LDS
+  uint32_t off_u, off_rec, off_done, off_blocks, off_cnt, off_epoch, off_ctr, off_desc;  // LDS byte offsets
+  uint32_t ndesc;  // descriptors of a workgroup's units that are kept in LDS
 };
+
+// A kernel's own arguments, in the memory they were passed in.
+#ifdef __HIP_DEVICE_COMPILE__
+typedef const __attribute__((address_space(4))) KArgs* KArgsPtr;
+__device__ __forceinline__ KArgsPtr args_at(size_t offset) {
+  return (KArgsPtr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+}
+#else
+typedef const KArgs* KArgsPtr;
+__device__ KArgsPtr args_at(size_t);  // (the host pass only has to parse the kernels)
+#endif
+__device__ __forceinline__ KArgsPtr launder(KArgsPtr p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -158,60 +182,6 @@ template <int CTRL, int ROW_MASK, int BANK_MASK>
 __device__ __forceinline__ int dpp_get(int x) {
   return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, BANK_MASK, false);
 }
-// Inclusive prefix sum over the 64 lanes.  Lanes whose DPP source does not exist, or that the
-// masks exclude, receive 0.
-__device__ __forceinline__ int wave_inclusive_scan(int x) {
-  int y = x + dpp_get<0x111, 0xf, 0xf>(x);   // row_shr:1
-  y += dpp_get<0x112, 0xf, 0xf>(x);           // row_shr:2
-  y += dpp_get<0x113, 0xf, 0xf>(x);           // row_shr:3   -> y[i] = x[i-3..i]
-  y += dpp_get<0x114, 0xf, 0xe>(y);           // row_shr:4, lanes 4..15 of each row
-  y += dpp_get<0x118, 0xf, 0xc>(y);           // row_shr:8, lanes 8..15 -> prefix sums inside each row of 16
-  y += dpp_get<0x142, 0xa, 0xf>(y);           // row_bcast:15 into rows 1 and 3
-  y += dpp_get<0x143, 0xc, 0xf>(y);           // row_bcast:31 into rows 2 and 3
-  return y;
-}
-
-// Sum over the 64 lanes, returned to every lane (through a scalar register).
-template <typename AT>
-__device__ __forceinline__ AT wave_total(AT x) {
-  AT y = x + dpp_get<0x111, 0xf, 0xf>(x);
-  y += dpp_get<0x112, 0xf, 0xf>(x);
-  y += dpp_get<0x113, 0xf, 0xf>(x);
-  y += dpp_get<0x114, 0xf, 0xe>(y);
-  y += dpp_get<0x118, 0xf, 0xc>(y);
-  y += dpp_get<0x142, 0xa, 0xf>(y);
-  y += dpp_get<0x143, 0xc, 0xf>(y);
-  return __builtin_bit_cast(AT, __builtin_amdgcn_readlane(__builtin_bit_cast(int, y), 63));
-}
-
-// Sums of eight values over the 16 lanes of each DPP row, all at once: after every exchange a
-// lane keeps half of its values and hands the other half to its partner, so the three halving
-// exchanges (lane xor 1, 2, 4) cost 4 + 2 + 1 additions instead of 8 each; a last exchange
-// (lane xor 8) completes the row.  On return every lane holds the row sum of v[lane & 7].
-template <typename AT>
-__device__ __forceinline__ AT row_sums_of_eight(const AT (&v)[8], int lane) {
-  const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
-  AT w[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const AT keep = b0 ? v[2 * i + 1] : v[2 * i];
-    const AT give = b0 ? v[2 * i] : v[2 * i + 1];
-    w[i] = keep + dpp_get<0xB1, 0xf, 0xf>(give);  // quad_perm [1,0,3,2]: lane xor 1
-  }
-  AT x2[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const AT keep = b1 ? w[2 * i + 1] : w[2 * i];
-    const AT give = b1 ? w[2 * i] : w[2 * i + 1];
-    x2[i] = keep + dpp_get<0x4E, 0xf, 0xf>(give);  // quad_perm [2,3,0,1]: lane xor 2
-  }
-  const AT keep = b2 ? x2[1] : x2[0];
-  const AT give = b2 ? x2[0] : x2[1];
-  // lane xor 4: lanes 0-3 and 8-11 of a row read 4 lanes up, lanes 4-7 and 12-15 read 4 lanes down
-  const AT y = keep + dpp_get<0x104, 0xf, 0x5>(give) + dpp_get<0x114, 0xf, 0xa>(give);
-  return y + dpp_get<0x128, 0xf, 0xf>(y);  // row_ror:8 is lane xor 8 inside a row
-}
-
 // Lane swaps of a value with itself, in assembly: the compiler takes the two results of the swap
 // builtins for equal when they are combined as floats.  (The s_nop covers the wait states a lane
 // swap needs after a vector write of its operands.)
@@ -242,523 +212,856 @@ __device__ __forceinline__ uint32_t lds_count_up(uint32_t lds_byte_addr) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)old);
 }
 
-template <typename VT> struct Acc;
-template <> struct Acc<float> { using type = float; };
-template <> struct Acc<int8_t> { using type = int32_t; };
-
-// ---- the stream positions of a unit, eight (one granule) or two (one dword) at a time ----
-// Per position and lane the stream holds a row index x (uint16) and a flag, the top bit of `f`
-// (f is shifted left by one per position).  A flagged entry starts a new value: the running sum
-// `a` of the segment that ends here goes to the current window slot (LDS byte address `sa`), the
-// lane moves to the next slot and the sum restarts; then, flagged or not, the activation with row
-// index x is added.  All eight gathers are issued before the first sum so that their latencies
-// overlap.  Written in assembly: a position costs one address extraction, one LDS read, one
-// add-with-carry that shifts the flags and puts the flag of every lane into vcc, three
-// instructions under that mask (store, next slot, restart) and one add; there are no branches.
-// (The wait before the add of position q allows 7 - q LDS operations to be outstanding: the
-// gathers behind it, whether or not the stores of masked-off lanes are counted.)
-//   float activations:  LDS byte address of row x = 4 * x (the vector sits at LDS offset 0)
-//   int8 activations:   LDS byte address of row x = x
-#define RSR_X4_LO(d, w) "v_lshlrev_b32_sdwa " d ", 2, " w " dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n"
-#define RSR_X4_HI(d, w) "v_lshlrev_b32_sdwa " d ", 2, " w " dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n"
-#define RSR_X1_LO(d, w) "v_and_b32 " d ", 0xffff, " w "\n"
-#define RSR_X1_HI(d, w) "v_lshrrev_b32 " d ", 16, " w "\n"
-#define RSR_POS(q, cnt, ADD)                                                                             \
-  "v_add_co_u32 %[f], vcc, %[f], %[f]\n s_mov_b64 exec, vcc\n ds_write_b32 %[sa], %[a]\n"              \
-  "v_add_u32 %[sa], 4, %[sa]\n v_mov_b32 %[a], 0\n s_mov_b64 exec, -1\n s_waitcnt lgkmcnt(" #cnt ")\n " \
-  ADD " %[a], %[a], %[t" #q "]\n"
-
-// In a granule the eight flags are shifted out first, each carry into a scalar register pair: the execution
-// masks are then ready when their positions come up, and no position waits for a vector result to reach
-// the scalar unit (0.4 us per product at 16384 x 16384).  The wait count of a position in a granule is 8:
-// behind the read it needs, the granule has issued 7 - q more reads and q + 1 stores, and LDS operations
-// complete in order.
-#define RSR_MASK(q) "v_add_co_u32_e64 %[f], %[m" #q "], %[f], %[f]\n"
-#define RSR_POSM(q, ADD)                                                                              \
-  "s_mov_b64 exec, %[m" #q "]\n ds_write_b32 %[sa], %[a]\n"                                          \
-  "v_add_u32 %[sa], 4, %[sa]\n v_mov_b32 %[a], 0\n s_mov_b64 exec, -1\n s_waitcnt lgkmcnt(8)\n "     \
-  ADD " %[a], %[a], %[t" #q "]\n"
-#define RSR_MASK_REGS                                                                                              \
-  [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3), [m4] "=&s"(m4), [m5] "=&s"(m5), [m6] "=&s"(m6), \
-      [m7] "=&s"(m7)
-
-__device__ __forceinline__ void granule_step(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, float& a, uint32_t& sa,
-                                             uint32_t& f, const float*) {
-  uint32_t s0, s1, s2, s3, s4, s5, s6, s7;
-  float t0, t1, t2, t3, t4, t5, t6, t7;
-  uint64_t m0, m1, m2, m3, m4, m5, m6, m7;
-  asm volatile(
-      RSR_X4_LO("%[s0]", "%[w0]") RSR_X4_HI("%[s1]", "%[w0]") RSR_X4_LO("%[s2]", "%[w1]") RSR_X4_HI("%[s3]", "%[w1]")
-      RSR_X4_LO("%[s4]", "%[w2]") RSR_X4_HI("%[s5]", "%[w2]") RSR_X4_LO("%[s6]", "%[w3]") RSR_X4_HI("%[s7]", "%[w3]")
-      "ds_read_b32 %[t0], %[s0]\n ds_read_b32 %[t1], %[s1]\n ds_read_b32 %[t2], %[s2]\n ds_read_b32 %[t3], %[s3]\n"
-      "ds_read_b32 %[t4], %[s4]\n ds_read_b32 %[t5], %[s5]\n ds_read_b32 %[t6], %[s6]\n ds_read_b32 %[t7], %[s7]\n"
-      RSR_MASK(0) RSR_MASK(1) RSR_MASK(2) RSR_MASK(3) RSR_MASK(4) RSR_MASK(5) RSR_MASK(6) RSR_MASK(7)
-      RSR_POSM(0, "v_add_f32") RSR_POSM(1, "v_add_f32") RSR_POSM(2, "v_add_f32") RSR_POSM(3, "v_add_f32")
-      RSR_POSM(4, "v_add_f32") RSR_POSM(5, "v_add_f32") RSR_POSM(6, "v_add_f32") RSR_POSM(7, "v_add_f32")
-      : [a] "+v"(a), [sa] "+v"(sa), [f] "+v"(f), [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3),
-        [s4] "=&v"(s4), [s5] "=&v"(s5), [s6] "=&v"(s6), [s7] "=&v"(s7), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),
-        [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7), RSR_MASK_REGS
-      : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3)
-      : "vcc", "memory");
+// LDS words of the workgroup's bookkeeping, in assembly: through generic pointers a volatile access becomes a flat
+// instruction, and the wait for one is a wait for everything the wavefront has under way in memory.
+__device__ __forceinline__ uint32_t lds_load(uint32_t lds_byte_addr) {
+  uint32_t x;
+  asm volatile("ds_read_b32 %0, %1\n s_waitcnt lgkmcnt(0)" : "=v"(x) : "v"(lds_byte_addr) : "memory");
+  return x;
 }
-__device__ __forceinline__ void pair_step(uint32_t w0, float& a, uint32_t& sa, uint32_t& f, const float*) {
-  uint32_t s0, s1;
-  float t0, t1;
-  asm volatile(
-      RSR_X4_LO("%[s0]", "%[w0]") RSR_X4_HI("%[s1]", "%[w0]")
-      "ds_read_b32 %[t0], %[s0]\n ds_read_b32 %[t1], %[s1]\n"
-      RSR_POS(0, 1, "v_add_f32") RSR_POS(1, 0, "v_add_f32")
-      : [a] "+v"(a), [sa] "+v"(sa), [f] "+v"(f), [s0] "=&v"(s0), [s1] "=&v"(s1), [t0] "=&v"(t0), [t1] "=&v"(t1)
-      : [w0] "v"(w0)
-      : "vcc", "memory");
+// counter += 1 on behalf of the wavefront, without its old value
+__device__ __forceinline__ void lds_bump(uint32_t lds_byte_addr) {
+  uint64_t saved;
+  asm volatile("s_mov_b64 %[sv], exec\n s_mov_b64 exec, 1\n ds_add_u32 %[ad], %[one]\n s_mov_b64 exec, %[sv]\n"
+               : [sv] "=&s"(saved) : [ad] "v"(lds_byte_addr), [one] "v"(1u) : "memory");
 }
-__device__ __forceinline__ void single_step(uint32_t w0, float& a, uint32_t& sa, uint32_t& f, const float*) {
-  uint32_t s0;
-  float t0;
-  asm volatile(RSR_X4_LO("%[s0]", "%[w0]") "ds_read_b32 %[t0], %[s0]\n" RSR_POS(0, 0, "v_add_f32")
-               : [a] "+v"(a), [sa] "+v"(sa), [f] "+v"(f), [s0] "=&v"(s0), [t0] "=&v"(t0)
-               : [w0] "v"(w0)
-               : "vcc", "memory");
-}
-__device__ __forceinline__ void granule_step(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, int32_t& a, uint32_t& sa,
-                                             uint32_t& f, const int8_t*) {
-  uint32_t s0, s1, s2, s3, s4, s5, s6, s7;
-  int32_t t0, t1, t2, t3, t4, t5, t6, t7;
-  uint64_t m0, m1, m2, m3, m4, m5, m6, m7;
-  asm volatile(
-      RSR_X1_LO("%[s0]", "%[w0]") RSR_X1_HI("%[s1]", "%[w0]") RSR_X1_LO("%[s2]", "%[w1]") RSR_X1_HI("%[s3]", "%[w1]")
-      RSR_X1_LO("%[s4]", "%[w2]") RSR_X1_HI("%[s5]", "%[w2]") RSR_X1_LO("%[s6]", "%[w3]") RSR_X1_HI("%[s7]", "%[w3]")
-      "ds_read_i8 %[t0], %[s0]\n ds_read_i8 %[t1], %[s1]\n ds_read_i8 %[t2], %[s2]\n ds_read_i8 %[t3], %[s3]\n"
-      "ds_read_i8 %[t4], %[s4]\n ds_read_i8 %[t5], %[s5]\n ds_read_i8 %[t6], %[s6]\n ds_read_i8 %[t7], %[s7]\n"
-      RSR_MASK(0) RSR_MASK(1) RSR_MASK(2) RSR_MASK(3) RSR_MASK(4) RSR_MASK(5) RSR_MASK(6) RSR_MASK(7)
-      RSR_POSM(0, "v_add_u32") RSR_POSM(1, "v_add_u32") RSR_POSM(2, "v_add_u32") RSR_POSM(3, "v_add_u32")
-      RSR_POSM(4, "v_add_u32") RSR_POSM(5, "v_add_u32") RSR_POSM(6, "v_add_u32") RSR_POSM(7, "v_add_u32")
-      : [a] "+v"(a), [sa] "+v"(sa), [f] "+v"(f), [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3),
-        [s4] "=&v"(s4), [s5] "=&v"(s5), [s6] "=&v"(s6), [s7] "=&v"(s7), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),
-        [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7), RSR_MASK_REGS
-      : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3)
-      : "vcc", "memory");
-}
-__device__ __forceinline__ void pair_step(uint32_t w0, int32_t& a, uint32_t& sa, uint32_t& f, const int8_t*) {
-  uint32_t s0, s1;
-  int32_t t0, t1;
-  asm volatile(
-      RSR_X1_LO("%[s0]", "%[w0]") RSR_X1_HI("%[s1]", "%[w0]")
-      "ds_read_i8 %[t0], %[s0]\n ds_read_i8 %[t1], %[s1]\n"
-      RSR_POS(0, 1, "v_add_u32") RSR_POS(1, 0, "v_add_u32")
-      : [a] "+v"(a), [sa] "+v"(sa), [f] "+v"(f), [s0] "=&v"(s0), [s1] "=&v"(s1), [t0] "=&v"(t0), [t1] "=&v"(t1)
-      : [w0] "v"(w0)
-      : "vcc", "memory");
+__device__ __forceinline__ void lds_clear(uint32_t lds_byte_addr) {
+  asm volatile("ds_write_b32 %0, %1" ::"v"(lds_byte_addr), "v"(0u) : "memory");
 }
 
+// Two counters at once: one wait behind the gathers of the other wavefronts instead of two.
+__device__ __forceinline__ void lds_count_up(uint32_t addr_a, uint32_t addr_b, uint32_t& a, uint32_t& b) {
+  uint32_t x, y;
+  uint64_t saved;
+  asm volatile(
+      "s_mov_b64 %[sv], exec\n s_mov_b64 exec, 1\n ds_add_rtn_u32 %[x], %[aa], %[one]\n ds_add_rtn_u32 %[y], %[ab], %[one]\n"
+      "s_mov_b64 exec, %[sv]\n s_waitcnt lgkmcnt(0)\n"
+      : [x] "=&v"(x), [y] "=&v"(y), [sv] "=&s"(saved)
+      : [aa] "v"(addr_a), [ab] "v"(addr_b), [one] "v"(1u)
+      : "memory");
+  a = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+  b = (uint32_t)__builtin_amdgcn_readfirstlane((int)y);
+}
+
+// ---- the positions of a unit, eight (one granule) or two (one dword) at a time ----
+// Per position and lane the stream holds a uint16: a row index, or where the unit's mask (bit q of `hm` for position
+// q of the step, the same for all lanes) says that a group ends, the lane's slot.  A row costs one address
+// extraction, one LDS read and one add per activation vector; a head stores the running sums to the panel's slot
+// (byte address `ub` + slot) and restarts them.  The choice is a scalar branch: no lane needs a mask of its own,
+// which takes three of five vector instructions and the store that every position would otherwise issue out of
+// the loop (a store holds the LDS for 4.4 clocks however few lanes take part; a gather for 2.4).  All gathers of a
+// step are issued before the first sum so that their latencies overlap.  At the heads of a unit whose segments take
+// 8 lanes (`wd` = 1) the lanes' sums are first added with lane exchanges, by a routine behind the step (its
+// s_nop cover the wait states an exchange needs after a vector write).
+// The wait before the add of position q allows as many LDS operations as gathers follow it: they complete in
+// order, and stores or scalar loads issued in between only make the wait stricter.  A step must not end before
+// its last gather has arrived (its register is free for the compiler then), also if the last position is a head.
+// What an activation mode M defines: vectors V per pass, LDS bytes per row (1 << shift) and per slot, and its sums.
+#define RSR_EXTRACT(sh, q, w, half)                                                                            \
+  "v_lshlrev_b32_sdwa %[s" #q "], " #sh ", %[w" #w "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:" half "\n"
+#define RSR_EXTRACT2(sh, q0, q1, w) RSR_EXTRACT(sh, q0, w, "WORD_0") RSR_EXTRACT(sh, q1, w, "WORD_1")
+#define RSR_EXTRACT8(sh) RSR_EXTRACT2(sh, 0, 1, 0) RSR_EXTRACT2(sh, 2, 3, 1) RSR_EXTRACT2(sh, 4, 5, 2) RSR_EXTRACT2(sh, 6, 7, 3)
+#define RSR_ROW(q, wait, SUM)                                                                                  \
+  "s_bitcmp1_b32 %[hm], " #q "\n s_cbranch_scc1 .Lrsr_head" #q "_%=\n s_waitcnt lgkmcnt(" #wait ")\n" SUM     \
+  ".Lrsr_next" #q "_%=:\n"
+#define RSR_HEAD(q, STORE)                                                                                     \
+  ".Lrsr_head" #q "_%=: s_cmp_lg_u32 %[wd], 0\n s_cbranch_scc1 .Lrsr_wide" #q "_%=\n"                          \
+  ".Lrsr_store" #q "_%=:\n" STORE "s_branch .Lrsr_next" #q "_%=\n"                                             \
+  ".Lrsr_wide" #q "_%=: s_call_b64 s[94:95], .Lrsr_lanes_%=\n s_branch .Lrsr_store" #q "_%=\n"
+#define RSR_LANES(ADDS)                                                                                        \
+  ".Lrsr_lanes_%=: s_nop 1\n" ADDS("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")                           \
+  "s_nop 1\n" ADDS("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")                                           \
+  "s_nop 1\n" ADDS("row_half_mirror row_mask:0xf bank_mask:0xf")                                               \
+  "s_setpc_b64 s[94:95]\n"
+#define RSR_S6 [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3), [s4] "=&v"(s4), [s5] "=&v"(s5)
+#define RSR_S8 [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3), [s4] "=&v"(s4), [s5] "=&v"(s5), [s6] "=&v"(s6), [s7] "=&v"(s7)
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }  // (into a scalar register)
+#define RSR_CTL [hm] "s"(uniform(hm)), [wd] "s"(uniform(wd)), [ub] "s"(uniform(ub))
+#define RSR_CLOBBER "scc", "s94", "s95", "memory"
+
+// One 32-bit word per row and slot (a float, or an int8 widened when it is staged).
+#define RSR_SUM1(q, ADD) ADD " %[a], %[a], %[t" #q "]\n"
+#define RSR_STORE1(q) "v_add_u32 %[s" #q "], %[ub], %[s" #q "]\n ds_write_b32 %[s" #q "], %[a]\n v_mov_b32 %[a], 0\n"
+#define RSR_LANES1_F(x) "v_add_f32_dpp %[a], %[a], %[a] " x "\n"
+#define RSR_LANES1_P(x) "v_mov_b32_dpp %[x], %[a] " x "\n v_pk_add_u16 %[a], %[a], %[x]\n"
+#define RSR_LANES1_I(x) "v_add_u32_dpp %[a], %[a], %[a] " x "\n"
+#define RSR_STEPS1(AT, ADD, LANES)                                                                             \
+  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, AT (&acc)[1], uint32_t hm, \
+                                               uint32_t wd, uint32_t ub) {                                     \
+    uint32_t s0, s1, s2, s3, s4, s5, s6, s7;                                                                   \
+    AT t0, t1, t2, t3, t4, t5, t6, t7, x;                                                                       \
+    asm volatile(                                                                                              \
+        RSR_EXTRACT8(2)                                                                                        \
+        "ds_read_b32 %[t0], %[s0]\n ds_read_b32 %[t1], %[s1]\n ds_read_b32 %[t2], %[s2]\n ds_read_b32 %[t3], %[s3]\n" \
+        "ds_read_b32 %[t4], %[s4]\n ds_read_b32 %[t5], %[s5]\n ds_read_b32 %[t6], %[s6]\n ds_read_b32 %[t7], %[s7]\n" \
+        RSR_ROW(0, 7, RSR_SUM1(0, ADD)) RSR_ROW(1, 6, RSR_SUM1(1, ADD)) RSR_ROW(2, 5, RSR_SUM1(2, ADD)) RSR_ROW(3, 4, RSR_SUM1(3, ADD)) \
+        RSR_ROW(4, 3, RSR_SUM1(4, ADD)) RSR_ROW(5, 2, RSR_SUM1(5, ADD)) RSR_ROW(6, 1, RSR_SUM1(6, ADD)) RSR_ROW(7, 0, RSR_SUM1(7, ADD)) \
+        "s_branch .Lrsr_end_%=\n"                                                                              \
+        RSR_HEAD(0, RSR_STORE1(0)) RSR_HEAD(1, RSR_STORE1(1)) RSR_HEAD(2, RSR_STORE1(2)) RSR_HEAD(3, RSR_STORE1(3)) \
+        RSR_HEAD(4, RSR_STORE1(4)) RSR_HEAD(5, RSR_STORE1(5)) RSR_HEAD(6, RSR_STORE1(6)) RSR_HEAD(7, RSR_STORE1(7) "s_waitcnt lgkmcnt(1)\n") \
+        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
+        : [a] "+v"(acc[0]), [x] "=&v"(x), RSR_S8, [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4), \
+          [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7)                                                       \
+        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), RSR_CTL                                      \
+        : RSR_CLOBBER);                                                                                        \
+  }                                                                                                            \
+  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, AT (&acc)[1], uint32_t hm, uint32_t wd, uint32_t ub) { \
+    uint32_t s0, s1, s2, s3, s4, s5;                                                                           \
+    AT t0, t1, t2, t3, t4, t5, x;                                                                               \
+    asm volatile(                                                                                              \
+        RSR_EXTRACT2(2, 0, 1, 0) RSR_EXTRACT2(2, 2, 3, 1) RSR_EXTRACT2(2, 4, 5, 2)                             \
+        "ds_read_b32 %[t0], %[s0]\n ds_read_b32 %[t1], %[s1]\n ds_read_b32 %[t2], %[s2]\n ds_read_b32 %[t3], %[s3]\n" \
+        "ds_read_b32 %[t4], %[s4]\n ds_read_b32 %[t5], %[s5]\n"                                                \
+        RSR_ROW(0, 5, RSR_SUM1(0, ADD)) RSR_ROW(1, 4, RSR_SUM1(1, ADD)) RSR_ROW(2, 3, RSR_SUM1(2, ADD))        \
+        RSR_ROW(3, 2, RSR_SUM1(3, ADD)) RSR_ROW(4, 1, RSR_SUM1(4, ADD)) RSR_ROW(5, 0, RSR_SUM1(5, ADD)) "s_branch .Lrsr_end_%=\n" \
+        RSR_HEAD(0, RSR_STORE1(0)) RSR_HEAD(1, RSR_STORE1(1)) RSR_HEAD(2, RSR_STORE1(2)) RSR_HEAD(3, RSR_STORE1(3)) \
+        RSR_HEAD(4, RSR_STORE1(4)) RSR_HEAD(5, RSR_STORE1(5) "s_waitcnt lgkmcnt(1)\n")                         \
+        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
+        : [a] "+v"(acc[0]), [x] "=&v"(x), RSR_S6, [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5) \
+        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), RSR_CTL                                                    \
+        : RSR_CLOBBER);                                                                                        \
+  }
+
+// Several vectors per row.  A gather fills neighbouring registers, which have to be named: v[96:111].
+#define RSR_T16 "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", "v108", "v109", "v110", "v111"
+// two registers of sums: two floats, or four 16-bit sums
+#define RSR_SUM2(x, y, ADD) ADD " %[a], %[a], v" #x "\n" ADD " %[b], %[b], v" #y "\n"
+#define RSR_STORE2(q)                                                                                          \
+  "v_add_u32 %[s" #q "], %[ub], %[s" #q "]\n ds_write2_b32 %[s" #q "], %[a], %[b] offset1:1\n v_mov_b32 %[a], 0\n v_mov_b32 %[b], 0\n"
+#define RSR_LANES2_F(x) "v_add_f32_dpp %[a], %[a], %[a] " x "\n v_add_f32_dpp %[b], %[b], %[b] " x "\n"
+#define RSR_LANES2_P(x)                                                                                        \
+  "v_mov_b32_dpp %[x], %[a] " x "\n v_mov_b32_dpp %[y], %[b] " x "\n v_pk_add_u16 %[a], %[a], %[x]\n v_pk_add_u16 %[b], %[b], %[y]\n"
+#define RSR_STEPS2(AT, ADD, LANES)                                                                             \
+  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, AT (&acc)[2], uint32_t hm, \
+                                               uint32_t wd, uint32_t ub) {                                     \
+    uint32_t s0, s1, s2, s3, s4, s5, s6, s7;                                                                   \
+    AT x, y;                                                                                                   \
+    asm volatile(                                                                                              \
+        RSR_EXTRACT8(3)                                                                                        \
+        "ds_read_b64 v[96:97], %[s0]\n ds_read_b64 v[98:99], %[s1]\n ds_read_b64 v[100:101], %[s2]\n ds_read_b64 v[102:103], %[s3]\n" \
+        "ds_read_b64 v[104:105], %[s4]\n ds_read_b64 v[106:107], %[s5]\n ds_read_b64 v[108:109], %[s6]\n ds_read_b64 v[110:111], %[s7]\n" \
+        RSR_ROW(0, 7, RSR_SUM2(96, 97, ADD)) RSR_ROW(1, 6, RSR_SUM2(98, 99, ADD)) RSR_ROW(2, 5, RSR_SUM2(100, 101, ADD)) \
+        RSR_ROW(3, 4, RSR_SUM2(102, 103, ADD)) RSR_ROW(4, 3, RSR_SUM2(104, 105, ADD)) RSR_ROW(5, 2, RSR_SUM2(106, 107, ADD)) \
+        RSR_ROW(6, 1, RSR_SUM2(108, 109, ADD)) RSR_ROW(7, 0, RSR_SUM2(110, 111, ADD)) "s_branch .Lrsr_end_%=\n" \
+        RSR_HEAD(0, RSR_STORE2(0)) RSR_HEAD(1, RSR_STORE2(1)) RSR_HEAD(2, RSR_STORE2(2)) RSR_HEAD(3, RSR_STORE2(3)) \
+        RSR_HEAD(4, RSR_STORE2(4)) RSR_HEAD(5, RSR_STORE2(5)) RSR_HEAD(6, RSR_STORE2(6)) RSR_HEAD(7, RSR_STORE2(7) "s_waitcnt lgkmcnt(1)\n") \
+        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
+        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [x] "=&v"(x), [y] "=&v"(y), RSR_S8                               \
+        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), RSR_CTL                                      \
+        : RSR_CLOBBER, RSR_T16);                                                                               \
+  }                                                                                                            \
+  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, AT (&acc)[2], uint32_t hm, uint32_t wd, uint32_t ub) { \
+    uint32_t s0, s1, s2, s3, s4, s5;                                                                           \
+    AT x, y;                                                                                                   \
+    asm volatile(                                                                                              \
+        RSR_EXTRACT2(3, 0, 1, 0) RSR_EXTRACT2(3, 2, 3, 1) RSR_EXTRACT2(3, 4, 5, 2)                             \
+        "ds_read_b64 v[96:97], %[s0]\n ds_read_b64 v[98:99], %[s1]\n ds_read_b64 v[100:101], %[s2]\n ds_read_b64 v[102:103], %[s3]\n" \
+        "ds_read_b64 v[104:105], %[s4]\n ds_read_b64 v[106:107], %[s5]\n"                                      \
+        RSR_ROW(0, 5, RSR_SUM2(96, 97, ADD)) RSR_ROW(1, 4, RSR_SUM2(98, 99, ADD)) RSR_ROW(2, 3, RSR_SUM2(100, 101, ADD)) \
+        RSR_ROW(3, 2, RSR_SUM2(102, 103, ADD)) RSR_ROW(4, 1, RSR_SUM2(104, 105, ADD)) RSR_ROW(5, 0, RSR_SUM2(106, 107, ADD)) \
+        "s_branch .Lrsr_end_%=\n"                                                                              \
+        RSR_HEAD(0, RSR_STORE2(0)) RSR_HEAD(1, RSR_STORE2(1)) RSR_HEAD(2, RSR_STORE2(2)) RSR_HEAD(3, RSR_STORE2(3)) \
+        RSR_HEAD(4, RSR_STORE2(4)) RSR_HEAD(5, RSR_STORE2(5) "s_waitcnt lgkmcnt(1)\n")                         \
+        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
+        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [x] "=&v"(x), [y] "=&v"(y), RSR_S6                               \
+        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), RSR_CTL                                                    \
+        : RSR_CLOBBER, RSR_T16);                                                                               \
+  }
+// four floats
+#define RSR_SUM4(x, y, z, w)                                                                                   \
+  "v_add_f32 %[a], %[a], v" #x "\n v_add_f32 %[b], %[b], v" #y "\n v_add_f32 %[c], %[c], v" #z "\n v_add_f32 %[d], %[d], v" #w "\n"
+#define RSR_CLEAR4 "v_mov_b32 %[a], 0\n v_mov_b32 %[b], 0\n v_mov_b32 %[c], 0\n v_mov_b32 %[d], 0\n"
+#define RSR_STORE4(q)                                                                                          \
+  "v_add_u32 %[s" #q "], %[ub], %[s" #q "]\n ds_write2_b32 %[s" #q "], %[a], %[b] offset1:1\n"                 \
+  "ds_write2_b32 %[s" #q "], %[c], %[d] offset0:2 offset1:3\n" RSR_CLEAR4
+#define RSR_LANES4(x)                                                                                          \
+  "v_add_f32_dpp %[a], %[a], %[a] " x "\n v_add_f32_dpp %[b], %[b], %[b] " x "\n"                              \
+  "v_add_f32_dpp %[c], %[c], %[c] " x "\n v_add_f32_dpp %[d], %[d], %[d] " x "\n"
+// int8 activations of several vectors are widened to 16 bits when they are staged, two vectors to a dword, and
+// summed two at a time (v_pk_add_u16): a slot's segment has at most kWideRows rows, |sum| <= 32768, and 32768 is
+// reached only by -128 * 256, which 16 bits hold.
+struct F1 {  // one float vector
+  using In = float;
+  using Acc = float;
+  using Run = float;  // the running sums, R registers of them
+  static constexpr int V = 1, R = 1, shift = 2, slot_bytes = 4;
+  using Slot = float;  // the sums of a slot
+  __device__ static __forceinline__ float get(float x, int) { return x; }
+  RSR_STEPS1(float, "v_add_f32", RSR_LANES1_F)
+};
+struct I1 {  // one int8 vector
+  using In = int8_t;
+  using Acc = int32_t;
+  using Run = int32_t;
+  static constexpr int V = 1, R = 1, shift = 2, slot_bytes = 4;
+  using Slot = int32_t;
+  __device__ static __forceinline__ int32_t get(int32_t x, int) { return x; }
+  RSR_STEPS1(int32_t, "v_add_u32", RSR_LANES1_I)
+};
+struct F2 {  // two float vectors
+  using In = float;
+  using Acc = float;
+  using Run = float;
+  static constexpr int V = 2, R = 2, shift = 3, slot_bytes = 8;
+  typedef float Slot __attribute__((ext_vector_type(2)));
+  __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
+  RSR_STEPS2(float, "v_add_f32", RSR_LANES2_F)
+};
+struct P2 {  // two int8 vectors
+  using In = int8_t;
+  using Acc = int32_t;
+  using Run = uint32_t;
+  static constexpr int V = 2, R = 1, shift = 2, slot_bytes = 4;
+  typedef int16_t Slot __attribute__((ext_vector_type(2)));
+  __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
+  RSR_STEPS1(uint32_t, "v_pk_add_u16", RSR_LANES1_P)
+};
+struct P4 {  // four int8 vectors
+  using In = int8_t;
+  using Acc = int32_t;
+  using Run = uint32_t;
+  static constexpr int V = 4, R = 2, shift = 3, slot_bytes = 8;
+  typedef int16_t Slot __attribute__((ext_vector_type(4)));
+  __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
+  RSR_STEPS2(uint32_t, "v_pk_add_u16", RSR_LANES2_P)
+};
+struct F4 {  // four float vectors; four positions per step (16 registers of gathered sums)
+  using In = float;
+  using Acc = float;
+  using Run = float;
+  static constexpr int V = 4, R = 4, shift = 4, slot_bytes = 16;
+  typedef float Slot __attribute__((ext_vector_type(4)));
+  __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
+  __device__ static __forceinline__ void step4(uint32_t w0, uint32_t w1, float (&acc)[4], uint32_t hm, uint32_t wd, uint32_t ub) {
+    uint32_t s0, s1, s2, s3;
+    asm volatile(
+        RSR_EXTRACT2(4, 0, 1, 0) RSR_EXTRACT2(4, 2, 3, 1)
+        "ds_read_b128 v[96:99], %[s0]\n ds_read_b128 v[100:103], %[s1]\n ds_read_b128 v[104:107], %[s2]\n ds_read_b128 v[108:111], %[s3]\n"
+        RSR_ROW(0, 3, RSR_SUM4(96, 97, 98, 99)) RSR_ROW(1, 2, RSR_SUM4(100, 101, 102, 103))
+        RSR_ROW(2, 1, RSR_SUM4(104, 105, 106, 107)) RSR_ROW(3, 0, RSR_SUM4(108, 109, 110, 111))
+        "s_branch .Lrsr_end_%=\n"
+        RSR_HEAD(0, RSR_STORE4(0)) RSR_HEAD(1, RSR_STORE4(1)) RSR_HEAD(2, RSR_STORE4(2)) RSR_HEAD(3, RSR_STORE4(3) "s_waitcnt lgkmcnt(2)\n")
+        RSR_LANES(RSR_LANES4) ".Lrsr_end_%=:\n"
+        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [c] "+v"(acc[2]), [d] "+v"(acc[3]), [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3)
+        : [w0] "v"(w0), [w1] "v"(w1), RSR_CTL
+        : RSR_CLOBBER, RSR_T16);
+  }
+  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, float (&acc)[4], uint32_t hm,
+                                               uint32_t wd, uint32_t ub) {
+    step4(w0, w1, acc, hm, wd, ub);
+    step4(w2, w3, acc, hm >> 4, wd, ub);
+  }
+  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, float (&acc)[4], uint32_t hm, uint32_t wd, uint32_t ub) {
+    step4(w0, w1, acc, hm, wd, ub);
+    uint32_t s0, s1;
+    asm volatile(
+        RSR_EXTRACT2(4, 0, 1, 0) "ds_read_b128 v[96:99], %[s0]\n ds_read_b128 v[100:103], %[s1]\n"
+        RSR_ROW(0, 1, RSR_SUM4(96, 97, 98, 99)) RSR_ROW(1, 0, RSR_SUM4(100, 101, 102, 103)) "s_branch .Lrsr_end_%=\n"
+        RSR_HEAD(0, RSR_STORE4(0)) RSR_HEAD(1, RSR_STORE4(1) "s_waitcnt lgkmcnt(2)\n")
+        RSR_LANES(RSR_LANES4) ".Lrsr_end_%=:\n"
+        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [c] "+v"(acc[2]), [d] "+v"(acc[3]), [s0] "=&v"(s0), [s1] "=&v"(s1)
+        : [w0] "v"(w2), [hm] "s"(uniform(hm >> 4)), [wd] "s"(uniform(wd)), [ub] "s"(uniform(ub))
+        : RSR_CLOBBER, "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103");
+  }
+};
 // The scalar fields of a unit descriptor.  The unit number is wavefront-uniform, so the descriptor is
 // read with scalar loads: these do not queue with the vector loads of the compute unit, which
 // return in the order they were issued across all its wavefronts - a descriptor that has to come
 // from memory would hold back everything requested after it (the other wavefronts' share of the
 // activation vector at the start, stream data later).
-__device__ __forceinline__ void single_step(uint32_t w0, int32_t& a, uint32_t& sa, uint32_t& f, const int8_t*) {
-  uint32_t s0;
-  int32_t t0;
-  asm volatile(RSR_X1_LO("%[s0]", "%[w0]") "ds_read_i8 %[t0], %[s0]\n" RSR_POS(0, 0, "v_add_u32")
-               : [a] "+v"(a), [sa] "+v"(sa), [f] "+v"(f), [s0] "=&v"(s0), [t0] "=&v"(t0)
-               : [w0] "v"(w0)
-               : "vcc", "memory");
-}
-
 struct Desc {
-  uint32_t stream_off, block;
-  int window, part, npos, units_in_block, index_in_block, slot0;
+  uint32_t stream_off, block, panel, heads_lo;
+  uint32_t heads_hi, npos, wide;
+  uint32_t units_in_panel, extras;
 };
+__device__ __forceinline__ Desc make_desc(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t w4, uint32_t w5) {
+  Desc d;
+  d.stream_off = w0;
+  d.block = w1;
+  d.panel = w2;
+  d.heads_lo = w3;
+  d.heads_hi = w4 & 0xffffu;
+  d.npos = (w4 >> 16) & 0xffu;
+  d.wide = w4 >> 24;
+  d.units_in_panel = w5 & 0xffffu;
+  d.extras = w5 >> 16;
+  return d;
+}
 __device__ __forceinline__ Desc load_desc(const uint32_t* __restrict__ unit_words, uint32_t u) {
   const uint32_t* w = unit_words + (size_t)__builtin_amdgcn_readfirstlane((int)u) * 8;
-  Desc d;
-  d.stream_off = w[0];
-  d.block = w[1];
-  const uint32_t w2 = w[2], w3 = w[3], w4 = w[4];
-  d.window = (int)(w2 & 0xffffu);
-  d.part = (int)((w2 >> 16) & 0xffu);
-  d.npos = (int)(w2 >> 24);
-  d.units_in_block = (int)(w3 & 0xffffu);
-  d.index_in_block = (int)(w3 >> 16);
-  d.slot0 = (int)(w4 & 0xffffu);
-  return d;
+  return make_desc(w[0], w[1], w[2], w[3], w[4], w[5]);
+}
+
+template <typename AT>
+__device__ __forceinline__ AT exchange_add(AT even, AT odd, bool take_odd, int step) {
+  const AT keep = take_odd ? odd : even, give = take_odd ? even : odd;
+  switch (step) {
+    case 0: return keep + dpp_get<0xB1, 0xf, 0xf>(give);  // quad_perm [1,0,3,2]: lane xor 1
+    case 1: return keep + dpp_get<0x4E, 0xf, 0xf>(give);  // quad_perm [2,3,0,1]: lane xor 2
+    // lane xor 4: lanes 0-3 and 8-11 of a row read 4 lanes up, lanes 4-7 and 12-15 read 4 lanes down
+    case 2: return keep + (dpp_get<0x104, 0xf, 0x5>(give) + dpp_get<0x114, 0xf, 0xa>(give));
+    default: return keep + dpp_get<0x128, 0xf, 0xf>(give);  // row_ror:8 is lane xor 8 inside a row
+  }
+}
+// Sums of sixteen values over the 64 lanes, all at once: after every exchange a lane keeps half of its values and
+// hands the other half to its partner, so the four halving exchanges (lane xor 1, 2, 4, 8) cost 8 + 4 + 2 + 1
+// additions instead of 16 each; the four rows of 16 lanes follow with lane swaps.  On return every lane holds the
+// sum of v[lane & 15].
+template <typename AT>
+__device__ __forceinline__ AT sums_of_sixteen(const AT (&v)[16], int lane) {
+  AT w[8], x[4], y[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) w[i] = exchange_add(v[2 * i], v[2 * i + 1], lane & 1, 0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x[i] = exchange_add(w[2 * i], w[2 * i + 1], lane & 2, 1);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) y[i] = exchange_add(x[2 * i], x[2 * i + 1], lane & 4, 2);
+  const AT row = exchange_add(y[0], y[1], lane & 8, 3);
+  const Swapped h = swap32(__builtin_bit_cast(uint32_t, row));
+  const AT two = __builtin_bit_cast(AT, h.x) + __builtin_bit_cast(AT, h.y);
+  const Swapped q = swap16(__builtin_bit_cast(uint32_t, two));
+  return __builtin_bit_cast(AT, q.x) + __builtin_bit_cast(AT, q.y);
 }
 
 constexpr int NG = rsr::kMaxGranules;
-#ifndef RSR_HEAD_GRANULES
-#define RSR_HEAD_GRANULES 1
-#endif
+constexpr int kItems = 16;      // per panel and vector: value bits 0 .. 11, the total (kTotal), unused
+constexpr int kTotal = 12;
+constexpr int kExtraAhead = 128;  // extra sums of a panel whose slots are fetched ahead of the fold
+
+// u . Bin_[k] by its definition, for the four values value, value + 64, + 128, + 192: for every column (value bit) the sum
+// of the u[j] with that bit.
+template <typename AT>
+__device__ __forceinline__ void plain_sums(AT (&sums)[12], int value, AT d0, AT d1, AT d2, AT d3) {
+#pragma unroll
+  for (int bit = 0; bit < 12; ++bit) {
+    sums[bit] += ((value >> bit) & 1) ? d0 : (AT)0;
+    sums[bit] += (((value + 64) >> bit) & 1) ? d1 : (AT)0;
+    sums[bit] += (((value + 128) >> bit) & 1) ? d2 : (AT)0;
+    sums[bit] += (((value + 192) >> bit) & 1) ? d3 : (AT)0;
+  }
+}
+
+// The activations of a workgroup's V vectors go to LDS, row by row, the vectors of a row next to each other (int8:
+// widened to 32 bits, or to 16 where there are several).  Vectors past the batch are zeros.
+template <class M>
+__device__ __forceinline__ void stage(unsigned char* lds, const typename M::In* __restrict__ v, int64_t vstride, int nv, int rows, int first) {
+  const int tid = threadIdx.x, nt = blockDim.x;
+  if constexpr (M::V == 1 && sizeof(typename M::In) == 1) {
+    const int n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? rows / 16 : 0;
+    const uint4* v16 = reinterpret_cast<const uint4*>(v);
+    for (int i = tid; i < n16; i += nt) {
+      const uint4 x = v16[i];
+      const uint32_t d[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        reinterpret_cast<int4*>(lds)[4 * i + j] =
+            make_int4((int32_t)(d[j] << 24) >> 24, (int32_t)(d[j] << 16) >> 24, (int32_t)(d[j] << 8) >> 24, (int32_t)d[j] >> 24);
+    }
+    for (int i = n16 * 16 + tid; i < rows; i += nt) reinterpret_cast<int32_t*>(lds)[i] = v[i];
+  } else if constexpr (M::V == 1) {  // rows from `first` on (the caller has staged the ones before)
+    const int n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? rows / 4 : 0;
+    for (int i = first + tid; i < n16; i += nt) reinterpret_cast<uint4*>(lds)[i] = reinterpret_cast<const uint4*>(v)[i];
+    for (int i = n16 * 4 + tid; i < rows; i += nt) reinterpret_cast<float*>(lds)[i] = v[i];
+  } else if constexpr (sizeof(typename M::In) == 4) {
+    // four rows at a time where every vector starts on 16 bytes; kAtOnce of them so that the loads wait together
+    const int n4 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0 && (vstride & 3) == 0) ? rows / 4 : 0;
+    constexpr int kAtOnce = M::V == 2 ? 4 : 2;
+    for (int i0 = tid; i0 < n4; i0 += kAtOnce * nt) {
+      float x[kAtOnce][M::V][4];
+#pragma unroll
+      for (int a = 0; a < kAtOnce; ++a)
+#pragma unroll
+        for (int j = 0; j < M::V; ++j) {
+          float4 y = make_float4(0, 0, 0, 0);
+          if (j < nv) y = reinterpret_cast<const float4*>(v + j * vstride)[min(i0 + a * nt, n4 - 1)];
+          x[a][j][0] = y.x; x[a][j][1] = y.y; x[a][j][2] = y.z; x[a][j][3] = y.w;
+        }
+#pragma unroll
+      for (int a = 0; a < kAtOnce; ++a) {
+        const int i = i0 + a * nt;
+        if (i >= n4) break;
+        float4* to = reinterpret_cast<float4*>(lds + ((size_t)i * 4 << M::shift));
+        if constexpr (M::V == 2) {
+          to[0] = make_float4(x[a][0][0], x[a][1][0], x[a][0][1], x[a][1][1]);
+          to[1] = make_float4(x[a][0][2], x[a][1][2], x[a][0][3], x[a][1][3]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) to[r] = make_float4(x[a][0][r], x[a][1][r], x[a][2][r], x[a][3][r]);
+        }
+      }
+    }
+    for (int i0 = n4 * 4 + tid; i0 < rows; i0 += 4 * nt) {
+      float x[4][M::V];
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int j = 0; j < M::V; ++j) x[a][j] = j < nv ? v[j * vstride + min(i0 + a * nt, rows - 1)] : 0.0f;
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        if (i0 + a * nt < rows)
+#pragma unroll
+          for (int j = 0; j < M::V; ++j) reinterpret_cast<float*>(lds)[(i0 + a * nt) * M::V + j] = x[a][j];
+    }
+  } else {
+    const int n4 = ((reinterpret_cast<uintptr_t>(v) & 3) == 0 && (vstride & 3) == 0) ? rows / 4 : 0;
+    constexpr int kAtOnce = 4;
+    for (int i0 = tid; i0 < n4; i0 += kAtOnce * nt) {
+      uint32_t x[kAtOnce][M::V];
+#pragma unroll
+      for (int a = 0; a < kAtOnce; ++a)
+#pragma unroll
+        for (int j = 0; j < M::V; ++j) x[a][j] = j < nv ? reinterpret_cast<const uint32_t*>(v + j * vstride)[min(i0 + a * nt, n4 - 1)] : 0u;
+#pragma unroll
+      for (int a = 0; a < kAtOnce; ++a) {
+        const int i = i0 + a * nt;
+        if (i >= n4) break;
+        uint32_t w[4][M::V / 2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < M::V / 2; ++j)
+            w[r][j] = ((uint32_t)((int32_t)(x[a][2 * j] << (24 - 8 * r)) >> 24) & 0xffffu) | ((uint32_t)((int32_t)(x[a][2 * j + 1] << (24 - 8 * r)) >> 24) << 16);
+        if constexpr (M::V == 2) {
+          reinterpret_cast<uint4*>(lds)[i] = make_uint4(w[0][0], w[1][0], w[2][0], w[3][0]);
+        } else {
+          reinterpret_cast<uint4*>(lds)[2 * i] = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
+          reinterpret_cast<uint4*>(lds)[2 * i + 1] = make_uint4(w[2][0], w[2][1], w[3][0], w[3][1]);
+        }
+      }
+    }
+    for (int i0 = n4 * 4 + tid; i0 < rows; i0 += kAtOnce * nt) {
+      int16_t x[kAtOnce][M::V];
+#pragma unroll
+      for (int a = 0; a < kAtOnce; ++a)
+#pragma unroll
+        for (int j = 0; j < M::V; ++j) x[a][j] = j < nv ? (int16_t)v[j * vstride + min(i0 + a * nt, rows - 1)] : (int16_t)0;
+#pragma unroll
+      for (int a = 0; a < kAtOnce; ++a)
+        if (i0 + a * nt < rows)
+#pragma unroll
+          for (int j = 0; j < M::V; ++j) reinterpret_cast<int16_t*>(lds)[(i0 + a * nt) * M::V + j] = x[a][j];
+    }
+  }
+}
 
 // The work of one workgroup: `wg` is its number among the workgroups of this product (a launch may
 // carry several products, see rsr_multi_kernel).  The workgroup may have more wavefronts than the
-// product's LDS layout has windows for (p.waves): the others help to stage the activation vector
-// and take no units.
+// product has use for (p.waves): the others help to stage the activations and take no units.
 // PLAIN selects step 2 of Algorithm 2 as printed there (the product u . Bin_[k] term by term,
 // O(k 2^k)) instead of the RSR++ fold of Algorithm 3: kept for the comparison of Appendix F.2.
-template <typename VT, bool PLAIN>
+template <class M, bool PLAIN>
 __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ stream, const uint32_t* __restrict__ unit_words,
-                                         const uint32_t* __restrict__ blk_unit, const VT* __restrict__ vin,
-                                         typename Acc<VT>::type* __restrict__ out, const KArgs& p, const int wg) {
-  using AT = typename Acc<VT>::type;
+                                         const uint32_t* __restrict__ blk_unit, const uint16_t* __restrict__ extra_slots,
+                                         const typename M::In* __restrict__ vin, typename M::Acc* __restrict__ out, const KArgsPtr pa,
+                                         const int wg) {
+  const KArgs p = *pa;
+  using AT = typename M::Acc;
+  constexpr int V = M::V;
   extern __shared__ __align__(16) unsigned char lds[];
-  VT* vl = reinterpret_cast<VT*>(lds);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nwaves = p.waves;
-  const bool worker = wave < nwaves;
+  const bool worker = wave < p.waves;
 
-  // workgroup -> (batch lane b, block range g): the `batch` siblings of a block range sit 8
+  // workgroup -> (set of V vectors, block range g): the siblings of a block range sit 8
   // workgroup ids apart so that round-robin dispatch puts them on the same XCD (shared L2).
-  const int per = 8 * p.batch;
+  const int sets = (p.batch + V - 1) / V;
+  const int per = 8 * sets;
   const int grp = wg / per, rem = wg % per;
-  const int b = rem >> 3;
+  const int b = (rem >> 3) * V;
   const int g = grp * 8 + (rem & 7);
   if (g >= p.g1) return;
   const int blk_begin = (int)((int64_t)g * p.nblocks / p.g1);
   const int blk_end = (int)((int64_t)(g + 1) * p.nblocks / p.g1);
   if (blk_begin >= blk_end) return;
-
-  const uint32_t winbase = p.off_win + (uint32_t)(worker ? wave : 0) * (rsr::kWindow * 4);
-  AT* win = reinterpret_cast<AT*>(lds + winbase);
-  AT* rec = reinterpret_cast<AT*>(lds + p.off_rec);
-  unsigned* done = reinterpret_cast<unsigned*>(lds + p.off_done);
-  unsigned* ctr = reinterpret_cast<unsigned*>(lds + p.off_ctr);
-  uint32_t* bu = reinterpret_cast<uint32_t*>(lds + p.off_bu);  // first unit of the round's blocks
-  AT* outp = out + (int64_t)b * p.cols;
-  const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u, lane2 = (uint32_t)lane * 2u;
+  const int nv = min(V, p.batch - b);
+  const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
 
   // Two register buffers: while one unit is summed from one, the next unit's stream arrives in the
-  // other.  Every unit issues the same number of loads (the ones it does not need read the first
-  // bytes of the stream, which stay cached), so that the wait counts between units are exact and a
-  // wait for the current unit never waits for the next one.
+  // other.  A unit's stream is read through a buffer descriptor that covers exactly the unit: a load past
+  // its end (a granule or a dword row the unit does not have, or a unit that does not exist: npos = 0)
+  // returns zeros without touching memory, and an address costs no vector arithmetic.  Every unit
+  // issues the same number of loads, so that the wait counts between units are exact and a wait for
+  // the current unit never waits for the next one.
   uint32_t eA[NG][4], eB[NG][4];
-  uint32_t tA[4], tB[4];  // positions behind the last full granule: up to three rows of dwords and one of uint16
-  uint32_t fA[2], fB[2];  // the lane's flags: positions 0..31 from bit 31 down, positions 32..47 from bit 15 down
-  // A unit's stream is read through a buffer descriptor that covers exactly the unit: a load past
-  // its end (a granule, a dword row or the second flag word the unit does not have, or a unit that
-  // does not exist: npos = 0) returns zeros without touching memory, and an address costs no
-  // vector arithmetic.
-  auto unit_rsrc = [&](uint32_t stream_off, int npos) {
+  uint32_t tA[3], tB[3];  // positions behind the last full granule: up to three rows of dwords
+  auto unit_rsrc = [&](uint32_t stream_off, uint32_t npos) {
     unsigned char* us = const_cast<unsigned char*>(stream) + (size_t)stream_off * rsr::kStreamAlign;
-    const int bytes = npos * rsr::kPositionBytes + (npos > 0 ? rsr::kFlagBytes0 : 0) + (npos > 32 ? rsr::kFlagBytes1 : 0);
-    return __builtin_amdgcn_make_buffer_rsrc(us, 0, bytes, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(us, 0, (int)(npos * rsr::kPositionBytes), 0x00020000);
   };
-  constexpr int kNonTemporal = 2;  // the stream is read once per product: keep it from displacing reused data
+  // The stream is read once per product (per set of vectors, by siblings that share an L2): non-temporal loads keep
+  // it from displacing reused data.
+  constexpr int kNonTemporal = 2;
   // (the offsets go into the per-lane offset, which the range check covers; the scalar offset stays 0)
   const uint32_t lane16_hi = lane16 + 4096u;
   auto issue_granule = [&](__amdgpu_buffer_rsrc_t rs, int gq, uint32_t (&e)[NG][4]) {
     const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(gq < 4 ? lane16 : lane16_hi) + (gq & 3) * 1024, 0, kNonTemporal);
     e[gq][0] = x.x; e[gq][1] = x.y; e[gq][2] = x.z; e[gq][3] = x.w;
   };
-  auto issue_pair = [&](__amdgpu_buffer_rsrc_t rs, uint32_t pair_base, int j, uint32_t (&et)[4]) {
+  auto issue_pair = [&](__amdgpu_buffer_rsrc_t rs, uint32_t pair_base, int j, uint32_t (&et)[3]) {
     et[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)pair_base + j * 256, 0, kNonTemporal);
   };
-  // the last position of an odd count: a row of uint16 behind the dword rows (for an even count this
-  // reads flag bytes, which nobody uses)
-  auto issue_single = [&](__amdgpu_buffer_rsrc_t rs, int npos, uint32_t (&et)[4]) {
-    et[3] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)((uint32_t)(npos & ~1) * rsr::kPositionBytes + lane2), 0, kNonTemporal);
-  };
-  auto issue_flags = [&](__amdgpu_buffer_rsrc_t rs, int npos, uint32_t (&f)[2]) {
-    const uint32_t fbase = (uint32_t)npos * rsr::kPositionBytes;
-    f[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(fbase + lane4), 0, kNonTemporal);
-    f[1] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)(fbase + rsr::kFlagBytes0 + lane2), 0, kNonTemporal);
-  };
-  // A wavefront's first unit is requested in two parts: the flags and the first kHeadGranules
-  // granules before the workgroup's barrier, the rest behind it (see there).
-  constexpr int kHeadGranules = RSR_HEAD_GRANULES;
-  auto issue_head = [&](uint32_t stream_off, int npos, uint32_t (&e)[NG][4], uint32_t (&f)[2]) {
-    const __amdgpu_buffer_rsrc_t rs = unit_rsrc(stream_off, npos);
-    issue_flags(rs, npos, f);
-#pragma unroll
-    for (int gq = 0; gq < kHeadGranules; ++gq) issue_granule(rs, gq, e);
-  };
-  auto issue_rest = [&](uint32_t stream_off, int npos, uint32_t (&e)[NG][4], uint32_t (&et)[4]) {
-    const __amdgpu_buffer_rsrc_t rs = unit_rsrc(stream_off, npos);
-#pragma unroll
-    for (int gq = kHeadGranules; gq < NG; ++gq) issue_granule(rs, gq, e);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) issue_pair(rs, lane4 + (uint32_t)(npos >> 3) * 1024u, j, et);
-    issue_single(rs, npos, et);
-  };
 
-  // The activation vector is staged first: its loads go out before anything else so that they do
+  // The activations are staged first: their loads go out before anything else so that they do
   // not queue behind the (much larger) first stream loads of the other wavefronts.
-  const VT* __restrict__ v = vin + (int64_t)b * p.vstride + p.row0;
-  constexpr int per16 = 16 / (int)sizeof(VT);
-  const int n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? p.rows / per16 : 0;
-  const uint4* v16 = reinterpret_cast<const uint4*>(v);
-  constexpr int kEarly = 4;  // 16-byte pieces per thread fetched before the descriptors
-  uint4 sv[kEarly];
+  const typename M::In* __restrict__ v = vin + (int64_t)b * p.vstride + p.row0;
+  constexpr int kEarly = (V == 1 && sizeof(typename M::In) == 4) ? 4 : 0;  // 16-byte pieces per thread fetched before the descriptors
+  uint4 sv[kEarly ? kEarly : 1];
+  int n16 = 0;
+  if constexpr (kEarly > 0) {
+    n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? p.rows / 4 : 0;
 #pragma unroll
-  for (int j = 0; j < kEarly; ++j) {
-    const int i = tid + j * (int)blockDim.x;
-    sv[j] = make_uint4(0, 0, 0, 0);
-    if (i < n16) sv[j] = v16[i];
+    for (int j = 0; j < kEarly; ++j) {
+      const int i = tid + j * (int)blockDim.x;
+      sv[j] = make_uint4(0, 0, 0, 0);
+      if (i < n16) sv[j] = reinterpret_cast<const uint4*>(v)[i];
+    }
+  }
+  const uint32_t u_begin = blk_unit[blk_begin];
+  const uint32_t n_tot = blk_unit[blk_end] - u_begin;  // units of this workgroup, numbered 0 .. n_tot-1
+  // The first two units of every wavefront are fixed (its own number and that plus the number of wavefronts); the first
+  // one's descriptor and the beginning of its stream are requested before the barrier.  Later units come from a counter.
+  const uint32_t u_first = u_begin + (uint32_t)wave;
+  Desc D = load_desc(unit_words, u_first < (uint32_t)p.nunits ? u_first : 0u);
+  uint32_t ix = worker ? (uint32_t)wave : n_tot, ix1 = ix + (uint32_t)p.waves;
+  if (ix >= n_tot) D.npos = 0;  // (its loads then fall outside the buffer descriptor and read nothing)
+  {
+    const __amdgpu_buffer_rsrc_t rs = unit_rsrc(D.stream_off, D.npos);
+    issue_granule(rs, 0, eA);
+  }
+  // Slots start from zero.  Where every panel stores all its values (`fill`) only slots that are no value's have to be: those
+  // of panels of fewer values than a step of the fold reads.  (The slot of value 0 is not stored, but counts under no bit.)
+  if (!p.fill || (1 << p.kc) < rsr::kFoldRow)
+    for (uint32_t i = (uint32_t)tid * 16u; i < (uint32_t)p.nbuf * p.ubytes; i += blockDim.x * 16u)
+      *reinterpret_cast<uint4*>(lds + p.off_u + i) = make_uint4(0, 0, 0, 0);
+  if (tid < p.nbuf) {
+    reinterpret_cast<uint32_t*>(lds + p.off_cnt)[tid] = 0;
+    reinterpret_cast<uint32_t*>(lds + p.off_epoch)[tid] = 0;
+  }
+  if (tid < p.nrec) {
+    reinterpret_cast<uint32_t*>(lds + p.off_done)[tid] = 0;
+    reinterpret_cast<uint32_t*>(lds + p.off_blocks)[tid] = 0;
+  }
+  if (tid == 0) *reinterpret_cast<uint32_t*>(lds + p.off_ctr) = 2u * (uint32_t)p.waves;
+  // The descriptors of the workgroup's units: from LDS they come without a wait for memory, which would also hold up
+  // the gathers (scalar loads and LDS operations share a counter).
+  const uint32_t ndesc = n_tot <= (uint32_t)p.waves ? 0u : min(n_tot, p.ndesc);
+  for (uint32_t i = (uint32_t)tid; i < 2 * ndesc; i += blockDim.x)
+    reinterpret_cast<uint4*>(lds + p.off_desc)[i] = reinterpret_cast<const uint4*>(unit_words + (size_t)u_begin * 8)[i];
+  if constexpr (kEarly > 0) {
+#pragma unroll
+    for (int j = 0; j < kEarly; ++j) {
+      const int i = tid + j * (int)blockDim.x;
+      if (i < n16) reinterpret_cast<uint4*>(lds)[i] = sv[j];
+    }
+  }
+  stage<M>(lds, v, p.vstride, nv, p.rows, kEarly * (int)blockDim.x);
+  if (tid < (1 << M::shift) / 4) reinterpret_cast<uint32_t*>(lds + ((size_t)p.rows << M::shift))[tid] = 0;  // the null row
+  __syncthreads();
+  {
+    const __amdgpu_buffer_rsrc_t rs = unit_rsrc(D.stream_off, D.npos);
+#pragma unroll
+    for (int gq = 1; gq < NG; ++gq) issue_granule(rs, gq, eA);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) issue_pair(rs, lane4 + (D.npos >> 3) * 1024u, j, tA);
   }
 
-  // where a lane puts its part of a unit record (see below), in bytes from the record's start
-  const uint32_t rec_lane = 4u * (lane < 7 ? (uint32_t)lane : lane == 7 ? 9u : lane == 15 ? 7u : lane == 23 ? 8u : lane == 31 ? 10u : 12u);
-  bool first_round = true;
-  for (int rb0 = blk_begin; rb0 < blk_end;) {
-    // ---- round set-up.  A round covers as many consecutive blocks as there are completion
-    //      counters (nslot <= 64) and unit records (ucap). ----
-    // Usually all blocks of the workgroup fit in one round; otherwise the block table of the next
-    // nslot blocks is fetched to find out how many do.  (By the last threads of the workgroup:
-    // vector loads return in the order of issue across the wavefronts of a compute unit.)
-    const uint32_t u_begin = blk_unit[rb0];
-    const uint32_t u_last = blk_unit[blk_end];
-    const bool one_round = (blk_end - rb0 <= p.nslot) && (u_last - u_begin <= (uint32_t)p.ucap);
-    if (!one_round) {
-      for (int i = (int)blockDim.x - 1 - tid; i <= p.nslot; i += (int)blockDim.x) {
-        const int blk = rb0 + i;
-        bu[i] = blk_unit[blk < blk_end ? blk : blk_end];
-      }
+  const uint32_t panel_begin = (uint32_t)blk_begin * (uint32_t)p.panels;
+  uint32_t open_panel = ~0u;  // the panel (counted from panel_begin) that is known to have room
+
+  // ---- the fold of a panel, and the completion of its block, by the wavefront that has summed its last unit ----
+  auto fold = [&](const Desc& D, uint32_t buf, uint32_t ubase, uint32_t extra_pair) {
+    // (so are the lane masks below, for which the lane's number has to look new)
+    int lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // the sums were written by this workgroup
+    // (the arguments are fetched again: kept in scalar registers from the start of the kernel they would crowd out what
+    // the units need)
+    const KArgsPtr again = launder(pa);
+    const KArgs f = *again;
+    unsigned char* const u = lds + ubase;
+    // Lane l holds the slots 256 i + 64 c + l: value bits 0..5 are lane bits, bits 6 and 7 (c) and the higher ones
+    // (i) are folded inside the lane: "sum the odd-indexed entries, then add neighbours".
+    const int frows = f.pslots / rsr::kFoldRow;
+    AT hi[V][6], tot[V], pl[V][PLAIN ? 12 : 1];
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      tot[j] = (AT)0;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) hi[j][i] = (AT)0;
+      if constexpr (PLAIN)
+#pragma unroll
+        for (int i = 0; i < 12; ++i) pl[j][i] = (AT)0;
     }
-    if (tid < p.nslot) done[tid] = 0;
-    // the first unit of every wavefront is fixed (u_begin + wave), so that its descriptor can be
-    // fetched before the barrier; later ones come from the counter
-    if (tid == 0) *ctr = (unsigned)nwaves;
-    // The first stream loads go out before anything waits for the activation vector: they are
-    // behind it in the queue anyway.
-    const uint32_t u_first = u_begin + (uint32_t)wave;
-    Desc D = load_desc(unit_words, u_first < (uint32_t)p.nunits ? u_first : 0u);
-    if (!worker) D.npos = 0;  // (its loads then fall outside the buffer descriptor and read nothing)
-    issue_head(D.stream_off, D.npos, eA, fA);
-    if (first_round) {
-      // vl[rows] = 0 serves the null row index.
-      uint4* l16 = reinterpret_cast<uint4*>(vl);
+    constexpr int kRowBytes = rsr::kFoldRow * M::slot_bytes;
+    unsigned char* const first_row = u + lane * M::slot_bytes;
+    using Slot = typename M::Slot;
+    // G steps together, P of them read at a time: reads that are in flight together share the wait (behind the gathers of
+    // fifteen other wavefronts the LDS answers after several hundred clocks).
+    auto fold_steps = [&]<int G>(int i0) {
+      constexpr int P = V < 4 ? G : M::slot_bytes == 16 ? 1 : G < 2 ? G : 2;
+      AT x[G][V];
 #pragma unroll
-      for (int j = 0; j < kEarly; ++j) {
-        const int i = tid + j * (int)blockDim.x;
-        if (i < n16) l16[i] = sv[j];
-      }
-      for (int i = tid + kEarly * (int)blockDim.x; i < n16; i += blockDim.x) l16[i] = v16[i];
-      for (int i = n16 * per16 + tid; i < p.rows; i += blockDim.x) vl[i] = v[i];
-      if (tid == 0) vl[p.rows] = (VT)0;
-      first_round = false;
-    }
-    __syncthreads();
-    issue_rest(D.stream_off, D.npos, eA, tA);
-    int nblk = blk_end - rb0;
-    if (!one_round) {
-      const bool ok = (lane < p.nslot) && (rb0 + lane < blk_end) && (bu[lane + 1] - u_begin <= (uint32_t)p.ucap);
-      const uint64_t mask = __ballot(ok);
-      nblk = (~mask == 0) ? 64 : __builtin_ctzll(~mask);
-      if (nblk < 1) nblk = 1;  // a single block always fits: ucap >= the largest block
-    }
-    const int rb1 = rb0 + nblk;
-    const uint32_t n_tot = (one_round ? u_last : bu[nblk]) - u_begin;  // units of this round, numbered 0 .. n_tot-1
-
-    // A wavefront reserves its next unit only when it starts on the current one (not earlier): the
-    // last units of the round then go to the wavefronts that get there first.
-    auto take = [&]() { return lds_count_up(p.off_ctr); };
-    auto fetch_desc = [&](uint32_t ixq) {  // past the end it reads unit 0 (unused)
-      return load_desc(unit_words, ixq < n_tot ? u_begin + ixq : 0u);
-    };
-    uint32_t ix = worker ? (uint32_t)wave : n_tot;
-
-    // One unit from buffer (e, et, f); the next unit's stream goes into (en, etn, fn) meanwhile.
-    auto unit = [&](uint32_t (&e)[NG][4], uint32_t (&et)[4], uint32_t (&f)[2], uint32_t (&en)[NG][4], uint32_t (&etn)[4],
-                    uint32_t (&fn)[2]) {
-      const uint32_t ix1 = take();
-      Desc D1 = fetch_desc(ix1);
-      // (the next unit's descriptor arrives during the first granules; its loads go out one by one
-      // between the later steps: a wavefront that issues a whole unit at once waits for room in
-      // the memory pipeline while it could be summing)
-
-      // ---- step 1: segmented sums (Eq. SS2) into the window (u of Algorithm 2, this window's slice) ----
-      {
-        uint4* w16 = reinterpret_cast<uint4*>(win);
-        w16[lane] = make_uint4(0, 0, 0, 0);
-        w16[lane + 64] = make_uint4(0, 0, 0, 0);
-        static_assert(rsr::kWindow == 512, "zeroing above");
-      }
-      // The lane's first slot: the unit's first slot plus the flags of the lanes before it.
-      const uint32_t f1 = f[1] << 16;
-      const int nflag = __builtin_popcount(f[0]) + __builtin_popcount(f1);
-      const int flags_before = wave_inclusive_scan(nflag) - nflag;
-      uint32_t sa = winbase + (uint32_t)(D.slot0 + flags_before) * 4u;
-      AT a = (AT)0;
-      const int full = D.npos >> 3;
-      uint32_t fl = f[0];
-      auto step = [&](int gq) {
-        if (gq == 4) fl = f1;
-        if (gq < full) granule_step(e[gq][0], e[gq][1], e[gq][2], e[gq][3], a, sa, fl, vl);
-      };
+      for (int r0 = 0; r0 < G; r0 += P) {
+        unsigned char* const row = first_row + (i0 + r0) * kRowBytes;
+        Slot q[P][4];
 #pragma unroll
-      for (int gq = 0; gq < NG / 2; ++gq) step(gq);
-      if (ix1 >= n_tot) D1.npos = 0;
-      const __amdgpu_buffer_rsrc_t rs1 = unit_rsrc(D1.stream_off, D1.npos);
-      const uint32_t pair_base1 = lane4 + (uint32_t)(D1.npos >> 3) * 1024u;
-      issue_flags(rs1, D1.npos, fn);
+        for (int r = 0; r < P; ++r)
 #pragma unroll
-      for (int gq = NG / 2; gq < NG; ++gq) {
-        step(gq);
-        issue_granule(rs1, 2 * (gq - NG / 2), en);
-        issue_granule(rs1, 2 * (gq - NG / 2) + 1, en);
-      }
-      {
-        // the positions behind the last full granule; their flags follow those of the granules
-        const int pairs = (D.npos & 7) >> 1;
-        fl = (full < 4) ? (f[0] << (8 * full)) : (f1 << (8 * (full - 4)));
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          if (j < pairs) pair_step(et[j], a, sa, fl, vl);
-          issue_pair(rs1, pair_base1, j, etn);
-        }
-        if (D.npos & 1) single_step(et[3], a, sa, fl, vl);
-        issue_single(rs1, D1.npos, etn);
-      }
-      // What a lane is left with belongs to a segment that goes on in the next lane (or ends with
-      // the unit): it is added to its slot, which by now holds what the lane that saw the end of the
-      // segment has stored there (or zero).  Consecutive lanes without any flag share a slot: their
-      // sums are first added up along the lanes, and the last lane of such a run adds the total.
-      {
-        const bool owner = (nflag > 0) || (lane == 0);
-        const bool has = (a != (AT)0);
-        if (__builtin_amdgcn_ballot_w64(!owner && has) != 0) {
-#pragma unroll
-          for (int d = 1; d < 64; d *= 2) {
-            const AT oa = __shfl_up(a, d);
-            const uint32_t osa = (uint32_t)__shfl_up((int)sa, d);
-            if (lane >= d && osa == sa) a += oa;
-          }
-          const uint32_t nsa = (uint32_t)__shfl_down((int)sa, 1);
-          if (lane == 63 || nsa != sa) *reinterpret_cast<AT*>(lds + sa) += a;
-        } else if (owner) {
-          *reinterpret_cast<AT*>(lds + sa) += a;
-        }
-      }
-
-      // ---- step 2: the low levels of the RSR++ fold on this window ----
-      // lane l holds the values 8l .. 8l+7 of the window: three levels in registers ...
-      AT u[8];
-      {
-        const uint4 x0 = reinterpret_cast<const uint4*>(win)[2 * lane];
-        const uint4 x1 = reinterpret_cast<const uint4*>(win)[2 * lane + 1];
-        const uint32_t raw[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) u[i] = __builtin_bit_cast(AT, raw[i]);
-      }
-      AT total, bit7, bit8;
-      if constexpr (PLAIN) {
-        // u . Bin_[kw] by its definition: for every column (value bit) the sum of bit * u[j] over all j.
-        AT sb[rsr::kMaxWindowBits];
-#pragma unroll
-        for (int bit = 0; bit < rsr::kMaxWindowBits; ++bit) {
-          AT acc = (AT)0;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) acc += (AT)(((8 * lane + i) >> bit) & 1) * u[i];
-          sb[bit] = wave_total<AT>(acc);
-        }
-        AT all = (AT)0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) all += u[i];
-        total = wave_total<AT>(all);  // the window's total, for the value bits above the window
-#pragma unroll
-        for (int bit = 0; bit < 7; ++bit) total = ((lane & 7) == bit) ? sb[bit] : total;  // lanes 0..6 carry the bit sums
-        bit7 = sb[7];
-        bit8 = sb[8];
-      } else {
-      // vals[0..2]: the three levels inside the lane; vals[3..6]: lane bits 0..3 (value bits 3..6);
-      // vals[7]: the lane's total, from which the two row-index bits (value bits 7, 8) and the
-      // window total follow.
-      AT vals[8];
-      const AT s01 = u[0] + u[1], s23 = u[2] + u[3], s45 = u[4] + u[5], s67 = u[6] + u[7];
-      vals[0] = (u[1] + u[3]) + (u[5] + u[7]);  // odd-indexed entries
-      vals[1] = s23 + s67;                      // odd-indexed pair sums
-      vals[2] = s45 + s67;                      // odd-indexed sums of four
-      const AT x = (s01 + s23) + (s45 + s67);
-#pragma unroll
-      for (int beta = 0; beta < 4; ++beta) vals[3 + beta] = ((lane >> beta) & 1) ? x : (AT)0;
-      vals[7] = x;
-      // Sums over the 16 lanes of each row, then across the four rows with lane swaps: total
-      // (all rows), value bit 7 (rows 1 and 3) and value bit 8 (rows 2 and 3).
-      const uint32_t rowsum = __builtin_bit_cast(uint32_t, row_sums_of_eight<AT>(vals, lane));
-      const Swapped h32 = swap32(rowsum);                                              // .x: rows 0,1,0,1  .y: rows 2,3,2,3
-      const AT s02_13 = __builtin_bit_cast(AT, h32.x) + __builtin_bit_cast(AT, h32.y);  // rows 0+2, 1+3, 0+2, 1+3
-      const Swapped t16 = swap16(__builtin_bit_cast(uint32_t, s02_13));                // .x: 0+2 everywhere  .y: 1+3 everywhere
-      const Swapped b16 = swap16(h32.y);                                               // .x: row 2 everywhere  .y: row 3
-      total = __builtin_bit_cast(AT, t16.x) + __builtin_bit_cast(AT, t16.y);
-      bit7 = __builtin_bit_cast(AT, t16.y);
-      bit8 = __builtin_bit_cast(AT, b16.x) + __builtin_bit_cast(AT, b16.y);
-      }
-      // ---- record, and completion of the block: lanes 0..7 finish the sums ----
-      // One store writes the record: lanes 0..6 hold the sums of value bits 0..6, lane 7 the
-      // window's total, lane 15 (second row) bit 7, lane 23 bit 8; lane 31 adds part and window.
-      const int slot = (int)D.block - rb0;
-      {
-        AT val = total;
-        val = (lane == 15) ? bit7 : val;  // lane bit 4 = rows 1 and 3 = value bit 7
-        val = (lane == 23) ? bit8 : val;  // lane bit 5 = rows 2 and 3 = value bit 8
-        val = (lane == 31) ? __builtin_bit_cast(AT, (uint32_t)((D.part << 16) | D.window)) : val;
-        *reinterpret_cast<AT*>(lds + p.off_rec + ix * (rsr::kRecordWords * 4) + rec_lane) = val;
-      }
-      const unsigned before = lds_count_up(p.off_done + (uint32_t)slot * 4u);
-      if ((int)before + 1 == D.units_in_block) {
-        // ---- last unit of the block: remaining fold levels, ternary combine, store ----
-        // Lane (bit + 16 * part) adds up, over the block's units, "sum of u[j] over the values j
-        // with bit `bit` set".  Bits below kw are in the unit records; a higher bit sees only
-        // window totals (the remaining levels of the fold act on the windows' sums).
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // the records were written by this workgroup
-        // (the two halves of the wavefront take every other record, two records per step, so that
-        // four LDS reads are in flight instead of one dependent pair)
-        const int bit = lane & 15, q = (lane >> 4) & 1, half = lane >> 5;
-        const AT* base = rec + (size_t)((int)ix - D.index_in_block) * rsr::kRecordWords;  // the block's units are consecutive
-        const int word = (bit < p.kw) ? bit : 9;
-        auto term = [&](uint32_t meta, AT t) {
-          const bool use = ((int)(meta >> 16) == q) && (bit < p.kw || (((meta & 0xffffu) >> (bit - p.kw)) & 1u));
-          return use ? t : (AT)0;
+          for (int c = 0; c < 4; ++c) q[r][c] = *reinterpret_cast<const Slot*>(row + r * kRowBytes + c * 64 * M::slot_bytes);
+        auto sums = [&](int r, int j, AT d0, AT d1, AT d2, AT d3) {
+          hi[j][0] += d1 + d3;
+          hi[j][1] += d2 + d3;
+          x[r0 + r][j] = (d0 + d1) + (d2 + d3);
+          if constexpr (PLAIN) plain_sums(pl[j], 256 * (i0 + r0 + r) + lane, d0, d1, d2, d3);
         };
-        AT sum_a = (AT)0, sum_b = (AT)0;
-        int j = half;
-        for (; j + 2 < D.units_in_block; j += 4) {
-          const AT* ra = base + (size_t)j * rsr::kRecordWords;
-          const AT* rb = ra + 2 * rsr::kRecordWords;
-          const uint32_t ma = __builtin_bit_cast(uint32_t, ra[10]), mb = __builtin_bit_cast(uint32_t, rb[10]);
-          const AT ta = ra[word], tb = rb[word];
-          sum_a += term(ma, ta);
-          sum_b += term(mb, tb);
+        if (f.both) {  // Proposition 2.1, v.B(1) - v.B(2): the fold is linear in u
+          unsigned char* const row1 = row + (uint32_t)f.pslots * M::slot_bytes;
+          Slot m[P][4];
+#pragma unroll
+          for (int r = 0; r < P; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) m[r][c] = *reinterpret_cast<const Slot*>(row1 + r * kRowBytes + c * 64 * M::slot_bytes);
+          if (!f.fill)
+#pragma unroll
+            for (int r = 0; r < P; ++r)
+#pragma unroll
+              for (int c = 0; c < 4; ++c) *reinterpret_cast<Slot*>(row1 + r * kRowBytes + c * 64 * M::slot_bytes) = Slot{};
+#pragma unroll
+          for (int r = 0; r < P; ++r)
+#pragma unroll
+            for (int j = 0; j < V; ++j)
+              sums(r, j, M::get(q[r][0], j) - M::get(m[r][0], j), M::get(q[r][1], j) - M::get(m[r][1], j),
+                   M::get(q[r][2], j) - M::get(m[r][2], j), M::get(q[r][3], j) - M::get(m[r][3], j));
+        } else {
+#pragma unroll
+          for (int r = 0; r < P; ++r)
+#pragma unroll
+            for (int j = 0; j < V; ++j) sums(r, j, M::get(q[r][0], j), M::get(q[r][1], j), M::get(q[r][2], j), M::get(q[r][3], j));
         }
-        if (j < D.units_in_block) {
-          const AT* ra = base + (size_t)j * rsr::kRecordWords;
-          sum_a += term(__builtin_bit_cast(uint32_t, ra[10]), ra[word]);
-        }
-        // the two halves of the wavefront, then part 1 (second 16-lane row) from part 0: lane swaps
-        const Swapped hs = swap32(__builtin_bit_cast(uint32_t, sum_a + sum_b));
-        const AT sum = __builtin_bit_cast(AT, hs.x) + __builtin_bit_cast(AT, hs.y);
-        const Swapped ps = swap16(__builtin_bit_cast(uint32_t, sum));  // .x: row 0 (part 0), .y: row 1 (part 1)
-        const AT res = __builtin_bit_cast(AT, ps.x) - __builtin_bit_cast(AT, ps.y);  // Proposition 2.1: v.B(1) - v.B(2)
-        // value bit `bit` belongs to column k-1-bit of the block (first column most significant)
-        const int width = ((int)D.block == p.nblocks - 1) ? p.last_width : p.k;
-        const int col = p.k - 1 - bit;
-        if (lane < 16 && bit < p.k && col < width) {
-          AT* dst = outp + (int64_t)D.block * p.k + col;
-          const AT term = p.scaled ? res * __builtin_bit_cast(AT, p.scale) : res;
-          *dst = p.accumulate ? *dst + term : term;  // row tiles add up: the product is linear in the rows
+        if (!f.fill)
+#pragma unroll
+          for (int r = 0; r < P; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) *reinterpret_cast<Slot*>(row + r * kRowBytes + c * 64 * M::slot_bytes) = Slot{};
+        if constexpr (P < G) asm volatile("" ::: "memory");  // (the next steps' reads stay behind: registers)
+      }
+      // (two steps at a time, in this order, for every G: the sums do not depend on how many vectors share a pass)
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        if constexpr (G == 1) {  // a panel of one step
+          tot[j] += x[0][j];
+        } else {
+#pragma unroll
+          for (int r = 0; r < G; r += 2) {
+            const AT g = x[r][j] + x[r + 1][j];
+            hi[j][2] += x[r + 1][j];
+            if (G == 2 ? ((i0 >> 1) & 1) : ((r >> 1) & 1)) hi[j][3] += g;
+            if (G <= 4 ? ((i0 >> 2) & 1) : ((r >> 2) & 1)) hi[j][4] += g;
+            if ((i0 >> 3) & 1) hi[j][5] += g;
+            tot[j] += g;
+          }
         }
       }
-      ix = ix1; D = D1;
     };
-
-    while (ix < n_tot) {
-      unit(eA, tA, fA, eB, tB, fB);
-      if (ix >= n_tot) break;
-      unit(eB, tB, fB, eA, tA, fA);
-      if (ix >= n_tot) break;
+    constexpr int kTogether = PLAIN || M::slot_bytes == 16 ? 2 : V > 1 ? 4 : 8;
+    if (frows % kTogether == 0)
+#pragma unroll 1
+      for (int i = 0; i < frows; i += kTogether) fold_steps.template operator()<kTogether>(i);
+    else if (frows == 1)
+      fold_steps.template operator()<1>(0);
+    else
+#pragma unroll 1
+      for (int i = 0; i < frows; i += 2) fold_steps.template operator()<2>(i);
+    // The further pieces of segments that were cut: lane l takes the extra sums 2l and 2l + 1, which count under the bits of
+    // their segments' values.
+    const uint32_t first_extra = (uint32_t)(f.pslots << f.both) + rsr::kDummySlots;
+    Slot ex[2] = {Slot{}, Slot{}};
+    if (D.extras != 0)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (2u * (uint32_t)lane + i < D.extras) ex[i] = reinterpret_cast<const Slot*>(u)[first_extra + 2 * lane + i];
+    // The panel's room is free again as soon as its sums have been read: LDS operations of a wavefront execute in
+    // order, so they are read, and the slots cleared, before the epoch moves.
+    auto release = [&]() {
+      lds_clear(f.off_cnt + buf * 4u);
+      lds_bump(f.off_epoch + buf * 4u);
+    };
+    const bool more = D.extras > (uint32_t)kExtraAhead;
+    if (!more) release();
+    AT sum[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      AT items[kItems];
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        if constexpr (PLAIN) {
+          items[i] = pl[j][i]; items[6 + i] = pl[j][6 + i];
+        } else {
+          items[i] = ((lane >> i) & 1) ? tot[j] : (AT)0;
+          items[6 + i] = hi[j][i];
+        }
+      }
+      items[kTotal] = tot[j];
+      items[13] = items[14] = items[15] = (AT)0;
+      auto add_extra = [&](uint32_t slot, AT z) {
+        const AT y = f.both && slot >= (uint32_t)f.pslots ? -z : z;
+#pragma unroll
+        for (int i = 0; i < 12; ++i) items[i] += ((slot & (uint32_t)(f.pslots - 1)) >> i) & 1 ? y : (AT)0;
+        items[kTotal] += y;
+      };
+      if (D.extras != 0) {
+        uint32_t pair = extra_pair;
+        asm volatile("" : "+v"(pair));  // (the masks of its bits are taken anew for every vector: scalar registers)
+        add_extra(pair & 0xffffu, M::get(ex[0], j));
+        add_extra(pair >> 16, M::get(ex[1], j));
+        if (more)
+          for (uint32_t e = (uint32_t)kExtraAhead + (uint32_t)lane; e < D.extras; e += 64)
+            add_extra(extra_slots[(size_t)D.panel * f.extra_stride + e], M::get(reinterpret_cast<const Slot*>(u)[first_extra + e], j));
+      }
+      sum[j] = sums_of_sixteen<AT>(items, lane);
     }
-    rb0 = rb1;
-    __syncthreads();
+    if (more) release();
+    // ---- the block: its panels' sums, the parts with their weights, k outputs ----
+    const int blk = (int)D.block;
+    auto put = [&](int bit, int j, AT res) {
+      // value bit `bit` belongs to column k-1-bit of the block (first column most significant)
+      const int width = (blk == f.nblocks - 1) ? f.last_width : f.k;
+      const int col = f.k - 1 - bit;
+      if (lane < 16 && bit < f.k && col < width && j < nv) {
+        AT* dst = out + (int64_t)(b + j) * f.cols + (int64_t)blk * f.k + col;
+        const AT term = f.scaled ? res * __builtin_bit_cast(AT, f.scale) : res;
+        *dst = f.accumulate ? *dst + term : term;  // row tiles add up: the product is linear in the rows
+      }
+    };
+    if (f.nrec == 0) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) put(lane & 15, j, sum[j]);
+    } else {
+      const uint32_t bl = (uint32_t)(blk - blk_begin);
+      const uint32_t earlier = __umulhi(bl, f.rec_magic);  // blocks that have used these records before
+      const uint32_t ring = bl - earlier * (uint32_t)f.nrec;
+      while (uniform(lds_load(f.off_blocks + ring * 4u)) < earlier) __builtin_amdgcn_s_sleep(1);
+      AT* rec = reinterpret_cast<AT*>(lds + f.off_rec) + (size_t)ring * f.panels * V * kItems;
+      const int mine = (int)(D.panel - D.block * (uint32_t)f.panels);
+      if (lane < kItems)
+#pragma unroll
+        for (int j = 0; j < V; ++j) rec[(mine * V + j) * kItems + lane] = sum[j];
+      const uint32_t before = lds_count_up(f.off_done + ring * 4u);
+      if ((int)before + 1 == f.panels) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        // The four rows of 16 lanes take every fourth panel.  Bits below kc are in the records; a higher bit sees
+        // only the totals of the panels whose values have it (the remaining levels of the fold).
+        const int bit = lane & 15, word = bit < f.kc ? bit : kTotal;
+        const int wbits = f.k - f.kc;  // panel = part << wbits | window
+        AT acc[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc[j] = (AT)0;
+        for (int pi = lane >> 4; pi < f.panels; pi += 4) {
+          const int part = pi >> wbits, window = pi & ((1 << wbits) - 1);
+          const int w = 1 << (part * f.wshift + f.wfirst);
+          const bool use = bit < f.kc || ((window >> (bit - f.kc)) & 1);
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            const AT t = rec[(pi * V + j) * kItems + word] * (AT)(part == f.wneg ? -w : w);
+            acc[j] += use ? t : (AT)0;
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+          const Swapped hs = swap32(__builtin_bit_cast(uint32_t, acc[j]));
+          const AT two = __builtin_bit_cast(AT, hs.x) + __builtin_bit_cast(AT, hs.y);
+          const Swapped qs = swap16(__builtin_bit_cast(uint32_t, two));
+          put(bit, j, __builtin_bit_cast(AT, qs.x) + __builtin_bit_cast(AT, qs.y));
+        }
+        lds_clear(f.off_done + ring * 4u);
+        lds_bump(f.off_blocks + ring * 4u);
+      }
+    }
+  };
+
+  // One unit from buffer (e, et); the next unit's stream goes into (en, etn) meanwhile.
+  auto unit = [&](uint32_t (&e)[NG][4], uint32_t (&et)[3], uint32_t (&en)[NG][4], uint32_t (&etn)[3]) {
+    const bool listed = ix1 < ndesc;
+    uint4 d0 = make_uint4(0, 0, 0, 0);
+    uint2 d1 = make_uint2(0, 0);
+    if (listed) {
+      d0 = *reinterpret_cast<const uint4*>(lds + p.off_desc + ix1 * 32u);
+      d1 = *reinterpret_cast<const uint2*>(lds + p.off_desc + ix1 * 32u + 16u);
+    }
+    // Panel P of the workgroup uses buffer P mod nbuf, and may start when the sums of panel P - nbuf have been read.  (Units
+    // are handed out in panel order and a wavefront sums its units in order, so the oldest unit in flight never waits:
+    // no deadlock.)
+    const uint32_t panel = D.panel - panel_begin;
+    const uint32_t turn = p.nbuf == 1 ? 0u : __umulhi(panel, p.buf_magic);
+    const uint32_t buf = panel - turn * (uint32_t)p.nbuf;
+    const uint32_t ubase = p.off_u + buf * p.ubytes;
+    if (turn != 0 && panel != open_panel) {
+      while (uniform(lds_load(p.off_epoch + buf * 4u)) < turn) __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      open_panel = panel;
+    }
+
+    // The slots of the panel's extra sums, two per lane, in case this unit is the panel's last: requested here, ahead of the
+    // next unit's stream, they are there when the fold wants them.
+    const uint16_t* const extra_list = extra_slots + (size_t)D.panel * p.extra_stride;
+    const __amdgpu_buffer_rsrc_t rsx =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(extra_list), 0, (int)((min(D.extras, (uint32_t)kExtraAhead) + 1u) / 2u * 4u), 0x00020000);
+    const uint32_t extra_pair = __builtin_amdgcn_raw_buffer_load_b32(rsx, (int)lane4, 0, 0);
+    // ---- step 1: segmented sums (Eq. SS2) into the panel's slots (u of Algorithm 2) ----
+    typename M::Run acc[M::R];
+#pragma unroll
+    for (int j = 0; j < M::R; ++j) acc[j] = 0;
+    const uint32_t full = D.npos >> 3;
+    auto step = [&](int gq) {
+      const uint32_t hm = gq < 4 ? D.heads_lo >> (8 * gq) : D.heads_hi >> (8 * (gq - 4));
+      if ((uint32_t)gq < full) M::step8(e[gq][0], e[gq][1], e[gq][2], e[gq][3], acc, hm, D.wide, ubase);
+    };
+#pragma unroll
+    for (int gq = 0; gq < NG / 2; ++gq) step(gq);
+    // (the next unit's descriptor has arrived by now; its loads go out one by one between the later steps: a
+    // wavefront that issues a whole unit at once waits for room in the memory pipeline while it could be summing)
+    Desc D1;
+    if (listed) D1 = make_desc(uniform(d0.x), uniform(d0.y), uniform(d0.z), uniform(d0.w), uniform(d1.x), uniform(d1.y));
+    else D1 = load_desc(unit_words, ix1 < n_tot ? u_begin + ix1 : 0u);  // past the end it reads unit 0 (unused)
+    if (ix1 >= n_tot) D1.npos = 0;
+    const __amdgpu_buffer_rsrc_t rs1 = unit_rsrc(D1.stream_off, D1.npos);
+    const uint32_t pair_base1 = lane4 + (D1.npos >> 3) * 1024u;
+#pragma unroll
+    for (int gq = NG / 2; gq < NG; ++gq) {
+      step(gq);
+      issue_granule(rs1, 2 * (gq - NG / 2), en);
+      issue_granule(rs1, 2 * (gq - NG / 2) + 1, en);
+    }
+    {
+      // the positions behind the last full granule, always six: a row that the unit does not have is read as row 0
+      // and added to sums that no head stores
+      const uint32_t hm = (full < 4 ? D.heads_lo >> (8 * full) : D.heads_hi >> (8 * (full - 4)));
+      if (D.npos & 7) M::step6(et[0], et[1], et[2], acc, hm, D.wide, ubase);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) issue_pair(rs1, pair_base1, j, etn);
+    }
+    // The wavefront reserves the unit after the next only now: the last units then go to the wavefronts that get there
+    // first.
+    uint32_t before, ix2;
+    lds_count_up(p.off_cnt + buf * 4u, p.off_ctr, before, ix2);
+    if (before + 1 == D.units_in_panel) fold(D, buf, ubase, extra_pair);
+    ix = ix1; ix1 = ix2; D = D1;
+  };
+
+  while (ix < n_tot) {
+    unit(eA, tA, eB, tB);
+    if (ix >= n_tot) break;
+    unit(eB, tB, eA, tA);
   }
 }
 
-template <typename VT, bool PLAIN>
+template <class M, bool PLAIN>
 __global__ void __launch_bounds__(1024)
 rsr_matvec_kernel(const unsigned char* __restrict__ stream, const uint32_t* __restrict__ unit_words,
-                  const uint32_t* __restrict__ blk_unit, const VT* __restrict__ vin,
-                  typename Acc<VT>::type* __restrict__ out, const KArgs p) {
-  rsr_body<VT, PLAIN>(stream, unit_words, blk_unit, vin, out, p, (int)blockIdx.x);
+                  const uint32_t* __restrict__ blk_unit, const uint16_t* __restrict__ extra_slots, const typename M::In* __restrict__ vin,
+                  typename M::Acc* __restrict__ out, const KArgs) {
+  rsr_body<M, PLAIN>(stream, unit_words, blk_unit, extra_slots, vin, out, args_at(6 * sizeof(void*)), (int)blockIdx.x);
 }
 
 // Several products in one launch (rsr_matvec_multi): every product owns a range of workgroups and
@@ -768,6 +1071,7 @@ struct KJob {
   const unsigned char* stream;
   const uint32_t* unit_words;
   const uint32_t* blk_unit;
+  const uint16_t* extra_slots;
   const void* vin;
   void* out;
   int wg_begin;  // first workgroup of this product
@@ -780,7 +1084,7 @@ struct MultiArgs {
   KJob job[kMaxJobs];
 };
 
-template <typename VT>
+template <class M>
 __global__ void __launch_bounds__(1024) rsr_multi_kernel(const MultiArgs m) {
   int j = 0;
 #pragma unroll
@@ -788,8 +1092,9 @@ __global__ void __launch_bounds__(1024) rsr_multi_kernel(const MultiArgs m) {
     if (i < m.njobs && (int)blockIdx.x >= m.job[i].wg_begin) j = i;
   // (selected with a wavefront-uniform index: the arguments stay in scalar registers)
   const KJob& J = m.job[j];
-  rsr_body<VT, false>(J.stream, J.unit_words, J.blk_unit, static_cast<const VT*>(J.vin),
-               static_cast<typename Acc<VT>::type*>(J.out), J.p, (int)blockIdx.x - J.wg_begin);
+  rsr_body<M, false>(J.stream, J.unit_words, J.blk_unit, J.extra_slots, static_cast<const typename M::In*>(J.vin),
+                     static_cast<typename M::Acc*>(J.out), args_at(offsetof(MultiArgs, job) + (size_t)uniform((uint32_t)j) * sizeof(KJob) + offsetof(KJob, p)),
+                     (int)blockIdx.x - J.wg_begin);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -804,45 +1109,43 @@ struct LaunchPlan {
   size_t lds = 0;
 };
 
-// Launch shape of one row tile for `batch` vectors on `num_cu` compute units.
+// x / d for small x as the high half of a product (d >= 2)
+uint32_t magic(uint32_t d) { return d < 2 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+
+// Launch shape of one row tile for `batch` vectors on `num_cu` compute units in mode M.
 // `max_wg_per_cu`: how many workgroups of this product may share a compute unit (a launch that carries
 // several products gives every workgroup the largest LDS size any of them needs, so it plans with 1).
-template <typename VT>
+// Returns RSR_ERR_UNSUPPORTED (without a message) if the mode does not fit in LDS.
+template <class M>
 int plan_tile(const rsr_handle* h, const DeviceTile& T, bool accumulate, int batch, int num_cu, int max_wg_per_cu, LaunchPlan* plan) {
   KArgs& p = plan->p;
   std::memset(&p, 0, sizeof(p));
-  p.rows = (int)T.rows; p.cols = (int)h->cols; p.k = h->k; p.kw = h->kw; p.parts = h->parts;
+  const rsr::Shape& S = T.shape;
+  p.rows = (int)T.rows; p.cols = (int)h->cols; p.k = h->k;
   p.nblocks = (int)h->nblocks; p.last_width = h->last_width; p.batch = batch;
   p.vstride = (int)h->rows; p.row0 = (int)T.row0; p.accumulate = accumulate ? 1 : 0;
+  p.kc = S.kc; p.both = S.both; p.pslots = S.pslots; p.panels = S.panels;
+  p.fill = T.fill ? 1 : 0; p.extra_stride = T.extra_stride;
+  p.wshift = h->qbit ? 1 : 0; p.wfirst = h->first_plane; p.wneg = h->negative_part;
+  p.nunits = (int)T.nunits;
 
-  // LDS budget: activation vector + per-wavefront windows + unit records + counters
-  const size_t vbytes = align_up(((size_t)T.rows + 1) * sizeof(VT), 16);
-  const size_t win_bytes = (size_t)rsr::kWindow * 4;
-  const size_t rec_bytes = (size_t)rsr::kRecordWords * 4;
-  int nslot = 64;
-  // Unit records of a round: room for wavefronts comes first, then as many records as fit (a round
-  // ends with a barrier); a block's units always fit in a round.
-  size_t ucap = 0;
-  int waves = 0;
-  auto total = [&](int w, size_t uc) { return vbytes + (size_t)w * win_bytes + uc * rec_bytes + (size_t)nslot * 4 + 16 + ((size_t)nslot + 1) * 4 + 12; };
-  for (size_t cand : {(size_t)512, (size_t)256, (size_t)128, (size_t)64, (size_t)1}) {
-    const size_t uc = std::max<size_t>(T.max_units_per_block, cand);
-    int w = h->waves;
-    while (w > 1 && total(w, uc) > h->lds_max) --w;
-    if (total(w, uc) <= h->lds_max && w > waves) { waves = w; ucap = uc; }
-  }
-  if (waves == 0)
-    return fail(RSR_ERR_UNSUPPORTED, "a row tile of " + std::to_string(T.rows) + " rows with " + std::to_string(T.max_units_per_block) +
-                                         " work units in a column block does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
+  // LDS: activations, panels in flight, records of the blocks in flight, counters
+  const size_t vbytes = align_up((size_t)(T.rows + 1) << M::shift, 16);
+  p.ubytes = (uint32_t)((size_t)(S.nslots + rsr::kDummySlots + (T.max_extras + 7) / 8 * 8) * M::slot_bytes);
+  const bool records = S.panels > 1 || h->qbit;
+  const size_t rec_bytes = (size_t)S.panels * M::V * kItems * 4;
+  auto recs = [&](int nbuf) { return records ? 1 + (nbuf - 1 + S.panels - 1) / S.panels : 0; };
+  auto total = [&](int nbuf) { return vbytes + (size_t)nbuf * p.ubytes + (size_t)recs(nbuf) * (rec_bytes + 8) + (size_t)nbuf * 8 + 16; };
   // Grid and workgroup size.  Up to four workgroups per compute unit if they fit together (LDS, and 16
   // wavefronts per compute unit at this kernel's register count); never more workgroups than blocks; and
   // no more wavefronts than the largest share of a workgroup has units: idle wavefronts only lengthen
   // the start of the launch (1024 x 1024: 5.5 -> 4.0 us per product).
-  const int waves_fit = waves;
-  const size_t ucap_fit = ucap;
+  const int64_t sets = ((int64_t)batch + M::V - 1) / M::V;
   int64_t g1 = 1;
+  int waves = 0, nbuf = 0, wgs = 1;
   for (int wg = max_wg_per_cu; wg >= 1; --wg) {
-    g1 = ((int64_t)num_cu * wg + batch - 1) / batch;
+    wgs = wg;
+    g1 = ((int64_t)num_cu * wg + sets - 1) / sets;
     g1 = (g1 + 7) / 8 * 8;
     if (g1 > h->nblocks) g1 = h->nblocks;
     if (g1 < 1) g1 = 1;
@@ -853,44 +1156,143 @@ int plan_tile(const rsr_handle* h, const DeviceTile& T, bool accumulate, int bat
     // workgroups with the larger share finish last either way, only later when more of them compete.)
     g1 = (h->nblocks + blocks_per_wg - 1) / blocks_per_wg;
     const int64_t units_per_wg = blocks_per_wg * (int64_t)std::max<uint32_t>(1, T.max_units_per_block);
-    waves = (int)std::min<int64_t>(waves_fit, units_per_wg);
-    ucap = std::min<size_t>(ucap_fit, (size_t)units_per_wg);  // records for the units a workgroup can have
-    if (wg == 1 || (wg * waves <= 16 && (size_t)wg * total(waves, ucap) <= h->lds_max)) break;
+    waves = (int)std::min<int64_t>(h->waves, units_per_wg);
+    // Up to eight panels in flight where the LDS holds them (a wavefront whose unit belongs to a later panel waits).
+    const int64_t panels_per_wg = blocks_per_wg * S.panels;
+    const int most = (int)std::min<int64_t>(8, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
+    for (nbuf = most; nbuf > least && (total(nbuf) > h->lds_max || (wg > 1 && (size_t)wg * total(nbuf) > h->lds_max)); --nbuf) {}
+    if (total(nbuf) > h->lds_max) return RSR_ERR_UNSUPPORTED;
+    if (wg == 1 || (wg * waves <= 16 && (size_t)wg * total(nbuf) <= h->lds_max)) break;
   }
   p.g1 = (int)g1;
-  const int64_t grid = (g1 + 7) / 8 * 8 * (int64_t)batch;
+  const int64_t grid = (g1 + 7) / 8 * 8 * sets;
   if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
 
-  plan->lds = total(waves, ucap);
+  // what is left of the LDS (of a share of it where several workgroups are meant to fit) holds descriptors of the units
+  const size_t share = std::max(total(nbuf), h->lds_max / (size_t)wgs);
+  const size_t want = (size_t)((h->nblocks + g1 - 1) / g1) * std::max<uint32_t>(1, T.max_units_per_block);
+  const size_t used = align_up(total(nbuf), 16);
+  p.ndesc = share > used ? (uint32_t)std::min<size_t>(want, (share - used) / 32) : 0;
+  if (want <= (size_t)waves) p.ndesc = 0;
+  p.off_desc = (uint32_t)used;
+  plan->lds = p.ndesc ? used + (size_t)p.ndesc * 32 : total(nbuf);
   plan->grid = grid;
   plan->waves = waves;
   p.waves = waves;
-  p.ucap = (int)ucap; p.nslot = nslot;
-  p.off_win = (uint32_t)vbytes;
-  p.off_rec = (uint32_t)(vbytes + (size_t)waves * win_bytes);
-  p.off_done = (uint32_t)(p.off_rec + ucap * rec_bytes);
-  p.off_ctr = (uint32_t)(p.off_done + (size_t)nslot * 4);
-  p.off_bu = p.off_ctr + 16;
-  p.nunits = (int)T.nunits;
+  p.nbuf = nbuf; p.buf_magic = magic((uint32_t)nbuf);
+  p.nrec = recs(nbuf); p.rec_magic = magic((uint32_t)p.nrec);
+  p.off_u = (uint32_t)vbytes;
+  p.off_rec = (uint32_t)(vbytes + (size_t)nbuf * p.ubytes);
+  p.off_done = (uint32_t)(p.off_rec + (size_t)p.nrec * rec_bytes);
+  p.off_blocks = p.off_done + (uint32_t)p.nrec * 4;
+  p.off_cnt = p.off_blocks + (uint32_t)p.nrec * 4;
+  p.off_epoch = p.off_cnt + (uint32_t)nbuf * 4;
+  p.off_ctr = p.off_epoch + (uint32_t)nbuf * 4;
   return RSR_OK;
 }
 
-template <typename VT>
-int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const VT* v, void* out, int batch, void* stream) {
+// How many vectors share a pass: the most for which a workgroup's wavefronts do not wait for room.  A unit of the stream
+// keeps its share of a panel's sums in LDS from its start until the panel is folded, about one and a half times as long as it
+// is summed: with sums of fewer than kRoom units in flight wavefronts stand still.  (sixteen vectors at 2560 x 7680, k = 10:
+// room for 14 units with four vectors per pass, 34 with two.)
+enum class Mode { one, two, four };
+constexpr int kRoom = 24;
+template <class M>
+bool mode_fits(const rsr_handle* h, const DeviceTile& T, int batch) {
   LaunchPlan plan;
-  const int rc = plan_tile<VT>(h, T, accumulate, batch, h->num_cu, 4, &plan);
+  if (plan_tile<M>(h, T, false, batch, h->num_cu, 1, &plan) != RSR_OK) return false;
+  const int64_t panels = h->nblocks * T.shape.panels, per_wg = (h->nblocks + plan.p.g1 - 1) / plan.p.g1 * T.shape.panels;
+  return plan.p.nbuf >= per_wg || plan.p.nbuf * T.nunits >= kRoom * panels;
+}
+// A pass over V vectors costs a wavefront `cost` times as much as a pass over one, and launches with less than a unit per
+// wavefront of the device take as long as one unit does: few units are better spread out, a vector per pass.
+// `units`: of all products that share the launch.
+double pass_cost(int64_t units, int num_cu, int waves, int batch, int V, double cost) {
+  return cost * std::max(1.0, (double)units * ((batch + V - 1) / V) / ((double)num_cu * waves));
+}
+Mode pick_mode(const rsr_handle* h, const DeviceTile& T, int batch, int64_t units, const float*) {
+  if (h->step2_plain || batch < 2) return Mode::one;
+  const double c1 = pass_cost(units, h->num_cu, h->waves, batch, 1, 1.0), c2 = pass_cost(units, h->num_cu, h->waves, batch, 2, 1.4);
+  const double c4 = pass_cost(units, h->num_cu, h->waves, batch, 4, 2.2);
+  if (c4 < c2 && c4 < c1 && mode_fits<F4>(h, T, batch)) return Mode::four;
+  return c2 < c1 && mode_fits<F2>(h, T, batch) ? Mode::two : Mode::one;
+}
+Mode pick_mode(const rsr_handle* h, const DeviceTile& T, int batch, int64_t units, const int8_t*) {
+  if (h->step2_plain || batch < 2) return Mode::one;
+  const double c1 = pass_cost(units, h->num_cu, h->waves, batch, 1, 1.0), c2 = pass_cost(units, h->num_cu, h->waves, batch, 2, 1.1);
+  const double c4 = pass_cost(units, h->num_cu, h->waves, batch, 4, 1.5);
+  if (c4 < c2 && c4 < c1 && mode_fits<P4>(h, T, batch)) return Mode::four;
+  return c2 < c1 ? Mode::two : Mode::one;  // (two need no more LDS than one)
+}
+
+template <class M, bool PLAIN>
+int launch_mode(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const typename M::In* v, void* out, int batch,
+                void* stream) {
+  LaunchPlan plan;
+  const int rc = plan_tile<M>(h, T, accumulate, batch, h->num_cu, 4, &plan);
+  if (rc == RSR_ERR_UNSUPPORTED) return fail(rc, "a row tile of " + std::to_string(T.rows) + " rows does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
   if (rc != RSR_OK) return rc;
   if (scale) { plan.p.scaled = 1; plan.p.scale = *scale; }
-  auto kern = h->step2_plain ? rsr_matvec_kernel<VT, true> : rsr_matvec_kernel<VT, false>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)plan.grid), dim3((unsigned)(plan.waves * 64)), plan.lds, static_cast<hipStream_t>(stream),
-                     static_cast<const unsigned char*>(T.d_stream), static_cast<const uint32_t*>(T.d_units), static_cast<const uint32_t*>(T.d_blk_unit), v,
-                     static_cast<typename Acc<VT>::type*>(out), plan.p);
+  hipLaunchKernelGGL((rsr_matvec_kernel<M, PLAIN>), dim3((unsigned)plan.grid), dim3((unsigned)(plan.waves * 64)), plan.lds,
+                     static_cast<hipStream_t>(stream), static_cast<const unsigned char*>(T.d_stream), static_cast<const uint32_t*>(T.d_units),
+                     static_cast<const uint32_t*>(T.d_blk_unit), static_cast<const uint16_t*>(T.d_extras), v,
+                     static_cast<typename M::Acc*>(out), plan.p);
   RSR_HIP_TRY(hipGetLastError());
   return RSR_OK;
 }
 
+int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const float* v, void* out, int batch, void* stream) {
+  if (h->step2_plain) return launch_mode<F1, true>(h, T, accumulate, scale, v, out, batch, stream);
+  switch (pick_mode(h, T, batch, T.nunits, v)) {
+    case Mode::four: return launch_mode<F4, false>(h, T, accumulate, scale, v, out, batch, stream);
+    case Mode::two: return launch_mode<F2, false>(h, T, accumulate, scale, v, out, batch, stream);
+    default: return launch_mode<F1, false>(h, T, accumulate, scale, v, out, batch, stream);
+  }
+}
+int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const int8_t* v, void* out, int batch, void* stream) {
+  if (h->step2_plain) return launch_mode<I1, true>(h, T, accumulate, scale, v, out, batch, stream);
+  switch (pick_mode(h, T, batch, T.nunits, v)) {
+    case Mode::four: return launch_mode<P4, false>(h, T, accumulate, scale, v, out, batch, stream);
+    case Mode::two: return launch_mode<P2, false>(h, T, accumulate, scale, v, out, batch, stream);
+    default: return launch_mode<I1, false>(h, T, accumulate, scale, v, out, batch, stream);
+  }
+}
+
 // Several products as one launch: the compute units are shared out in proportion to the bytes of the
 // products' tables; every product is then planned as if it had its share of the device to itself.
+template <class M>
+int launch_multi_mode(const rsr_job* jobs, int njobs, int batch, void* stream, const int* share) {
+  MultiArgs m;
+  std::memset(&m, 0, sizeof(m));
+  m.njobs = njobs;
+  int64_t grid = 0;
+  int waves = 1;
+  size_t lds = 0;
+  for (int j = 0; j < njobs; ++j) {
+    rsr_handle* h = jobs[j].h;
+    const DeviceTile& T = h->tiles[0];
+    LaunchPlan plan;
+    const int rc = plan_tile<M>(h, T, false, batch, std::min(share[j], h->num_cu), 1, &plan);
+    if (rc == RSR_ERR_UNSUPPORTED) return fail(rc, "a row tile of " + std::to_string(T.rows) + " rows does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
+    if (rc != RSR_OK) return rc;
+    KJob& J = m.job[j];
+    J.stream = static_cast<const unsigned char*>(T.d_stream);
+    J.unit_words = static_cast<const uint32_t*>(T.d_units);
+    J.blk_unit = static_cast<const uint32_t*>(T.d_blk_unit);
+    J.extra_slots = static_cast<const uint16_t*>(T.d_extras);
+    J.vin = jobs[j].v; J.out = jobs[j].out;
+    J.wg_begin = (int)grid;
+    J.p = plan.p;
+    grid += plan.grid;  // (a multiple of 8: every product starts on the first XCD of the round-robin)
+    waves = std::max(waves, plan.waves);
+    lds = std::max(lds, plan.lds);
+    if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
+  }
+  hipLaunchKernelGGL(rsr_multi_kernel<M>, dim3((unsigned)grid), dim3((unsigned)(waves * 64)), lds, static_cast<hipStream_t>(stream), m);
+  RSR_HIP_TRY(hipGetLastError());
+  return RSR_OK;
+}
+
 template <typename VT>
 int launch_multi(const rsr_job* jobs, int njobs, int batch, void* stream) {
   if (!jobs || njobs < 1) return fail(RSR_ERR_INVALID_ARGUMENT, "no jobs");
@@ -904,12 +1306,6 @@ int launch_multi(const rsr_job* jobs, int njobs, int batch, void* stream) {
     if (jobs[j].h->device != jobs[0].h->device) return fail(RSR_ERR_INVALID_ARGUMENT, "the handles belong to different devices");
     bytes_total += (double)jobs[j].h->stream_bytes + 1.0;
   }
-  MultiArgs m;
-  std::memset(&m, 0, sizeof(m));
-  m.njobs = njobs;
-  int64_t grid = 0;
-  int waves = 1;
-  size_t lds = 0;
   const int num_cu = jobs[0].h->num_cu;
   // shares in multiples of 8 compute units (one per XCD), at least 8, together no more than the device has
   // (a workgroup that has to wait for a free compute unit would start when the others are nearly done)
@@ -931,27 +1327,19 @@ int launch_multi(const rsr_job* jobs, int njobs, int batch, void* stream) {
       if ((double)jobs[j].h->stream_bytes / share[j] > (double)jobs[best].h->stream_bytes / share[best]) best = j;
     share[best] += 8; given += 8;
   }
-  for (int j = 0; j < njobs; ++j) {
-    rsr_handle* h = jobs[j].h;
-    LaunchPlan plan;
-    const int rc = plan_tile<VT>(h, h->tiles[0], false, batch, std::min(share[j], num_cu), 1, &plan);
-    if (rc != RSR_OK) return rc;
-    KJob& J = m.job[j];
-    J.stream = static_cast<const unsigned char*>(h->tiles[0].d_stream);
-    J.unit_words = static_cast<const uint32_t*>(h->tiles[0].d_units);
-    J.blk_unit = static_cast<const uint32_t*>(h->tiles[0].d_blk_unit);
-    J.vin = jobs[j].v; J.out = jobs[j].out;
-    J.wg_begin = (int)grid;
-    J.p = plan.p;
-    grid += plan.grid;  // (a multiple of 8: every product starts on the first XCD of the round-robin)
-    waves = std::max(waves, plan.waves);
-    lds = std::max(lds, plan.lds);
-    if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
+  Mode mode = Mode::four;  // the widest that suits every product
+  int64_t units = 0;
+  for (int j = 0; j < njobs; ++j) units += jobs[j].h->nunits;
+  for (int j = 0; j < njobs; ++j) mode = std::min(mode, pick_mode(jobs[j].h, jobs[j].h->tiles[0], batch, units, static_cast<const VT*>(nullptr)));
+  if constexpr (sizeof(VT) == 4) {
+    if (mode == Mode::four) return launch_multi_mode<F4>(jobs, njobs, batch, stream, share);
+    if (mode == Mode::two) return launch_multi_mode<F2>(jobs, njobs, batch, stream, share);
+    return launch_multi_mode<F1>(jobs, njobs, batch, stream, share);
+  } else {
+    if (mode == Mode::four) return launch_multi_mode<P4>(jobs, njobs, batch, stream, share);
+    if (mode == Mode::two) return launch_multi_mode<P2>(jobs, njobs, batch, stream, share);
+    return launch_multi_mode<I1>(jobs, njobs, batch, stream, share);
   }
-  auto kern = rsr_multi_kernel<VT>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)(waves * 64)), lds, static_cast<hipStream_t>(stream), m);
-  RSR_HIP_TRY(hipGetLastError());
-  return RSR_OK;
 }
 
 // One launch per row tile, in order, on the caller's stream: the first overwrites `out`, the others add.
@@ -963,7 +1351,7 @@ int launch(rsr_handle* h, const VT* v, void* out, int batch, void* stream, const
   if (batch < 1) return fail(RSR_ERR_INVALID_ARGUMENT, "batch must be >= 1");
   if (batch > 65535) return fail(RSR_ERR_INVALID_ARGUMENT, "batch must be <= 65535");
   for (size_t t = 0; t < h->tiles.size(); ++t) {
-    const int rc = launch_tile<VT>(h, h->tiles[t], t > 0 || scale != nullptr, scale, v, out, batch, stream);
+    const int rc = launch_tile(h, h->tiles[t], t > 0 || scale != nullptr, scale, v, out, batch, stream);
     if (rc != RSR_OK) return rc;
   }
   return RSR_OK;
@@ -971,132 +1359,151 @@ int launch(rsr_handle* h, const VT* v, void* out, int batch, void* stream, const
 
 void free_tables(rsr_handle* h) {
   for (DeviceTile& T : h->tiles) {
-    if (T.d_stream) (void)hipFree(T.d_stream);
-    if (T.d_units) (void)hipFree(T.d_units);
-    if (T.d_blk_unit) (void)hipFree(T.d_blk_unit);
-    T.d_stream = T.d_units = T.d_blk_unit = nullptr;
+    if (T.d_tables) (void)hipFree(T.d_tables);
+    T = DeviceTile();
   }
 }
 
-int upload(DeviceTile* T, const rsr::Packed& P) {
-  T->stream_bytes = P.stream.size() * sizeof(uint16_t);
-  T->unit_bytes = P.units.size() * sizeof(rsr::Unit);
-  T->blk_bytes = P.blk_unit.size() * sizeof(uint32_t);
-  RSR_HIP_TRY(hipMalloc(&T->d_stream, T->stream_bytes + 1024));
-  RSR_HIP_TRY(hipMalloc(&T->d_units, T->unit_bytes + 32));
-  RSR_HIP_TRY(hipMalloc(&T->d_blk_unit, T->blk_bytes + 16));
-  RSR_HIP_TRY(hipMemset(static_cast<unsigned char*>(T->d_stream) + T->stream_bytes, 0, 1024));
-  if (T->stream_bytes) RSR_HIP_TRY(hipMemcpy(T->d_stream, P.stream.data(), T->stream_bytes, hipMemcpyHostToDevice));
-  if (T->unit_bytes) RSR_HIP_TRY(hipMemcpy(T->d_units, P.units.data(), T->unit_bytes, hipMemcpyHostToDevice));
-  RSR_HIP_TRY(hipMemcpy(T->d_blk_unit, P.blk_unit.data(), T->blk_bytes, hipMemcpyHostToDevice));
-  RSR_HIP_TRY(hipDeviceSynchronize());
-  return RSR_OK;
+// A handle for the matrix at A (DEVICE).  plane0 < 0: parts = 1 or 2; otherwise the bit planes plane0 .. plane0 + parts - 1
+// of entries with q bits.
+rsr_handle* make_handle(const int8_t* A, int64_t rows, int64_t cols, int k, int parts, int plane0, int q, const char* who) {
+  std::unique_ptr<rsr_handle> h(new (std::nothrow) rsr_handle());
+  if (!h) { fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory"); return nullptr; }
+  hipError_t e = hipGetDevice(&h->device);
+  int cu = 0, lds = 0;
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, h->device);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device);
+  if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string(who) + ": " + hipGetErrorString(e)); return nullptr; }
+  h->num_cu = cu;
+  h->lds_max = (size_t)lds;
+  h->rows = rows; h->cols = cols; h->k = k; h->parts = parts;
+  h->qbit = plane0 >= 0;
+  h->first_plane = plane0 > 0 ? plane0 : 0;
+  h->negative_part = plane0 < 0 ? (parts == 2 ? 1 : -1) : (plane0 + parts == q ? parts - 1 : -1);
+  h->nblocks = (cols + k - 1) / k;
+  h->last_width = (int)(cols - (h->nblocks - 1) * k);
+  // the kernels may use the whole LDS of a compute unit as dynamic shared memory
+  for (const void* kern : {reinterpret_cast<const void*>(rsr_matvec_kernel<F1, false>), reinterpret_cast<const void*>(rsr_matvec_kernel<F2, false>),
+                           reinterpret_cast<const void*>(rsr_matvec_kernel<F4, false>), reinterpret_cast<const void*>(rsr_matvec_kernel<I1, false>),
+                           reinterpret_cast<const void*>(rsr_matvec_kernel<P2, false>), reinterpret_cast<const void*>(rsr_matvec_kernel<P4, false>), reinterpret_cast<const void*>(rsr_matvec_kernel<F1, true>),
+                           reinterpret_cast<const void*>(rsr_matvec_kernel<I1, true>), reinterpret_cast<const void*>(rsr_multi_kernel<F1>),
+                           reinterpret_cast<const void*>(rsr_multi_kernel<F2>), reinterpret_cast<const void*>(rsr_multi_kernel<F4>),
+                           reinterpret_cast<const void*>(rsr_multi_kernel<I1>), reinterpret_cast<const void*>(rsr_multi_kernel<P2>),
+                           reinterpret_cast<const void*>(rsr_multi_kernel<P4>)}) {
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e)); return nullptr; }
+  }
+  const int64_t ntiles = (rows + rsr::kTileRows - 1) / rsr::kTileRows;
+  // equal heights, multiples of 16 rows (a tile's share of an activation vector stays 16-byte aligned)
+  const int64_t height = ((rows + ntiles - 1) / ntiles + 15) / 16 * 16;
+  std::string err;
+  for (int64_t t = 0; t < ntiles; ++t) {
+    const int64_t r0 = t * height, r1 = std::min(rows, r0 + height);
+    rsr_internal::BuiltTile B;
+    int rc;
+    try {
+      h->tiles.reserve((size_t)ntiles);
+      rc = rsr_internal::device_build_tile(A + r0 * cols, r1 - r0, cols, cols, k, parts, plane0, &B, &err);
+    } catch (const std::bad_alloc&) {
+      rc = RSR_ERR_OUT_OF_MEMORY; err = "out of host memory";
+    }
+    if (rc != 0) { free_tables(h.get()); fail(rc, std::string(who) + ": " + err); return nullptr; }
+    DeviceTile T;
+    T.rows = r1 - r0; T.row0 = r0;
+    T.shape = B.shape; T.extra_stride = B.extra_stride; T.max_extras = B.max_extras; T.fill = B.fill;
+    T.max_units_per_block = B.max_units_per_block; T.nunits = B.nunits;
+    T.stream_bytes = B.stream_bytes; T.unit_bytes = B.unit_bytes; T.blk_bytes = B.blk_bytes; T.extra_bytes = B.extra_bytes;
+    T.d_tables = B.d_tables;
+    T.d_stream = B.d_stream; T.d_units = B.d_units; T.d_blk_unit = B.d_blk_unit; T.d_extras = B.d_extras;
+    h->tiles.push_back(T);
+    h->stored_rows += B.stored_rows; h->segments += B.segments; h->nunits += B.nunits;
+    h->head_bytes += B.head_bytes; h->stream_bytes += (int64_t)B.stream_bytes;
+    h->schedule_bytes += (int64_t)(B.unit_bytes + B.blk_bytes + B.extra_bytes);
+  }
+  h->magic = kMagic;
+  return h.release();
 }
 
+bool valid_shape(const void* A, int64_t rows, int64_t cols, int k, const char* who) {
+  const std::string at = std::string(who) + ": ";
+  if (!A) { fail(RSR_ERR_INVALID_ARGUMENT, at + "null pointer"); return false; }
+  if (rows < 1 || rows > rsr::kMaxRows) { fail(RSR_ERR_INVALID_ARGUMENT, at + "rows must be in 1..65534"); return false; }
+  if (cols < 1) { fail(RSR_ERR_INVALID_ARGUMENT, at + "cols must be >= 1"); return false; }
+  if (k < 1 || k > rsr::kMaxK) { fail(RSR_ERR_INVALID_ARGUMENT, at + "k must be in 1..16"); return false; }
+  return true;
+}
+
+// A host matrix in device memory for the time of a build.
+struct DeviceCopy {
+  int8_t* p = nullptr;
+  ~DeviceCopy() { if (p) (void)hipFree(p); }
+  bool fill(const int8_t* A, int64_t count, const char* who) {
+    hipError_t e = hipMalloc(&p, (size_t)count);
+    if (e == hipSuccess) e = hipMemcpy(p, A, (size_t)count, hipMemcpyHostToDevice);
+    if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string(who) + ": " + hipGetErrorString(e)); }
+    return e == hipSuccess;
+  }
+};
+
 }  // namespace
+
+namespace rsr_internal {
+
+int planes_per_handle(int64_t rows, int k, int q) {
+  const int64_t height = std::min<int64_t>(rows, rsr::kTileRows);
+  for (int n = q; n > 1; --n) {
+    const rsr::Shape s = rsr::panel_shape(height, k, n, false);
+    const int64_t lds = align_up((size_t)(height + 1) * 4, 16) + 2 * (int64_t)(s.nslots + rsr::kDummySlots + rsr::kMaxExtras) * 4 +
+                        2 * ((int64_t)s.panels * kItems * 4 + 8) + 64;
+    if (lds <= 160 * 1024) return n;
+  }
+  return 1;
+}
+
+int8_t* device_copy(const int8_t* A, int64_t count, const char* who) {
+  DeviceCopy d;
+  if (!d.fill(A, count, who)) return nullptr;
+  int8_t* p = d.p;
+  d.p = nullptr;
+  return p;
+}
+void device_release(int8_t* p) { (void)hipFree(p); }
+
+rsr_handle* build_planes(const int8_t* dA, int64_t rows, int64_t cols, int k, int plane0, int planes, int q) {
+  return make_handle(dA, rows, cols, k, planes, plane0, q, "rsr_qbit_preprocess");
+}
+
+}  // namespace rsr_internal
 
 extern "C" {
 
 rsr_handle* rsr_preprocess(const int8_t* A, int64_t rows, int64_t cols, int k) {
   g_error.clear();
-  std::unique_ptr<rsr_handle> h(new (std::nothrow) rsr_handle());
-  if (!h) { fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory"); return nullptr; }
-  rsr::Index X;
+  if (!valid_shape(A, rows, cols, k, "rsr_preprocess")) return nullptr;
+  DeviceCopy d;
+  if (!d.fill(A, rows * cols, "rsr_preprocess")) return nullptr;
   std::string err;
-  int rc;
-  try {
-    rc = rsr::pack_tiles(A, rows, cols, k, 0, &X, &err);
-  } catch (const std::bad_alloc&) {
-    fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory while packing");
+  int kind = 0;
+  const int rc = rsr_internal::device_matrix_kind(d.p, rows * cols, &kind, &err);
+  if (rc != 0) { fail(rc, "rsr_preprocess: " + err); return nullptr; }
+  if (kind == 0) {
+    int64_t i = 0;
+    while (i + 1 < rows * cols && A[i] >= -1 && A[i] <= 1) ++i;
+    fail(RSR_ERR_INVALID_ARGUMENT, "rsr_preprocess: entry outside {-1,0,1} at row " + std::to_string(i / cols) + ", column " + std::to_string(i % cols));
     return nullptr;
   }
-  if (rc != 0) { fail(rc, "rsr_preprocess: " + err); return nullptr; }
-
-  hipError_t e = hipGetDevice(&h->device);
-  if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(e)); return nullptr; }
-  hipDeviceProp_t prop;
-  e = hipGetDeviceProperties(&prop, h->device);
-  if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string("hipGetDeviceProperties: ") + hipGetErrorString(e)); return nullptr; }
-  h->num_cu = prop.multiProcessorCount;
-  h->lds_max = prop.sharedMemPerBlock;
-  rsr_info_t info;
-  fill_info(X, &info);
-  h->rows = rows; h->cols = cols; h->nblocks = info.nblocks;
-  h->k = info.k; h->kw = info.lo_bits; h->parts = info.parts; h->last_width = info.last_block_width;
-  h->stored_rows = info.stored_rows; h->segments = info.segments; h->nunits = info.work_units;
-  h->flag_bytes = info.segment_bytes; h->stream_bytes = info.index_bytes + info.segment_bytes; h->schedule_bytes = info.schedule_bytes;
-  // both kernels may use the whole LDS of a compute unit as dynamic shared memory
-  for (const void* kern : {reinterpret_cast<const void*>(rsr_matvec_kernel<float, false>),
-                           reinterpret_cast<const void*>(rsr_matvec_kernel<int8_t, false>),
-                           reinterpret_cast<const void*>(rsr_matvec_kernel<float, true>),
-                           reinterpret_cast<const void*>(rsr_matvec_kernel<int8_t, true>),
-                           reinterpret_cast<const void*>(rsr_multi_kernel<float>),
-                           reinterpret_cast<const void*>(rsr_multi_kernel<int8_t>)}) {
-    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->lds_max);
-    if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e)); return nullptr; }
-  }
-  h->tiles.resize(X.tiles.size());
-  for (size_t t = 0; t < X.tiles.size(); ++t) {
-    DeviceTile& T = h->tiles[t];
-    T.rows = X.tiles[t].rows; T.row0 = X.row0[t];
-    T.max_units_per_block = X.tiles[t].max_units_per_block;
-    T.nunits = (int64_t)X.tiles[t].units.size();
-    if (upload(&T, X.tiles[t]) != RSR_OK) { free_tables(h.get()); return nullptr; }
-  }
-  h->magic = kMagic;
-  return h.release();
+  return make_handle(d.p, rows, cols, k, kind, -1, 0, "rsr_preprocess");
 }
 
 rsr_handle* rsr_preprocess_device(const int8_t* A, int64_t rows, int64_t cols, int k) {
   g_error.clear();
-  if (!A) { fail(RSR_ERR_INVALID_ARGUMENT, "rsr_preprocess_device: null pointer"); return nullptr; }
-  if (rows < 1 || rows > rsr::kMaxRows) { fail(RSR_ERR_INVALID_ARGUMENT, "rsr_preprocess_device: rows must be in 1..65534"); return nullptr; }
-  if (cols < 1) { fail(RSR_ERR_INVALID_ARGUMENT, "rsr_preprocess_device: cols must be >= 1"); return nullptr; }
-  if (k < 1 || k > rsr::kMaxK) { fail(RSR_ERR_INVALID_ARGUMENT, "rsr_preprocess_device: k must be in 1..16"); return nullptr; }
-  std::unique_ptr<rsr_handle> h(new (std::nothrow) rsr_handle());
-  if (!h) { fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory"); return nullptr; }
-  hipError_t e = hipGetDevice(&h->device);
-  hipDeviceProp_t prop;
-  if (e == hipSuccess) e = hipGetDeviceProperties(&prop, h->device);
-  if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string("rsr_preprocess_device: ") + hipGetErrorString(e)); return nullptr; }
-  h->num_cu = prop.multiProcessorCount;
-  h->lds_max = prop.sharedMemPerBlock;
+  if (!valid_shape(A, rows, cols, k, "rsr_preprocess_device")) return nullptr;
   std::string err;
   int kind = 0;
-  int rc = rsr_internal::device_matrix_kind(A, rows * cols, &kind, &err);
+  const int rc = rsr_internal::device_matrix_kind(A, rows * cols, &kind, &err);
   if (rc != 0) { fail(rc, "rsr_preprocess_device: " + err); return nullptr; }
   if (kind == 0) { fail(RSR_ERR_INVALID_ARGUMENT, "rsr_preprocess_device: an entry lies outside {-1,0,1}"); return nullptr; }
-  h->rows = rows; h->cols = cols; h->k = k; h->kw = std::min(k, rsr::kMaxWindowBits); h->parts = kind;
-  h->nblocks = (cols + k - 1) / k;
-  h->last_width = (int)(cols - (h->nblocks - 1) * k);
-  for (const void* kern : {reinterpret_cast<const void*>(rsr_matvec_kernel<float, false>),
-                           reinterpret_cast<const void*>(rsr_matvec_kernel<int8_t, false>),
-                           reinterpret_cast<const void*>(rsr_matvec_kernel<float, true>),
-                           reinterpret_cast<const void*>(rsr_matvec_kernel<int8_t, true>),
-                           reinterpret_cast<const void*>(rsr_multi_kernel<float>),
-                           reinterpret_cast<const void*>(rsr_multi_kernel<int8_t>)}) {
-    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->lds_max);
-    if (e != hipSuccess) { (void)hipGetLastError(); fail(RSR_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e)); return nullptr; }
-  }
-  const int64_t ntiles = (rows + rsr::kTileRows - 1) / rsr::kTileRows;
-  const int64_t height = ((rows + ntiles - 1) / ntiles + 15) / 16 * 16;
-  for (int64_t t = 0; t < ntiles; ++t) {
-    const int64_t r0 = t * height, r1 = std::min(rows, r0 + height);
-    rsr_internal::BuiltTile B;
-    rc = rsr_internal::device_build_tile(A + r0 * cols, r1 - r0, cols, cols, k, kind, &B, &err);
-    if (rc != 0) { free_tables(h.get()); fail(rc, "rsr_preprocess_device: " + err); return nullptr; }
-    DeviceTile T;
-    T.rows = r1 - r0; T.row0 = r0;
-    T.max_units_per_block = B.max_units_per_block; T.nunits = B.nunits;
-    T.stream_bytes = B.stream_bytes; T.unit_bytes = B.unit_bytes; T.blk_bytes = B.blk_bytes;
-    T.d_stream = B.d_stream; T.d_units = B.d_units; T.d_blk_unit = B.d_blk_unit;
-    h->tiles.push_back(T);
-    h->stored_rows += B.stored_rows; h->segments += B.segments; h->nunits += B.nunits;
-    h->flag_bytes += B.flag_bytes; h->stream_bytes += (int64_t)B.stream_bytes;
-    h->schedule_bytes += (int64_t)(B.unit_bytes + B.blk_bytes);
-  }
-  h->magic = kMagic;
-  return h.release();
+  return make_handle(A, rows, cols, k, kind, -1, 0, "rsr_preprocess_device");
 }
 
 int rsr_matvec(rsr_handle* h, const float* v, float* out, int batch, void* stream) {
@@ -1219,10 +1626,10 @@ int rsr_info(const rsr_handle* h, rsr_info_t* info) {
   std::memset(info, 0, sizeof(*info));
   info->rows = h->rows; info->cols = h->cols; info->k = h->k; info->parts = h->parts;
   info->nblocks = h->nblocks; info->last_block_width = h->last_width;
-  info->lo_bits = h->kw; info->hi_bits = h->k - h->kw;
+  info->lo_bits = h->tiles[0].shape.kc; info->hi_bits = h->k - info->lo_bits;
   info->stored_rows = h->stored_rows; info->segments = h->segments; info->work_units = h->nunits;
-  info->segment_bytes = h->flag_bytes;
-  info->index_bytes = h->stream_bytes - h->flag_bytes;
+  info->segment_bytes = h->head_bytes;
+  info->index_bytes = h->stream_bytes - h->head_bytes;
   info->schedule_bytes = h->schedule_bytes;
   info->table_bytes = info->index_bytes + info->segment_bytes + info->schedule_bytes;
   info->device = h->device; info->compute_units = h->num_cu;
@@ -1232,37 +1639,39 @@ int rsr_info(const rsr_handle* h, rsr_info_t* info) {
 
 int rsr_export_block(rsr_handle* h, int part, int64_t block, int32_t* sigma, int32_t* L) {
   if (!valid(h)) return fail(RSR_ERR_INVALID_ARGUMENT, "invalid handle");
-  if (!h->downloaded) {
-    std::unique_ptr<rsr::Index> X(new (std::nothrow) rsr::Index());
-    if (!X) return fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory");
+  if (h->downloaded.empty()) {
     int dev = 0;
     RSR_HIP_TRY(hipGetDevice(&dev));
     RSR_HIP_TRY(hipSetDevice(h->device));
-    X->rows = h->rows; X->cols = h->cols;
     try {
-      X->tiles.resize(h->tiles.size());
-      for (size_t t = 0; t < h->tiles.size(); ++t) {
+      std::vector<rsr_internal::TileTables> X(h->tiles.size());
+      for (size_t t = 0; t < X.size(); ++t) {
         const DeviceTile& T = h->tiles[t];
-        rsr::Packed& P = X->tiles[t];
-        X->row0.push_back(T.row0);
+        rsr_internal::TileTables& P = X[t];
+        P.rows = T.rows; P.row0 = T.row0; P.shape = T.shape; P.extra_stride = T.extra_stride;
         P.stream.resize(T.stream_bytes / sizeof(uint16_t));
-        P.units.resize(T.unit_bytes / sizeof(rsr::Unit));
+        P.units.resize(T.unit_bytes / sizeof(rsr::PUnit));
         P.blk_unit.resize(T.blk_bytes / sizeof(uint32_t));
-        P.rows = T.rows; P.cols = h->cols; P.k = h->k; P.kw = h->kw; P.parts = h->parts;
-        P.nblocks = h->nblocks; P.last_width = h->last_width;
+        P.extras.resize(T.extra_bytes / sizeof(uint16_t));
         if (T.stream_bytes) RSR_HIP_TRY(hipMemcpy(P.stream.data(), T.d_stream, T.stream_bytes, hipMemcpyDeviceToHost));
         if (T.unit_bytes) RSR_HIP_TRY(hipMemcpy(P.units.data(), T.d_units, T.unit_bytes, hipMemcpyDeviceToHost));
+        if (T.extra_bytes) RSR_HIP_TRY(hipMemcpy(P.extras.data(), T.d_extras, T.extra_bytes, hipMemcpyDeviceToHost));
         RSR_HIP_TRY(hipMemcpy(P.blk_unit.data(), T.d_blk_unit, T.blk_bytes, hipMemcpyDeviceToHost));
       }
+      h->downloaded = std::move(X);
     } catch (const std::bad_alloc&) {
       (void)hipSetDevice(dev);
       return fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory");
     }
     RSR_HIP_TRY(hipSetDevice(dev));
-    h->downloaded = std::move(X);
   }
   std::string err;
-  const int rc = rsr::decode_block(*h->downloaded, part, block, sigma, L, &err);
+  int rc;
+  try {
+    rc = rsr_internal::decode_tables(h->downloaded, h->rows, h->cols, h->k, h->parts, part, block, sigma, L, &err);
+  } catch (const std::bad_alloc&) {
+    return fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory");
+  }
   if (rc != 0) return fail(rc, "rsr_export_block: " + err);
   return RSR_OK;
 }

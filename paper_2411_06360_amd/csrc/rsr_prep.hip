@@ -1,19 +1,17 @@
-// Algorithm 1 (Section 3.4) on the device: the index of a matrix that already sits in device memory
-// is built there, in the packed layout of rsr_format.h.
+// Algorithm 1 (Section 3.4) on the device: the index of a matrix in device memory is built there, in the layout of
+// rsr_layout.h.
 //
 //   1. values_kernel     the k-bit value of every row in every column block and part (Definition 3.2,
 //                        first column most significant; a narrow last block is shifted left).
 //   2. sort_kernel       per (block, part), by one wavefront: histogram of the values, its exclusive prefix
-//                        (the full segmentation L of Section 3.3) and the stable counting sort that gives
-//                        sigma ("bucket sort" in the proof of Theorem 3.6; equal rows stay in row order: the
-//                        wavefront walks the rows in order, 64 at a time, and ranks equal values by lane).
-//   3. window_kernel     per window of 2^kw values: how many entries its stream has (its rows, plus one
-//                        null entry for every absent value between two present ones).
-//   (host)               the unit descriptors and stream offsets from those counts: O(windows), no row data.
-//   4. emit_kernel       per unit: the entries dealt out to the 64 lanes, row indices in granule order, flags.
-//
-// Inside emit_kernel the rows of a segment are then dealt out over the LDS banks (as the host packer does in
-// rsr_pack.cpp, by the same exchange rule): that changes the speed of the product, not the index it encodes.
+//                        (the full segmentation L of Section 3.3) and the counting sort that gives sigma
+//                        ("bucket sort" in the proof of Theorem 3.6).
+//   3. plan_kernel       per panel: the segments ranked by their number of rows, the groups they form, how many
+//                        units and stream bytes those take.
+//   (host)               where every panel's units and streams begin: O(panels), no row data.
+//   4. units_kernel      per panel: the unit descriptors.
+//   5. emit_kernel       per unit: the rows dealt out to the 64 lanes, the rows of a lane's segment spread over the
+//                        LDS banks, granule order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -23,12 +21,12 @@
 #include <vector>
 
 #include "../../include/rsr.h"
-#include "rsr_format.h"
 #include "rsr_internal.h"
+#include "rsr_layout.h"
 
 namespace {
 
-using rsr::Unit;
+using rsr::PUnit;
 
 #define PREP_TRY(expr)                                                        \
   do {                                                                        \
@@ -40,37 +38,82 @@ using rsr::Unit;
     }                                                                         \
   } while (0)
 
+// bit 0: some entry is -1, bit 1: some entry lies outside {-1,0,1}.  Bound by the reading of A: 16 bytes per load
+// where A is aligned.
 __global__ void kind_kernel(const int8_t* __restrict__ A, int64_t count, unsigned* __restrict__ flags) {
+  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
   unsigned f = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
-    const int x = A[i];
+  auto look = [&](int x) {
     if (x < -1 || x > 1) f |= 2u;
     if (x == -1) f |= 1u;
+  };
+  const int64_t n16 = (reinterpret_cast<uintptr_t>(A) & 15) == 0 ? count / 16 : 0;
+  for (int64_t i = id; i < n16; i += step) {
+    const uint4 x = reinterpret_cast<const uint4*>(A)[i];
+    const uint32_t d[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) look((int)(d[j] << (24 - 8 * b)) >> 24);
   }
+  for (int64_t i = n16 * 16 + id; i < count; i += step) look(A[i]);
   if (f) atomicOr(flags, f);
 }
 
-// val[(block * parts + part) * rows + r]
-__global__ void values_kernel(const int8_t* __restrict__ A, int rows, int cols, int64_t ld, int k, int parts, int nblocks,
-                              uint16_t* __restrict__ val) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  for (int b = blockIdx.y; b < nblocks; b += gridDim.y) {
-    const int width = min(k, cols - b * k);
-    const int8_t* a = A + (int64_t)r * ld + (int64_t)b * k;
-    uint32_t plus = 0, minus = 0;
-    for (int c = 0; c < width; ++c) {
-      const int x = a[c];
-      plus = (plus << 1) | (uint32_t)(x == 1);
-      minus = (minus << 1) | (uint32_t)(x == -1);
+// val[(block * parts + part) * rows + r].  A workgroup takes 64 rows of kValueBlocks column blocks through LDS, so that
+// A is read in whole lines and the values are written in runs of 64 rows.
+constexpr int kValueBlocks = 8;
+constexpr int kValueStride = kValueBlocks * rsr::kMaxK + 4;  // bytes between rows in LDS: an odd number of dwords
+__global__ void __launch_bounds__(256)
+values_kernel(const int8_t* __restrict__ A, int rows, int cols, int64_t ld, int k, int parts, int plane0, int nblocks, uint16_t* __restrict__ val) {
+  __shared__ __align__(16) int8_t tile[64 * kValueStride];
+  const int r0 = blockIdx.x * 64, tid = threadIdx.x;
+  for (int b0 = blockIdx.y * kValueBlocks; b0 < nblocks; b0 += gridDim.y * kValueBlocks) {
+    const int c0 = b0 * k, nc = min(kValueBlocks * k, cols - c0), nr = min(64, rows - r0);
+    const int8_t* a = A + (int64_t)r0 * ld + c0;
+    const bool words = ((reinterpret_cast<uintptr_t>(a) | (uintptr_t)ld) & 3) == 0;
+    const int nw = words ? nc / 4 : 0;
+    for (int i = tid; i < nr * nw; i += 256) {
+      const int r = i / nw, c = i - r * nw;
+      reinterpret_cast<uint32_t*>(tile + r * kValueStride)[c] = reinterpret_cast<const uint32_t*>(a + (int64_t)r * ld)[c];
     }
-    const int shift = k - width;
-    val[((int64_t)b * parts) * rows + r] = (uint16_t)(plus << shift);
-    if (parts == 2) val[((int64_t)b * parts + 1) * rows + r] = (uint16_t)(minus << shift);
+    const int rest = nc - nw * 4;
+    for (int i = tid; i < nr * rest; i += 256) {
+      const int r = i / rest, c = nw * 4 + i - r * rest;
+      tile[r * kValueStride + c] = a[(int64_t)r * ld + c];
+    }
+    __syncthreads();
+    for (int i = tid; i < 64 * kValueBlocks; i += 256) {
+      const int r = i & 63, bi = i >> 6, b = b0 + bi;
+      if (r < nr && b < nblocks) {
+        const int width = min(k, cols - b * k), shift = k - width;
+        const int8_t* t = tile + r * kValueStride + bi * k;
+        uint16_t* out = val + (int64_t)b * parts * rows + r0 + r;
+        if (plane0 >= 0) {  // bit planes of q-bit entries
+          for (int p = 0; p < parts; ++p) {
+            uint32_t x = 0;
+            for (int c = 0; c < width; ++c) x = (x << 1) | (((uint32_t)(uint8_t)t[c] >> (plane0 + p)) & 1u);
+            out[(int64_t)p * rows] = (uint16_t)(x << shift);
+          }
+        } else {
+          uint32_t plus = 0, minus = 0;
+          for (int c = 0; c < width; ++c) {
+            const int x = t[c];
+            plus = (plus << 1) | (uint32_t)(x == 1);
+            minus = (minus << 1) | (uint32_t)(x == -1);
+          }
+          out[0] = (uint16_t)(plus << shift);
+          if (parts == 2) out[rows] = (uint16_t)(minus << shift);
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
-// One wavefront per (block, part).  LDS: 2^k counters of 16 bits per wavefront (a tile has at most 32768 rows).
+// One wavefront per (block, part).  LDS: 2^k counters of 16 bits per wavefront (a tile has at most 32768 rows).  Both
+// passes are LDS atomics of one wavefront, 64 rows per instruction, in row order; the counters are private to
+// the wavefront, so the result does not depend on timing.
 __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, int nbp, int waves_per_wg,
                             uint32_t* __restrict__ off, uint16_t* __restrict__ sigma) {
   extern __shared__ uint32_t lds_hist[];
@@ -83,13 +126,14 @@ __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, i
   volatile uint32_t* h = lds_hist + (size_t)wave * ndw;
   const uint16_t* v = val + (int64_t)bp * rows;
   for (int i = lane; i < ndw; i += 64) h[i] = 0;
-  // histogram
-  for (int r0 = 0; r0 < rows; r0 += 64) {
-    const int r = r0 + lane;
-    if (r < rows) {
-      const uint32_t x = v[r];
-      atomicAdd(const_cast<uint32_t*>(&h[x >> 1]), 1u << (16 * (x & 1)));
-    }
+  constexpr int kAhead = 8;  // chunks of 64 rows whose values are fetched together
+  for (int r0 = 0; r0 < rows; r0 += 64 * kAhead) {
+    uint32_t x[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) x[j] = v[min(r0 + 64 * j + lane, rows - 1)];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+      if (r0 + 64 * j + lane < rows) atomicAdd(const_cast<uint32_t*>(&h[x[j] >> 1]), 1u << (16 * (x[j] & 1)));
   }
   // exclusive prefix: the full segmentation (kept in LDS as the next free position of every value)
   uint32_t carry = 0;
@@ -114,188 +158,377 @@ __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, i
     carry += __shfl(incl, 63);
   }
   if (lane == 0) o[nvals] = (uint32_t)rows;
-  // stable placement: rows in order, 64 at a time; equal values of a chunk are ranked by lane
   uint16_t* sg = sigma + (int64_t)bp * rows;
-  for (int r0 = 0; r0 < rows; r0 += 64) {
-    const int r = r0 + lane;
-    const bool active = r < rows;
-    const uint32_t x = active ? (uint32_t)v[r] : 0xffffffffu;
-    unsigned long long todo = __ballot(active);
-    while (todo) {
-      const int leader = __ffsll((long long)todo) - 1;
-      const uint32_t s = (uint32_t)__shfl((int)x, leader);
-      const unsigned long long m = __ballot(active && x == s);
-      const uint32_t cur = (h[s >> 1] >> (16 * (s & 1))) & 0xffffu;
-      if (active && x == s) {
-        const int rank = __popcll(m & ((1ull << lane) - 1ull));
-        sg[cur + rank] = (uint16_t)r;
+  for (int r0 = 0; r0 < rows; r0 += 64 * kAhead) {
+    uint32_t x[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) x[j] = v[min(r0 + 64 * j + lane, rows - 1)];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int r = r0 + 64 * j + lane;
+      if (r < rows) {
+        const uint32_t sh = 16 * (x[j] & 1);
+        const uint32_t at = (atomicAdd(const_cast<uint32_t*>(&h[x[j] >> 1]), 1u << sh) >> sh) & 0xffffu;
+        sg[at] = (uint16_t)r;
       }
-      if (lane == leader) h[s >> 1] = h[s >> 1] + ((uint32_t)__popcll(m) << (16 * (s & 1)));
-      todo &= ~m;
     }
   }
 }
 
-// Per (block-part, window): entries of the window's stream (rows + nulls for absent values between present ones).
-__global__ void window_kernel(const uint32_t* __restrict__ off, int k, int kw, int nbp, uint32_t* __restrict__ n_ext) {
-  const int nwin = 1 << (k - kw);
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)nbp * nwin) return;
-  const int bp = (int)(id / nwin), w = (int)(id % nwin);
-  const int W = 1 << kw;
-  const uint32_t* o = off + (int64_t)bp * ((1 << k) + 1) + (int64_t)w * W;
-  int first = -1, last = -1;
-  for (int j = (w == 0 ? 1 : 0); j < W; ++j)
-    if (o[j + 1] != o[j]) { if (first < 0) first = j; last = j; }
-  uint32_t n = 0;
-  if (first >= 0)
-    for (int j = first; j <= last; ++j) n += max(1u, o[j + 1] - o[j]);
-  n_ext[id] = n;
-}
-
-struct UnitJob {
-  uint32_t bp, window, entry_begin, n;
+// What the kernels below need to know of a tile.
+struct Geometry {
+  int rows, k, parts, nblocks;
+  rsr::Shape s;
+  int list_stride, group_stride, extra_stride;  // entries per panel in the lists
+  int fill;  // absent values form groups of no rows
 };
 
-__global__ void __launch_bounds__(256)
-emit_kernel(const UnitJob* __restrict__ jobs, Unit* __restrict__ units, const uint32_t* __restrict__ off,
-            const uint16_t* __restrict__ sigma, int rows, int k, int kw, uint16_t* __restrict__ stream) {
-  __shared__ uint32_t cnt[512], estart[513], f0[64], f1[64], wsum[4];
-  __shared__ uint16_t ent[64 * rsr::kMaxPositions];            // the unit's entries, [lane][position]
-  __shared__ uint32_t bank_load[2][rsr::kMaxPositions][32];    // rows per LDS bank, per half wavefront and position
-  __shared__ int first_s, last_s;
-  __shared__ uint32_t nrows_s, nheads_s;
-  const int u = blockIdx.x, tid = threadIdx.x;
-  const UnitJob J = jobs[u];
-  const int npos = units[u].npos;
-  if (npos == 0) return;  // a unit without entries (an all-zero block)
-  const int W = 1 << kw;
-  const uint32_t* o = off + (int64_t)J.bp * ((1 << k) + 1) + (int64_t)J.window * W;
-  const uint16_t* sg = sigma + (int64_t)J.bp * rows;
-  const uint16_t null_index = (uint16_t)rows;
-  if (tid == 0) { first_s = W; last_s = -1; nrows_s = 0; nheads_s = 0; }
-  if (tid < 64) { f0[tid] = 0; f1[tid] = 0; }
-  __syncthreads();
-  for (int j = tid; j < 512; j += 256) {
-    uint32_t c = 0;
-    if (j < W && !(J.window == 0 && j == 0)) c = o[j + 1] - o[j];
-    cnt[j] = c;
-    if (c) { atomicMin(&first_s, j); atomicMax(&last_s, j); }
-  }
-  __syncthreads();
-  const int first = first_s, last = last_s;
-  // exclusive prefix of the entries per value (two values per thread)
-  const int j0 = 2 * tid, j1 = 2 * tid + 1;
-  const uint32_t e0 = (j0 >= first && j0 <= last) ? max(1u, cnt[j0]) : 0u;
-  const uint32_t e1 = (j1 >= first && j1 <= last) ? max(1u, cnt[j1]) : 0u;
-  uint32_t incl = e0 + e1;
-  const int lane = tid & 63, wave = tid >> 6;
+struct PanelInfo {
+  uint32_t n8, n1;         // list entries that take 8 lanes, one lane
+  uint32_t units, stream;  // stream in multiples of kStreamAlign
+  uint32_t extras, rows, segments;
+};
+struct PanelBase {
+  uint32_t unit, stream;
+};
+
+constexpr int kKeys8 = 32, kKeys1 = 48;  // rank classes: 8 lanes with 32 .. 1 rows each, one lane with 47 .. 0
+constexpr int kKeys = kKeys8 + kKeys1;
+constexpr uint16_t kNoSegment = 0xffff;  // the number of rows of a slot that takes no part
+
+// The pieces a segment of n rows is cut into.
+__device__ __forceinline__ uint32_t pieces_of(uint32_t n) { return n <= (uint32_t)rsr::kWideRows ? 1u : (n + rsr::kWideRows - 1) / rsr::kWideRows; }
+// Its rank class, the widest and longest first.  `cap`: rows up to which a segment takes one lane.
+__device__ __forceinline__ int key_of(uint32_t n, int cap) {
+  if (n <= (uint32_t)cap) return kKeys8 + (kKeys1 - 1 - (int)n);
+  const uint32_t np = pieces_of(n), piece = (n + np - 1) / np;
+  return kKeys8 - (int)((piece + 7) / 8);
+}
+__device__ __forceinline__ int rows_of_key(int key) {  // positions a group of this class takes, without its head
+  return key < kKeys8 ? kKeys8 - key : kKeys8 + kKeys1 - 1 - key;
+}
+
+// The units of a panel: whole groups of one width, in order, at most kMaxPositions positions and about equally many
+// each.  f(wide, first list entry, first group, groups, positions) for every unit.
+template <typename G, typename F>
+__device__ __forceinline__ void walk_units(const PanelInfo& I, G group_rows, F f) {
+  uint32_t group = 0, entry = 0;
 #pragma unroll
-  for (int d = 1; d < 64; d *= 2) {
-    const uint32_t t = __shfl_up(incl, d);
-    if (lane >= d) incl += t;
-  }
-  if (lane == 63) wsum[wave] = incl;
-  __syncthreads();
-  uint32_t base = 0;
-  for (int w = 0; w < wave; ++w) base += wsum[w];
-  const uint32_t ex = base + incl - (e0 + e1);
-  estart[j0] = ex;
-  estart[j1] = ex + e0;
-  if (tid == 255) estart[512] = ex + e0 + e1;
-  __syncthreads();
-  const int full = npos / 8;
-  const int64_t sbase = (int64_t)units[u].stream_off * (rsr::kStreamAlign / 2);  // in uint16 elements
-  uint32_t my_rows = 0, my_heads = 0;
-  for (int idx = tid; idx < 64 * npos; idx += 256) {
-    const int l = idx / npos, p = idx - l * npos;
-    uint16_t row = null_index;
-    int flag = 0;
-    if ((uint32_t)idx < J.n) {
-      const uint32_t i = J.entry_begin + (uint32_t)idx;
-      int lo = 0, hi = 513;  // upper bound of i in estart[0..512]
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (estart[mid] <= i) lo = mid + 1; else hi = mid;
+  for (int wide = 1; wide >= 0; --wide) {
+    const uint32_t per = wide ? 8u : 64u, count = wide ? I.n8 : I.n1;
+    const uint32_t ng = (count + per - 1) / per;
+    uint32_t all = 0;
+    for (uint32_t i = 0; i < ng; ++i) all += group_rows(group + i) + 1;
+    const uint32_t nu = (all + rsr::kMaxPositions - 5) / (rsr::kMaxPositions - 4);
+    const uint32_t target = nu ? (all + nu - 1) / nu : 0;
+    uint32_t first = 0, cur = 0;
+    for (uint32_t i = 0; i < ng; ++i) {
+      const uint32_t m = group_rows(group + i) + 1;
+      if (cur && (cur >= target || cur + m > (uint32_t)rsr::kMaxPositions)) {
+        f(wide, entry + first * per, group + first, i - first, cur);
+        first = i; cur = 0;
       }
-      const int j = lo - 1;  // the value whose entries contain i
-      if (cnt[j]) { row = sg[o[j] + (i - estart[j])]; ++my_rows; }
-      flag = (i == estart[j]) && idx > 0;
-      if (idx == 0) units[u].slot0 = (uint16_t)j;
+      cur += m;
     }
-    ent[l * rsr::kMaxPositions + p] = row;
-    if (flag) {
-      ++my_heads;
-      if (p < 32) atomicOr(&f0[l], 1u << (31 - p)); else atomicOr(&f1[l], 1u << (47 - p));
-    }
+    if (cur) f(wide, entry + first * per, group + first, ng - first, cur);
+    group += ng;
+    entry += count;
   }
-  if (my_rows) atomicAdd(&nrows_s, my_rows);
-  if (my_heads) atomicAdd(&nheads_s, my_heads);
-  for (int i = tid; i < 2 * rsr::kMaxPositions * 32; i += 256) (&bank_load[0][0][0])[i] = 0;
+}
+
+// Part and value of a slot of a panel; false: no segment belongs to it.
+__device__ __forceinline__ bool slot_value(const Geometry& g, uint32_t panel, uint32_t slot, uint32_t* bp, uint32_t* value) {
+  const uint32_t block = panel / g.s.panels, pi = panel % g.s.panels;
+  const int wbits = g.k - g.s.kc;
+  const uint32_t part = g.s.both ? slot / g.s.pslots : pi >> wbits;
+  const uint32_t low = slot % g.s.pslots, window = g.s.both ? 0u : pi & ((1u << wbits) - 1);
+  *bp = block * g.parts + part;
+  *value = (window << g.s.kc) | low;
+  return low < (1u << g.s.kc) && *value != 0;
+}
+
+// One workgroup per panel.  A chain of short steps on LDS counters: bound by their latency; several workgroups share a
+// compute unit.
+__global__ void __launch_bounds__(256)
+plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__ list_all, uint8_t* __restrict__ group_all,
+            uint32_t* __restrict__ extra_all, PanelInfo* __restrict__ info) {
+  __shared__ uint16_t len[rsr::kMaxPanelSlots], rank[rsr::kMaxPanelSlots], list[rsr::kMaxPanelSlots + rsr::kMaxExtras];
+  __shared__ uint16_t cnt[kKeys][64];
+  __shared__ uint32_t hist[rsr::kWideRows + 1], start[kKeys + 1], ex_slot[rsr::kMaxExtras];
+  __shared__ uint16_t ex_rank[rsr::kMaxExtras];
+  __shared__ uint8_t ex_key[rsr::kMaxExtras], groups[1024];
+  __shared__ uint32_t cost[8], tot_rows, tot_segments, n_extra, best_cap;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t panel = blockIdx.x;
+  const int caps[7] = {47, 32, 24, 16, 12, 8, 6};
+  for (int i = tid; i < kKeys * 64; i += 256) (&cnt[0][0])[i] = 0;
+  for (int i = tid; i <= rsr::kWideRows; i += 256) hist[i] = 0;
+  if (tid == 0) { tot_rows = 0; tot_segments = 0; n_extra = 0; }
   __syncthreads();
-  // The order of the rows inside a segment is free.  As in the host packer, two rows of a lane's run that
-  // lies in one segment trade places while that lowers the squared loads of the LDS banks (row mod 32) at
-  // their two positions, counted per half wavefront: the gathers of the product then meet in fewer banks.
-  // One thread per lane; the loads are kept with atomics, a decision may see a neighbour's move late, which
-  // only costs quality.
+  {
+    uint32_t my_rows = 0, my_segments = 0;
+    for (int s = tid; s < g.s.nslots; s += 256) {
+      uint32_t bp, value, n = 0;
+      const bool real = slot_value(g, panel, (uint32_t)s, &bp, &value);
+      if (real) {
+        const uint32_t* o = off + (int64_t)bp * ((1 << g.k) + 1) + value;
+        n = o[1] - o[0];
+      }
+      len[s] = n || (real && g.fill) ? (uint16_t)n : kNoSegment;
+      if (n) {
+        my_rows += n; ++my_segments;
+        if (n <= (uint32_t)rsr::kWideRows) atomicAdd(&hist[n], 1u);
+      }
+    }
+    atomicAdd(&tot_rows, my_rows);
+    atomicAdd(&tot_segments, my_segments);
+  }
+  __syncthreads();
+  // Up to how many rows a segment takes one lane: the limit that gives the fewest positions.
+  if (tid < 7) {
+    const uint32_t cap = (uint32_t)caps[tid];
+    uint32_t c = 0, seen = 0, m = 0;
+    for (uint32_t n = rsr::kWideRows; n > cap; --n) {
+      const uint32_t h = hist[n];
+      if (h) m = (n + 7) / 8;
+      c += ((seen + h + 7) / 8 - (seen + 7) / 8) * (m + 1);
+      seen += h;
+    }
+    seen = 0;
+    for (uint32_t n = cap; n > 0; --n) {
+      const uint32_t h = hist[n];
+      c += ((seen + h + 63) / 64 - (seen + 63) / 64) * (n + 1);
+      seen += h;
+    }
+    cost[tid] = c;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int b = 0;
+    for (int i = 1; i < 7; ++i) if (cost[i] < cost[b]) b = i;
+    best_cap = (uint32_t)caps[b];
+  }
+  __syncthreads();
+  const int cap = (int)best_cap;
+  // Ranks: by class, and inside a class round robin over the 64 residues of the slot, so that the slots of
+  // neighbouring lanes lie in different LDS banks.  One wavefront counts, lane = residue.
   if (tid < 64) {
-    const int L = tid, h = L >> 5;
-    for (int p = 0; p < npos; ++p) {
-      const uint16_t r = ent[L * rsr::kMaxPositions + p];
-      if (r != null_index) atomicAdd(&bank_load[h][p][r & 31], 1u);
-    }
-  }
-  __syncthreads();
-  for (int pass = 0; pass < 6; ++pass) {
-    if (tid < 64) {
-      const int L = tid, h = L >> 5;
-      const uint32_t g0 = f0[L], g1 = f1[L];
-      auto flagged = [&](int q) { return q < 32 ? (g0 >> (31 - q)) & 1u : (g1 >> (47 - q)) & 1u; };
-      uint16_t* e = ent + L * rsr::kMaxPositions;
-      int p0 = 0;
-      while (p0 < npos) {
-        int p1 = p0 + 1;
-        while (p1 < npos && !flagged(p1)) ++p1;
-        for (int pp = p0; pp < p1; ++pp)
-          for (int q = pp + 1; q < p1; ++q) {
-            const uint16_t rp = e[pp], rq = e[q];
-            if (rp == null_index || rq == null_index) continue;
-            const int bp = rp & 31, bq = rq & 31;
-            if (bp == bq) continue;
-            volatile uint32_t* lp = bank_load[h][pp];
-            volatile uint32_t* lq = bank_load[h][q];
-            const int delta = ((int)lp[bq] - (int)lp[bp] + 1) + ((int)lq[bp] - (int)lq[bq] + 1);
-            if (delta < 0) {
-              atomicSub(&bank_load[h][pp][bp], 1u); atomicAdd(&bank_load[h][pp][bq], 1u);
-              atomicSub(&bank_load[h][q][bq], 1u); atomicAdd(&bank_load[h][q][bp], 1u);
-              e[pp] = rq; e[q] = rp;
-            }
+    uint32_t extras = 0;
+    for (int s0 = 0; s0 < g.s.nslots; s0 += 64) {
+      const uint32_t n = len[s0 + lane];
+      const bool in = n != kNoSegment;
+      if (in) {
+        const int key = key_of(n, cap);
+        const uint16_t r = cnt[key][lane];
+        rank[s0 + lane] = r; cnt[key][lane] = r + 1;
+      }
+      unsigned long long cut = __ballot(in && n > (uint32_t)rsr::kWideRows);
+      while (cut) {
+        const int l = __ffsll((long long)cut) - 1;
+        cut &= cut - 1;
+        const uint32_t n_l = (uint32_t)__shfl((int)n, l), np = pieces_of(n_l);
+        const int key_l = key_of(n_l, cap);
+        for (uint32_t i = 1; i < np; ++i) {
+          const uint32_t e = extras++;
+          if (lane == (int)(e & 63) && e < (uint32_t)g.extra_stride) {  // (pieces beyond the first: at most rows / kWideRows in all)
+            ex_slot[e] = (uint32_t)(s0 + l) | (i << 16);
+            ex_key[e] = (uint8_t)key_l;
+            const uint16_t r = cnt[key_l][lane];
+            ex_rank[e] = r; cnt[key_l][lane] = r + 1;
           }
-        p0 = p1;
+        }
       }
     }
-    __syncthreads();
+    if (lane == 0) n_extra = min(extras, (uint32_t)g.extra_stride);
   }
-  for (int idx = tid; idx < 64 * npos; idx += 256) {
-    const int l = idx / npos, p = idx - l * npos;
-    const uint16_t row = ent[l * rsr::kMaxPositions + p];
-    int64_t at;
-    if (p < full * 8) {
-      at = ((int64_t)(p / 8) * 64 + l) * 8 + (p % 8);
-    } else {
-      const int q = p - full * 8;
-      const int64_t rest = (int64_t)full * 8 * 64;
-      at = ((npos & 1) && p == npos - 1) ? rest + (int64_t)(q / 2) * 2 * 64 + l : rest + ((int64_t)(q / 2) * 64 + l) * 2 + (q & 1);
+  __syncthreads();
+  if (tid < kKeys) {
+    uint32_t s = 0;
+    for (int c = 0; c < 64; ++c) s += cnt[tid][(c + tid) & 63];
+    start[tid + 1] = s;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t s = 0;
+    start[0] = 0;
+    for (int i = 1; i <= kKeys; ++i) { s += start[i]; start[i] = s; }
+  }
+  __syncthreads();
+  auto place = [&](int key, uint32_t r, int residue) {
+    uint32_t at = start[key];
+    for (int i = 0; i < 64; ++i) {
+      const int c = (i + lane) & 63;
+      at += min((uint32_t)cnt[key][c], r + (c < residue ? 1u : 0u));
     }
-    stream[sbase + at] = row;
+    return at;
+  };
+  for (int s = tid; s < g.s.nslots; s += 256)
+    if (len[s] != kNoSegment) list[place(key_of(len[s], cap), rank[s], s & 63)] = (uint16_t)s;
+  if (tid < (int)n_extra) list[place(ex_key[tid], ex_rank[tid], tid & 63)] = (uint16_t)(g.s.nslots + rsr::kDummySlots + tid);
+  __syncthreads();
+  const uint32_t n8 = start[kKeys8], n1 = start[kKeys] - n8, g8 = (n8 + 7) / 8, ng = g8 + (n1 + 63) / 64;
+  uint8_t* group_out = group_all + (int64_t)panel * g.group_stride;
+  for (uint32_t i = tid; i < ng; i += 256) {
+    const uint32_t at = i < g8 ? i * 8 : n8 + (i - g8) * 64;
+    const uint32_t s = list[at];
+    const int key = s < (uint32_t)g.s.nslots ? key_of(len[s], cap) : (int)ex_key[s - g.s.nslots - rsr::kDummySlots];
+    groups[i] = (uint8_t)rows_of_key(key);
+    group_out[i] = groups[i];
   }
-  if (tid < 64) {
-    const int64_t fb = sbase + (int64_t)npos * 64;
-    stream[fb + 2 * tid] = (uint16_t)(f0[tid] & 0xffffu);
-    stream[fb + 2 * tid + 1] = (uint16_t)(f0[tid] >> 16);
-    if (npos > 32) stream[fb + 128 + tid] = (uint16_t)f1[tid];
+  uint16_t* list_out = list_all + (int64_t)panel * g.list_stride;
+  for (uint32_t i = tid; i < start[kKeys]; i += 256) list_out[i] = list[i];
+  if (tid < (int)n_extra) extra_all[(int64_t)panel * g.extra_stride + tid] = ex_slot[tid];
+  __syncthreads();
+  if (tid == 0) {
+    PanelInfo I;
+    I.n8 = n8; I.n1 = n1;
+    I.units = 0; I.stream = 0;
+    I.extras = n_extra; I.rows = tot_rows; I.segments = tot_segments;
+    walk_units(I, [&](uint32_t i) { return (uint32_t)groups[i]; },
+               [&](int, uint32_t, uint32_t, uint32_t, uint32_t npos) { ++I.units; I.stream += (npos + 1) & ~1u; });
+    if (I.units == 0) I.units = 1;  // a panel without entries still has to count for its block
+    info[panel] = I;
   }
-  if (tid == 0) { units[u].nrows = nrows_s; units[u].nheads = nheads_s; }
+}
+
+// One wavefront per panel; lane 0 walks the groups.
+__global__ void __launch_bounds__(64)
+units_kernel(Geometry g, const uint8_t* __restrict__ group_all, const PanelInfo* __restrict__ info, const PanelBase* __restrict__ base,
+             PUnit* __restrict__ units) {
+  __shared__ uint8_t groups[1024];
+  const uint32_t panel = blockIdx.x;
+  const PanelInfo I = info[panel];
+  const uint32_t ng = (I.n8 + 7) / 8 + (I.n1 + 63) / 64;
+  for (uint32_t i = threadIdx.x; i < ng; i += 64) groups[i] = group_all[(int64_t)panel * g.group_stride + i];
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  PUnit u;
+  u.block = panel / g.s.panels; u.panel = panel;
+  u.units_in_panel = (uint16_t)I.units; u.extras = (uint16_t)I.extras; u.reserved = 0;
+  uint32_t at = base[panel].unit, stream = base[panel].stream;
+  if (ng == 0) {
+    u.stream_off = stream; u.heads_lo = 0; u.heads_hi = 0; u.npos = 0; u.wide = 0; u.first = 0;
+    units[at] = u;
+    return;
+  }
+  walk_units(I, [&](uint32_t i) { return (uint32_t)groups[i]; },
+             [&](int wide, uint32_t first, uint32_t group, uint32_t n, uint32_t npos) {
+               uint64_t heads = 0;
+               uint32_t p = 0;
+               for (uint32_t i = 0; i < n; ++i) { p += groups[group + i]; heads |= 1ull << p; ++p; }
+               u.stream_off = stream;
+               u.heads_lo = (uint32_t)heads; u.heads_hi = (uint16_t)(heads >> 32);
+               u.npos = (uint8_t)((npos + 1) & ~1u); u.wide = (uint8_t)wide;
+               u.first = first;
+               units[at++] = u;
+               stream += (npos + 1) & ~1u;
+             });
+}
+
+// One wavefront per unit.
+constexpr int kEmitWaves = 4;
+__global__ void __launch_bounds__(64 * kEmitWaves)
+emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const PanelInfo* __restrict__ info, const uint16_t* __restrict__ list_all,
+            const uint32_t* __restrict__ extra_all, const uint32_t* __restrict__ off, const uint16_t* __restrict__ sigma,
+            unsigned char* __restrict__ stream) {
+  __shared__ uint16_t ent_all[kEmitWaves][rsr::kMaxPositions][64];
+  __shared__ uint32_t load_all[kEmitWaves][2][rsr::kMaxPositions][8];  // rows per LDS bank (a byte each), half wavefront and position
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t ui = blockIdx.x * kEmitWaves + wave;
+  if (ui >= nunits) return;  // (no barriers below: the wavefronts are independent)
+  const PUnit U = units[ui];
+  const int npos = U.npos;
+  if (npos == 0) return;
+  volatile uint16_t (*ent)[64] = ent_all[wave];
+  volatile uint32_t (*load)[8] = load_all[wave][lane >> 5];
+  uint32_t* load_words = &load_all[wave][0][0][0];
+  const PanelInfo I = info[U.panel];
+  const uint64_t heads = (uint64_t)U.heads_lo | ((uint64_t)U.heads_hi << 32);
+  const int wbits = U.wide ? 3 : 0;
+  const uint32_t end = U.wide ? I.n8 : I.n8 + I.n1;
+  const uint32_t sub = (uint32_t)lane & ((1u << wbits) - 1);
+  const bool owner = sub == 0;
+  const uint16_t* list = list_all + (int64_t)U.panel * g.list_stride;
+  const uint16_t null_index = (uint16_t)g.rows;
+  for (int i = lane; i < 2 * rsr::kMaxPositions * 8; i += 64) load_words[i] = 0;
+  uint32_t entry = U.first + ((uint32_t)lane >> wbits);
+  for (int p0 = 0; p0 < npos;) {
+    const uint64_t rest = heads >> p0;
+    if (rest == 0) {  // the position that makes the count even
+      for (; p0 < npos; ++p0) ent[p0][lane] = null_index;
+      break;
+    }
+    const int m = __ffsll((long long)rest) - 1;
+    uint32_t n = 0, slot = (uint32_t)g.s.nslots + (lane & (rsr::kDummySlots - 1));
+    const uint16_t* rows = sigma;
+    if (entry < end) {
+      const uint32_t s = list[entry];
+      uint32_t of = s, piece = 0;
+      if (s >= (uint32_t)g.s.nslots) {
+        const uint32_t x = extra_all[(int64_t)U.panel * g.extra_stride + (s - g.s.nslots - rsr::kDummySlots)];
+        of = x & 0xffffu; piece = x >> 16;
+      }
+      uint32_t bp, value;
+      slot_value(g, U.panel, of, &bp, &value);
+      const uint32_t* o = off + (int64_t)bp * ((1 << g.k) + 1) + value;
+      const uint32_t o0 = o[0], all = o[1] - o0, np = pieces_of(all);
+      const uint32_t a = all * piece / np, b = all * (piece + 1) / np;
+      rows = sigma + (int64_t)bp * g.rows + o0 + a;
+      n = b - a;
+      if (owner) slot = s;
+    }
+    for (int j = 0; j < m; ++j) {
+      const uint32_t r = ((uint32_t)j << wbits) + sub;
+      const uint16_t row = r < n ? rows[r] : null_index;
+      ent[p0 + j][lane] = row;
+      if (row != null_index) atomicAdd(const_cast<uint32_t*>(&load[p0 + j][(row & 31) >> 2]), 1u << (8 * (row & 3)));
+    }
+    ent[p0 + m][lane] = (uint16_t)slot;
+    p0 += m + 1;
+    entry += 64u >> wbits;
+  }
+  // The order of the rows inside a segment is free (a segment is a sum).  The LDS has 32 banks of 4 bytes and
+  // serves the two halves of a wavefront one after the other; a half costs as many clocks as its fullest bank has
+  // distinct addresses.  Two rows of a lane's segment trade places while that lowers the squared loads of the banks
+  // (row mod 32) at their two positions: the gathers of the product then meet in fewer banks.  The loads
+  // are kept with atomics; a decision may see a neighbour's move late, which only costs quality.
+  auto bank_load = [&](int p, int b) { return (int)((load[p][b >> 2] >> (8 * (b & 3))) & 0xffu); };
+  auto add_load = [&](int p, int b, uint32_t x) { atomicAdd(const_cast<uint32_t*>(&load[p][b >> 2]), x << (8 * (b & 3))); };
+  // A quarter of the lanes at a time: the lanes of a group stand at the same position, and would all leave a crowded bank
+  // at once.
+  constexpr int kReach = 12;  // positions a row may move per trade
+  for (int pass = 0; pass < 16; ++pass) {
+    if (((lane + pass) & 3) != 0) continue;
+    for (int p0 = 0; p0 < npos;) {
+      const uint64_t rest = heads >> p0;
+      if (rest == 0) break;
+      const int p1 = p0 + __ffsll((long long)rest) - 1;
+      for (int p = p0; p < p1; ++p)
+        for (int q = p + 1; q < min(p1, p + 1 + kReach); ++q) {
+          const uint16_t rp = ent[p][lane], rq = ent[q][lane];
+          if (rp == null_index || rq == null_index) continue;
+          const int bp = rp & 31, bq = rq & 31;
+          if (bp == bq) continue;
+          const int delta = (bank_load(p, bq) - bank_load(p, bp) + 1) + (bank_load(q, bp) - bank_load(q, bq) + 1);
+          if (delta < 0) {
+            add_load(p, bp, (uint32_t)-1); add_load(p, bq, 1u);
+            add_load(q, bq, (uint32_t)-1); add_load(q, bp, 1u);
+            ent[p][lane] = rq; ent[q][lane] = rp;
+          }
+        }
+      p0 = p1 + 1;
+    }
+  }
+  unsigned char* to = stream + (int64_t)U.stream_off * rsr::kStreamAlign;
+  const int full = npos / rsr::kGranulePositions;
+  for (int gq = 0; gq < full; ++gq) {
+    uint32_t w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)ent[gq * 8 + 2 * j][lane] | ((uint32_t)ent[gq * 8 + 2 * j + 1][lane] << 16);
+    reinterpret_cast<uint4*>(to)[gq * 64 + lane] = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  for (int p = full * 8; p < npos; p += 2)
+    reinterpret_cast<uint32_t*>(to)[p * 32 + lane] = (uint32_t)ent[p][lane] | ((uint32_t)ent[p + 1][lane] << 16);
 }
 
 struct DevBuf {  // frees on scope exit
@@ -312,7 +545,7 @@ int device_matrix_kind(const int8_t* dA, int64_t count, int* kind, std::string* 
   DevBuf flags;
   PREP_TRY(hipMalloc(&flags.p, 4));
   PREP_TRY(hipMemset(flags.p, 0, 4));
-  const int grid = (int)std::min<int64_t>(4096, (count + 255) / 256);
+  const int grid = (int)std::min<int64_t>(4096, (count + 4095) / 4096);
   hipLaunchKernelGGL(kind_kernel, dim3((unsigned)grid), dim3(256), 0, nullptr, dA, count, static_cast<unsigned*>(flags.p));
   PREP_TRY(hipGetLastError());
   unsigned f = 0;
@@ -321,27 +554,48 @@ int device_matrix_kind(const int8_t* dA, int64_t count, int* kind, std::string* 
   return 0;
 }
 
-int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, int k, int parts, BuiltTile* out, std::string* err) {
-  const int kw = std::min(k, rsr::kMaxWindowBits);
+int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, int k, int parts, int plane0, BuiltTile* out, std::string* err) {
   const int64_t nblocks = (cols + k - 1) / k;
   const int64_t nbp = nblocks * parts;
-  const int nvals = 1 << k, nwin = 1 << (k - kw);
+  const int nvals = 1 << k;
   if (rows < 1 || rows > rsr::kTileRows) { *err = "tile height out of range"; return RSR_ERR_INVALID_ARGUMENT; }
-  if (nbp * nwin > 0x7fffffff) { *err = "too many column blocks"; return RSR_ERR_UNSUPPORTED; }
-  hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
-  struct EvGuard { hipEvent_t* e; ~EvGuard() { for (int i = 0; i < 4; ++i) if (e[i]) (void)hipEventDestroy(e[i]); } } evg{ev};
-  for (auto& e : ev) PREP_TRY(hipEventCreate(&e));
+  Geometry g;
+  g.rows = (int)rows; g.k = k; g.parts = parts; g.nblocks = (int)nblocks;
+  g.s = rsr::panel_shape(rows, k, parts, plane0 < 0);
+  const int64_t npanels = nblocks * g.s.panels;
+  if (nblocks > 0x3fffffff || npanels > 0x7fffffff || nbp > 0x7fffffff) { *err = "too many column blocks"; return RSR_ERR_UNSUPPORTED; }
+  g.extra_stride = (int)std::max<int64_t>(2, (rows * (g.s.both ? 2 : 1) / rsr::kWideRows + 1) / 2 * 2);  // (even: read two at a time)
+  g.list_stride = g.s.nslots + g.extra_stride;
+  // Clearing a slot costs a share of an LDS store, an absent value two bytes of the stream and a share of a gather and a store:
+  // with rows spread evenly over the values, one in eight is absent where there are about two rows per value.
+  g.fill = rows >= (int64_t)2 << k ? 1 : 0;
+  // groups of a panel at most: one lane per segment; 8 lanes (segments of more than 6 rows, and pieces)
+  const int64_t seen = rows * (g.s.both ? 2 : 1);
+  g.group_stride = (int)((g.s.nslots + 63) / 64 + (std::min<int64_t>(g.s.nslots, seen / 7) + g.extra_stride + 7) / 8 + 1);
+  if (g.group_stride > 1024) { *err = "too many segments in a panel"; return RSR_ERR_UNSUPPORTED; }
 
-  DevBuf val, sigma, off, next;
-  PREP_TRY(hipMalloc(&val.p, (size_t)nbp * rows * 2));
-  PREP_TRY(hipMalloc(&sigma.p, (size_t)nbp * rows * 2));
-  PREP_TRY(hipMalloc(&off.p, (size_t)nbp * (nvals + 1) * 4));
-  PREP_TRY(hipMalloc(&next.p, (size_t)nbp * nwin * 4));
-  PREP_TRY(hipEventRecord(ev[0], nullptr));
-  hipLaunchKernelGGL(values_kernel, dim3((unsigned)((rows + 255) / 256), (unsigned)std::min<int64_t>(nblocks, 32768)), dim3(256), 0, nullptr, dA, (int)rows,
-                     (int)cols, ld, k, parts, (int)nblocks, static_cast<uint16_t*>(val.p));
+  // One allocation for all working memory.
+  DevBuf work;
+  size_t bytes = 0;
+  auto take = [&](size_t n) { const size_t at = bytes; bytes += (n + 255) / 256 * 256; return at; };
+  const size_t at_val = take((size_t)nbp * rows * 2), at_sigma = take((size_t)nbp * rows * 2), at_off = take((size_t)nbp * (nvals + 1) * 4);
+  const size_t at_list = take((size_t)npanels * g.list_stride * 2), at_group = take((size_t)npanels * g.group_stride);
+  const size_t at_extra = take((size_t)npanels * g.extra_stride * 4), at_info = take((size_t)npanels * sizeof(PanelInfo));
+  const size_t at_base = take((size_t)npanels * sizeof(PanelBase));
+  PREP_TRY(hipMalloc(&work.p, bytes));
+  unsigned char* const w = static_cast<unsigned char*>(work.p);
+  uint16_t* const val = reinterpret_cast<uint16_t*>(w + at_val);
+  uint16_t* const sigma = reinterpret_cast<uint16_t*>(w + at_sigma);
+  uint32_t* const off = reinterpret_cast<uint32_t*>(w + at_off);
+  uint16_t* const list = reinterpret_cast<uint16_t*>(w + at_list);
+  uint8_t* const group = w + at_group;
+  uint32_t* const extra = reinterpret_cast<uint32_t*>(w + at_extra);
+  PanelInfo* const info = reinterpret_cast<PanelInfo*>(w + at_info);
+  PanelBase* const base = reinterpret_cast<PanelBase*>(w + at_base);
+
+  hipLaunchKernelGGL(values_kernel, dim3((unsigned)((rows + 63) / 64), (unsigned)std::min<int64_t>((nblocks + kValueBlocks - 1) / kValueBlocks, 32768)),
+                     dim3(256), 0, nullptr, dA, (int)rows, (int)cols, ld, k, parts, plane0, (int)nblocks, val);
   PREP_TRY(hipGetLastError());
-  PREP_TRY(hipEventRecord(ev[1], nullptr));
   {
     const size_t per_wave = (size_t)std::max(1, nvals >> 1) * 4;
     int waves = (int)std::min<size_t>(4, (size_t)(128 * 1024) / per_wave);
@@ -349,101 +603,77 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
     const void* kern = reinterpret_cast<const void*>(sort_kernel);
     PREP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
     hipLaunchKernelGGL(sort_kernel, dim3((unsigned)((nbp + waves - 1) / waves)), dim3((unsigned)(64 * waves)), per_wave * waves, nullptr,
-                       static_cast<const uint16_t*>(val.p), (int)rows, k, (int)nbp, waves, static_cast<uint32_t*>(off.p),
-                       static_cast<uint16_t*>(sigma.p));
+                       static_cast<const uint16_t*>(val), (int)rows, k, (int)nbp, waves, off, sigma);
     PREP_TRY(hipGetLastError());
   }
-  hipLaunchKernelGGL(window_kernel, dim3((unsigned)((nbp * nwin + 255) / 256)), dim3(256), 0, nullptr, static_cast<const uint32_t*>(off.p), k,
-                     kw, (int)nbp, static_cast<uint32_t*>(next.p));
+  hipLaunchKernelGGL(plan_kernel, dim3((unsigned)npanels), dim3(256), 0, nullptr, g, static_cast<const uint32_t*>(off), list, group, extra, info);
   PREP_TRY(hipGetLastError());
-  PREP_TRY(hipEventRecord(ev[2], nullptr));
-  std::vector<uint32_t> n_ext((size_t)nbp * nwin);
-  PREP_TRY(hipMemcpy(n_ext.data(), next.p, n_ext.size() * 4, hipMemcpyDeviceToHost));
+  std::vector<PanelInfo> hinfo((size_t)npanels);
+  PREP_TRY(hipMemcpy(hinfo.data(), info, hinfo.size() * sizeof(PanelInfo), hipMemcpyDeviceToHost));
 
-  // ---- descriptors and stream offsets (host; no row data involved) ----
-  std::vector<Unit> units;
-  std::vector<UnitJob> jobs;
+  // ---- where every panel's units and streams begin (host; no row data involved) ----
+  std::vector<PanelBase> hbase((size_t)npanels);
   std::vector<uint32_t> blk_unit((size_t)nblocks + 1);
-  uint64_t stream_units = 0;  // in multiples of kStreamAlign
-  int64_t flag_bytes = 0;
+  uint64_t nunits = 0, nstream = 0;
   uint32_t max_units = 0;
+  uint32_t extras = 0;
+  out->stored_rows = 0; out->segments = 0; out->head_bytes = 0;
   for (int64_t b = 0; b < nblocks; ++b) {
-    blk_unit[(size_t)b] = (uint32_t)units.size();
-    const size_t first_unit = units.size();
-    for (int p = 0; p < parts; ++p)
-      for (int w = 0; w < nwin; ++w) {
-        const uint32_t total = n_ext[(size_t)((b * parts + p) * nwin + w)];
-        if (!total) continue;
-        const uint32_t nu = (total + rsr::kMaxUnitEntries - 1) / rsr::kMaxUnitEntries;
-        for (uint32_t ui = 0; ui < nu; ++ui) {
-          const uint32_t eb = (uint32_t)((uint64_t)total * ui / nu), ee = (uint32_t)((uint64_t)total * (ui + 1) / nu);
-          Unit u;
-          std::memset(&u, 0, sizeof(u));
-          u.block = (uint32_t)b; u.window = (uint16_t)w; u.part = (uint8_t)p;
-          u.npos = (uint8_t)((ee - eb + rsr::kLanes - 1) / rsr::kLanes);
-          u.nentries = ee - eb;
-          u.stream_off = (uint32_t)stream_units;
-          const uint32_t bytes = rsr::unit_stream_bytes(u.npos);
-          stream_units += (bytes + rsr::kStreamAlign - 1) / rsr::kStreamAlign;
-          flag_bytes += rsr::kFlagBytes0 + (u.npos > 32 ? rsr::kFlagBytes1 : 0);
-          units.push_back(u);
-          jobs.push_back(UnitJob{(uint32_t)(b * parts + p), (uint32_t)w, eb, ee - eb});
-        }
-      }
-    if (units.size() == first_unit) {  // an all-zero block still has to write its outputs
-      Unit u;
-      std::memset(&u, 0, sizeof(u));
-      u.block = (uint32_t)b;
-      u.stream_off = (uint32_t)stream_units;
-      units.push_back(u);
-      jobs.push_back(UnitJob{(uint32_t)(b * parts), 0, 0, 0});
+    blk_unit[(size_t)b] = (uint32_t)nunits;
+    const uint64_t first = nunits;
+    for (int i = 0; i < g.s.panels; ++i) {
+      const size_t at = (size_t)(b * g.s.panels + i);
+      const PanelInfo& I = hinfo[at];
+      hbase[at] = PanelBase{(uint32_t)nunits, (uint32_t)nstream};
+      nunits += I.units; nstream += I.stream;
+      extras = std::max(extras, I.extras);
+      out->stored_rows += I.rows; out->segments += I.segments;
+      out->head_bytes += ((int64_t)(I.n8 + 7) / 8 + (I.n1 + 63) / 64) * rsr::kPositionBytes;
+      if (nunits > 0x7fffffffull || nstream > 0xffffffffull) { *err = "index too large"; return RSR_ERR_UNSUPPORTED; }
     }
-    const size_t nub = units.size() - first_unit;
-    if (nub > 0xffffu) { *err = "too many work units in one column block"; return RSR_ERR_UNSUPPORTED; }
-    for (size_t i = 0; i < nub; ++i) {
-      units[first_unit + i].units_in_block = (uint16_t)nub;
-      units[first_unit + i].index_in_block = (uint16_t)i;
-    }
-    max_units = std::max<uint32_t>(max_units, (uint32_t)nub);
-    if (stream_units > 0xffffffffull) { *err = "index too large"; return RSR_ERR_UNSUPPORTED; }
+    max_units = std::max<uint32_t>(max_units, (uint32_t)(nunits - first));
   }
-  blk_unit[(size_t)nblocks] = (uint32_t)units.size();
+  blk_unit[(size_t)nblocks] = (uint32_t)nunits;
 
-  DevBuf d_stream, d_units, d_blk, d_jobs;
-  const size_t stream_bytes = (size_t)stream_units * rsr::kStreamAlign;
-  PREP_TRY(hipMalloc(&d_stream.p, stream_bytes + 1024));
-  PREP_TRY(hipMalloc(&d_units.p, units.size() * sizeof(Unit) + 32));
-  PREP_TRY(hipMalloc(&d_blk.p, blk_unit.size() * 4 + 16));
-  PREP_TRY(hipMalloc(&d_jobs.p, jobs.size() * sizeof(UnitJob)));
-  PREP_TRY(hipMemset(d_stream.p, 0, stream_bytes + 1024));
-  PREP_TRY(hipMemcpy(d_units.p, units.data(), units.size() * sizeof(Unit), hipMemcpyHostToDevice));
-  PREP_TRY(hipMemcpy(d_blk.p, blk_unit.data(), blk_unit.size() * 4, hipMemcpyHostToDevice));
-  PREP_TRY(hipMemcpy(d_jobs.p, jobs.data(), jobs.size() * sizeof(UnitJob), hipMemcpyHostToDevice));
-  hipLaunchKernelGGL(emit_kernel, dim3((unsigned)units.size()), dim3(256), 0, nullptr, static_cast<const UnitJob*>(d_jobs.p),
-                     static_cast<Unit*>(d_units.p), static_cast<const uint32_t*>(off.p), static_cast<const uint16_t*>(sigma.p), (int)rows, k, kw,
-                     static_cast<uint16_t*>(d_stream.p));
-  PREP_TRY(hipGetLastError());
-  PREP_TRY(hipEventRecord(ev[3], nullptr));
-  PREP_TRY(hipMemcpy(units.data(), d_units.p, units.size() * sizeof(Unit), hipMemcpyDeviceToHost));  // (synchronises)
-  float ms = 0;
-  PREP_TRY(hipEventElapsedTime(&ms, ev[0], ev[1])); out->ms_values = ms;
-  PREP_TRY(hipEventElapsedTime(&ms, ev[1], ev[2])); out->ms_sort = ms;
-  PREP_TRY(hipEventElapsedTime(&ms, ev[2], ev[3])); out->ms_emit = ms;
-  out->stored_rows = 0; out->segments = 0;
-  for (const Unit& u : units) {
-    out->stored_rows += u.nrows;
-    if (u.npos) out->segments += u.nheads + 1;
-  }
-  out->nunits = (int64_t)units.size();
-  out->max_units_per_block = max_units;
-  out->flag_bytes = flag_bytes;
-  out->parts = parts;
-  out->stream_bytes = stream_bytes;
-  out->unit_bytes = units.size() * sizeof(Unit);
+  // One allocation for the tables: streams, descriptors, block offsets, slots of cut segments.
+  DevBuf tables;
+  bytes = 0;
+  out->stream_bytes = (size_t)nstream * rsr::kStreamAlign;
+  out->unit_bytes = (size_t)nunits * sizeof(PUnit);
   out->blk_bytes = blk_unit.size() * 4;
-  out->d_stream = d_stream.release();
-  out->d_units = d_units.release();
-  out->d_blk_unit = d_blk.release();
+  out->extra_bytes = extras ? (size_t)npanels * g.extra_stride * 2 : 0;
+  const size_t at_stream = take(out->stream_bytes + 1024), at_units = take(out->unit_bytes + 32), at_blk = take(out->blk_bytes + 16);
+  const size_t at_slots = take(out->extra_bytes);
+  PREP_TRY(hipMalloc(&tables.p, bytes));
+  unsigned char* const t = static_cast<unsigned char*>(tables.p);
+  PREP_TRY(hipMemcpy(base, hbase.data(), hbase.size() * sizeof(PanelBase), hipMemcpyHostToDevice));
+  PREP_TRY(hipMemcpy(t + at_blk, blk_unit.data(), out->blk_bytes, hipMemcpyHostToDevice));
+  PUnit* const units = reinterpret_cast<PUnit*>(t + at_units);
+  hipLaunchKernelGGL(units_kernel, dim3((unsigned)npanels), dim3(64), 0, nullptr, g, static_cast<const uint8_t*>(group),
+                     static_cast<const PanelInfo*>(info), static_cast<const PanelBase*>(base), units);
+  PREP_TRY(hipGetLastError());
+  hipLaunchKernelGGL(emit_kernel, dim3((unsigned)((nunits + kEmitWaves - 1) / kEmitWaves)), dim3(64 * kEmitWaves), 0, nullptr, g, (uint32_t)nunits,
+                     static_cast<const PUnit*>(units), static_cast<const PanelInfo*>(info), static_cast<const uint16_t*>(list),
+                     static_cast<const uint32_t*>(extra), static_cast<const uint32_t*>(off), static_cast<const uint16_t*>(sigma), t + at_stream);
+  PREP_TRY(hipGetLastError());
+  if (extras) {
+    std::vector<uint32_t> x((size_t)npanels * g.extra_stride);
+    std::vector<uint16_t> slots(x.size(), 0);
+    PREP_TRY(hipMemcpy(x.data(), extra, x.size() * 4, hipMemcpyDeviceToHost));
+    for (size_t i = 0; i < x.size(); ++i)
+      if (i % g.extra_stride < hinfo[i / g.extra_stride].extras) slots[i] = (uint16_t)(x[i] & 0xffffu);
+    PREP_TRY(hipMemcpy(t + at_slots, slots.data(), out->extra_bytes, hipMemcpyHostToDevice));
+  }
+  PREP_TRY(hipStreamSynchronize(nullptr));
+  out->shape = g.s;
+  out->extra_stride = g.extra_stride; out->max_extras = (int)extras; out->fill = g.fill != 0;
+  out->nunits = (int64_t)nunits;
+  out->max_units_per_block = max_units;
+  out->d_stream = t + at_stream;
+  out->d_units = units;
+  out->d_blk_unit = t + at_blk;
+  out->d_extras = extras ? t + at_slots : nullptr;
+  out->d_tables = tables.release();
   return 0;
 }
 

@@ -1,5 +1,6 @@
 // q-bit matrices as weighted sums of binary matrices (include/rsr_qbit.h): host code on top of the
 // C ABI of rsr.h; the products themselves are the binary kernel's.
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <memory>
@@ -13,7 +14,7 @@
 struct rsr_qbit {
   uint64_t magic = 0;
   int q = 0;
-  std::vector<rsr_handle*> planes;  // plane i: bit i of the two's complement entries
+  std::vector<rsr_handle*> groups;  // each the weighted sum of some of the bit planes: one, unless their records do not fit in LDS together
   int64_t table_bytes = 0;
 };
 
@@ -21,8 +22,6 @@ namespace {
 constexpr uint64_t kMagic = 0x7162697452535221ull;
 bool valid(const rsr_qbit* h) { return h && h->magic == kMagic; }
 int fail(int code, const std::string& msg) { return rsr_internal::set_error(code, msg); }
-// weight of plane i: 2^i, and -2^(q-1) for the sign plane
-int32_t weight(int i, int q) { return i == q - 1 ? -(1 << i) : (1 << i); }
 }  // namespace
 
 extern "C" {
@@ -39,21 +38,31 @@ rsr_qbit* rsr_qbit_preprocess(const int8_t* A, int64_t rows, int64_t cols, int k
                                          " lies outside " + std::to_string(lo) + ".." + std::to_string(hi));
       return nullptr;
     }
+  if (rows > 65534 || k < 1 || k > 16) { fail(RSR_ERR_INVALID_ARGUMENT, "rsr_qbit_preprocess: rows must be in 1..65534 and k in 1..16"); return nullptr; }
   std::unique_ptr<rsr_qbit> h(new (std::nothrow) rsr_qbit());
-  std::vector<int8_t> plane;
-  try { plane.resize((size_t)count); } catch (const std::bad_alloc&) { h.reset(); }
   if (!h) { fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory"); return nullptr; }
   h->q = q;
-  for (int i = 0; i < q; ++i) {
-    for (int64_t j = 0; j < count; ++j) plane[(size_t)j] = (int8_t)(((uint8_t)A[j] >> i) & 1u);
-    rsr_handle* p = rsr_preprocess(plane.data(), rows, cols, k);
-    if (!p) {  // (the message of rsr_preprocess stands)
-      for (rsr_handle* x : h->planes) rsr_destroy(x);
-      return nullptr;
+  int8_t* dA = rsr_internal::device_copy(A, count, "rsr_qbit_preprocess");
+  if (!dA) return nullptr;
+  const int per = rsr_internal::planes_per_handle(rows, k, q);
+  bool ok = true;
+  try {
+    for (int p0 = 0; ok && p0 < q; p0 += per) {
+      h->groups.reserve((size_t)q);
+      rsr_handle* p = rsr_internal::build_planes(dA, rows, cols, k, p0, std::min(per, q - p0), q);
+      if (!p) { ok = false; break; }  // (its message stands)
+      h->groups.push_back(p);
+      rsr_info_t info;
+      if (rsr_info(p, &info) == RSR_OK) h->table_bytes += info.table_bytes;
     }
-    h->planes.push_back(p);
-    rsr_info_t info;
-    if (rsr_info(p, &info) == RSR_OK) h->table_bytes += info.table_bytes;
+  } catch (const std::bad_alloc&) {
+    ok = false;
+    fail(RSR_ERR_OUT_OF_MEMORY, "out of host memory");
+  }
+  rsr_internal::device_release(dA);
+  if (!ok) {
+    for (rsr_handle* x : h->groups) rsr_destroy(x);
+    return nullptr;
   }
   h->magic = kMagic;
   return h.release();
@@ -61,15 +70,15 @@ rsr_qbit* rsr_qbit_preprocess(const int8_t* A, int64_t rows, int64_t cols, int k
 
 int rsr_qbit_matvec(rsr_qbit* h, const float* v, float* out, int batch, void* stream) {
   if (!valid(h)) return fail(RSR_ERR_INVALID_ARGUMENT, "invalid handle");
-  int rc = rsr_matvec(h->planes[0], v, out, batch, stream);
-  for (int i = 1; i < h->q && rc == RSR_OK; ++i) rc = rsr_matvec_acc(h->planes[(size_t)i], v, out, (float)weight(i, h->q), batch, stream);
+  int rc = rsr_matvec(h->groups[0], v, out, batch, stream);
+  for (size_t i = 1; i < h->groups.size() && rc == RSR_OK; ++i) rc = rsr_matvec_acc(h->groups[i], v, out, 1.0f, batch, stream);
   return rc;
 }
 
 int rsr_qbit_matvec_i8(rsr_qbit* h, const int8_t* v, int32_t* out, int batch, void* stream) {
   if (!valid(h)) return fail(RSR_ERR_INVALID_ARGUMENT, "invalid handle");
-  int rc = rsr_matvec_i8(h->planes[0], v, out, batch, stream);
-  for (int i = 1; i < h->q && rc == RSR_OK; ++i) rc = rsr_matvec_acc_i8(h->planes[(size_t)i], v, out, weight(i, h->q), batch, stream);
+  int rc = rsr_matvec_i8(h->groups[0], v, out, batch, stream);
+  for (size_t i = 1; i < h->groups.size() && rc == RSR_OK; ++i) rc = rsr_matvec_acc_i8(h->groups[i], v, out, 1, batch, stream);
   return rc;
 }
 
@@ -78,7 +87,7 @@ int64_t rsr_qbit_table_bytes(const rsr_qbit* h) { return valid(h) ? h->table_byt
 
 void rsr_qbit_destroy(rsr_qbit* h) {
   if (!valid(h)) return;
-  for (rsr_handle* p : h->planes) rsr_destroy(p);
+  for (rsr_handle* p : h->groups) rsr_destroy(p);
   h->magic = 0;
   delete h;
 }
