@@ -58,7 +58,8 @@ typedef struct rsr_handle rsr_handle; /* opaque; owns the device-resident index 
  * For every part and every k-column block the call builds the row permutation that sorts the
  * rows by their binary value, first column most significant (Definition 3.2; equal rows stay in
  * ascending row order) and the boundaries of the groups of equal rows (the full segmentation,
- * Section 3.3), packs them for the GPU and uploads them to the current HIP device.
+ * Section 3.3), packed for the GPU, on the current HIP device: A is copied there and indexed as by
+ * rsr_preprocess_device.
  * The packed form is a layout choice, not a different index: rsr_export_block returns the
  * permutation and the full segmentation in the paper's form.  Rows whose value in a block is 0
  * contribute nothing to that block (row 0 of Bin_[k] is all zeros) and are not stored.
@@ -72,17 +73,15 @@ rsr_handle *rsr_preprocess(const int8_t *A, int64_t rows, int64_t cols, int k);
  * rsr_preprocess_device - Algorithm 1 (Section 3.4) run on the GPU, for a matrix that is already in
  * device memory (weights loaded there): row values per column block (Definition 3.2), the stable
  * counting sort that yields the permutation (the bucket sort in the proof of Theorem 3.6), the full
- * segmentation (Section 3.3) and the packing all happen on the device; the host only turns per-window
- * entry counts into the schedule.  The handle is used exactly like one from rsr_preprocess and encodes
- * the same index (rsr_export_block returns identical tables).  Both builders order the rows inside
- * every group of equal rows so that the gathers of the product spread over the LDS banks; their
- * searches differ, so the two packed streams may differ in that order (and float results in their
- * summation order), not in the index or in the speed of the product.
+ * segmentation (Section 3.3) and the packing all happen on the device; the host only adds up how many
+ * units each panel takes.  The handle is the same as the one rsr_preprocess makes of the same matrix.
+ * The rows inside every group of equal rows are ordered so that the gathers of the product spread
+ * over the LDS banks.
  *
  *   A     DEVICE pointer, row-major rows x cols int8 in {-1,0,1}; read during the call only.
  *   rows, cols, k   as for rsr_preprocess.
  * Returns a handle, or NULL on error.  Synchronous; allocates temporary device memory of about
- * 4 bytes per row and column block and part, plus 4 * 2^k bytes per column block and part.
+ * 4 bytes per row and column block and part, plus 6 * 2^k bytes per column block and part.
  */
 rsr_handle *rsr_preprocess_device(const int8_t *A, int64_t rows, int64_t cols, int k);
 
@@ -244,9 +243,9 @@ int rsr_info(const rsr_handle *h, rsr_info_t *info); /* info: HOST pointer */
 int rsr_export_block(rsr_handle *h, int part, int64_t block, int32_t *sigma, int32_t *L);
 
 /* ------------------------------------------------------------------------------------------
- * Host-only entry points: the index builder without a device.  They run the same code as
- * rsr_preprocess up to, but not including, the upload, so that the tables can be checked on a
- * machine with no GPU.  They compute no product.
+ * Host-only entry points: Algorithm 1 on the host.  They build the same permutations and segmentations
+ * as rsr_preprocess, packed as sorted rows with one flag bit each (csrc/rsr_format.h), so that Algorithm 1
+ * can be checked on a machine with no GPU.  They compute no product.
  * ------------------------------------------------------------------------------------------ */
 typedef struct rsr_host_index rsr_host_index; /* opaque; owns host memory only */
 

@@ -8,8 +8,9 @@
  *
  * q binary matrices (the appendix speaks of recursive use of Proposition 2.1 and of a larger number
  * of matrices; any decomposition into weighted binary matrices gives the same product, and this one
- * has the fewest).  One product costs q launches of the binary kernel: the first writes v . B_0,
- * the others add their weighted products (rsr_matvec_acc).
+ * has the fewest).  The planes are the parts of one index, and a product is one launch per row tile, in
+ * which every block adds its planes up with their weights (for large q, k and row counts the planes go out in
+ * two or more such launches: their partial results have to fit in LDS together).
  *
  * Conventions as in rsr.h: plain C types, HOST / DEVICE stated per pointer, RSR_OK or a negative
  * rsr_status, message through rsr_last_error().
@@ -25,7 +26,7 @@
 extern "C" {
 #endif
 
-typedef struct rsr_qbit rsr_qbit; /* opaque; owns q handles of rsr.h */
+typedef struct rsr_qbit rsr_qbit; /* opaque */
 
 /* A: HOST, row-major rows x cols int8, every entry in -2^(q-1) .. 2^(q-1)-1.  q: 2 .. 8.
  * rows, cols, k as for rsr_preprocess.  Returns NULL on error (an entry out of range is
@@ -33,7 +34,7 @@ typedef struct rsr_qbit rsr_qbit; /* opaque; owns q handles of rsr.h */
 rsr_qbit *rsr_qbit_preprocess(const int8_t *A, int64_t rows, int64_t cols, int k, int q);
 
 /* v: DEVICE [batch][rows]; out: DEVICE [batch][cols], fully overwritten.  Asynchronous on `stream`
- * (q launches per row tile, in order).  Float: every plane's product is rounded as in rsr_matvec,
+ * (the launches go out in order).  Float: every plane's product is rounded as in rsr_matvec,
  * the weights are powers of two (exact), the q-1 additions round once each;
  * |out - exact| <= 1e-5 * 2^(q-1) * sum_i |v_i|.  int8: exact; |sum| <= 127 * 128 * rows < 2^31. */
 int rsr_qbit_matvec(rsr_qbit *h, const float *v, float *out, int batch, void *stream);

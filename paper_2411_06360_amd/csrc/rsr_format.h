@@ -1,11 +1,11 @@
-// Packed device layout of the RSR index (internal to the library; shared by the host packer,
-// the host decoder and the HIP kernels).
+// Packed layout of the RSR index as the host builder makes it (rsr_host_pack: Algorithm 1 without a device), and
+// the constants it shares with the layout of the device (rsr_layout.h).
 //
 // Logical content, per part (B(1), B(2) of Proposition 2.1) and per k-column block
 // (Definition 3.1): the row permutation sigma of Definition 3.2 and the full segmentation L of
 // Section 3.3.  Physical layout: sigma itself, 16 bits per row, in sorted order, plus one bit per
-// row that says "a new value starts here" (L in unary), arranged for 64-lane wavefronts and
-// 16-byte coalesced loads:
+// row that says "a new value starts here" (L in unary), arranged for 64 lanes and 16-byte
+// granules:
 //
 //   * A row's value in a block is its k bits read with the first column most significant.  A
 //     last block narrower than k is treated as if its missing columns were zero, i.e. its
@@ -40,7 +40,7 @@
 //     positions 0..31 (position p = bit 31-p) and, if npos > 32, one uint16 per lane for positions
 //     32..47 (position p = bit 47-p).  A unit's stream starts on a 128-byte boundary.
 //
-// Streams on the device:
+// Streams:
 //   stream    bytes   unit streams, back to back
 //   units     Unit    32-byte descriptors, ordered by block
 //   blk_unit  uint32  nblocks+1 offsets into `units`
@@ -65,7 +65,6 @@ constexpr int kStreamAlign = 128;      // unit streams start on multiples of thi
 constexpr int kMaxK = 16;
 constexpr int kMaxRows = 65534;        // 65535 values of uint16 minus the null index
 constexpr int64_t kTileRows = 32768;   // a matrix with more rows is indexed in row tiles of at most this height
-constexpr int kRecordWords = 16;       // per-unit result record in LDS: 9 low-bit sums, total, meta
 
 // bytes of a unit's stream before alignment
 constexpr uint32_t unit_stream_bytes(int npos) {

@@ -152,8 +152,7 @@ struct KArgs {
   int nrec;      // blocks whose panel records are kept (panels > 1)
   uint32_t buf_magic, rec_magic;  // x / nbuf and x / nrec as high halves of products
   uint32_t ubytes;  // bytes of a panel's sums in LDS
-  uint32_t off_u, off_rec, off_done, off_blocks, off_cnt, off_epoch, off_ctr, off_desc;  // LDS byte offsets
-  uint32_t ndesc;  // descriptors of a workgroup's units that are kept in LDS
+  uint32_t off_u, off_rec, off_done, off_blocks, off_cnt, off_epoch, off_ctr;  // LDS byte offsets
 };
 
 // A kernel's own arguments, in the memory they were passed in.
@@ -164,7 +163,7 @@ __device__ __forceinline__ KArgsPtr args_at(size_t offset) {
 }
 #else
 typedef const KArgs* KArgsPtr;
-__device__ KArgsPtr args_at(size_t);  // (the host pass only has to parse the kernels)
+__device__ inline KArgsPtr args_at(size_t) { return nullptr; }  // (the host pass only has to parse the kernels)
 #endif
 __device__ __forceinline__ KArgsPtr launder(KArgsPtr p) {
   asm volatile("" : "+s"(p));
@@ -743,11 +742,6 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     reinterpret_cast<uint32_t*>(lds + p.off_blocks)[tid] = 0;
   }
   if (tid == 0) *reinterpret_cast<uint32_t*>(lds + p.off_ctr) = 2u * (uint32_t)p.waves;
-  // The descriptors of the workgroup's units: from LDS they come without a wait for memory, which would also hold up
-  // the gathers (scalar loads and LDS operations share a counter).
-  const uint32_t ndesc = n_tot <= (uint32_t)p.waves ? 0u : min(n_tot, p.ndesc);
-  for (uint32_t i = (uint32_t)tid; i < 2 * ndesc; i += blockDim.x)
-    reinterpret_cast<uint4*>(lds + p.off_desc)[i] = reinterpret_cast<const uint4*>(unit_words + (size_t)u_begin * 8)[i];
   if constexpr (kEarly > 0) {
 #pragma unroll
     for (int j = 0; j < kEarly; ++j) {
@@ -982,13 +976,6 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
 
   // One unit from buffer (e, et); the next unit's stream goes into (en, etn) meanwhile.
   auto unit = [&](uint32_t (&e)[NG][4], uint32_t (&et)[3], uint32_t (&en)[NG][4], uint32_t (&etn)[3]) {
-    const bool listed = ix1 < ndesc;
-    uint4 d0 = make_uint4(0, 0, 0, 0);
-    uint2 d1 = make_uint2(0, 0);
-    if (listed) {
-      d0 = *reinterpret_cast<const uint4*>(lds + p.off_desc + ix1 * 32u);
-      d1 = *reinterpret_cast<const uint2*>(lds + p.off_desc + ix1 * 32u + 16u);
-    }
     // Panel P of the workgroup uses buffer P mod nbuf, and may start when the sums of panel P - nbuf have been read.  (Units
     // are handed out in panel order and a wavefront sums its units in order, so the oldest unit in flight never waits:
     // no deadlock.)
@@ -1019,11 +1006,9 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     };
 #pragma unroll
     for (int gq = 0; gq < NG / 2; ++gq) step(gq);
-    // (the next unit's descriptor has arrived by now; its loads go out one by one between the later steps: a
-    // wavefront that issues a whole unit at once waits for room in the memory pipeline while it could be summing)
-    Desc D1;
-    if (listed) D1 = make_desc(uniform(d0.x), uniform(d0.y), uniform(d0.z), uniform(d0.w), uniform(d1.x), uniform(d1.y));
-    else D1 = load_desc(unit_words, ix1 < n_tot ? u_begin + ix1 : 0u);  // past the end it reads unit 0 (unused)
+    // The next unit's loads go out one by one between the later steps: a wavefront that issues a whole unit at once waits
+    // for room in the memory pipeline while it could be summing.
+    Desc D1 = load_desc(unit_words, ix1 < n_tot ? u_begin + ix1 : 0u);  // past the end it reads unit 0 (unused)
     if (ix1 >= n_tot) D1.npos = 0;
     const __amdgpu_buffer_rsrc_t rs1 = unit_rsrc(D1.stream_off, D1.npos);
     const uint32_t pair_base1 = lane4 + (D1.npos >> 3) * 1024u;
@@ -1142,9 +1127,8 @@ int plan_tile(const rsr_handle* h, const DeviceTile& T, bool accumulate, int bat
   // the start of the launch (1024 x 1024: 5.5 -> 4.0 us per product).
   const int64_t sets = ((int64_t)batch + M::V - 1) / M::V;
   int64_t g1 = 1;
-  int waves = 0, nbuf = 0, wgs = 1;
+  int waves = 0, nbuf = 0;
   for (int wg = max_wg_per_cu; wg >= 1; --wg) {
-    wgs = wg;
     g1 = ((int64_t)num_cu * wg + sets - 1) / sets;
     g1 = (g1 + 7) / 8 * 8;
     if (g1 > h->nblocks) g1 = h->nblocks;
@@ -1168,14 +1152,7 @@ int plan_tile(const rsr_handle* h, const DeviceTile& T, bool accumulate, int bat
   const int64_t grid = (g1 + 7) / 8 * 8 * sets;
   if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
 
-  // what is left of the LDS (of a share of it where several workgroups are meant to fit) holds descriptors of the units
-  const size_t share = std::max(total(nbuf), h->lds_max / (size_t)wgs);
-  const size_t want = (size_t)((h->nblocks + g1 - 1) / g1) * std::max<uint32_t>(1, T.max_units_per_block);
-  const size_t used = align_up(total(nbuf), 16);
-  p.ndesc = share > used ? (uint32_t)std::min<size_t>(want, (share - used) / 32) : 0;
-  if (want <= (size_t)waves) p.ndesc = 0;
-  p.off_desc = (uint32_t)used;
-  plan->lds = p.ndesc ? used + (size_t)p.ndesc * 32 : total(nbuf);
+  plan->lds = total(nbuf);
   plan->grid = grid;
   plan->waves = waves;
   p.waves = waves;

@@ -1,4 +1,4 @@
-// Host side of rsr_preprocess: Algorithm 1 (Section 3.4) and the device packing.
+// Algorithm 1 (Section 3.4) on the host, and its packing (rsr_format.h).
 #include "rsr_pack.h"
 
 #include <algorithm>

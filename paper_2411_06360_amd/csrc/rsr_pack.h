@@ -1,6 +1,6 @@
-// Host side of rsr_preprocess: Algorithm 1 (Section 3.4) plus the packing of its output
-// (permutations and full segmentations) into the device layout of rsr_format.h, and the
-// inverse used by rsr_export_block.
+// Algorithm 1 (Section 3.4) on the host (rsr_host_pack) plus the packing of its output
+// (permutations and full segmentations) into the layout of rsr_format.h, and the
+// inverse used by rsr_host_export_block.
 #ifndef RSR_PACK_H_
 #define RSR_PACK_H_
 

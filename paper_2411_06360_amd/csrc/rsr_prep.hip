@@ -497,7 +497,7 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   // A quarter of the lanes at a time: the lanes of a group stand at the same position, and would all leave a crowded bank
   // at once.
   constexpr int kReach = 12;  // positions a row may move per trade
-  for (int pass = 0; pass < 16; ++pass) {
+  for (int pass = 0; pass < 8; ++pass) {
     if (((lane + pass) & 3) != 0) continue;
     for (int p0 = 0; p0 < npos;) {
       const uint64_t rest = heads >> p0;
