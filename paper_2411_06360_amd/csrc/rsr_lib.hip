@@ -1196,7 +1196,11 @@ Mode pick_mode(const rsr_handle* h, const DeviceTile& T, int batch, int64_t unit
 }
 Mode pick_mode(const rsr_handle* h, const DeviceTile& T, int batch, int64_t units, const int8_t*) {
   if (h->step2_plain || batch < 2) return Mode::one;
-  const double c1 = pass_cost(units, h->num_cu, h->waves, batch, 1, 1.0), c2 = pass_cost(units, h->num_cu, h->waves, batch, 2, 1.1);
+  // (a device that is nearly full of units is slower than one that is half full: 2048 x 2888, four vectors, 0.96 units per
+  // wavefront: 7.6 us with one vector per pass, 6.8 with two; 3584 x 2432, 0.57 units: 5.7 and 6.5)
+  const double full = (double)units * batch / ((double)h->num_cu * h->waves);
+  const double c1 = std::max(0.55 + 0.6 * full, pass_cost(units, h->num_cu, h->waves, batch, 1, 1.0));
+  const double c2 = pass_cost(units, h->num_cu, h->waves, batch, 2, 1.1);
   const double c4 = pass_cost(units, h->num_cu, h->waves, batch, 4, 1.5);
   if (c4 < c2 && c4 < c1 && mode_fits<P4>(h, T, batch)) return Mode::four;
   return c2 < c1 ? Mode::two : Mode::one;  // (two need no more LDS than one)
