@@ -42,9 +42,7 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
 int device_matrix_kind(const int8_t* dA, int64_t count, int* kind, std::string* err);
 
 // The product of the bit planes plane0 .. plane0 + planes - 1 of the q-bit matrix dA (DEVICE), weighted and added up:
-// a handle of rsr.h.  The planes share a launch if their records fit in LDS beside the activations; planes_per_handle
-// says how many do.
-int planes_per_handle(int64_t rows, int k, int q);
+// a handle of rsr.h (rsr_plan.h says how many planes one can hold).
 rsr_handle* build_planes(const int8_t* dA, int64_t rows, int64_t cols, int k, int plane0, int planes, int q);
 
 // A host matrix in device memory, for code that is not compiled for the device (null: failed, the message is set).

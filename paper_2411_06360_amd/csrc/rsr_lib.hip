@@ -35,6 +35,7 @@
 #include "rsr_internal.h"
 #include "rsr_layout.h"
 #include "rsr_pack.h"
+#include "rsr_plan.h"
 
 namespace {
 
@@ -68,13 +69,7 @@ constexpr uint64_t kMagic = 0x5253522b2b763031ull;  // "RSR++v01"
 }  // namespace
 
 // One row tile of the index on the device (a matrix of up to rsr::kTileRows rows has one).
-struct DeviceTile {
-  int64_t rows = 0, row0 = 0;
-  rsr::Shape shape{};
-  int extra_stride = 0, max_extras = 0;  // entries per panel in d_extras; extra slots of a panel at most
-  bool fill = false;  // absent values are stored as zeros: a panel's slots need no clearing
-  uint32_t max_units_per_block = 0;
-  int64_t nunits = 0;
+struct DeviceTile : rsr::PlanTile {
   size_t stream_bytes = 0, unit_bytes = 0, blk_bytes = 0, extra_bytes = 0;
   void* d_tables = nullptr;  // the allocation that holds them all
   void* d_stream = nullptr;
@@ -83,20 +78,12 @@ struct DeviceTile {
   void* d_extras = nullptr;  // slots of the pieces of segments that were cut (null if there are none)
 };
 
-struct rsr_handle {
+struct rsr_handle : rsr::PlanMatrix {
   uint64_t magic = 0;
-  int device = 0, num_cu = 0;
-  size_t lds_max = 0;
-  // shape
-  int64_t rows = 0, cols = 0, nblocks = 0;
-  int k = 0, parts = 0, last_width = 0;
-  bool qbit = false;      // the parts are bit planes: part i weighs 2^(first_plane + i), negative_part its negative
-  int first_plane = 0, negative_part = -1;
+  int device = 0, parts = 0;
   int64_t stored_rows = 0, segments = 0, nunits = 0;
   int64_t head_bytes = 0, stream_bytes = 0, schedule_bytes = 0;
   std::vector<DeviceTile> tiles;
-  int waves = 16;  // wavefronts per workgroup at most
-  bool step2_plain = false;  // rsr_set_step2
   // host copy of the device tables, fetched on the first rsr_export_block
   std::vector<rsr_internal::TileTables> downloaded;
 };
@@ -134,26 +121,10 @@ bool valid(const rsr_handle* h) { return h && h->magic == kMagic; }
 // ---------------------------------------------------------------------------------------------
 // device code
 // ---------------------------------------------------------------------------------------------
-struct KArgs {
-  int rows, cols, k, nblocks, last_width, batch;
-  int vstride;   // elements between the activation vectors of consecutive batch lanes (the matrix's row count)
-  int row0;      // first row of this row tile
-  int accumulate;  // add to `out` instead of overwriting it (second and later row tiles, rsr_matvec_acc)
-  int scaled;      // multiply the product by `scale` first (rsr_matvec_acc)
-  uint32_t scale;  // bits of a float (float activations) or of an int (int8 activations)
-  int kc, both, pslots, panels;  // panels of a block (rsr_layout.h)
-  int fill, extra_stride;        // absent values are stored as zeros; entries per panel in the list of extra slots
-  // a part's weight: 1 << (part * wshift + wfirst), negative for part `wneg` (-1: none)
-  int wshift, wfirst, wneg;
-  int g1;        // workgroups per set of vectors
-  int waves;     // wavefronts that take units
-  int nunits;    // unit descriptors in the index
-  int nbuf;      // panels in flight per workgroup
-  int nrec;      // blocks whose panel records are kept (panels > 1)
-  uint32_t buf_magic, rec_magic;  // x / nbuf and x / nrec as high halves of products
-  uint32_t ubytes;  // bytes of a panel's sums in LDS
-  uint32_t off_u, off_rec, off_done, off_blocks, off_cnt, off_epoch, off_ctr;  // LDS byte offsets
-};
+using rsr::KArgs;
+using rsr::kItems;
+using rsr::LaunchPlan;
+using rsr::Mode;
 
 // A kernel's own arguments, in the memory they were passed in.
 #ifdef __HIP_DEVICE_COMPILE__
@@ -382,8 +353,9 @@ __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__bui
 struct F1 {  // one float vector
   using In = float;
   using Acc = float;
-  using Run = float;  // the running sums, R registers of them
-  static constexpr int V = 1, R = 1, shift = 2, slot_bytes = 4;
+  using Run = float;  // the running sums
+  static constexpr rsr::Pass pass = rsr::kF1;
+  static constexpr int V = pass.V, R = 1, shift = pass.shift, slot_bytes = pass.slot_bytes;  // (R: registers of running sums)
   using Slot = float;  // the sums of a slot
   __device__ static __forceinline__ float get(float x, int) { return x; }
   RSR_STEPS1(float, "v_add_f32", RSR_LANES1_F)
@@ -392,7 +364,8 @@ struct I1 {  // one int8 vector
   using In = int8_t;
   using Acc = int32_t;
   using Run = int32_t;
-  static constexpr int V = 1, R = 1, shift = 2, slot_bytes = 4;
+  static constexpr rsr::Pass pass = rsr::kI1;
+  static constexpr int V = pass.V, R = 1, shift = pass.shift, slot_bytes = pass.slot_bytes;
   using Slot = int32_t;
   __device__ static __forceinline__ int32_t get(int32_t x, int) { return x; }
   RSR_STEPS1(int32_t, "v_add_u32", RSR_LANES1_I)
@@ -401,7 +374,8 @@ struct F2 {  // two float vectors
   using In = float;
   using Acc = float;
   using Run = float;
-  static constexpr int V = 2, R = 2, shift = 3, slot_bytes = 8;
+  static constexpr rsr::Pass pass = rsr::kF2;
+  static constexpr int V = pass.V, R = 2, shift = pass.shift, slot_bytes = pass.slot_bytes;
   typedef float Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
   RSR_STEPS2(float, "v_add_f32", RSR_LANES2_F)
@@ -410,7 +384,8 @@ struct P2 {  // two int8 vectors
   using In = int8_t;
   using Acc = int32_t;
   using Run = uint32_t;
-  static constexpr int V = 2, R = 1, shift = 2, slot_bytes = 4;
+  static constexpr rsr::Pass pass = rsr::kP2;
+  static constexpr int V = pass.V, R = 1, shift = pass.shift, slot_bytes = pass.slot_bytes;
   typedef int16_t Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
   RSR_STEPS1(uint32_t, "v_pk_add_u16", RSR_LANES1_P)
@@ -419,7 +394,8 @@ struct P4 {  // four int8 vectors
   using In = int8_t;
   using Acc = int32_t;
   using Run = uint32_t;
-  static constexpr int V = 4, R = 2, shift = 3, slot_bytes = 8;
+  static constexpr rsr::Pass pass = rsr::kP4;
+  static constexpr int V = pass.V, R = 2, shift = pass.shift, slot_bytes = pass.slot_bytes;
   typedef int16_t Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
   RSR_STEPS2(uint32_t, "v_pk_add_u16", RSR_LANES2_P)
@@ -428,7 +404,8 @@ struct F4 {  // four float vectors; four positions per step (16 registers of gat
   using In = float;
   using Acc = float;
   using Run = float;
-  static constexpr int V = 4, R = 4, shift = 4, slot_bytes = 16;
+  static constexpr rsr::Pass pass = rsr::kF4;
+  static constexpr int V = pass.V, R = 4, shift = pass.shift, slot_bytes = pass.slot_bytes;
   typedef float Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
   __device__ static __forceinline__ void step4(uint32_t w0, uint32_t w1, float (&acc)[4], uint32_t hm, uint32_t wd, uint32_t ub) {
@@ -523,8 +500,7 @@ __device__ __forceinline__ AT sums_of_sixteen(const AT (&v)[16], int lane) {
 }
 
 constexpr int NG = rsr::kMaxGranules;
-constexpr int kItems = 16;      // per panel and vector: value bits 0 .. 11, the total (kTotal), unused
-constexpr int kTotal = 12;
+constexpr int kTotal = 12;      // where a record (kItems words) holds its panel's total
 constexpr int kExtraAhead = 128;  // extra sums of a panel whose slots are fetched ahead of the fold
 
 // u . Bin_[k] by its definition, for the four values value, value + 64, + 128, + 192: for every column (value bit) the sum
@@ -1085,134 +1061,13 @@ __global__ void __launch_bounds__(1024) rsr_multi_kernel(const MultiArgs m) {
 // ---------------------------------------------------------------------------------------------
 // host code
 // ---------------------------------------------------------------------------------------------
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
-struct LaunchPlan {
-  KArgs p;
-  int64_t grid = 0;
-  int waves = 0;
-  size_t lds = 0;
-};
-
-// x / d for small x as the high half of a product (d >= 2)
-uint32_t magic(uint32_t d) { return d < 2 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
-
-// Launch shape of one row tile for `batch` vectors on `num_cu` compute units in mode M.
-// `max_wg_per_cu`: how many workgroups of this product may share a compute unit (a launch that carries
-// several products gives every workgroup the largest LDS size any of them needs, so it plans with 1).
-// Returns RSR_ERR_UNSUPPORTED (without a message) if the mode does not fit in LDS.
-template <class M>
-int plan_tile(const rsr_handle* h, const DeviceTile& T, bool accumulate, int batch, int num_cu, int max_wg_per_cu, LaunchPlan* plan) {
-  KArgs& p = plan->p;
-  std::memset(&p, 0, sizeof(p));
-  const rsr::Shape& S = T.shape;
-  p.rows = (int)T.rows; p.cols = (int)h->cols; p.k = h->k;
-  p.nblocks = (int)h->nblocks; p.last_width = h->last_width; p.batch = batch;
-  p.vstride = (int)h->rows; p.row0 = (int)T.row0; p.accumulate = accumulate ? 1 : 0;
-  p.kc = S.kc; p.both = S.both; p.pslots = S.pslots; p.panels = S.panels;
-  p.fill = T.fill ? 1 : 0; p.extra_stride = T.extra_stride;
-  p.wshift = h->qbit ? 1 : 0; p.wfirst = h->first_plane; p.wneg = h->negative_part;
-  p.nunits = (int)T.nunits;
-
-  // LDS: activations, panels in flight, records of the blocks in flight, counters
-  const size_t vbytes = align_up((size_t)(T.rows + 1) << M::shift, 16);
-  p.ubytes = (uint32_t)((size_t)(S.nslots + rsr::kDummySlots + (T.max_extras + 7) / 8 * 8) * M::slot_bytes);
-  const bool records = S.panels > 1 || h->qbit;
-  const size_t rec_bytes = (size_t)S.panels * M::V * kItems * 4;
-  auto recs = [&](int nbuf) { return records ? 1 + (nbuf - 1 + S.panels - 1) / S.panels : 0; };
-  auto total = [&](int nbuf) { return vbytes + (size_t)nbuf * p.ubytes + (size_t)recs(nbuf) * (rec_bytes + 8) + (size_t)nbuf * 8 + 16; };
-  // Grid and workgroup size.  Up to four workgroups per compute unit if they fit together (LDS, and 16
-  // wavefronts per compute unit at this kernel's register count); never more workgroups than blocks; and
-  // no more wavefronts than the largest share of a workgroup has units: idle wavefronts only lengthen
-  // the start of the launch (1024 x 1024: 5.5 -> 4.0 us per product).
-  const int64_t sets = ((int64_t)batch + M::V - 1) / M::V;
-  int64_t g1 = 1;
-  int waves = 0, nbuf = 0;
-  for (int wg = max_wg_per_cu; wg >= 1; --wg) {
-    g1 = ((int64_t)num_cu * wg + sets - 1) / sets;
-    g1 = (g1 + 7) / 8 * 8;
-    if (g1 > h->nblocks) g1 = h->nblocks;
-    if (g1 < 1) g1 = 1;
-    const int64_t blocks_per_wg = (h->nblocks + g1 - 1) / g1;
-    // Equal shares: no more workgroups than it takes to keep the largest share this small.  (1366 blocks
-    // over 256 compute units would be 5 or 6 blocks each; 228 workgroups get 6 each, 28 compute units
-    // stay idle, and the product is 0.5 us faster: the stream is shared by all compute units and the
-    // workgroups with the larger share finish last either way, only later when more of them compete.)
-    g1 = (h->nblocks + blocks_per_wg - 1) / blocks_per_wg;
-    const int64_t units_per_wg = blocks_per_wg * (int64_t)std::max<uint32_t>(1, T.max_units_per_block);
-    waves = (int)std::min<int64_t>(h->waves, units_per_wg);
-    // Up to eight panels in flight where the LDS holds them (a wavefront whose unit belongs to a later panel waits).
-    const int64_t panels_per_wg = blocks_per_wg * S.panels;
-    const int most = (int)std::min<int64_t>(8, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
-    for (nbuf = most; nbuf > least && (total(nbuf) > h->lds_max || (wg > 1 && (size_t)wg * total(nbuf) > h->lds_max)); --nbuf) {}
-    if (total(nbuf) > h->lds_max) return RSR_ERR_UNSUPPORTED;
-    if (wg == 1 || (wg * waves <= 16 && (size_t)wg * total(nbuf) <= h->lds_max)) break;
-  }
-  p.g1 = (int)g1;
-  const int64_t grid = (g1 + 7) / 8 * 8 * sets;
-  if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
-
-  plan->lds = total(nbuf);
-  plan->grid = grid;
-  plan->waves = waves;
-  p.waves = waves;
-  p.nbuf = nbuf; p.buf_magic = magic((uint32_t)nbuf);
-  p.nrec = recs(nbuf); p.rec_magic = magic((uint32_t)p.nrec);
-  p.off_u = (uint32_t)vbytes;
-  p.off_rec = (uint32_t)(vbytes + (size_t)nbuf * p.ubytes);
-  p.off_done = (uint32_t)(p.off_rec + (size_t)p.nrec * rec_bytes);
-  p.off_blocks = p.off_done + (uint32_t)p.nrec * 4;
-  p.off_cnt = p.off_blocks + (uint32_t)p.nrec * 4;
-  p.off_epoch = p.off_cnt + (uint32_t)nbuf * 4;
-  p.off_ctr = p.off_epoch + (uint32_t)nbuf * 4;
-  return RSR_OK;
-}
-
-// How many vectors share a pass: the most for which a workgroup's wavefronts do not wait for room.  A unit of the stream
-// keeps its share of a panel's sums in LDS from its start until the panel is folded, about one and a half times as long as it
-// is summed: with sums of fewer than kRoom units in flight wavefronts stand still.  (sixteen vectors at 2560 x 7680, k = 10:
-// room for 14 units with four vectors per pass, 34 with two.)
-enum class Mode { one, two, four };
-constexpr int kRoom = 24;
-template <class M>
-bool mode_fits(const rsr_handle* h, const DeviceTile& T, int batch) {
-  LaunchPlan plan;
-  if (plan_tile<M>(h, T, false, batch, h->num_cu, 1, &plan) != RSR_OK) return false;
-  const int64_t panels = h->nblocks * T.shape.panels, per_wg = (h->nblocks + plan.p.g1 - 1) / plan.p.g1 * T.shape.panels;
-  return plan.p.nbuf >= per_wg || plan.p.nbuf * T.nunits >= kRoom * panels;
-}
-// A pass over V vectors costs a wavefront `cost` times as much as a pass over one, and launches with less than a unit per
-// wavefront of the device take as long as one unit does: few units are better spread out, a vector per pass.
-// `units`: of all products that share the launch.
-double pass_cost(int64_t units, int num_cu, int waves, int batch, int V, double cost) {
-  return cost * std::max(1.0, (double)units * ((batch + V - 1) / V) / ((double)num_cu * waves));
-}
-Mode pick_mode(const rsr_handle* h, const DeviceTile& T, int batch, int64_t units, const float*) {
-  if (h->step2_plain || batch < 2) return Mode::one;
-  const double c1 = pass_cost(units, h->num_cu, h->waves, batch, 1, 1.0), c2 = pass_cost(units, h->num_cu, h->waves, batch, 2, 1.4);
-  const double c4 = pass_cost(units, h->num_cu, h->waves, batch, 4, 2.2);
-  if (c4 < c2 && c4 < c1 && mode_fits<F4>(h, T, batch)) return Mode::four;
-  return c2 < c1 && mode_fits<F2>(h, T, batch) ? Mode::two : Mode::one;
-}
-Mode pick_mode(const rsr_handle* h, const DeviceTile& T, int batch, int64_t units, const int8_t*) {
-  if (h->step2_plain || batch < 2) return Mode::one;
-  // (a device that is nearly full of units is slower than one that is half full: 2048 x 2888, four vectors, 0.96 units per
-  // wavefront: 7.6 us with one vector per pass, 6.8 with two; 3584 x 2432, 0.57 units: 5.7 and 6.5)
-  const double full = (double)units * batch / ((double)h->num_cu * h->waves);
-  const double c1 = std::max(0.55 + 0.6 * full, pass_cost(units, h->num_cu, h->waves, batch, 1, 1.0));
-  const double c2 = pass_cost(units, h->num_cu, h->waves, batch, 2, 1.1);
-  const double c4 = pass_cost(units, h->num_cu, h->waves, batch, 4, 1.5);
-  if (c4 < c2 && c4 < c1 && mode_fits<P4>(h, T, batch)) return Mode::four;
-  return c2 < c1 ? Mode::two : Mode::one;  // (two need no more LDS than one)
-}
-
 template <class M, bool PLAIN>
 int launch_mode(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const typename M::In* v, void* out, int batch,
                 void* stream) {
   LaunchPlan plan;
-  const int rc = plan_tile<M>(h, T, accumulate, batch, h->num_cu, 4, &plan);
+  const int rc = rsr::plan_tile(M::pass, *h, T, accumulate, batch, h->num_cu, 4, &plan);
   if (rc == RSR_ERR_UNSUPPORTED) return fail(rc, "a row tile of " + std::to_string(T.rows) + " rows does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
-  if (rc != RSR_OK) return rc;
+  if (rc != RSR_OK) return fail(rc, "batch too large");
   if (scale) { plan.p.scaled = 1; plan.p.scale = *scale; }
   hipLaunchKernelGGL((rsr_matvec_kernel<M, PLAIN>), dim3((unsigned)plan.grid), dim3((unsigned)(plan.waves * 64)), plan.lds,
                      static_cast<hipStream_t>(stream), static_cast<const unsigned char*>(T.d_stream), static_cast<const uint32_t*>(T.d_units),
@@ -1224,7 +1079,7 @@ int launch_mode(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint3
 
 int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const float* v, void* out, int batch, void* stream) {
   if (h->step2_plain) return launch_mode<F1, true>(h, T, accumulate, scale, v, out, batch, stream);
-  switch (pick_mode(h, T, batch, T.nunits, v)) {
+  switch (rsr::pick_mode(*h, T, batch, T.nunits, v)) {
     case Mode::four: return launch_mode<F4, false>(h, T, accumulate, scale, v, out, batch, stream);
     case Mode::two: return launch_mode<F2, false>(h, T, accumulate, scale, v, out, batch, stream);
     default: return launch_mode<F1, false>(h, T, accumulate, scale, v, out, batch, stream);
@@ -1232,7 +1087,7 @@ int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint3
 }
 int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const int8_t* v, void* out, int batch, void* stream) {
   if (h->step2_plain) return launch_mode<I1, true>(h, T, accumulate, scale, v, out, batch, stream);
-  switch (pick_mode(h, T, batch, T.nunits, v)) {
+  switch (rsr::pick_mode(*h, T, batch, T.nunits, v)) {
     case Mode::four: return launch_mode<P4, false>(h, T, accumulate, scale, v, out, batch, stream);
     case Mode::two: return launch_mode<P2, false>(h, T, accumulate, scale, v, out, batch, stream);
     default: return launch_mode<I1, false>(h, T, accumulate, scale, v, out, batch, stream);
@@ -1253,9 +1108,9 @@ int launch_multi_mode(const rsr_job* jobs, int njobs, int batch, void* stream, c
     rsr_handle* h = jobs[j].h;
     const DeviceTile& T = h->tiles[0];
     LaunchPlan plan;
-    const int rc = plan_tile<M>(h, T, false, batch, std::min(share[j], h->num_cu), 1, &plan);
+    const int rc = rsr::plan_tile(M::pass, *h, T, false, batch, std::min(share[j], h->num_cu), 1, &plan);
     if (rc == RSR_ERR_UNSUPPORTED) return fail(rc, "a row tile of " + std::to_string(T.rows) + " rows does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
-    if (rc != RSR_OK) return rc;
+    if (rc != RSR_OK) return fail(rc, "batch too large");
     KJob& J = m.job[j];
     J.stream = static_cast<const unsigned char*>(T.d_stream);
     J.unit_words = static_cast<const uint32_t*>(T.d_units);
@@ -1279,39 +1134,21 @@ int launch_multi(const rsr_job* jobs, int njobs, int batch, void* stream) {
   if (!jobs || njobs < 1) return fail(RSR_ERR_INVALID_ARGUMENT, "no jobs");
   if (njobs > kMaxJobs) return fail(RSR_ERR_INVALID_ARGUMENT, "at most " + std::to_string(kMaxJobs) + " products per launch");
   if (batch < 1 || batch > 65535) return fail(RSR_ERR_INVALID_ARGUMENT, "batch must be in 1..65535");
-  double bytes_total = 0;
+  int64_t bytes[kMaxJobs];
   for (int j = 0; j < njobs; ++j) {
     if (!valid(jobs[j].h)) return fail(RSR_ERR_INVALID_ARGUMENT, "invalid handle in job " + std::to_string(j));
     if (!jobs[j].v || !jobs[j].out) return fail(RSR_ERR_INVALID_ARGUMENT, "null pointer in job " + std::to_string(j));
     if (jobs[j].h->tiles.size() != 1) return fail(RSR_ERR_UNSUPPORTED, "a matrix with more than 32768 rows takes a launch per row tile: use rsr_matvec");
     if (jobs[j].h->device != jobs[0].h->device) return fail(RSR_ERR_INVALID_ARGUMENT, "the handles belong to different devices");
-    bytes_total += (double)jobs[j].h->stream_bytes + 1.0;
+    bytes[j] = jobs[j].h->stream_bytes;
   }
   const int num_cu = jobs[0].h->num_cu;
-  // shares in multiples of 8 compute units (one per XCD), at least 8, together no more than the device has
-  // (a workgroup that has to wait for a free compute unit would start when the others are nearly done)
   int share[kMaxJobs];
-  int given = 0;
-  for (int j = 0; j < njobs; ++j) {
-    share[j] = std::max(8, (int)((double)num_cu * ((double)jobs[j].h->stream_bytes + 1.0) / bytes_total) / 8 * 8);
-    given += share[j];
-  }
-  while (given > num_cu) {
-    int big = 0;
-    for (int j = 1; j < njobs; ++j) if (share[j] > share[big]) big = j;
-    if (share[big] <= 8) break;
-    share[big] -= 8; given -= 8;
-  }
-  while (given + 8 <= num_cu) {  // what is left over goes to the products with the most bytes per compute unit
-    int best = 0;
-    for (int j = 1; j < njobs; ++j)
-      if ((double)jobs[j].h->stream_bytes / share[j] > (double)jobs[best].h->stream_bytes / share[best]) best = j;
-    share[best] += 8; given += 8;
-  }
+  rsr::split_device(bytes, njobs, num_cu, share);
   Mode mode = Mode::four;  // the widest that suits every product
   int64_t units = 0;
   for (int j = 0; j < njobs; ++j) units += jobs[j].h->nunits;
-  for (int j = 0; j < njobs; ++j) mode = std::min(mode, pick_mode(jobs[j].h, jobs[j].h->tiles[0], batch, units, static_cast<const VT*>(nullptr)));
+  for (int j = 0; j < njobs; ++j) mode = std::min(mode, rsr::pick_mode(*jobs[j].h, jobs[j].h->tiles[0], batch, units, static_cast<const VT*>(nullptr)));
   if constexpr (sizeof(VT) == 4) {
     if (mode == Mode::four) return launch_multi_mode<F4>(jobs, njobs, batch, stream, share);
     if (mode == Mode::two) return launch_multi_mode<F2>(jobs, njobs, batch, stream, share);
@@ -1429,17 +1266,6 @@ struct DeviceCopy {
 }  // namespace
 
 namespace rsr_internal {
-
-int planes_per_handle(int64_t rows, int k, int q) {
-  const int64_t height = std::min<int64_t>(rows, rsr::kTileRows);
-  for (int n = q; n > 1; --n) {
-    const rsr::Shape s = rsr::panel_shape(height, k, n, false);
-    const int64_t lds = align_up((size_t)(height + 1) * 4, 16) + 2 * (int64_t)(s.nslots + rsr::kDummySlots + rsr::kMaxExtras) * 4 +
-                        2 * ((int64_t)s.panels * kItems * 4 + 8) + 64;
-    if (lds <= 160 * 1024) return n;
-  }
-  return 1;
-}
 
 int8_t* device_copy(const int8_t* A, int64_t count, const char* who) {
   DeviceCopy d;

@@ -1,0 +1,224 @@
+// Launch planning of the product kernels (rsr_lib.hip): grid, workgroup size, LDS layout, and how many vectors share a
+// pass.  Host code without any HIP call, so that a program on a machine with no GPU can check it.
+#ifndef RSR_PLAN_H_
+#define RSR_PLAN_H_
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+#include <cstring>
+
+#include "../../include/rsr.h"
+#include "rsr_layout.h"
+
+namespace rsr {
+
+constexpr int kItems = 16;  // words of a panel's record per vector: value bits 0 .. 11, the total, unused
+
+// An activation mode as the planner sees it: vectors per pass, LDS bytes per row (1 << shift) and per slot of a panel.
+struct Pass {
+  int V, shift, slot_bytes;
+};
+constexpr Pass kF1{1, 2, 4}, kF2{2, 3, 8}, kF4{4, 4, 16};  // float
+constexpr Pass kI1{1, 2, 4}, kP2{2, 2, 4}, kP4{4, 3, 8};   // int8: one vector in 32 bits, two and four in 16
+
+// What a launch has to know of a row tile and of its matrix.
+struct PlanTile {
+  int64_t rows = 0, row0 = 0;
+  Shape shape{};
+  int extra_stride = 0, max_extras = 0;  // entries per panel in the list of extra slots; extra slots of a panel at most
+  bool fill = false;  // absent values are stored as zeros: a panel's slots need no clearing
+  uint32_t max_units_per_block = 0;
+  int64_t nunits = 0;
+};
+struct PlanMatrix {
+  int num_cu = 0;
+  size_t lds_max = 0;
+  int64_t rows = 0, cols = 0, nblocks = 0;
+  int k = 0, last_width = 0;
+  bool qbit = false;      // the parts are bit planes: part i weighs 2^(first_plane + i), negative_part its negative
+  int first_plane = 0, negative_part = -1;
+  int waves = 16;  // wavefronts per workgroup at most
+  bool step2_plain = false;  // rsr_set_step2
+};
+
+// Kernel arguments.
+struct KArgs {
+  int rows, cols, k, nblocks, last_width, batch;
+  int vstride;   // elements between the activation vectors of consecutive batch lanes (the matrix's row count)
+  int row0;      // first row of this row tile
+  int accumulate;  // add to `out` instead of overwriting it (second and later row tiles, rsr_matvec_acc)
+  int scaled;      // multiply the product by `scale` first (rsr_matvec_acc)
+  uint32_t scale;  // bits of a float (float activations) or of an int (int8 activations)
+  int kc, both, pslots, panels;  // panels of a block (rsr_layout.h)
+  int fill, extra_stride;        // absent values are stored as zeros; entries per panel in the list of extra slots
+  // a part's weight: 1 << (part * wshift + wfirst), negative for part `wneg` (-1: none)
+  int wshift, wfirst, wneg;
+  int g1;        // workgroups per set of vectors
+  int waves;     // wavefronts that take units
+  int nunits;    // unit descriptors in the index
+  int nbuf;      // panels in flight per workgroup
+  int nrec;      // blocks whose panel records are kept (panels > 1)
+  uint32_t buf_magic, rec_magic;  // x / nbuf and x / nrec as high halves of products
+  uint32_t ubytes;  // bytes of a panel's sums in LDS
+  uint32_t off_u, off_rec, off_done, off_blocks, off_cnt, off_epoch, off_ctr;  // LDS byte offsets
+};
+
+struct LaunchPlan {
+  KArgs p;
+  int64_t grid = 0;
+  int waves = 0;
+  size_t lds = 0;
+};
+
+inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// x / d for small x as the high half of a product (d >= 2)
+inline uint32_t magic(uint32_t d) { return d < 2 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+
+// Launch shape of one row tile for `batch` vectors on `num_cu` compute units in mode M.
+// `max_wg_per_cu`: how many workgroups of this product may share a compute unit (a launch that carries
+// several products gives every workgroup the largest LDS size any of them needs, so it plans with 1).
+// Returns RSR_ERR_UNSUPPORTED if the mode does not fit in LDS, RSR_ERR_INVALID_ARGUMENT if the batch is too large for a grid.
+inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool accumulate, int batch, int num_cu, int max_wg_per_cu, LaunchPlan* plan) {
+  KArgs& p = plan->p;
+  std::memset(&p, 0, sizeof(p));
+  const Shape& S = T.shape;
+  p.rows = (int)T.rows; p.cols = (int)h.cols; p.k = h.k;
+  p.nblocks = (int)h.nblocks; p.last_width = h.last_width; p.batch = batch;
+  p.vstride = (int)h.rows; p.row0 = (int)T.row0; p.accumulate = accumulate ? 1 : 0;
+  p.kc = S.kc; p.both = S.both; p.pslots = S.pslots; p.panels = S.panels;
+  p.fill = T.fill ? 1 : 0; p.extra_stride = T.extra_stride;
+  p.wshift = h.qbit ? 1 : 0; p.wfirst = h.first_plane; p.wneg = h.negative_part;
+  p.nunits = (int)T.nunits;
+
+  // LDS: activations, panels in flight, records of the blocks in flight, counters
+  const size_t vbytes = align_up((size_t)(T.rows + 1) << M.shift, 16);
+  p.ubytes = (uint32_t)((size_t)(S.nslots + kDummySlots + (T.max_extras + 7) / 8 * 8) * M.slot_bytes);
+  const bool records = S.panels > 1 || h.qbit;
+  const size_t rec_bytes = (size_t)S.panels * M.V * kItems * 4;
+  auto recs = [&](int nbuf) { return records ? 1 + (nbuf - 1 + S.panels - 1) / S.panels : 0; };
+  auto total = [&](int nbuf) { return vbytes + (size_t)nbuf * p.ubytes + (size_t)recs(nbuf) * (rec_bytes + 8) + (size_t)nbuf * 8 + 16; };
+  // Grid and workgroup size.  Up to four workgroups per compute unit if they fit together (LDS, and 16
+  // wavefronts per compute unit at this kernel's register count); never more workgroups than blocks; and
+  // no more wavefronts than the largest share of a workgroup has units: idle wavefronts only lengthen
+  // the start of the launch (1024 x 1024: 5.5 -> 4.0 us per product).
+  const int64_t sets = ((int64_t)batch + M.V - 1) / M.V;
+  int64_t g1 = 1;
+  int waves = 0, nbuf = 0;
+  for (int wg = max_wg_per_cu; wg >= 1; --wg) {
+    g1 = ((int64_t)num_cu * wg + sets - 1) / sets;
+    g1 = (g1 + 7) / 8 * 8;
+    if (g1 > h.nblocks) g1 = h.nblocks;
+    if (g1 < 1) g1 = 1;
+    const int64_t blocks_per_wg = (h.nblocks + g1 - 1) / g1;
+    // Equal shares: no more workgroups than it takes to keep the largest share this small.  (1366 blocks
+    // over 256 compute units would be 5 or 6 blocks each; 228 workgroups get 6 each, 28 compute units
+    // stay idle, and the product is 0.5 us faster: the stream is shared by all compute units and the
+    // workgroups with the larger share finish last either way, only later when more of them compete.)
+    g1 = (h.nblocks + blocks_per_wg - 1) / blocks_per_wg;
+    const int64_t units_per_wg = blocks_per_wg * (int64_t)std::max<uint32_t>(1, T.max_units_per_block);
+    waves = (int)std::min<int64_t>(h.waves, units_per_wg);
+    // Up to eight panels in flight where the LDS holds them (a wavefront whose unit belongs to a later panel waits).
+    const int64_t panels_per_wg = blocks_per_wg * S.panels;
+    const int most = (int)std::min<int64_t>(8, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
+    for (nbuf = most; nbuf > least && (total(nbuf) > h.lds_max || (wg > 1 && (size_t)wg * total(nbuf) > h.lds_max)); --nbuf) {}
+    if (total(nbuf) > h.lds_max) return RSR_ERR_UNSUPPORTED;
+    if (wg == 1 || (wg * waves <= 16 && (size_t)wg * total(nbuf) <= h.lds_max)) break;
+  }
+  p.g1 = (int)g1;
+  const int64_t grid = (g1 + 7) / 8 * 8 * sets;
+  if (grid > 0x7fffffff) return RSR_ERR_INVALID_ARGUMENT;
+
+  plan->lds = total(nbuf);
+  plan->grid = grid;
+  plan->waves = waves;
+  p.waves = waves;
+  p.nbuf = nbuf; p.buf_magic = magic((uint32_t)nbuf);
+  p.nrec = recs(nbuf); p.rec_magic = magic((uint32_t)p.nrec);
+  p.off_u = (uint32_t)vbytes;
+  p.off_rec = (uint32_t)(vbytes + (size_t)nbuf * p.ubytes);
+  p.off_done = (uint32_t)(p.off_rec + (size_t)p.nrec * rec_bytes);
+  p.off_blocks = p.off_done + (uint32_t)p.nrec * 4;
+  p.off_cnt = p.off_blocks + (uint32_t)p.nrec * 4;
+  p.off_epoch = p.off_cnt + (uint32_t)nbuf * 4;
+  p.off_ctr = p.off_epoch + (uint32_t)nbuf * 4;
+  return RSR_OK;
+}
+
+// How many vectors share a pass: the most for which a workgroup's wavefronts do not wait for room.  A unit of the stream
+// keeps its share of a panel's sums in LDS from its start until the panel is folded, about one and a half times as long as it
+// is summed: with sums of fewer than kRoom units in flight wavefronts stand still.  (sixteen vectors at 2560 x 7680, k = 10:
+// room for 14 units with four vectors per pass, 34 with two.)
+enum class Mode { one, two, four };
+constexpr int kRoom = 24;
+inline bool mode_fits(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch) {
+  LaunchPlan plan;
+  if (plan_tile(M, h, T, false, batch, h.num_cu, 1, &plan) != RSR_OK) return false;
+  const int64_t panels = h.nblocks * T.shape.panels, per_wg = (h.nblocks + plan.p.g1 - 1) / plan.p.g1 * T.shape.panels;
+  return plan.p.nbuf >= per_wg || plan.p.nbuf * T.nunits >= kRoom * panels;
+}
+// A pass over V vectors costs a wavefront `cost` times as much as a pass over one, and launches with less than a unit per
+// wavefront of the device take as long as one unit does: few units are better spread out, a vector per pass.
+// `units`: of all products that share the launch.
+inline double pass_cost(int64_t units, int num_cu, int waves, int batch, int V, double cost) {
+  return cost * std::max(1.0, (double)units * ((batch + V - 1) / V) / ((double)num_cu * waves));
+}
+inline Mode pick_mode(const PlanMatrix& h, const PlanTile& T, int batch, int64_t units, const float*) {
+  if (h.step2_plain || batch < 2) return Mode::one;
+  const double c1 = pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0), c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.4);
+  const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 2.2);
+  if (c4 < c2 && c4 < c1 && mode_fits(kF4, h, T, batch)) return Mode::four;
+  return c2 < c1 && mode_fits(kF2, h, T, batch) ? Mode::two : Mode::one;
+}
+inline Mode pick_mode(const PlanMatrix& h, const PlanTile& T, int batch, int64_t units, const int8_t*) {
+  if (h.step2_plain || batch < 2) return Mode::one;
+  // (a device that is nearly full of units is slower than one that is half full: 2048 x 2888, four vectors, 0.96 units per
+  // wavefront: 7.6 us with one vector per pass, 6.8 with two; 3584 x 2432, 0.57 units: 5.7 and 6.5)
+  const double full = (double)units * batch / ((double)h.num_cu * h.waves);
+  const double c1 = std::max(0.55 + 0.6 * full, pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0));
+  const double c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.1);
+  const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 1.5);
+  if (c4 < c2 && c4 < c1 && mode_fits(kP4, h, T, batch)) return Mode::four;
+  return c2 < c1 ? Mode::two : Mode::one;  // (two need no more LDS than one)
+}
+
+// The compute units of several products that share a launch, in proportion to the bytes of their tables: multiples of 8
+// (one per XCD), at least 8, together no more than the device has (a workgroup that has to wait for a free compute unit
+// would start when the others are nearly done).
+inline void split_device(const int64_t* bytes, int njobs, int num_cu, int* share) {
+  double bytes_total = 0;
+  for (int j = 0; j < njobs; ++j) bytes_total += (double)bytes[j] + 1.0;
+  int given = 0;
+  for (int j = 0; j < njobs; ++j) {
+    share[j] = std::max(8, (int)((double)num_cu * ((double)bytes[j] + 1.0) / bytes_total) / 8 * 8);
+    given += share[j];
+  }
+  while (given > num_cu) {
+    int big = 0;
+    for (int j = 1; j < njobs; ++j) if (share[j] > share[big]) big = j;
+    if (share[big] <= 8) break;
+    share[big] -= 8; given -= 8;
+  }
+  while (given + 8 <= num_cu) {  // what is left over goes to the products with the most bytes per compute unit
+    int best = 0;
+    for (int j = 1; j < njobs; ++j)
+      if ((double)bytes[j] / share[j] > (double)bytes[best] / share[best]) best = j;
+    share[best] += 8; given += 8;
+  }
+}
+
+// How many of the q bit planes of a matrix share a launch: as many as leave room for their records beside the activations.
+inline int planes_per_handle(int64_t rows, int k, int q) {
+  const int64_t height = std::min<int64_t>(rows, kTileRows);
+  for (int n = q; n > 1; --n) {
+    const Shape s = panel_shape(height, k, n, false);
+    const int64_t lds = align_up((size_t)(height + 1) * 4, 16) + 2 * (int64_t)(s.nslots + kDummySlots + kMaxExtras) * 4 +
+                        2 * ((int64_t)s.panels * kItems * 4 + 8) + 64;
+    if (lds <= 160 * 1024) return n;
+  }
+  return 1;
+}
+
+}  // namespace rsr
+#endif  // RSR_PLAN_H_

@@ -10,6 +10,7 @@
 
 #include "../../include/rsr_qbit.h"
 #include "rsr_internal.h"
+#include "rsr_plan.h"
 
 struct rsr_qbit {
   uint64_t magic = 0;
@@ -44,7 +45,7 @@ rsr_qbit* rsr_qbit_preprocess(const int8_t* A, int64_t rows, int64_t cols, int k
   h->q = q;
   int8_t* dA = rsr_internal::device_copy(A, count, "rsr_qbit_preprocess");
   if (!dA) return nullptr;
-  const int per = rsr_internal::planes_per_handle(rows, k, q);
+  const int per = rsr::planes_per_handle(rows, k, q);
   bool ok = true;
   try {
     for (int p0 = 0; ok && p0 < q; p0 += per) {
