@@ -1062,13 +1062,7 @@ __global__ void __launch_bounds__(1024) rsr_multi_kernel(const MultiArgs m) {
 // host code
 // ---------------------------------------------------------------------------------------------
 template <class M, bool PLAIN>
-int launch_mode(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const typename M::In* v, void* out, int batch,
-                void* stream) {
-  LaunchPlan plan;
-  const int rc = rsr::plan_tile(M::pass, *h, T, accumulate, batch, h->num_cu, 4, &plan);
-  if (rc == RSR_ERR_UNSUPPORTED) return fail(rc, "a row tile of " + std::to_string(T.rows) + " rows does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
-  if (rc != RSR_OK) return fail(rc, "batch too large");
-  if (scale) { plan.p.scaled = 1; plan.p.scale = *scale; }
+int enqueue(const DeviceTile& T, const LaunchPlan& plan, const typename M::In* v, void* out, void* stream) {
   hipLaunchKernelGGL((rsr_matvec_kernel<M, PLAIN>), dim3((unsigned)plan.grid), dim3((unsigned)(plan.waves * 64)), plan.lds,
                      static_cast<hipStream_t>(stream), static_cast<const unsigned char*>(T.d_stream), static_cast<const uint32_t*>(T.d_units),
                      static_cast<const uint32_t*>(T.d_blk_unit), static_cast<const uint16_t*>(T.d_extras), v,
@@ -1077,20 +1071,33 @@ int launch_mode(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint3
   return RSR_OK;
 }
 
-int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const float* v, void* out, int batch, void* stream) {
-  if (h->step2_plain) return launch_mode<F1, true>(h, T, accumulate, scale, v, out, batch, stream);
-  switch (rsr::pick_mode(*h, T, batch, T.nunits, v)) {
-    case Mode::four: return launch_mode<F4, false>(h, T, accumulate, scale, v, out, batch, stream);
-    case Mode::two: return launch_mode<F2, false>(h, T, accumulate, scale, v, out, batch, stream);
-    default: return launch_mode<F1, false>(h, T, accumulate, scale, v, out, batch, stream);
-  }
+int plan_failed(int rc, const rsr_handle* h, const DeviceTile& T) {
+  if (rc == RSR_ERR_UNSUPPORTED) return fail(rc, "a row tile of " + std::to_string(T.rows) + " rows does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
+  return fail(rc, "batch too large");
 }
-int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const int8_t* v, void* out, int batch, void* stream) {
-  if (h->step2_plain) return launch_mode<I1, true>(h, T, accumulate, scale, v, out, batch, stream);
-  switch (rsr::pick_mode(*h, T, batch, T.nunits, v)) {
-    case Mode::four: return launch_mode<P4, false>(h, T, accumulate, scale, v, out, batch, stream);
-    case Mode::two: return launch_mode<P2, false>(h, T, accumulate, scale, v, out, batch, stream);
-    default: return launch_mode<I1, false>(h, T, accumulate, scale, v, out, batch, stream);
+
+template <typename VT>
+int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint32_t* scale, const VT* v, void* out, int batch, void* stream) {
+  constexpr bool i8 = sizeof(VT) == 1;
+  Mode mode;
+  LaunchPlan plan;
+  const int rc = rsr::plan_product(i8, *h, T, accumulate, batch, &mode, &plan);
+  if (rc != RSR_OK) return plan_failed(rc, h, T);
+  if (scale) { plan.p.scaled = 1; plan.p.scale = *scale; }
+  if constexpr (i8) {
+    if (h->step2_plain) return enqueue<I1, true>(T, plan, v, out, stream);
+    switch (mode) {
+      case Mode::four: return enqueue<P4, false>(T, plan, v, out, stream);
+      case Mode::two: return enqueue<P2, false>(T, plan, v, out, stream);
+      default: return enqueue<I1, false>(T, plan, v, out, stream);
+    }
+  } else {
+    if (h->step2_plain) return enqueue<F1, true>(T, plan, v, out, stream);
+    switch (mode) {
+      case Mode::four: return enqueue<F4, false>(T, plan, v, out, stream);
+      case Mode::two: return enqueue<F2, false>(T, plan, v, out, stream);
+      default: return enqueue<F1, false>(T, plan, v, out, stream);
+    }
   }
 }
 
@@ -1109,8 +1116,7 @@ int launch_multi_mode(const rsr_job* jobs, int njobs, int batch, void* stream, c
     const DeviceTile& T = h->tiles[0];
     LaunchPlan plan;
     const int rc = rsr::plan_tile(M::pass, *h, T, false, batch, std::min(share[j], h->num_cu), 1, &plan);
-    if (rc == RSR_ERR_UNSUPPORTED) return fail(rc, "a row tile of " + std::to_string(T.rows) + " rows does not fit in " + std::to_string(h->lds_max) + " bytes of LDS");
-    if (rc != RSR_OK) return fail(rc, "batch too large");
+    if (rc != RSR_OK) return plan_failed(rc, h, T);
     KJob& J = m.job[j];
     J.stream = static_cast<const unsigned char*>(T.d_stream);
     J.unit_words = static_cast<const uint32_t*>(T.d_units);
@@ -1148,7 +1154,7 @@ int launch_multi(const rsr_job* jobs, int njobs, int batch, void* stream) {
   Mode mode = Mode::four;  // the widest that suits every product
   int64_t units = 0;
   for (int j = 0; j < njobs; ++j) units += jobs[j].h->nunits;
-  for (int j = 0; j < njobs; ++j) mode = std::min(mode, rsr::pick_mode(*jobs[j].h, jobs[j].h->tiles[0], batch, units, static_cast<const VT*>(nullptr)));
+  for (int j = 0; j < njobs; ++j) mode = std::min(mode, rsr::pick_mode(sizeof(VT) == 1, *jobs[j].h, jobs[j].h->tiles[0], batch, units));
   if constexpr (sizeof(VT) == 4) {
     if (mode == Mode::four) return launch_multi_mode<F4>(jobs, njobs, batch, stream, share);
     if (mode == Mode::two) return launch_multi_mode<F2>(jobs, njobs, batch, stream, share);

@@ -151,7 +151,14 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
 // is summed: with sums of fewer than kRoom units in flight wavefronts stand still.  (sixteen vectors at 2560 x 7680, k = 10:
 // room for 14 units with four vectors per pass, 34 with two.)
 enum class Mode { one, two, four };
+inline const Pass& pass_of(bool i8, Mode m) {
+  return m == Mode::four ? (i8 ? kP4 : kF4) : m == Mode::two ? (i8 ? kP2 : kF2) : (i8 ? kI1 : kF1);
+}
 constexpr int kRoom = 24;
+inline bool fits_lds(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch) {
+  LaunchPlan plan;
+  return plan_tile(M, h, T, false, batch, h.num_cu, 1, &plan) == RSR_OK;
+}
 inline bool mode_fits(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch) {
   LaunchPlan plan;
   if (plan_tile(M, h, T, false, batch, h.num_cu, 1, &plan) != RSR_OK) return false;
@@ -164,15 +171,14 @@ inline bool mode_fits(const Pass& M, const PlanMatrix& h, const PlanTile& T, int
 inline double pass_cost(int64_t units, int num_cu, int waves, int batch, int V, double cost) {
   return cost * std::max(1.0, (double)units * ((batch + V - 1) / V) / ((double)num_cu * waves));
 }
-inline Mode pick_mode(const PlanMatrix& h, const PlanTile& T, int batch, int64_t units, const float*) {
+inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, int64_t units) {
   if (h.step2_plain || batch < 2) return Mode::one;
-  const double c1 = pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0), c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.4);
-  const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 2.2);
-  if (c4 < c2 && c4 < c1 && mode_fits(kF4, h, T, batch)) return Mode::four;
-  return c2 < c1 && mode_fits(kF2, h, T, batch) ? Mode::two : Mode::one;
-}
-inline Mode pick_mode(const PlanMatrix& h, const PlanTile& T, int batch, int64_t units, const int8_t*) {
-  if (h.step2_plain || batch < 2) return Mode::one;
+  if (!i8) {
+    const double c1 = pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0), c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.4);
+    const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 2.2);
+    if (c4 < c2 && c4 < c1 && mode_fits(kF4, h, T, batch)) return Mode::four;
+    return c2 < c1 && mode_fits(kF2, h, T, batch) ? Mode::two : Mode::one;
+  }
   // (a device that is nearly full of units is slower than one that is half full: 2048 x 2888, four vectors, 0.96 units per
   // wavefront: 7.6 us with one vector per pass, 6.8 with two; 3584 x 2432, 0.57 units: 5.7 and 6.5)
   const double full = (double)units * batch / ((double)h.num_cu * h.waves);
@@ -180,7 +186,14 @@ inline Mode pick_mode(const PlanMatrix& h, const PlanTile& T, int batch, int64_t
   const double c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.1);
   const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 1.5);
   if (c4 < c2 && c4 < c1 && mode_fits(kP4, h, T, batch)) return Mode::four;
-  return c2 < c1 ? Mode::two : Mode::one;  // (two need no more LDS than one)
+  // (two have a vector's rows and slots in the bytes of one, but twice its records: 16 KB a block at 128 panels)
+  return c2 < c1 && fits_lds(kP2, h, T, batch) ? Mode::two : Mode::one;
+}
+
+// The launch of one row tile's product.
+inline int plan_product(bool i8, const PlanMatrix& h, const PlanTile& T, bool accumulate, int batch, Mode* mode, LaunchPlan* plan) {
+  *mode = pick_mode(i8, h, T, batch, T.nunits);
+  return plan_tile(pass_of(i8, *mode), h, T, accumulate, batch, h.num_cu, 4, plan);
 }
 
 // The compute units of several products that share a launch, in proportion to the bytes of their tables: multiples of 8

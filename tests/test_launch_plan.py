@@ -1,0 +1,69 @@
+"""The launch planner (csrc/rsr_plan.h) on the host: every product that the headers admit has a launch whose LDS layout
+fits, whatever the planner takes for its pass.  The planner is compiled here as it stands; the indexes are made up, with as
+many units and extra slots as the builder can give them."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CUS, LDS = 256, 160 * 1024  # of an MI355X
+
+
+class Request(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int64) for n in ("rows", "cols", "units")] + [(n, ctypes.c_int32) for n in ("k", "parts", "planes", "max_extras", "batch", "i8")]
+
+
+class Answer(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int64) for n in ("grid", "lds", "vectors", "waves", "buffers", "workgroups", "end_of_lds")]
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "plan_shim.so")
+    subprocess.run(["g++", "-O2", "-std=c++20", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2411_06360_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "plan_shim.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    lib.shim_panels.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    lib.shim_planes_per_handle.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 2
+    lib.shim_product.argtypes = [ctypes.POINTER(Request), ctypes.c_int, ctypes.c_int64, ctypes.POINTER(Answer)]
+    return lib
+
+
+def request(shim, rows, cols, k, parts=2, planes=0, batch=1, i8=0, units_per_panel=2):
+    blocks = -(-cols // k)
+    units = blocks * shim.shim_panels(rows, k, parts, planes) * units_per_panel
+    extras = rows * (1 if planes or parts == 1 else 2) // 256 if units_per_panel > 1 else 0
+    return Request(rows, cols, units, k, parts, planes, extras, batch, i8)
+
+
+def product(shim, *args, **kw):
+    r, a = request(shim, *args, **kw), Answer()
+    rc = shim.shim_product(ctypes.byref(r), CUS, LDS, ctypes.byref(a))
+    assert rc == 0, (rc, args, kw)
+    assert a.lds <= LDS and a.end_of_lds <= a.lds, (args, kw)
+    assert 1 <= a.waves <= 16 and a.grid >= a.workgroups >= 1 and a.buffers >= 1, (args, kw)
+    return a
+
+
+ROWS = (1, 17, 1024, 5003, 8191, 12288, 16384, 20000, 24577, 27648, 27649, 30000, 30642, 30643, 32767, 32768)
+
+
+@pytest.mark.parametrize("k", range(1, 17))
+@pytest.mark.parametrize("i8", [0, 1])
+def test_every_product_has_a_launch(shim, k, i8):
+    for rows in ROWS:
+        for parts, planes in [(1, 0), (2, 0)] + [(0, shim.shim_planes_per_handle(rows, k, q)) for q in (2, 4, 8)]:
+            for blocks in (1, 7, 300, 3000):
+                for batch in (1, 2, 3, 4, 16, 1201, 65535):
+                    for per_panel in (1, 4):
+                        product(shim, rows, blocks * k, k, parts, planes, batch, i8, per_panel)
+
+
+@pytest.mark.parametrize("rows,cols,k,parts,planes", [(30643, 1024, 16, 2, 0), (32768, 1024, 16, 2, 0), (32768, 1024, 14, 0, 8), (30000, 1024, 15, 0, 8)])
+def test_two_int8_vectors_share_a_pass_only_where_their_records_fit(shim, rows, cols, k, parts, planes):
+    """Records of a block's panels are as many words per vector as there are panels: with 128 panels two vectors' do not fit."""
+    for batch in (2, 3, 8):
+        assert product(shim, rows, cols, k, parts, planes, batch, 1).vectors == 1
+    assert product(shim, 16384, 16384, 12, 1, 0, 8, 1).vectors == 2  # (and where they do, they share one)
