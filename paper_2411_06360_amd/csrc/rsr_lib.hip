@@ -1027,7 +1027,7 @@ rsr_matvec_kernel(const unsigned char* __restrict__ stream, const uint32_t* __re
 
 // Several products in one launch (rsr_matvec_multi): every product owns a range of workgroups and
 // brings its own tables, activations, results and LDS layout.
-constexpr int kMaxJobs = 8;
+using rsr::kMaxJobs;
 struct KJob {
   const unsigned char* stream;
   const uint32_t* unit_words;
@@ -1101,10 +1101,9 @@ int launch_tile(rsr_handle* h, const DeviceTile& T, bool accumulate, const uint3
   }
 }
 
-// Several products as one launch: the compute units are shared out in proportion to the bytes of the
-// products' tables; every product is then planned as if it had its share of the device to itself.
+// Several products as one launch: every product is planned as if it had its share of the device to itself.
 template <class M>
-int launch_multi_mode(const rsr_job* jobs, int njobs, int batch, void* stream, const int* share) {
+int enqueue_multi(const rsr_job* jobs, int njobs, const LaunchPlan* plans, void* stream) {
   MultiArgs m;
   std::memset(&m, 0, sizeof(m));
   m.njobs = njobs;
@@ -1112,11 +1111,7 @@ int launch_multi_mode(const rsr_job* jobs, int njobs, int batch, void* stream, c
   int waves = 1;
   size_t lds = 0;
   for (int j = 0; j < njobs; ++j) {
-    rsr_handle* h = jobs[j].h;
-    const DeviceTile& T = h->tiles[0];
-    LaunchPlan plan;
-    const int rc = rsr::plan_tile(M::pass, *h, T, false, batch, std::min(share[j], h->num_cu), 1, &plan);
-    if (rc != RSR_OK) return plan_failed(rc, h, T);
+    const DeviceTile& T = jobs[j].h->tiles[0];
     KJob& J = m.job[j];
     J.stream = static_cast<const unsigned char*>(T.d_stream);
     J.unit_words = static_cast<const uint32_t*>(T.d_units);
@@ -1124,10 +1119,10 @@ int launch_multi_mode(const rsr_job* jobs, int njobs, int batch, void* stream, c
     J.extra_slots = static_cast<const uint16_t*>(T.d_extras);
     J.vin = jobs[j].v; J.out = jobs[j].out;
     J.wg_begin = (int)grid;
-    J.p = plan.p;
-    grid += plan.grid;  // (a multiple of 8: every product starts on the first XCD of the round-robin)
-    waves = std::max(waves, plan.waves);
-    lds = std::max(lds, plan.lds);
+    J.p = plans[j].p;
+    grid += plans[j].grid;  // (a multiple of 8: every product starts on the first XCD of the round-robin)
+    waves = std::max(waves, plans[j].waves);
+    lds = std::max(lds, plans[j].lds);
     if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
   }
   hipLaunchKernelGGL(rsr_multi_kernel<M>, dim3((unsigned)grid), dim3((unsigned)(waves * 64)), lds, static_cast<hipStream_t>(stream), m);
@@ -1140,29 +1135,27 @@ int launch_multi(const rsr_job* jobs, int njobs, int batch, void* stream) {
   if (!jobs || njobs < 1) return fail(RSR_ERR_INVALID_ARGUMENT, "no jobs");
   if (njobs > kMaxJobs) return fail(RSR_ERR_INVALID_ARGUMENT, "at most " + std::to_string(kMaxJobs) + " products per launch");
   if (batch < 1 || batch > 65535) return fail(RSR_ERR_INVALID_ARGUMENT, "batch must be in 1..65535");
-  int64_t bytes[kMaxJobs];
+  rsr::SharedJob each[kMaxJobs];
   for (int j = 0; j < njobs; ++j) {
     if (!valid(jobs[j].h)) return fail(RSR_ERR_INVALID_ARGUMENT, "invalid handle in job " + std::to_string(j));
     if (!jobs[j].v || !jobs[j].out) return fail(RSR_ERR_INVALID_ARGUMENT, "null pointer in job " + std::to_string(j));
     if (jobs[j].h->tiles.size() != 1) return fail(RSR_ERR_UNSUPPORTED, "a matrix with more than 32768 rows takes a launch per row tile: use rsr_matvec");
     if (jobs[j].h->device != jobs[0].h->device) return fail(RSR_ERR_INVALID_ARGUMENT, "the handles belong to different devices");
-    bytes[j] = jobs[j].h->stream_bytes;
+    each[j] = {jobs[j].h, &jobs[j].h->tiles[0], jobs[j].h->stream_bytes};
   }
-  const int num_cu = jobs[0].h->num_cu;
-  int share[kMaxJobs];
-  rsr::split_device(bytes, njobs, num_cu, share);
-  Mode mode = Mode::four;  // the widest that suits every product
-  int64_t units = 0;
-  for (int j = 0; j < njobs; ++j) units += jobs[j].h->nunits;
-  for (int j = 0; j < njobs; ++j) mode = std::min(mode, rsr::pick_mode(sizeof(VT) == 1, *jobs[j].h, jobs[j].h->tiles[0], batch, units));
+  Mode mode;
+  LaunchPlan plans[kMaxJobs];
+  int failed = 0;
+  const int rc = rsr::plan_shared(sizeof(VT) == 1, each, njobs, jobs[0].h->num_cu, batch, &mode, plans, &failed);
+  if (rc != RSR_OK) return plan_failed(rc, jobs[failed].h, jobs[failed].h->tiles[0]);
   if constexpr (sizeof(VT) == 4) {
-    if (mode == Mode::four) return launch_multi_mode<F4>(jobs, njobs, batch, stream, share);
-    if (mode == Mode::two) return launch_multi_mode<F2>(jobs, njobs, batch, stream, share);
-    return launch_multi_mode<F1>(jobs, njobs, batch, stream, share);
+    if (mode == Mode::four) return enqueue_multi<F4>(jobs, njobs, plans, stream);
+    if (mode == Mode::two) return enqueue_multi<F2>(jobs, njobs, plans, stream);
+    return enqueue_multi<F1>(jobs, njobs, plans, stream);
   } else {
-    if (mode == Mode::four) return launch_multi_mode<P4>(jobs, njobs, batch, stream, share);
-    if (mode == Mode::two) return launch_multi_mode<P2>(jobs, njobs, batch, stream, share);
-    return launch_multi_mode<I1>(jobs, njobs, batch, stream, share);
+    if (mode == Mode::four) return enqueue_multi<P4>(jobs, njobs, plans, stream);
+    if (mode == Mode::two) return enqueue_multi<P2>(jobs, njobs, plans, stream);
+    return enqueue_multi<I1>(jobs, njobs, plans, stream);
   }
 }
 

@@ -155,13 +155,15 @@ inline const Pass& pass_of(bool i8, Mode m) {
   return m == Mode::four ? (i8 ? kP4 : kF4) : m == Mode::two ? (i8 ? kP2 : kF2) : (i8 ? kI1 : kF1);
 }
 constexpr int kRoom = 24;
-inline bool fits_lds(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch) {
+// `cus`: the compute units that the product has, the device's or its share of a launch (fewer: more blocks per workgroup,
+// which need a second panel in flight).
+inline bool fits_lds(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch, int cus) {
   LaunchPlan plan;
-  return plan_tile(M, h, T, false, batch, h.num_cu, 1, &plan) == RSR_OK;
+  return plan_tile(M, h, T, false, batch, cus, 1, &plan) == RSR_OK;
 }
-inline bool mode_fits(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch) {
+inline bool has_room(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch, int cus) {
   LaunchPlan plan;
-  if (plan_tile(M, h, T, false, batch, h.num_cu, 1, &plan) != RSR_OK) return false;
+  if (plan_tile(M, h, T, false, batch, cus, 1, &plan) != RSR_OK) return false;
   const int64_t panels = h.nblocks * T.shape.panels, per_wg = (h.nblocks + plan.p.g1 - 1) / plan.p.g1 * T.shape.panels;
   return plan.p.nbuf >= per_wg || plan.p.nbuf * T.nunits >= kRoom * panels;
 }
@@ -171,13 +173,13 @@ inline bool mode_fits(const Pass& M, const PlanMatrix& h, const PlanTile& T, int
 inline double pass_cost(int64_t units, int num_cu, int waves, int batch, int V, double cost) {
   return cost * std::max(1.0, (double)units * ((batch + V - 1) / V) / ((double)num_cu * waves));
 }
-inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, int64_t units) {
+inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, int64_t units, int cus) {
   if (h.step2_plain || batch < 2) return Mode::one;
   if (!i8) {
     const double c1 = pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0), c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.4);
     const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 2.2);
-    if (c4 < c2 && c4 < c1 && mode_fits(kF4, h, T, batch)) return Mode::four;
-    return c2 < c1 && mode_fits(kF2, h, T, batch) ? Mode::two : Mode::one;
+    if (c4 < c2 && c4 < c1 && has_room(kF4, h, T, batch, cus)) return Mode::four;
+    return c2 < c1 && has_room(kF2, h, T, batch, cus) ? Mode::two : Mode::one;
   }
   // (a device that is nearly full of units is slower than one that is half full: 2048 x 2888, four vectors, 0.96 units per
   // wavefront: 7.6 us with one vector per pass, 6.8 with two; 3584 x 2432, 0.57 units: 5.7 and 6.5)
@@ -185,14 +187,14 @@ inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch
   const double c1 = std::max(0.55 + 0.6 * full, pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0));
   const double c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.1);
   const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 1.5);
-  if (c4 < c2 && c4 < c1 && mode_fits(kP4, h, T, batch)) return Mode::four;
+  if (c4 < c2 && c4 < c1 && has_room(kP4, h, T, batch, cus)) return Mode::four;
   // (two have a vector's rows and slots in the bytes of one, but twice its records: 16 KB a block at 128 panels)
-  return c2 < c1 && fits_lds(kP2, h, T, batch) ? Mode::two : Mode::one;
+  return c2 < c1 && fits_lds(kP2, h, T, batch, cus) ? Mode::two : Mode::one;
 }
 
 // The launch of one row tile's product.
 inline int plan_product(bool i8, const PlanMatrix& h, const PlanTile& T, bool accumulate, int batch, Mode* mode, LaunchPlan* plan) {
-  *mode = pick_mode(i8, h, T, batch, T.nunits);
+  *mode = pick_mode(i8, h, T, batch, T.nunits, h.num_cu);
   return plan_tile(pass_of(i8, *mode), h, T, accumulate, batch, h.num_cu, 4, plan);
 }
 
@@ -219,6 +221,39 @@ inline void split_device(const int64_t* bytes, int njobs, int num_cu, int* share
       if ((double)bytes[j] / share[j] > (double)bytes[best] / share[best]) best = j;
     share[best] += 8; given += 8;
   }
+}
+
+// One launch for several products.
+struct SharedJob {
+  const PlanMatrix* h;
+  const PlanTile* T;
+  int64_t bytes;  // of its tables
+};
+constexpr int kMaxJobs = 8;
+// The widest pass that every product takes on its own share, or narrower until all of them fit (a narrower pass has more sets
+// of vectors, so fewer workgroups a set and more blocks a workgroup: that one product fits does not say that all do).  On
+// failure *failed is the product that has no launch.
+inline int plan_shared(bool i8, const SharedJob* jobs, int njobs, int num_cu, int batch, Mode* mode, LaunchPlan* plans, int* failed) {
+  int64_t bytes[kMaxJobs], units = 0;
+  int share[kMaxJobs];
+  for (int j = 0; j < njobs; ++j) { bytes[j] = jobs[j].bytes; units += jobs[j].T->nunits; }
+  split_device(bytes, njobs, num_cu, share);
+  Mode most = Mode::four;
+  for (int j = 0; j < njobs; ++j) {
+    share[j] = std::min(share[j], jobs[j].h->num_cu);
+    most = std::min(most, pick_mode(i8, *jobs[j].h, *jobs[j].T, batch, units, share[j]));
+  }
+  int rc = RSR_OK;
+  for (const Mode m : {Mode::four, Mode::two, Mode::one}) {
+    if (m > most) continue;
+    rc = RSR_OK;
+    for (int j = 0; j < njobs && rc == RSR_OK; ++j) {
+      *failed = j;
+      rc = plan_tile(pass_of(i8, m), *jobs[j].h, *jobs[j].T, false, batch, share[j], 1, &plans[j]);
+    }
+    if (rc == RSR_OK) { *mode = m; break; }
+  }
+  return rc;
 }
 
 // How many of the q bit planes of a matrix share a launch: as many as leave room for their records beside the activations.

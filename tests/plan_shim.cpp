@@ -47,4 +47,21 @@ int shim_product(const Request* r, int num_cu, int64_t lds_max, Answer* a) {
   return rc;
 }
 
+int shim_shared(const Request* r, int n, int num_cu, int64_t lds_max, Answer* a) {
+  PlanMatrix h[kMaxJobs];
+  PlanTile t[kMaxJobs];
+  SharedJob jobs[kMaxJobs];
+  LaunchPlan p[kMaxJobs];
+  for (int j = 0; j < n; ++j) {
+    h[j] = matrix_of(r[j], num_cu, lds_max);
+    t[j] = tile_of(r[j], h[j]);
+    jobs[j] = {&h[j], &t[j], r[j].units * 40 * 128};
+  }
+  Mode mode;
+  int failed = 0;
+  const int rc = plan_shared(r[0].i8 != 0, jobs, n, num_cu, r[0].batch, &mode, p, &failed);
+  for (int j = 0; rc == RSR_OK && j < n; ++j) answer(p[j], pass_of(r[0].i8 != 0, mode), &a[j]);
+  return rc;
+}
+
 }  // extern "C"

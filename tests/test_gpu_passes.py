@@ -5,7 +5,7 @@ import pytest
 
 import paper_2411_06360_amd as R
 from oracle import dense
-from tests.gpu_util import DeviceIndex
+from tests.gpu_util import DeviceIndex, assert_f32_close
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +45,42 @@ def test_int8_vectors_at_many_bit_planes_of_a_tall_tile(rows, k):
     finally:
         torch.cuda.synchronize()
         R.rsr_qbit_destroy(h)
+
+
+@pytest.mark.parametrize("shapes,batches", [
+    ([(6912, 2560, 10)] * 3, (3, 4)),                     # a panel of 2048 slots: on the whole device it would be alone in LDS
+    ([(4096, 2560, 11)] * 4, (4,)),
+    ([(17000, 1280, 10)] * 2, (4, 9)),
+    ([(1024, 3000, 8), (701, 4001, 8)], (2, 13, 62)),     # passes over two and four vectors, odd batches
+    ([(1024, 3000, 8), (14336, 650, 11), (33, 500, 4)], (7, 33)),  # products that would take different passes alone
+])
+def test_shared_launches_with_several_vectors(shapes, batches):
+    import torch
+
+    g = np.random.default_rng(403)
+    mats = [g.integers(-1, 2, size=(r, c)).astype(np.int8) for r, c, _ in shapes]
+    hs = [R.rsr_preprocess(A, k) for A, (_, _, k) in zip(mats, shapes)]
+    try:
+        for batch in batches:
+            print(f"shared launch of {shapes}, batch {batch}", flush=True)
+            vf = [torch.from_numpy(g.standard_normal((batch, A.shape[0])).astype(np.float32)).cuda() for A in mats]
+            v8 = [torch.from_numpy(g.integers(-128, 128, size=(batch, A.shape[0]), dtype=np.int8)).cuda() for A in mats]
+            for v, dtype, one, many, exact in ((vf, torch.float32, R.rsr_matvec, R.rsr_matvec_multi, dense.matvec_f32),
+                                               (v8, torch.int32, R.rsr_matvec_i8, R.rsr_matvec_multi_i8, dense.matvec_i8)):
+                alone = [torch.full((batch, A.shape[1]), -7, dtype=dtype, device="cuda") for A in mats]
+                both = [torch.full((batch, A.shape[1]), -9, dtype=dtype, device="cuda") for A in mats]
+                for h, x, o in zip(hs, v, alone):
+                    one(h, x, o, batch, stream())
+                many(list(zip(hs, v, both)), batch, stream())
+                torch.cuda.synchronize()
+                for A, x, p, q in zip(mats, v, alone, both):
+                    assert torch.equal(p, q)  # float: bit for bit
+                    got, want = q.cpu().numpy(), exact(A, x.cpu().numpy())
+                    if dtype is torch.int32:
+                        assert np.array_equal(got.astype(np.int64), want)
+                    else:
+                        assert_f32_close(got, want, x.cpu().numpy())
+    finally:
+        torch.cuda.synchronize()
+        for h in hs:
+            R.rsr_destroy(h)

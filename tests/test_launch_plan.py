@@ -28,6 +28,7 @@ def shim(tmp_path_factory):
     lib.shim_panels.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     lib.shim_planes_per_handle.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 2
     lib.shim_product.argtypes = [ctypes.POINTER(Request), ctypes.c_int, ctypes.c_int64, ctypes.POINTER(Answer)]
+    lib.shim_shared.argtypes = [ctypes.POINTER(Request), ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.POINTER(Answer)]
     return lib
 
 
@@ -38,12 +39,27 @@ def request(shim, rows, cols, k, parts=2, planes=0, batch=1, i8=0, units_per_pan
     return Request(rows, cols, units, k, parts, planes, extras, batch, i8)
 
 
+def check(a, what):
+    assert a.lds <= LDS and a.end_of_lds <= a.lds, what
+    assert 1 <= a.waves <= 16 and a.grid >= a.workgroups >= 1 and a.buffers >= 1, what
+
+
 def product(shim, *args, **kw):
     r, a = request(shim, *args, **kw), Answer()
     rc = shim.shim_product(ctypes.byref(r), CUS, LDS, ctypes.byref(a))
     assert rc == 0, (rc, args, kw)
-    assert a.lds <= LDS and a.end_of_lds <= a.lds, (args, kw)
-    assert 1 <= a.waves <= 16 and a.grid >= a.workgroups >= 1 and a.buffers >= 1, (args, kw)
+    check(a, (args, kw))
+    return a
+
+
+def shared(shim, requests):
+    n = len(requests)
+    r, a = (Request * n)(*requests), (Answer * n)()
+    what = [(x.rows, x.cols, x.k, x.parts, x.batch, x.i8) for x in requests]
+    assert shim.shim_shared(r, n, CUS, LDS, a) == 0, what
+    for x in a:
+        check(x, what)
+    assert len({x.vectors for x in a}) == 1
     return a
 
 
@@ -67,3 +83,25 @@ def test_two_int8_vectors_share_a_pass_only_where_their_records_fit(shim, rows, 
     for batch in (2, 3, 8):
         assert product(shim, rows, cols, k, parts, planes, batch, 1).vectors == 1
     assert product(shim, 16384, 16384, 12, 1, 0, 8, 1).vectors == 2  # (and where they do, they share one)
+
+
+@pytest.mark.parametrize("rows,cols,k,n,batches,i8", [
+    (6912, 2560, 10, 3, (3, 4), 0), (4096, 2560, 11, 4, (4,), 0), (17000, 2560, 10, 2, (4,), 1), (14336, 2816, 11, 2, (2,), 0)])
+def test_a_shared_launch_takes_passes_that_fit_on_its_share(shim, rows, cols, k, n, batches, i8):
+    """On the whole device a workgroup has one block here, whose panel is alone in LDS; on a share it has several."""
+    for batch in batches:
+        for per_panel in (4, 6, 9, 14, 20):
+            shared(shim, [request(shim, rows, cols, k, 2, 0, batch, i8, per_panel)] * n)
+
+
+@pytest.mark.parametrize("i8", [0, 1])
+def test_every_shared_launch_fits(shim, i8):
+    kinds = [(64, 4, 1), (1024, 8, 2), (2560, 10, 2), (5003, 11, 2), (6912, 10, 2), (14336, 11, 2), (16384, 12, 1), (24577, 13, 2), (30643, 16, 2), (32768, 16, 2)]
+    for a in kinds:
+        for b in kinds:
+            for blocks in (1, 40, 256, 1500):
+                for n in (2, 3, 8):
+                    for batch in (1, 2, 3, 4, 7, 16, 400):
+                        for per_panel in (1, 5):
+                            make = lambda x, m: request(shim, x[0], m * x[1], x[1], x[2], 0, batch, i8, per_panel)
+                            shared(shim, [make(a, blocks)] + [make(b, 256)] * (n - 1))
