@@ -58,8 +58,8 @@ typedef struct rsr_handle rsr_handle; /* opaque; owns the device-resident index 
  * For every part and every k-column block the call builds the row permutation that sorts the
  * rows by their binary value, first column most significant (Definition 3.2; equal rows stay in
  * ascending row order) and the boundaries of the groups of equal rows (the full segmentation,
- * Section 3.3), packed for the GPU, on the current HIP device: A is copied there and indexed as by
- * rsr_preprocess_device.
+ * Section 3.3), packed for the GPU, on the current HIP device: A is copied there (rows * cols bytes of
+ * device memory until the call returns) and indexed as by rsr_preprocess_device, with its working memory.
  * The packed form is a layout choice, not a different index: rsr_export_block returns the
  * permutation and the full segmentation in the paper's form.  Rows whose value in a block is 0
  * contribute nothing to that block (row 0 of Bin_[k] is all zeros) and are not stored.
@@ -81,7 +81,8 @@ rsr_handle *rsr_preprocess(const int8_t *A, int64_t rows, int64_t cols, int k);
  *   A     DEVICE pointer, row-major rows x cols int8 in {-1,0,1}; read during the call only.
  *   rows, cols, k   as for rsr_preprocess.
  * Returns a handle, or NULL on error.  Synchronous; allocates temporary device memory of about
- * 4 bytes per row and column block and part, plus 6 * 2^k bytes per column block and part.
+ * 4 bytes per row and column block and part, plus 6 * 2^k bytes per column block and part (above 4 GiB: at
+ * most a quarter of the free memory, the column blocks are then indexed a range at a time).
  */
 rsr_handle *rsr_preprocess_device(const int8_t *A, int64_t rows, int64_t cols, int k);
 

@@ -12,6 +12,10 @@
 //   4. units_kernel      per panel: the unit descriptors.
 //   5. emit_kernel       per unit: the rows dealt out to the 64 lanes, the rows of a lane's segment spread over the
 //                        LDS banks, granule order.
+//
+// Steps 1 to 3 and 4 to 5 run over all column blocks at once where a grid can hold their panels and the device has the
+// working memory, otherwise over as many blocks at a time as that allows (steps 1 to 3 then run twice per block: once to
+// find how large the tables are, once more ahead of steps 4 and 5).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -179,7 +183,8 @@ __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, i
 
 // What the kernels below need to know of a tile.
 struct Geometry {
-  int rows, k, parts, nblocks;
+  int rows, k, parts;
+  uint32_t block0, panel0;  // first column block and panel of this run: the lists below count from them
   rsr::Shape s;
   int list_stride, group_stride, extra_stride;  // entries per panel in the lists
   int fill;  // absent values form groups of no rows
@@ -238,7 +243,7 @@ __device__ __forceinline__ void walk_units(const PanelInfo& I, G group_rows, F f
   }
 }
 
-// Part and value of a slot of a panel; false: no segment belongs to it.
+// Part and value of a slot of a panel (counted from g.panel0); false: no segment belongs to it.
 __device__ __forceinline__ bool slot_value(const Geometry& g, uint32_t panel, uint32_t slot, uint32_t* bp, uint32_t* value) {
   const uint32_t block = panel / g.s.panels, pi = panel % g.s.panels;
   const int wbits = g.k - g.s.kc;
@@ -405,7 +410,7 @@ units_kernel(Geometry g, const uint8_t* __restrict__ group_all, const PanelInfo*
   __syncthreads();
   if (threadIdx.x != 0) return;
   PUnit u;
-  u.block = panel / g.s.panels; u.panel = panel;
+  u.block = g.block0 + panel / g.s.panels; u.panel = g.panel0 + panel;
   u.units_in_panel = (uint16_t)I.units; u.extras = (uint16_t)I.extras; u.reserved = 0;
   uint32_t at = base[panel].unit, stream = base[panel].stream;
   if (ng == 0) {
@@ -444,13 +449,14 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   volatile uint16_t (*ent)[64] = ent_all[wave];
   volatile uint32_t (*load)[8] = load_all[wave][lane >> 5];
   uint32_t* load_words = &load_all[wave][0][0][0];
-  const PanelInfo I = info[U.panel];
+  const uint32_t panel = U.panel - g.panel0;
+  const PanelInfo I = info[panel];
   const uint64_t heads = (uint64_t)U.heads_lo | ((uint64_t)U.heads_hi << 32);
   const int wbits = U.wide ? 3 : 0;
   const uint32_t end = U.wide ? I.n8 : I.n8 + I.n1;
   const uint32_t sub = (uint32_t)lane & ((1u << wbits) - 1);
   const bool owner = sub == 0;
-  const uint16_t* list = list_all + (int64_t)U.panel * g.list_stride;
+  const uint16_t* list = list_all + (int64_t)panel * g.list_stride;
   const uint16_t null_index = (uint16_t)g.rows;
   for (int i = lane; i < 2 * rsr::kMaxPositions * 8; i += 64) load_words[i] = 0;
   uint32_t entry = U.first + ((uint32_t)lane >> wbits);
@@ -467,11 +473,11 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
       const uint32_t s = list[entry];
       uint32_t of = s, piece = 0;
       if (s >= (uint32_t)g.s.nslots) {
-        const uint32_t x = extra_all[(int64_t)U.panel * g.extra_stride + (s - g.s.nslots - rsr::kDummySlots)];
+        const uint32_t x = extra_all[(int64_t)panel * g.extra_stride + (s - g.s.nslots - rsr::kDummySlots)];
         of = x & 0xffffu; piece = x >> 16;
       }
       uint32_t bp, value;
-      slot_value(g, U.panel, of, &bp, &value);
+      slot_value(g, panel, of, &bp, &value);
       const uint32_t* o = off + (int64_t)bp * ((1 << g.k) + 1) + value;
       const uint32_t o0 = o[0], all = o[1] - o0, np = pieces_of(all);
       const uint32_t a = all * piece / np, b = all * (piece + 1) / np;
@@ -558,14 +564,14 @@ int device_matrix_kind(const int8_t* dA, int64_t count, int* kind, std::string* 
 
 int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, int k, int parts, int plane0, BuiltTile* out, std::string* err) {
   const int64_t nblocks = (cols + k - 1) / k;
-  const int64_t nbp = nblocks * parts;
   const int nvals = 1 << k;
   if (rows < 1 || rows > rsr::kTileRows) { *err = "tile height out of range"; return RSR_ERR_INVALID_ARGUMENT; }
   Geometry g;
-  g.rows = (int)rows; g.k = k; g.parts = parts; g.nblocks = (int)nblocks;
+  g.rows = (int)rows; g.k = k; g.parts = parts;
+  g.block0 = 0; g.panel0 = 0;
   g.s = rsr::panel_shape(rows, k, parts, plane0 < 0);
   const int64_t npanels = nblocks * g.s.panels;
-  if (nblocks > 0x3fffffff || npanels > 0x7fffffff || nbp > 0x7fffffff) { *err = "too many column blocks"; return RSR_ERR_UNSUPPORTED; }
+  if (nblocks > 0x3fffffff || npanels > 0x7fffffff || nblocks * parts > 0x7fffffff) { *err = "too many column blocks"; return RSR_ERR_UNSUPPORTED; }
   g.extra_stride = (int)std::max<int64_t>(2, (rows * (g.s.both ? 2 : 1) / rsr::kWideRows + 1) / 2 * 2);  // (even: read two at a time)
   g.list_stride = g.s.nslots + g.extra_stride;
   // Clearing a slot costs a share of an LDS store, an absent value two bytes of the stream and a share of a gather and a store:
@@ -576,14 +582,30 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
   g.group_stride = (int)((g.s.nslots + 63) / 64 + (std::min<int64_t>(g.s.nslots, seen / 7) + g.extra_stride + 7) / 8 + 1);
   if (g.group_stride > 1024) { *err = "too many segments in a panel"; return RSR_ERR_UNSUPPORTED; }
 
-  // One allocation for all working memory.
-  DevBuf work;
+  // One allocation for all working memory, for `at_once` blocks: as many as a grid of 256 threads per panel holds (2^32 threads
+  // in a launch) and, where that is much, as fit in a quarter of the free memory (the tables have to fit beside it).
   size_t bytes = 0;
   auto take = [&](size_t n) { const size_t at = bytes; bytes += (n + 255) / 256 * 256; return at; };
-  const size_t at_val = take((size_t)nbp * rows * 2), at_sigma = take((size_t)nbp * rows * 2), at_off = take((size_t)nbp * (nvals + 1) * 4);
-  const size_t at_list = take((size_t)npanels * g.list_stride * 2), at_group = take((size_t)npanels * g.group_stride);
-  const size_t at_extra = take((size_t)npanels * g.extra_stride * 4), at_info = take((size_t)npanels * sizeof(PanelInfo));
-  const size_t at_base = take((size_t)npanels * sizeof(PanelBase));
+  constexpr int64_t kPanelsAtOnce = (int64_t)1 << 23;
+  int64_t at_once = std::min(nblocks, std::max<int64_t>(1, kPanelsAtOnce / g.s.panels));
+  DevBuf work;
+  size_t most = 0;  // bytes; 0: not asked yet
+  constexpr size_t kMuch = (size_t)4 << 30;
+  size_t at_val, at_sigma, at_off, at_list, at_group, at_extra, at_info, at_base;
+  for (;;) {
+    const size_t nbp = (size_t)at_once * parts, np = (size_t)at_once * g.s.panels;
+    bytes = 0;
+    at_val = take(nbp * rows * 2); at_sigma = take(nbp * rows * 2); at_off = take(nbp * (nvals + 1) * 4);
+    at_list = take(np * g.list_stride * 2); at_group = take(np * g.group_stride); at_extra = take(np * g.extra_stride * 4);
+    at_info = take(np * sizeof(PanelInfo)); at_base = take(np * sizeof(PanelBase));
+    if (bytes > kMuch && most == 0) {
+      size_t total = 0;
+      PREP_TRY(hipMemGetInfo(&most, &total));
+      most = std::max(kMuch, most / 4);
+    }
+    if (bytes <= kMuch || bytes <= most || at_once == 1) break;
+    at_once = (at_once + 1) / 2;
+  }
   PREP_TRY(hipMalloc(&work.p, bytes));
   unsigned char* const w = static_cast<unsigned char*>(work.p);
   uint16_t* const val = reinterpret_cast<uint16_t*>(w + at_val);
@@ -595,10 +617,13 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
   PanelInfo* const info = reinterpret_cast<PanelInfo*>(w + at_info);
   PanelBase* const base = reinterpret_cast<PanelBase*>(w + at_base);
 
-  hipLaunchKernelGGL(values_kernel, dim3((unsigned)((rows + 63) / 64), (unsigned)std::min<int64_t>((nblocks + kValueBlocks - 1) / kValueBlocks, 32768)),
-                     dim3(256), 0, nullptr, dA, (int)rows, (int)cols, ld, k, parts, plane0, (int)nblocks, val);
-  PREP_TRY(hipGetLastError());
-  {
+  // Steps 1 to 3 for the blocks b0 .. b0 + nb - 1.
+  auto plan = [&](int64_t b0, int64_t nb) -> int {
+    const int64_t c0 = b0 * k, nc = std::min(cols - c0, nb * k), nbp = nb * parts;
+    g.block0 = (uint32_t)b0; g.panel0 = (uint32_t)(b0 * g.s.panels);
+    hipLaunchKernelGGL(values_kernel, dim3((unsigned)((rows + 63) / 64), (unsigned)std::min<int64_t>((nb + kValueBlocks - 1) / kValueBlocks, 32768)),
+                       dim3(256), 0, nullptr, dA + c0, (int)rows, (int)nc, ld, k, parts, plane0, (int)nb, val);
+    PREP_TRY(hipGetLastError());
     const size_t per_wave = (size_t)std::max(1, nvals >> 1) * 4;
     int waves = (int)std::min<size_t>(4, (size_t)(128 * 1024) / per_wave);
     if (waves < 1) waves = 1;
@@ -607,11 +632,17 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
     hipLaunchKernelGGL(sort_kernel, dim3((unsigned)((nbp + waves - 1) / waves)), dim3((unsigned)(64 * waves)), per_wave * waves, nullptr,
                        static_cast<const uint16_t*>(val), (int)rows, k, (int)nbp, waves, off, sigma);
     PREP_TRY(hipGetLastError());
-  }
-  hipLaunchKernelGGL(plan_kernel, dim3((unsigned)npanels), dim3(256), 0, nullptr, g, static_cast<const uint32_t*>(off), list, group, extra, info);
-  PREP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(plan_kernel, dim3((unsigned)(nb * g.s.panels)), dim3(256), 0, nullptr, g, static_cast<const uint32_t*>(off), list, group, extra, info);
+    PREP_TRY(hipGetLastError());
+    return 0;
+  };
   std::vector<PanelInfo> hinfo((size_t)npanels);
-  PREP_TRY(hipMemcpy(hinfo.data(), info, hinfo.size() * sizeof(PanelInfo), hipMemcpyDeviceToHost));
+  for (int64_t b0 = 0; b0 < nblocks; b0 += at_once) {
+    const int64_t nb = std::min(at_once, nblocks - b0);
+    const int rc = plan(b0, nb);
+    if (rc != 0) return rc;
+    PREP_TRY(hipMemcpy(&hinfo[(size_t)(b0 * g.s.panels)], info, (size_t)(nb * g.s.panels) * sizeof(PanelInfo), hipMemcpyDeviceToHost));
+  }
 
   // ---- where every panel's units and streams begin (host; no row data involved) ----
   std::vector<PanelBase> hbase((size_t)npanels);
@@ -648,23 +679,36 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
   const size_t at_slots = take(out->extra_bytes);
   PREP_TRY(hipMalloc(&tables.p, bytes));
   unsigned char* const t = static_cast<unsigned char*>(tables.p);
-  PREP_TRY(hipMemcpy(base, hbase.data(), hbase.size() * sizeof(PanelBase), hipMemcpyHostToDevice));
   PREP_TRY(hipMemcpy(t + at_blk, blk_unit.data(), out->blk_bytes, hipMemcpyHostToDevice));
   PUnit* const units = reinterpret_cast<PUnit*>(t + at_units);
-  hipLaunchKernelGGL(units_kernel, dim3((unsigned)npanels), dim3(64), 0, nullptr, g, static_cast<const uint8_t*>(group),
-                     static_cast<const PanelInfo*>(info), static_cast<const PanelBase*>(base), units);
-  PREP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(emit_kernel, dim3((unsigned)((nunits + kEmitWaves - 1) / kEmitWaves)), dim3(64 * kEmitWaves), 0, nullptr, g, (uint32_t)nunits,
-                     static_cast<const PUnit*>(units), static_cast<const PanelInfo*>(info), static_cast<const uint16_t*>(list),
-                     static_cast<const uint32_t*>(extra), static_cast<const uint32_t*>(off), static_cast<const uint16_t*>(sigma), t + at_stream);
-  PREP_TRY(hipGetLastError());
-  if (extras) {
-    std::vector<uint32_t> x((size_t)npanels * g.extra_stride);
-    std::vector<uint16_t> slots(x.size(), 0);
-    PREP_TRY(hipMemcpy(x.data(), extra, x.size() * 4, hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < x.size(); ++i)
-      if (i % g.extra_stride < hinfo[i / g.extra_stride].extras) slots[i] = (uint16_t)(x[i] & 0xffffu);
-    PREP_TRY(hipMemcpy(t + at_slots, slots.data(), out->extra_bytes, hipMemcpyHostToDevice));
+  for (int64_t b0 = 0; b0 < nblocks; b0 += at_once) {
+    const int64_t nb = std::min(at_once, nblocks - b0), p0 = b0 * g.s.panels, np = nb * g.s.panels;
+    if (at_once < nblocks) {
+      const int rc = plan(b0, nb);
+      if (rc != 0) return rc;
+    }
+    const uint32_t u0 = blk_unit[(size_t)b0], nu = blk_unit[(size_t)(b0 + nb)] - u0;
+    PREP_TRY(hipMemcpy(base, hbase.data() + p0, (size_t)np * sizeof(PanelBase), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(units_kernel, dim3((unsigned)np), dim3(64), 0, nullptr, g, static_cast<const uint8_t*>(group),
+                       static_cast<const PanelInfo*>(info), static_cast<const PanelBase*>(base), units);
+    PREP_TRY(hipGetLastError());
+    // (a grid holds 2^32 threads)
+    constexpr uint32_t kUnitsAtOnce = 1u << 25;
+    for (uint32_t u = 0; u < nu; u += kUnitsAtOnce) {
+      const uint32_t n = std::min(kUnitsAtOnce, nu - u);
+      hipLaunchKernelGGL(emit_kernel, dim3((n + kEmitWaves - 1) / kEmitWaves), dim3(64 * kEmitWaves), 0, nullptr, g, n,
+                         static_cast<const PUnit*>(units) + u0 + u, static_cast<const PanelInfo*>(info), static_cast<const uint16_t*>(list),
+                         static_cast<const uint32_t*>(extra), static_cast<const uint32_t*>(off), static_cast<const uint16_t*>(sigma), t + at_stream);
+      PREP_TRY(hipGetLastError());
+    }
+    if (extras) {
+      std::vector<uint32_t> x((size_t)np * g.extra_stride);
+      std::vector<uint16_t> slots(x.size(), 0);
+      PREP_TRY(hipMemcpy(x.data(), extra, x.size() * 4, hipMemcpyDeviceToHost));
+      for (size_t i = 0; i < x.size(); ++i)
+        if (i % g.extra_stride < hinfo[(size_t)p0 + i / g.extra_stride].extras) slots[i] = (uint16_t)(x[i] & 0xffffu);
+      PREP_TRY(hipMemcpy(t + at_slots + (size_t)p0 * g.extra_stride * 2, slots.data(), slots.size() * 2, hipMemcpyHostToDevice));
+    }
   }
   PREP_TRY(hipStreamSynchronize(nullptr));
   out->shape = g.s;

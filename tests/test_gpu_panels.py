@@ -128,3 +128,19 @@ def test_bit_planes_in_one_launch_or_several(q, rows, k):
     finally:
         torch.cuda.synchronize()
         R.rsr_qbit_destroy(h)
+
+
+def test_more_panels_than_one_grid_of_the_builder_holds():
+    """9000001 columns at k = 1: the index is built over ranges of column blocks (2^32 threads are a launch's limit)."""
+    import torch
+
+    g = np.random.default_rng(29)
+    A = g.integers(0, 2, size=(2, 9000001)).astype(np.int8)
+    print("many panels 2x9000001 k=1", flush=True)
+    with DeviceIndex(A, 1) as d:
+        assert d.info.segments == int((A.sum(axis=0) > 0).sum()) and d.info.stored_rows == int(A.sum())
+        v8 = g.integers(-128, 128, size=(1, 2), dtype=np.int8)
+        assert np.array_equal(d.matvec(v8).astype(np.int64), v8.astype(np.int64) @ A)
+        vf = g.standard_normal((1, 2)).astype(np.float32)
+        assert_f32_close(d.matvec(vf), vf.astype(np.float64) @ A, vf)
+    torch.cuda.empty_cache()
