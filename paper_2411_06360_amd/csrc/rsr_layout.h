@@ -46,8 +46,9 @@ constexpr int kMaxPanelSlots = 1 << kMaxPanelBits;   // 16 KB of float sums
 constexpr int kFoldRow = 256;                        // slots one step of the fold reads (64 lanes x 4); parts start on multiples
 constexpr int kDummySlots = 32;                      // behind the slots of a panel: where lanes without a segment store
 constexpr int kWideRows = 256;                       // rows of a piece of a segment at most (8 lanes, 32 rows each)
+// Passes over several int8 vectors keep a slot's sum in 16 bits: kWideRows entries of -128 .. 127 are what these hold.
+static_assert(kWideRows * 128 <= 32768 && kWideRows * 127 <= 32767, "the sum of a slot has to fit 16 bits");
 constexpr int kMaxExtras = 2 * 32768 / kWideRows;    // extra slots of a panel at most (both parts of 32768 rows)
-constexpr int kMaxGroupRows = kMaxPositions - 1;     // rows per lane of a group at most (its head takes a position)
 
 struct alignas(16) PUnit {
   uint32_t stream_off;   // in multiples of kStreamAlign bytes

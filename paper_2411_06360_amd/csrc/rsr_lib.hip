@@ -348,8 +348,9 @@ __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__bui
   "v_add_f32_dpp %[a], %[a], %[a] " x "\n v_add_f32_dpp %[b], %[b], %[b] " x "\n"                              \
   "v_add_f32_dpp %[c], %[c], %[c] " x "\n v_add_f32_dpp %[d], %[d], %[d] " x "\n"
 // int8 activations of several vectors are widened to 16 bits when they are staged, two vectors to a dword, and
-// summed two at a time (v_pk_add_u16): a slot's segment has at most kWideRows rows, |sum| <= 32768, and 32768 is
-// reached only by -128 * 256, which 16 bits hold.
+// summed two at a time (v_pk_add_u16).  Nothing is lost: no lane and no slot sums more than kWideRows = 256 rows (the builder cuts
+// longer segments), so a sum lies in -128 * 256 .. 127 * 256, which 16 bits hold (rsr_layout.h asserts it); from the
+// slots on, and between pieces, panels and parts, sums are 32 bits wide.
 struct F1 {  // one float vector
   using In = float;
   using Acc = float;

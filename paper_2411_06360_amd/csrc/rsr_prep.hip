@@ -201,6 +201,8 @@ struct PanelBase {
 
 constexpr int kKeys8 = 32, kKeys1 = 48;  // rank classes: 8 lanes with 32 .. 1 rows each, one lane with 47 .. 0
 constexpr int kKeys = kKeys8 + kKeys1;
+static_assert(8 * kKeys8 == rsr::kWideRows, "eight lanes hold a piece of kWideRows rows");
+static_assert(kKeys1 - 1 <= rsr::kWideRows && kKeys1 <= rsr::kMaxPositions && kKeys8 + 1 <= rsr::kMaxPositions, "a group and its head fit in a unit");
 constexpr uint16_t kNoSegment = 0xffff;  // the number of rows of a slot that takes no part
 
 // The pieces a segment of n rows is cut into.

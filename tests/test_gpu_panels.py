@@ -35,7 +35,9 @@ def check_products(d, A, batches, seed):
     g = np.random.default_rng(seed)
     for batch in batches:
         v8 = g.integers(-128, 128, size=(batch, A.shape[0]), dtype=np.int8)
-        v8[:, : A.shape[0] // 2] = -128  # (a segment of 256 such rows sums to the lowest 16-bit number)
+        v8[:, : A.shape[0] // 2] = -128
+        v8[1:2] = -128  # (a segment of 256 such rows sums to the lowest 16-bit number)
+        v8[2:3] = 127
         got = d.matvec(v8)
         assert np.array_equal(got.astype(np.int64), dense.matvec_i8(A, v8)), batch
         vf = g.standard_normal((batch, A.shape[0])).astype(np.float32)
