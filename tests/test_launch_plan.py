@@ -105,3 +105,15 @@ def test_every_shared_launch_fits(shim, i8):
                         for per_panel in (1, 5):
                             make = lambda x, m: request(shim, x[0], m * x[1], x[1], x[2], 0, batch, i8, per_panel)
                             shared(shim, [make(a, blocks)] + [make(b, 256)] * (n - 1))
+
+
+@pytest.mark.parametrize("i8", [0, 1])
+@pytest.mark.parametrize("batch", [1, 2, 3, 5, 6, 7, 9, 11, 13, 16])
+def test_a_launch_is_one_round_of_workgroups(shim, batch, i8):
+    """A workgroup more than the device holds at a time is a second round for all."""
+    for rows, k, parts in [(1024, 8, 1), (2048, 9, 2), (2902, 9, 2), (5003, 11, 2), (8265, 9, 1), (16384, 12, 1), (32768, 13, 2)]:
+        for blocks in (64, 229, 300, 747, 911, 1821, 3000):
+            for per_panel in (1, 2, 3, 5):
+                a = product(shim, rows, blocks * k, k, parts, 0, batch, i8, per_panel)
+                per_cu = min(16 // a.waves, LDS // a.lds, 4)
+                assert a.grid <= CUS * per_cu, (rows, blocks, per_panel, a.waves, a.grid)
