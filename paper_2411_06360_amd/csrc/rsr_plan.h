@@ -125,7 +125,9 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
     const int most = (int)std::min<int64_t>(8, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
     for (nbuf = most; nbuf > least && (total(nbuf) > h.lds_max || (wg > 1 && (size_t)wg * total(nbuf) > h.lds_max)); --nbuf) {}
     if (total(nbuf) > h.lds_max) return RSR_ERR_UNSUPPORTED;
-    if (wg == 1 || (wg * waves <= 16 && (size_t)wg * total(nbuf) <= h.lds_max)) break;
+    // (of five wavefronts only two workgroups share a compute unit, all other sizes fill its sixteen: timed with kernels that spin,
+    // 256 * wg workgroups of n wavefronts at this register count, n = 1 .. 16)
+    if (wg == 1 || (wg * waves <= 16 && !(wg == 3 && waves == 5) && (size_t)wg * total(nbuf) <= h.lds_max)) break;
   }
   p.g1 = (int)g1;
   const int64_t grid = (g1 + 7) / 8 * 8 * sets;
