@@ -71,6 +71,8 @@ struct LaunchPlan {
   size_t lds = 0;
 };
 
+constexpr int kMostBuffers = 8;  // panels in flight per workgroup at most
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // x / d for small x as the high half of a product (d >= 2)
@@ -122,7 +124,7 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
     waves = (int)std::min<int64_t>(h.waves, units_per_wg);
     // Up to eight panels in flight where the LDS holds them (a wavefront whose unit belongs to a later panel waits).
     const int64_t panels_per_wg = blocks_per_wg * S.panels;
-    const int most = (int)std::min<int64_t>(8, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
+    const int most = (int)std::min<int64_t>(kMostBuffers, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
     for (nbuf = most; nbuf > least && (total(nbuf) > h.lds_max || (wg > 1 && (size_t)wg * total(nbuf) > h.lds_max)); --nbuf) {}
     if (total(nbuf) > h.lds_max) return RSR_ERR_UNSUPPORTED;
     // (of five wavefronts only two workgroups share a compute unit, all other sizes fill its sixteen: timed with kernels that spin,
@@ -149,55 +151,65 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
   return RSR_OK;
 }
 
-// How many vectors share a pass: the most for which a workgroup's wavefronts do not wait for room.  A unit of the stream
-// keeps its share of a panel's sums in LDS from its start until the panel is folded, about one and a half times as long as it
-// is summed: with sums of fewer than kRoom units in flight wavefronts stand still.  (sixteen vectors at 2560 x 7680, k = 10:
-// room for 14 units with four vectors per pass, 34 with two.)
+// ---- how many vectors share a pass ----
 enum class Mode { one, two, four };
 inline const Pass& pass_of(bool i8, Mode m) {
   return m == Mode::four ? (i8 ? kP4 : kF4) : m == Mode::two ? (i8 ? kP2 : kF2) : (i8 ? kI1 : kF1);
 }
-constexpr int kRoom = 24;
+// What a launch has to do per vector, over all products that share it: units, and steps of the fold (kFoldRow slots).
+struct Load {
+  double units = 0, folds = 0;
+  void add(const PlanMatrix& h, const PlanTile& T) {
+    units += (double)T.nunits;
+    folds += (double)h.nblocks * T.shape.panels * (T.shape.nslots / kFoldRow);
+  }
+};
+// A unit of the stream keeps its share of a panel's sums in LDS from its start until the panel is folded, about one and a half
+// times as long as it is summed: with room for the sums of fewer units in flight (kRoom: float, kRoom8: int8, whose sums
+// take half the LDS) wavefronts stand still.  Returns the sums of how many units a workgroup has room for, 1e9 if the LDS does not limit
+// the panels in flight, 0 if the pass does not fit.
 // `cus`: the compute units that the product has, the device's or its share of a launch (fewer: more blocks per workgroup,
 // which need a second panel in flight).
-inline bool fits_lds(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch, int cus) {
+constexpr double kRoom = 32, kRoom8 = 24;
+inline double room_for(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch, int cus) {
   LaunchPlan plan;
-  return plan_tile(M, h, T, false, batch, cus, 1, &plan) == RSR_OK;
-}
-inline bool has_room(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch, int cus) {
-  LaunchPlan plan;
-  if (plan_tile(M, h, T, false, batch, cus, 1, &plan) != RSR_OK) return false;
+  if (plan_tile(M, h, T, false, batch, cus, 1, &plan) != RSR_OK) return 0;
   const int64_t panels = h.nblocks * T.shape.panels, per_wg = (h.nblocks + plan.p.g1 - 1) / plan.p.g1 * T.shape.panels;
-  return plan.p.nbuf >= per_wg || plan.p.nbuf * T.nunits >= kRoom * panels;
+  return plan.p.nbuf >= std::min<int64_t>(kMostBuffers, per_wg) ? 1e9 : (double)plan.p.nbuf * (double)T.nunits / (double)panels;
 }
-// A pass over V vectors costs a wavefront `cost` times as much as a pass over one, and launches with less than a unit per
-// wavefront of the device take as long as one unit does: few units are better spread out, a vector per pass.
-// `units`: of all products that share the launch.
-inline double pass_cost(int64_t units, int num_cu, int waves, int batch, int V, double cost) {
-  return cost * std::max(1.0, (double)units * ((batch + V - 1) / V) / ((double)num_cu * waves));
-}
-inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, int64_t units, int cus) {
+// Which pass.  A pass over V vectors takes as many times less units and folds, each of which costs more, and a launch with less
+// than a unit per wavefront of the device takes as long as one unit does: few units are better spread out, a vector per
+// pass.  The constants, in the time of a full round of units with one vector (1.65 us), are fitted to 500 matrices of 1024 to
+// 32768 rows (binary, ternary, correlated; k from 8 to 13), 2 to 16 vectors, in all three passes: on average the choice is 0.7 %
+// (float) and 0.9 % (int8) slower than the best of the three.  Float without the folds, the staging and the waiting for room: 5.4 %
+// (1472 x 30464, k = 8, eleven vectors: 53 us with one vector per pass, 24 with four).
+inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, const Load& load, int cus) {
   if (h.step2_plain || batch < 2) return Mode::one;
+  const double device = (double)h.num_cu * h.waves;
+  auto rounds = [&](int V) { return std::max(1.0, load.units * ((batch + V - 1) / V) / device); };
   if (!i8) {
-    const double c1 = pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0), c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.4);
-    const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 2.2);
-    if (c4 < c2 && c4 < c1 && has_room(kF4, h, T, batch, cus)) return Mode::four;
-    return c2 < c1 && has_room(kF2, h, T, batch, cus) ? Mode::two : Mode::one;
+    const double rows = 0.4 * (double)T.rows / 16384;  // a wider pass has more to stage
+    auto cost = [&](Mode m, double start, double unit, double fold) {
+      const Pass& M = pass_of(false, m);
+      const double room = room_for(M, h, T, batch, cus);
+      return room == 0 ? 1e30 : start + unit * rounds(M.V) * std::max(1.0, kRoom / room) + fold * load.folds * ((batch + M.V - 1) / M.V) / device;
+    };
+    const double c1 = cost(Mode::one, 0, 1, 0.25), c2 = cost(Mode::two, rows, 1.1, 0.4), c4 = cost(Mode::four, 0.6 + rows, 2.0, 0.6);
+    return c4 < c2 && c4 < c1 ? Mode::four : c2 < c1 ? Mode::two : Mode::one;
   }
   // (a device that is nearly full of units is slower than one that is half full: 2048 x 2888, four vectors, 0.96 units per
   // wavefront: 7.6 us with one vector per pass, 6.8 with two; 3584 x 2432, 0.57 units: 5.7 and 6.5)
-  const double full = (double)units * batch / ((double)h.num_cu * h.waves);
-  const double c1 = std::max(0.55 + 0.6 * full, pass_cost(units, h.num_cu, h.waves, batch, 1, 1.0));
-  const double c2 = pass_cost(units, h.num_cu, h.waves, batch, 2, 1.1);
-  const double c4 = pass_cost(units, h.num_cu, h.waves, batch, 4, 1.5);
-  if (c4 < c2 && c4 < c1 && has_room(kP4, h, T, batch, cus)) return Mode::four;
+  const double c1 = std::max(0.55 + 0.6 * load.units * batch / device, rounds(1)), c2 = 1.1 * rounds(2), c4 = 1.5 * rounds(4);
+  if (c4 < c2 && c4 < c1 && room_for(kP4, h, T, batch, cus) >= kRoom8) return Mode::four;
   // (two have a vector's rows and slots in the bytes of one, but twice its records: 16 KB a block at 128 panels)
-  return c2 < c1 && fits_lds(kP2, h, T, batch, cus) ? Mode::two : Mode::one;
+  return c2 < c1 && room_for(kP2, h, T, batch, cus) > 0 ? Mode::two : Mode::one;
 }
 
 // The launch of one row tile's product.
 inline int plan_product(bool i8, const PlanMatrix& h, const PlanTile& T, bool accumulate, int batch, Mode* mode, LaunchPlan* plan) {
-  *mode = pick_mode(i8, h, T, batch, T.nunits, h.num_cu);
+  Load load;
+  load.add(h, T);
+  *mode = pick_mode(i8, h, T, batch, load, h.num_cu);
   return plan_tile(pass_of(i8, *mode), h, T, accumulate, batch, h.num_cu, 4, plan);
 }
 
@@ -237,14 +249,15 @@ constexpr int kMaxJobs = 8;
 // of vectors, so fewer workgroups a set and more blocks a workgroup: that one product fits does not say that all do).  On
 // failure *failed is the product that has no launch.
 inline int plan_shared(bool i8, const SharedJob* jobs, int njobs, int num_cu, int batch, Mode* mode, LaunchPlan* plans, int* failed) {
-  int64_t bytes[kMaxJobs], units = 0;
+  int64_t bytes[kMaxJobs];
+  Load load;
   int share[kMaxJobs];
-  for (int j = 0; j < njobs; ++j) { bytes[j] = jobs[j].bytes; units += jobs[j].T->nunits; }
+  for (int j = 0; j < njobs; ++j) { bytes[j] = jobs[j].bytes; load.add(*jobs[j].h, *jobs[j].T); }
   split_device(bytes, njobs, num_cu, share);
   Mode most = Mode::four;
   for (int j = 0; j < njobs; ++j) {
     share[j] = std::min(share[j], jobs[j].h->num_cu);
-    most = std::min(most, pick_mode(i8, *jobs[j].h, *jobs[j].T, batch, units, share[j]));
+    most = std::min(most, pick_mode(i8, *jobs[j].h, *jobs[j].T, batch, load, share[j]));
   }
   int rc = RSR_OK;
   for (const Mode m : {Mode::four, Mode::two, Mode::one}) {

@@ -117,3 +117,10 @@ def test_a_launch_is_one_round_of_workgroups(shim, batch, i8):
                 a = product(shim, rows, blocks * k, k, parts, 0, batch, i8, per_panel)
                 per_cu = min(2 if a.waves == 5 else 16 // a.waves, LDS // a.lds, 4)  # (five wavefronts: two workgroups, measured)
                 assert a.grid <= CUS * per_cu, (rows, blocks, per_panel, a.waves, a.grid)
+
+
+@pytest.mark.parametrize("i8", [0, 1])
+def test_small_panels_do_not_count_as_lack_of_room(shim, i8):
+    """Eight panels in flight are the most there can be: with a unit per panel that is no reason to take narrow passes."""
+    assert product(shim, 1472, 30464, 8, 1, 0, 11, i8, 1).vectors == 4
+    assert product(shim, 1024, 9881, 9, 1, 0, 2, i8, 1).vectors == 1  # (few units: a vector per pass)
