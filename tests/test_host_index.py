@@ -1,7 +1,7 @@
 """Host logic of the HIP library, without a GPU: the C ABI loads and exports what include/rsr.h
-declares; the index builder (Algorithm 1 + packing) reproduces the paper's tables; the packed
-streams satisfy the layout the kernels assume; and a numpy walk over the packed streams that
-mirrors the kernel's traversal reproduces the dense oracle's product.
+declares; Algorithm 1 on the host (rsr_host_pack) reproduces the paper's tables; its packed
+streams satisfy their layout (csrc/rsr_format.h); and a numpy walk over them reproduces the dense
+oracle's product.  (The layout that the kernels read is csrc/rsr_layout.h: tests/test_device_layout.py.)
 
 No product is computed by the library here (that needs the GPU); the numpy walk is test code.
 """
@@ -168,7 +168,7 @@ def test_ternary_without_minus_ones_is_binary_and_negative_only_is_ternary():
         assert sigma.tolist() == list(range(30)) and L.tolist() == [0] + [30] * 16
 
 
-# ---- the packed streams: what the kernels rely on ----------------------------------------------------
+# ---- the packed streams: csrc/rsr_format.h ----------------------------------------------------
 def unit_bytes(npos):
     raw = npos * 2 * LANES + (4 * LANES if npos else 0) + (2 * LANES if npos > 32 else 0)
     return -(-raw // ALIGN) * ALIGN
@@ -284,7 +284,7 @@ def test_stream_invariants(rows, cols, k, kind, seed):
 
 
 def walk(h, S, v):
-    """numpy mirror of the kernel's traversal of the packed streams (int64 arithmetic): every lane walks
+    """numpy walk over the packed streams (int64 arithmetic): every lane walks
     its run with one running sum, stores it where a flag says that a new value starts, and what it is
     left with is added to its last slot afterwards.  The products of the row tiles add up."""
     info = h.info
