@@ -504,17 +504,18 @@ constexpr int NG = rsr::kMaxGranules;
 constexpr int kTotal = 12;      // where a record (kItems words) holds its panel's total
 constexpr int kExtraAhead = 128;  // extra sums of a panel whose slots are fetched ahead of the fold
 
-// u . Bin_[k] by its definition, for the four values value, value + 64, + 128, + 192: for every column (value bit) the sum
-// of the u[j] with that bit.
+// u . Bin_[k] by its definition, for the values 256 step + 64 c + lane, c = 0 .. 3: for every column (value bit) the sum of the
+// u[j] with that bit, one addition per column and four values (which differ in bits 6 and 7 only).  Bound by vector
+// instructions of the wavefront that folds; `step` is the same for all lanes.
 template <typename AT>
-__device__ __forceinline__ void plain_sums(AT (&sums)[12], int value, AT d0, AT d1, AT d2, AT d3) {
+__device__ __forceinline__ void plain_sums(AT (&sums)[12], int step, int lane, AT d0, AT d1, AT d2, AT d3) {
+  const AT all = (d0 + d1) + (d2 + d3);
 #pragma unroll
-  for (int bit = 0; bit < 12; ++bit) {
-    sums[bit] += ((value >> bit) & 1) ? d0 : (AT)0;
-    sums[bit] += (((value + 64) >> bit) & 1) ? d1 : (AT)0;
-    sums[bit] += (((value + 128) >> bit) & 1) ? d2 : (AT)0;
-    sums[bit] += (((value + 192) >> bit) & 1) ? d3 : (AT)0;
-  }
+  for (int bit = 0; bit < 6; ++bit) sums[bit] += ((lane >> bit) & 1) ? all : (AT)0;
+  sums[6] += d1 + d3;
+  sums[7] += d2 + d3;
+#pragma unroll
+  for (int bit = 8; bit < 12; ++bit) sums[bit] += ((step >> (bit - 8)) & 1) ? all : (AT)0;
 }
 
 // The activations of a workgroup's V vectors go to LDS, row by row, the vectors of a row next to each other (int8:
@@ -784,7 +785,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
           hi[j][0] += d1 + d3;
           hi[j][1] += d2 + d3;
           x[r0 + r][j] = (d0 + d1) + (d2 + d3);
-          if constexpr (PLAIN) plain_sums(pl[j], 256 * (i0 + r0 + r) + lane, d0, d1, d2, d3);
+          if constexpr (PLAIN) plain_sums(pl[j], i0 + r0 + r, lane, d0, d1, d2, d3);
         };
         if (f.both) {  // Proposition 2.1, v.B(1) - v.B(2): the fold is linear in u
           unsigned char* const row1 = row + (uint32_t)f.pslots * M::slot_bytes;

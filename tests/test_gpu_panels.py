@@ -132,6 +132,22 @@ def test_bit_planes_in_one_launch_or_several(q, rows, k):
         R.rsr_qbit_destroy(h)
 
 
+@pytest.mark.parametrize("k", [1, 5, 6, 8, 9, 11, 12, 13])
+def test_plain_step_2_over_panel_shapes(k):
+    g = np.random.default_rng(500 + k)
+    A = g.integers(-1, 2, size=(2 ** min(k, 12) + 37, 2 * k + 1)).astype(np.int8)
+    v8 = g.integers(-128, 128, size=(3, A.shape[0]), dtype=np.int8)
+    vf = g.standard_normal((3, A.shape[0])).astype(np.float32)
+    print(f"plain step 2 {A.shape} k={k}", flush=True)
+    with DeviceIndex(A, k) as d:
+        R.rsr_set_step2(d.handle, R.RSR_STEP2_PLAIN)
+        assert np.array_equal(d.matvec(v8).astype(np.int64), dense.matvec_i8(A, v8))
+        assert_f32_close(d.matvec(vf), dense.matvec_f32(A, vf), vf)
+        vf[1, 5] = np.inf  # reaches the columns of its row only
+        got = d.matvec(vf)
+        assert np.isfinite(got[[0, 2]]).all() and np.array_equal(np.isfinite(got[1]), A[5] == 0)
+
+
 def test_more_panels_than_one_grid_of_the_builder_holds():
     """9000001 columns at k = 1: the index is built over ranges of column blocks (2^32 threads are a launch's limit)."""
     import torch
