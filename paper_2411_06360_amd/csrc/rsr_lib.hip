@@ -911,7 +911,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       for (int j = 0; j < V; ++j) put(lane & 15, j, sum[j]);
     } else {
       const uint32_t bl = (uint32_t)(blk - blk_begin);
-      const uint32_t earlier = __umulhi(bl, f.rec_magic);  // blocks that have used these records before
+      const uint32_t earlier = f.nrec == 1 ? bl : __umulhi(bl, f.rec_magic);  // blocks that have used these records before
       const uint32_t ring = bl - earlier * (uint32_t)f.nrec;
       while (uniform(lds_load(f.off_blocks + ring * 4u)) < earlier) __builtin_amdgcn_s_sleep(1);
       AT* rec = reinterpret_cast<AT*>(lds + f.off_rec) + (size_t)ring * f.panels * V * kItems;

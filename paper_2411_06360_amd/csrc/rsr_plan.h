@@ -71,6 +71,7 @@ struct LaunchPlan {
   size_t lds = 0;
 };
 
+constexpr int kManyPanels = 16;  // panels per block from which the records of one block may do
 constexpr int kMostBuffers = 8;  // panels in flight per workgroup at most
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -99,7 +100,10 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
   p.ubytes = (uint32_t)((size_t)(S.nslots + kDummySlots + (T.max_extras + 7) / 8 * 8) * M.slot_bytes);
   const bool records = S.panels > 1 || h.qbit;
   const size_t rec_bytes = (size_t)S.panels * M.V * kItems * 4;
-  auto recs = [&](int nbuf) { return records ? 1 + (nbuf - 1 + S.panels - 1) / S.panels : 0; };
+  // Records of as many blocks as can have a panel in flight.  Where those of one block leave room for more panels there is only one:
+  // a wavefront that folds a panel of the next block then waits for the block before, which is rare with many panels a block.
+  bool one_block = false;
+  auto recs = [&](int nbuf) { return records ? 1 + (one_block ? 0 : (nbuf - 1 + S.panels - 1) / S.panels) : 0; };
   auto total = [&](int nbuf) { return vbytes + (size_t)nbuf * p.ubytes + (size_t)recs(nbuf) * (rec_bytes + 8) + (size_t)nbuf * 8 + 16; };
   // Grid and workgroup size.  Up to four workgroups per compute unit if they fit together (LDS, and 16
   // wavefronts per compute unit at this kernel's register count); never more workgroups than blocks; and
@@ -125,8 +129,20 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
     // Up to eight panels in flight where the LDS holds them (a wavefront whose unit belongs to a later panel waits).
     const int64_t panels_per_wg = blocks_per_wg * S.panels;
     const int most = (int)std::min<int64_t>(kMostBuffers, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
-    for (nbuf = most; nbuf > least && (total(nbuf) > h.lds_max || (wg > 1 && (size_t)wg * total(nbuf) > h.lds_max)); --nbuf) {}
+    auto most_that_fit = [&]() {
+      int n = most;
+      while (n > least && (total(n) > h.lds_max || (wg > 1 && (size_t)wg * total(n) > h.lds_max))) --n;
+      return n;
+    };
+    one_block = false;
+    nbuf = most_that_fit();
     if (total(nbuf) > h.lds_max) return RSR_ERR_UNSUPPORTED;
+    if (S.panels >= kManyPanels && nbuf < most) {
+      one_block = true;
+      const int n = most_that_fit();
+      if (n > nbuf) nbuf = n;
+      else one_block = false;
+    }
     // (of five wavefronts only two workgroups share a compute unit, all other sizes fill its sixteen: timed with kernels that spin,
     // 256 * wg workgroups of n wavefronts at this register count, n = 1 .. 16)
     if (wg == 1 || (wg * waves <= 16 && !(wg == 3 && waves == 5) && (size_t)wg * total(nbuf) <= h.lds_max)) break;

@@ -17,7 +17,8 @@ def stream():
 
 
 def test_int8_vectors_at_many_panels_of_a_tall_tile():
-    """Ternary, k = 16, 32768 rows: 128 panels a block, whose records for two vectors do not fit in LDS beside the rows."""
+    """Ternary, k = 16, 32768 rows: 128 panels a block, whose records for two vectors do not fit in LDS beside the rows; those of one
+    block are kept, and a panel of the next block waits for them."""
     g = np.random.default_rng(401)
     A = g.integers(-1, 2, size=(32768, 1024)).astype(np.int8)
     print("tall ternary 32768x1024 k=16", flush=True)
@@ -25,6 +26,23 @@ def test_int8_vectors_at_many_panels_of_a_tall_tile():
         for batch in (1, 2, 5):
             v8 = g.integers(-128, 128, size=(batch, A.shape[0]), dtype=np.int8)
             assert np.array_equal(d.matvec(v8).astype(np.int64), dense.matvec_i8(A, v8)), batch
+        vf = g.standard_normal((3, A.shape[0])).astype(np.float32)
+        got = d.matvec(vf)
+        assert_f32_close(got, dense.matvec_f32(A, vf), vf)
+        for _ in range(20):  # (wavefronts meet at the records in another order every time)
+            assert np.array_equal(d.matvec(vf), got)
+
+
+@pytest.mark.parametrize("rows,cols,k", [(32768, 300, 14), (32768, 16 * 700, 16), (28001, 911, 14), (30001, 640, 15)])
+def test_records_of_one_block(rows, cols, k):
+    g = np.random.default_rng(404)
+    A = g.integers(-1, 2, size=(rows, cols)).astype(np.int8)
+    print(f"records of one block {rows}x{cols} k={k}", flush=True)
+    with DeviceIndex(A, k) as d:
+        vf = g.standard_normal((2, rows)).astype(np.float32)
+        assert_f32_close(d.matvec(vf), dense.matvec_f32(A, vf), vf)
+        v8 = g.integers(-128, 128, size=(2, rows), dtype=np.int8)
+        assert np.array_equal(d.matvec(v8).astype(np.int64), dense.matvec_i8(A, v8))
 
 
 @pytest.mark.parametrize("rows,k", [(32768, 14), (30000, 15)])
