@@ -640,17 +640,9 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool worker = wave < p.waves;
 
-  // workgroup -> (set of V vectors, block range g): the siblings of a block range sit 8
-  // workgroup ids apart so that round-robin dispatch puts them on the same XCD (shared L2).
-  const int sets = (p.batch + V - 1) / V;
-  const int per = 8 * sets;
-  const int grp = wg / per, rem = wg % per;
-  const int b = (rem >> 3) * V;
-  const int g = grp * 8 + (rem & 7);
-  if (g >= p.g1) return;
-  const int blk_begin = (int)((int64_t)g * p.nblocks / p.g1);
-  const int blk_end = (int)((int64_t)(g + 1) * p.nblocks / p.g1);
-  if (blk_begin >= blk_end) return;
+  const rsr::Share mine = rsr::share_of(p, (uint32_t)wg);
+  if (mine.first == mine.last) return;
+  const int b = (int)mine.set * V, blk_begin = (int)mine.first, blk_end = (int)mine.last;
   const int nv = min(V, p.batch - b);
   const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
 
