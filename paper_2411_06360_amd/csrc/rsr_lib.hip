@@ -504,18 +504,70 @@ constexpr int NG = rsr::kMaxGranules;
 constexpr int kTotal = 12;      // where a record (kItems words) holds its panel's total
 constexpr int kExtraAhead = 128;  // extra sums of a panel whose slots are fetched ahead of the fold
 
-// u . Bin_[k] by its definition, for the values 256 step + 64 c + lane, c = 0 .. 3: for every column (value bit) the sum of the
-// u[j] with that bit, one addition per column and four values (which differ in bits 6 and 7 only).  Bound by vector
+// ---- the slots of four neighbouring values, 4 lane .. 4 lane + 3 of a step's 256, as one lane reads them ----
+// 16 bytes per read: slots of 4 bytes take one ds_read_b128 (5.0 LDS clocks; four ds_read_b32 take 12), slots of 8 bytes two, of 16 bytes
+// four.  A ds_read_b128 is served 16 lanes at a time - lanes 0-3, 12-15, 20-27 and lanes 4-11, 16-19, 28-31 of each half, by
+// measurement - and meets in 16 classes of 16 bytes: lanes 32 or 64 bytes apart would meet two or four deep.  So lanes take their
+// pieces in an order of their own: piece c ^ turn first, with turn such that the lanes of a group of 16 differ in class.
+// The sums below do not depend on that order (a + b = b + a).
+typedef uint32_t u32x4a __attribute__((ext_vector_type(4)));
+template <class M>
+struct SlotRead {
+  static constexpr int kPieces = M::slot_bytes / 4;  // of 16 bytes
+  u32x4a piece[kPieces];
+  __device__ static __forceinline__ int turn(int lane) { return kPieces == 1 ? 0 : kPieces == 2 ? (lane >> 4) & 1 : (lane >> 3) & 3; }
+  __device__ __forceinline__ void read(const unsigned char* quad, int turn) {  // quad: the lane's first slot
+#pragma unroll
+    for (int c = 0; c < kPieces; ++c) piece[c] = *reinterpret_cast<const u32x4a*>(quad + ((c ^ turn) * 16));
+  }
+  __device__ static __forceinline__ void clear(unsigned char* quad) {
+#pragma unroll
+    for (int c = 0; c < kPieces; ++c) *reinterpret_cast<u32x4a*>(quad + c * 16) = u32x4a{0, 0, 0, 0};
+  }
+  // vector j's sum in slot i of the lane's four, in the order of the pieces: slot i ^ (turn << shift)
+  __device__ __forceinline__ typename M::Acc get(int i, int j) const {
+    constexpr int per = 16 / M::slot_bytes, words = M::slot_bytes / 4;  // slots per piece, words per slot
+    // (element by element: __builtin_bit_cast of a vector's element was compiled as one of its first element)
+    struct { uint32_t w[words]; } x;
+#pragma unroll
+    for (int k = 0; k < words; ++k) x.w[k] = piece[i / per][(i % per) * words + k];
+    return M::get(__builtin_bit_cast(typename M::Slot, x), j);
+  }
+};
+// What the fold needs of four neighbouring sums: those with value bit 0, those with bit 1, all.
+template <typename AT>
+struct Quad {
+  AT odd, high, all;
+};
+// d[i]: the sum of value i ^ swap, where swap = turn for slots of 16 bytes and 2 turn for slots of 8.
+template <class M>
+__device__ __forceinline__ Quad<typename M::Acc> quad_of(const typename M::Acc (&d)[4], int turn) {
+  using AT = typename M::Acc;
+  const AT lower = d[0] + d[1], upper = d[2] + d[3];
+  Quad<AT> q;
+  q.all = lower + upper;
+  q.odd = d[1] + d[3];
+  q.high = upper;
+  if constexpr (M::slot_bytes == 8) q.high = turn ? lower : upper;
+  if constexpr (M::slot_bytes == 16) {
+    const AT even = d[0] + d[2];
+    q.odd = (turn & 1) ? even : q.odd;
+    q.high = (turn & 2) ? lower : upper;
+  }
+  return q;
+}
+
+// u . Bin_[k] by its definition, for the values 256 step + 4 lane + c, c = 0 .. 3: for every column (value bit) the sum of the
+// u[j] with that bit, one addition per column and four values (which differ in bits 0 and 1 only).  Bound by vector
 // instructions of the wavefront that folds; `step` is the same for all lanes.
 template <typename AT>
-__device__ __forceinline__ void plain_sums(AT (&sums)[12], int step, int lane, AT d0, AT d1, AT d2, AT d3) {
-  const AT all = (d0 + d1) + (d2 + d3);
+__device__ __forceinline__ void plain_sums(AT (&sums)[12], int step, int lane, const Quad<AT>& d) {
+  sums[0] += d.odd;
+  sums[1] += d.high;
 #pragma unroll
-  for (int bit = 0; bit < 6; ++bit) sums[bit] += ((lane >> bit) & 1) ? all : (AT)0;
-  sums[6] += d1 + d3;
-  sums[7] += d2 + d3;
+  for (int bit = 2; bit < 8; ++bit) sums[bit] += ((lane >> (bit - 2)) & 1) ? d.all : (AT)0;
 #pragma unroll
-  for (int bit = 8; bit < 12; ++bit) sums[bit] += ((step >> (bit - 8)) & 1) ? all : (AT)0;
+  for (int bit = 8; bit < 12; ++bit) sums[bit] += ((step >> (bit - 8)) & 1) ? d.all : (AT)0;
 }
 
 // The activations of a workgroup's V vectors go to LDS, row by row, the vectors of a row next to each other (int8:
@@ -738,15 +790,17 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     // (so are the lane masks below, for which the lane's number has to look new)
     int lane = tid & 63;
     asm volatile("" : "+v"(lane));
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // the sums were written by this workgroup
-    // (the arguments are fetched again: kept in scalar registers from the start of the kernel they would crowd out what
-    // the units need)
+    // (The sums in LDS need no fence: LDS operations of a wavefront execute in order, so those of every unit of the panel were
+    // stored before its count, and the last count has returned.  A fence would also wait for the stream of the next unit.)
+    // (most arguments are fetched again: kept in scalar registers from the start of the kernel they would crowd out what
+    // the units need; what the reads of the sums depend on is one word that stays)
     const KArgsPtr again = launder(pa);
     const KArgs f = *again;
+    const int pslots = f.pslots; const bool both = f.both, fill = f.fill;
     unsigned char* const u = lds + ubase;
-    // Lane l holds the slots 256 i + 64 c + l: value bits 0..5 are lane bits, bits 6 and 7 (c) and the higher ones
-    // (i) are folded inside the lane: "sum the odd-indexed entries, then add neighbours".
-    const int frows = f.pslots / rsr::kFoldRow;
+    // Lane l holds the slots 256 i + 4 l + c: value bits 0 and 1 (c) and 8 and up (i) are folded inside the lane: "sum the
+    // odd-indexed entries, then add neighbours"; bits 2 to 7 are lane bits.
+    const int frows = pslots / rsr::kFoldRow;
     AT hi[V][6], tot[V], pl[V][PLAIN ? 12 : 1];
 #pragma unroll
     for (int j = 0; j < V; ++j) {
@@ -758,8 +812,10 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
         for (int i = 0; i < 12; ++i) pl[j][i] = (AT)0;
     }
     constexpr int kRowBytes = rsr::kFoldRow * M::slot_bytes;
-    unsigned char* const first_row = u + lane * M::slot_bytes;
+    unsigned char* const first_quad = u + lane * 4 * M::slot_bytes;
     using Slot = typename M::Slot;
+    using Read = SlotRead<M>;
+    const int turn = Read::turn(lane);
     // G steps together, P of them read at a time: reads that are in flight together share the wait (behind the gathers of
     // fifteen other wavefronts the LDS answers after several hundred clocks).
     auto fold_steps = [&]<int G>(int i0) {
@@ -767,47 +823,44 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       AT x[G][V];
 #pragma unroll
       for (int r0 = 0; r0 < G; r0 += P) {
-        unsigned char* const row = first_row + (i0 + r0) * kRowBytes;
-        Slot q[P][4];
+        unsigned char* const row = first_quad + (i0 + r0) * kRowBytes;
+        Read q[P];
 #pragma unroll
-        for (int r = 0; r < P; ++r)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) q[r][c] = *reinterpret_cast<const Slot*>(row + r * kRowBytes + c * 64 * M::slot_bytes);
-        auto sums = [&](int r, int j, AT d0, AT d1, AT d2, AT d3) {
-          hi[j][0] += d1 + d3;
-          hi[j][1] += d2 + d3;
-          x[r0 + r][j] = (d0 + d1) + (d2 + d3);
-          if constexpr (PLAIN) plain_sums(pl[j], i0 + r0 + r, lane, d0, d1, d2, d3);
+        for (int r = 0; r < P; ++r) q[r].read(row + r * kRowBytes, turn);
+        auto sums = [&](int r, int j, const AT (&d)[4]) {
+          const Quad<AT> s = quad_of<M>(d, turn);
+          hi[j][0] += s.odd;
+          hi[j][1] += s.high;
+          x[r0 + r][j] = s.all;
+          if constexpr (PLAIN) plain_sums(pl[j], i0 + r0 + r, lane, s);
         };
-        if (f.both) {  // Proposition 2.1, v.B(1) - v.B(2): the fold is linear in u
-          unsigned char* const row1 = row + (uint32_t)f.pslots * M::slot_bytes;
-          Slot m[P][4];
+        if (both) {  // Proposition 2.1, v.B(1) - v.B(2): the fold is linear in u
+          unsigned char* const row1 = row + (uint32_t)pslots * M::slot_bytes;
+          Read m[P];
+#pragma unroll
+          for (int r = 0; r < P; ++r) m[r].read(row1 + r * kRowBytes, turn);
+          if (!fill)
+#pragma unroll
+            for (int r = 0; r < P; ++r) Read::clear(row1 + r * kRowBytes);
 #pragma unroll
           for (int r = 0; r < P; ++r)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) m[r][c] = *reinterpret_cast<const Slot*>(row1 + r * kRowBytes + c * 64 * M::slot_bytes);
-          if (!f.fill)
-#pragma unroll
-            for (int r = 0; r < P; ++r)
-#pragma unroll
-              for (int c = 0; c < 4; ++c) *reinterpret_cast<Slot*>(row1 + r * kRowBytes + c * 64 * M::slot_bytes) = Slot{};
-#pragma unroll
-          for (int r = 0; r < P; ++r)
-#pragma unroll
-            for (int j = 0; j < V; ++j)
-              sums(r, j, M::get(q[r][0], j) - M::get(m[r][0], j), M::get(q[r][1], j) - M::get(m[r][1], j),
-                   M::get(q[r][2], j) - M::get(m[r][2], j), M::get(q[r][3], j) - M::get(m[r][3], j));
+            for (int j = 0; j < V; ++j) {
+              const AT d[4] = {q[r].get(0, j) - m[r].get(0, j), q[r].get(1, j) - m[r].get(1, j), q[r].get(2, j) - m[r].get(2, j), q[r].get(3, j) - m[r].get(3, j)};
+              sums(r, j, d);
+            }
         } else {
 #pragma unroll
           for (int r = 0; r < P; ++r)
 #pragma unroll
-            for (int j = 0; j < V; ++j) sums(r, j, M::get(q[r][0], j), M::get(q[r][1], j), M::get(q[r][2], j), M::get(q[r][3], j));
+            for (int j = 0; j < V; ++j) {
+              const AT d[4] = {q[r].get(0, j), q[r].get(1, j), q[r].get(2, j), q[r].get(3, j)};
+              sums(r, j, d);
+            }
         }
-        if (!f.fill)
+        if (!fill)
 #pragma unroll
-          for (int r = 0; r < P; ++r)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) *reinterpret_cast<Slot*>(row + r * kRowBytes + c * 64 * M::slot_bytes) = Slot{};
+          for (int r = 0; r < P; ++r) Read::clear(row + r * kRowBytes);
         if constexpr (P < G) asm volatile("" ::: "memory");  // (the next steps' reads stay behind: registers)
       }
       // (two steps at a time, in this order, for every G: the sums do not depend on how many vectors share a pass)
@@ -834,12 +887,14 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       for (int i = 0; i < frows; i += kTogether) fold_steps.template operator()<kTogether>(i);
     else if (frows == 1)
       fold_steps.template operator()<1>(0);
+    else if (kTogether == 8 && frows == 4)
+      fold_steps.template operator()<4>(0);
     else
 #pragma unroll 1
       for (int i = 0; i < frows; i += 2) fold_steps.template operator()<2>(i);
     // The further pieces of segments that were cut: lane l takes the extra sums 2l and 2l + 1, which count under the bits of
     // their segments' values.
-    const uint32_t first_extra = (uint32_t)(f.pslots << f.both) + rsr::kDummySlots;
+    const uint32_t first_extra = (uint32_t)(pslots << (both ? 1 : 0)) + rsr::kDummySlots;
     Slot ex[2] = {Slot{}, Slot{}};
     if (D.extras != 0)
 #pragma unroll
@@ -862,16 +917,16 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
         if constexpr (PLAIN) {
           items[i] = pl[j][i]; items[6 + i] = pl[j][6 + i];
         } else {
-          items[i] = ((lane >> i) & 1) ? tot[j] : (AT)0;
-          items[6 + i] = hi[j][i];
+          items[2 + i] = ((lane >> i) & 1) ? tot[j] : (AT)0;
+          items[i < 2 ? i : 6 + i] = hi[j][i];
         }
       }
       items[kTotal] = tot[j];
       items[13] = items[14] = items[15] = (AT)0;
       auto add_extra = [&](uint32_t slot, AT z) {
-        const AT y = f.both && slot >= (uint32_t)f.pslots ? -z : z;
+        const AT y = both && slot >= (uint32_t)pslots ? -z : z;
 #pragma unroll
-        for (int i = 0; i < 12; ++i) items[i] += ((slot & (uint32_t)(f.pslots - 1)) >> i) & 1 ? y : (AT)0;
+        for (int i = 0; i < 12; ++i) items[i] += ((slot & (uint32_t)(pslots - 1)) >> i) & 1 ? y : (AT)0;
         items[kTotal] += y;
       };
       if (D.extras != 0) {
@@ -912,8 +967,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
 #pragma unroll
         for (int j = 0; j < V; ++j) rec[(mine * V + j) * kItems + lane] = sum[j];
       const uint32_t before = lds_count_up(f.off_done + ring * 4u);
-      if ((int)before + 1 == f.panels) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      if ((int)before + 1 == f.panels) {  // (the other panels' records were stored before their counts)
         // The four rows of 16 lanes take every fourth panel.  Bits below kc are in the records; a higher bit sees
         // only the totals of the panels whose values have it (the remaining levels of the fold).
         const int bit = lane & 15, word = bit < f.kc ? bit : kTotal;
@@ -955,7 +1009,6 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     const uint32_t ubase = p.off_u + buf * p.ubytes;
     if (turn != 0 && panel != open_panel) {
       while (uniform(lds_load(p.off_epoch + buf * 4u)) < turn) __builtin_amdgcn_s_sleep(1);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
       open_panel = panel;
     }
 
