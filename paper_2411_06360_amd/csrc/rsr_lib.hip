@@ -213,232 +213,226 @@ __device__ __forceinline__ void lds_count_up(uint32_t addr_a, uint32_t addr_b, u
   b = (uint32_t)__builtin_amdgcn_readfirstlane((int)y);
 }
 
-// ---- the positions of a unit, eight (one granule) or two (one dword) at a time ----
-// Per position and lane the stream holds a uint16: a row index, or where the unit's mask (bit q of `hm` for position
-// q of the step, the same for all lanes) says that a group ends, the lane's slot.  A row costs one address
-// extraction, one LDS read and one add per activation vector; a head stores the running sums to the panel's slot
-// (byte address `ub` + slot) and restarts them.  The choice is a scalar branch: no lane needs a mask of its own,
-// which takes three of five vector instructions and the store that every position would otherwise issue out of
-// the loop (a store holds the LDS for 4.4 clocks however few lanes take part; a gather for 2.4).  All gathers of a
-// step are issued before the first sum so that their latencies overlap.  At the heads of a unit whose segments take
-// 8 lanes (`wd` = 1) the lanes' sums are first added with lane exchanges, by a routine behind the step (its
-// s_nop cover the wait states an exchange needs after a vector write).
-// The wait before the add of position q allows as many LDS operations as gathers follow it: they complete in
-// order, and stores or scalar loads issued in between only make the wait stricter.  A step must not end before
-// its last gather has arrived (its register is free for the compiler then), also if the last position is a head.
+// ---- the positions of a unit, eight (one granule) at a time, four in the pass over four float vectors ----
+// Per position and lane the stream holds a uint16: a row index, or where the unit's mask says that a group ends (the same
+// position for all lanes), the lane's slot.  A row costs one address extraction, one LDS read and one add per activation
+// vector; a head stores the running sums to the panel's slot (byte address s91 + slot) and restarts them.  Which positions of a
+// step are heads is one of 2^8 (2^4) patterns, the same for all lanes, and every pattern has straight code of its own
+// in a table that the assembler expands: the step's addresses are extracted to fixed registers and the code of its pattern is called.
+// With a bit test and a branch per position in their place a wavefront issued 90 branches per unit (26 now), and gathered at the
+// heads too (one position in five, an LDS read of 3 clocks each): binary 16384^2, k = 12, eight vectors 49.8 -> 44.5 us, eight int8
+// vectors 37.3 -> 35.2, transformer block with sixteen vectors 90.0 -> 85.7; one vector, bound by the stream: 13.6 -> 13.7.
+// A table takes 33 to 58 KB, of which an index uses the patterns of its groups' lengths (some sixty).
+// All gathers of a step are issued before the first sum so that their latencies overlap; the wait before the add of a
+// position allows as many LDS operations as follow it (they complete in order; scalar loads that are under way besides only make
+// the wait stricter).  Every gather has been waited for when its step returns.
+// Fixed registers: a position's address, then its gathered activations: v96 + (position of the step) * (16-byte row: 4, 8-byte
+// row: 2, else 1); the running sums from v112 on; s90 pattern, s91 panel base, s92-s95 addresses.
 // What an activation mode M defines: vectors V per pass, LDS bytes per row (1 << shift) and per slot, and its sums.
-#define RSR_EXTRACT(sh, q, w, half)                                                                            \
-  "v_lshlrev_b32_sdwa %[s" #q "], " #sh ", %[w" #w "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:" half "\n"
-#define RSR_EXTRACT2(sh, q0, q1, w) RSR_EXTRACT(sh, q0, w, "WORD_0") RSR_EXTRACT(sh, q1, w, "WORD_1")
-#define RSR_EXTRACT8(sh) RSR_EXTRACT2(sh, 0, 1, 0) RSR_EXTRACT2(sh, 2, 3, 1) RSR_EXTRACT2(sh, 4, 5, 2) RSR_EXTRACT2(sh, 6, 7, 3)
-#define RSR_ROW(q, wait, SUM)                                                                                  \
-  "s_bitcmp1_b32 %[hm], " #q "\n s_cbranch_scc1 .Lrsr_head" #q "_%=\n s_waitcnt lgkmcnt(" #wait ")\n" SUM     \
-  ".Lrsr_next" #q "_%=:\n"
-#define RSR_HEAD(q, STORE)                                                                                     \
-  ".Lrsr_head" #q "_%=: s_cmp_lg_u32 %[wd], 0\n s_cbranch_scc1 .Lrsr_wide" #q "_%=\n"                          \
-  ".Lrsr_store" #q "_%=:\n" STORE "s_branch .Lrsr_next" #q "_%=\n"                                             \
-  ".Lrsr_wide" #q "_%=: s_call_b64 s[94:95], .Lrsr_lanes_%=\n s_branch .Lrsr_store" #q "_%=\n"
-#define RSR_LANES(ADDS)                                                                                        \
-  ".Lrsr_lanes_%=: s_nop 1\n" ADDS("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")                           \
-  "s_nop 1\n" ADDS("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")                                           \
-  "s_nop 1\n" ADDS("row_half_mirror row_mask:0xf bank_mask:0xf")                                               \
-  "s_setpc_b64 s[94:95]\n"
-#define RSR_S6 [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3), [s4] "=&v"(s4), [s5] "=&v"(s5)
-#define RSR_S8 [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3), [s4] "=&v"(s4), [s5] "=&v"(s5), [s6] "=&v"(s6), [s7] "=&v"(s7)
+#define RSR_EXTRACT(sh, v, w, half) "v_lshlrev_b32_sdwa v" #v ", " #sh ", %[w" #w "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:" half "\n"
+#define RSR_EXTRACT2(sh, v0, v1, w) RSR_EXTRACT(sh, v0, w, "WORD_0") RSR_EXTRACT(sh, v1, w, "WORD_1")
+// The code of every pattern: rsr_p the pattern, rsr_q the position, rsr_n LDS operations that may be under way, rsr_z 1 where the
+// running sums have been stored and not restarted yet, rsr_b bytes of code so far.  A pattern takes `stride` bytes.  `row`, `first`
+// and `head` are the bytes of a position: a row, the first row of a group, a head; `zeros` those of ZERO.
+#define RSR_TABLE(positions, stride, row, first, head, zeros, READ, ADD, FIRST, STORE, ZERO)                   \
+  ".set rsr_p, 0\n.rept 1 << " #positions "\n.set rsr_q, 0\n.set rsr_n, 0\n.set rsr_z, 0\n.set rsr_b, 4\n"     \
+  ".rept " #positions "\n.if ((rsr_p >> rsr_q) & 1) == 0\n" READ ".set rsr_n, rsr_n+1\n.endif\n.set rsr_q, rsr_q+1\n.endr\n" \
+  ".set rsr_q, 0\n.rept " #positions "\n.if (rsr_p >> rsr_q) & 1\n.if rsr_z\n" ZERO ".set rsr_b, rsr_b+" #zeros "\n.endif\n" STORE \
+  ".set rsr_n, rsr_n+1\n.set rsr_z, 1\n.set rsr_b, rsr_b+" #head "\n"                                          \
+  ".else\n.set rsr_n, rsr_n-1\n s_waitcnt lgkmcnt(rsr_n)\n"                                                    \
+  ".if rsr_z\n" FIRST ".set rsr_b, rsr_b+" #first "\n.else\n" ADD ".set rsr_b, rsr_b+" #row "\n.endif\n.set rsr_z, 0\n" \
+  ".endif\n.set rsr_q, rsr_q+1\n.endr\n"                                                                       \
+  ".if rsr_z\n" ZERO ".set rsr_b, rsr_b+" #zeros "\n.endif\n s_setpc_b64 s[94:95]\n"                           \
+  ".if rsr_b > " #stride "\n.error \"a pattern does not fit\"\n.endif\n"                                       \
+  ".rept (" #stride "-rsr_b)/4\n s_nop 0\n.endr\n.set rsr_p, rsr_p+1\n.endr\n"
+// Behind the table, for units whose segments take 8 lanes: branches, 4 bytes per pattern, to the code of a step without heads or, with
+// one (a step in four or five: 32 rows a lane), to the code of any pattern, by a test and a branch per position; at a head the lanes' sums are first added with lane exchanges (the s_nop cover the wait states an exchange needs after a vector write).
+#define RSR_WIDE_READ(q, READ) ".set rsr_q, " #q "\n s_bitcmp1_b32 s90, " #q "\n s_cbranch_scc1 .Lrsr_r" #q "_%=\n" READ ".Lrsr_r" #q "_%=:\n"
+#define RSR_WIDE_SUM(q, ADD, LANES, STORE, ZERO)                                                               \
+  ".set rsr_q, " #q "\n s_bitcmp1_b32 s90, " #q "\n s_cbranch_scc1 .Lrsr_h" #q "_%=\n" ADD " s_branch .Lrsr_n" #q "_%=\n" \
+  ".Lrsr_h" #q "_%=:\n s_nop 1\n" LANES("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")                      \
+  " s_nop 1\n" LANES("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")                                         \
+  " s_nop 1\n" LANES("row_half_mirror row_mask:0xf bank_mask:0xf") STORE ZERO ".Lrsr_n" #q "_%=:\n"
+#define RSR_WIDE_PADS(positions) " s_branch .Lrsr_table_%=\n.rept (1 << " #positions ")-1\n s_branch .Lrsr_any_%=\n.endr\n.Lrsr_any_%=:\n"
+#define RSR_WIDE4(READ, ADD, LANES, STORE, ZERO)                                                               \
+  RSR_WIDE_PADS(4)                                                                                             \
+  RSR_WIDE_READ(0, READ) RSR_WIDE_READ(1, READ) RSR_WIDE_READ(2, READ) RSR_WIDE_READ(3, READ) " s_waitcnt lgkmcnt(0)\n" \
+  RSR_WIDE_SUM(0, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(1, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(2, ADD, LANES, STORE, ZERO) \
+  RSR_WIDE_SUM(3, ADD, LANES, STORE, ZERO) " s_setpc_b64 s[94:95]\n"
+#define RSR_WIDE8(READ, ADD, LANES, STORE, ZERO)                                                               \
+  RSR_WIDE_PADS(8)                                                                                             \
+  RSR_WIDE_READ(0, READ) RSR_WIDE_READ(1, READ) RSR_WIDE_READ(2, READ) RSR_WIDE_READ(3, READ) RSR_WIDE_READ(4, READ) \
+  RSR_WIDE_READ(5, READ) RSR_WIDE_READ(6, READ) RSR_WIDE_READ(7, READ) " s_waitcnt lgkmcnt(0)\n"               \
+  RSR_WIDE_SUM(0, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(1, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(2, ADD, LANES, STORE, ZERO) \
+  RSR_WIDE_SUM(3, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(4, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(5, ADD, LANES, STORE, ZERO) \
+  RSR_WIDE_SUM(6, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(7, ADD, LANES, STORE, ZERO) " s_setpc_b64 s[94:95]\n"
+// How a unit's steps find their code: pattern 0 at `code`, every further one `stride` bytes on.
+struct Steps {
+  uint64_t code;
+  uint32_t stride, base;  // base: LDS byte address of the panel's slots
+};
+// Emits a mode's table into the kernel (once per kernel: the wavefronts jump over it) and returns its address.
+#define RSR_STEPS(TABLE, WIDE)                                                                                 \
+  __device__ static __forceinline__ uint64_t table() {                                                         \
+    uint32_t lo, hi;                                                                                           \
+    asm volatile("s_getpc_b64 s[92:93]\n.Lrsr_here_%=:\n s_add_u32 %[lo], s92, .Lrsr_table_%=-.Lrsr_here_%=\n" \
+                 " s_addc_u32 %[hi], s93, 0\n s_branch .Lrsr_over_%=\n.p2align 6\n.Lrsr_table_%=:\n" TABLE WIDE ".Lrsr_over_%=:\n" \
+                 : [lo] "=&s"(lo), [hi] "=&s"(hi)::"s92", "s93", "scc");                                       \
+    return (uint64_t)hi << 32 | lo;                                                                            \
+  }
+#define RSR_FIND "s_mul_i32 s92, s90, %[stride]\n s_add_u32 s92, %[lo], s92\n s_addc_u32 s93, %[hi], 0\n"
+#define RSR_CALL " s_swappc_b64 s[94:95], s[92:93]\n"
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }  // (into a scalar register)
-#define RSR_CTL [hm] "s"(uniform(hm)), [wd] "s"(uniform(wd)), [ub] "s"(uniform(ub))
-#define RSR_CLOBBER "scc", "s94", "s95", "memory"
-
-// One 32-bit word per row and slot (a float, or an int8 widened when it is staged).
-#define RSR_SUM1(q, ADD) ADD " %[a], %[a], %[t" #q "]\n"
-#define RSR_STORE1(q) "v_add_u32 %[s" #q "], %[ub], %[s" #q "]\n ds_write_b32 %[s" #q "], %[a]\n v_mov_b32 %[a], 0\n"
-#define RSR_LANES1_F(x) "v_add_f32_dpp %[a], %[a], %[a] " x "\n"
-#define RSR_LANES1_P(x) "v_mov_b32_dpp %[x], %[a] " x "\n v_pk_add_u16 %[a], %[a], %[x]\n"
-#define RSR_LANES1_I(x) "v_add_u32_dpp %[a], %[a], %[a] " x "\n"
-#define RSR_STEPS1(AT, ADD, LANES)                                                                             \
-  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, AT (&acc)[1], uint32_t hm, \
-                                               uint32_t wd, uint32_t ub) {                                     \
-    uint32_t s0, s1, s2, s3, s4, s5, s6, s7;                                                                   \
-    AT t0, t1, t2, t3, t4, t5, t6, t7, x;                                                                       \
-    asm volatile(                                                                                              \
-        RSR_EXTRACT8(2)                                                                                        \
-        "ds_read_b32 %[t0], %[s0]\n ds_read_b32 %[t1], %[s1]\n ds_read_b32 %[t2], %[s2]\n ds_read_b32 %[t3], %[s3]\n" \
-        "ds_read_b32 %[t4], %[s4]\n ds_read_b32 %[t5], %[s5]\n ds_read_b32 %[t6], %[s6]\n ds_read_b32 %[t7], %[s7]\n" \
-        RSR_ROW(0, 7, RSR_SUM1(0, ADD)) RSR_ROW(1, 6, RSR_SUM1(1, ADD)) RSR_ROW(2, 5, RSR_SUM1(2, ADD)) RSR_ROW(3, 4, RSR_SUM1(3, ADD)) \
-        RSR_ROW(4, 3, RSR_SUM1(4, ADD)) RSR_ROW(5, 2, RSR_SUM1(5, ADD)) RSR_ROW(6, 1, RSR_SUM1(6, ADD)) RSR_ROW(7, 0, RSR_SUM1(7, ADD)) \
-        "s_branch .Lrsr_end_%=\n"                                                                              \
-        RSR_HEAD(0, RSR_STORE1(0)) RSR_HEAD(1, RSR_STORE1(1)) RSR_HEAD(2, RSR_STORE1(2)) RSR_HEAD(3, RSR_STORE1(3)) \
-        RSR_HEAD(4, RSR_STORE1(4)) RSR_HEAD(5, RSR_STORE1(5)) RSR_HEAD(6, RSR_STORE1(6)) RSR_HEAD(7, RSR_STORE1(7) "s_waitcnt lgkmcnt(1)\n") \
-        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
-        : [a] "+v"(acc[0]), [x] "=&v"(x), RSR_S8, [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4), \
-          [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7)                                                       \
-        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), RSR_CTL                                      \
-        : RSR_CLOBBER);                                                                                        \
+#define RSR_CTL(pattern) "{s90}"(uniform(pattern)), "{s91}"(uniform(s.base)), [stride] "s"(uniform(s.stride)), [lo] "s"(uniform((uint32_t)s.code)), [hi] "s"(uniform((uint32_t)(s.code >> 32)))
+#define RSR_CLOBBER                                                                                            \
+  "s92", "s93", "s94", "s95", "scc", "memory", "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", \
+      "v108", "v109", "v110", "v111"
+// A step of eight positions from four dwords; the last one of a unit, of up to six positions, from three dwords and the null row.
+#define RSR_STEP8(shift, sums, v0, v1, v2, v3, v4, v5, v6, v7, ...)                                    \
+  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, Sums& acc, uint32_t heads, const Steps& s) { \
+    asm volatile(RSR_FIND RSR_EXTRACT2(shift, v0, v1, 0) RSR_EXTRACT2(shift, v2, v3, 1) RSR_EXTRACT2(shift, v4, v5, 2) RSR_EXTRACT2(shift, v6, v7, 3) \
+                 RSR_CALL                                                                              \
+                 : "+{" sums "}"(acc)                                                                          \
+                 : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), RSR_CTL(heads & 0xffu)              \
+                 : RSR_CLOBBER __VA_OPT__(,) __VA_ARGS__);                                                     \
   }                                                                                                            \
-  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, AT (&acc)[1], uint32_t hm, uint32_t wd, uint32_t ub) { \
-    uint32_t s0, s1, s2, s3, s4, s5;                                                                           \
-    AT t0, t1, t2, t3, t4, t5, x;                                                                               \
-    asm volatile(                                                                                              \
-        RSR_EXTRACT2(2, 0, 1, 0) RSR_EXTRACT2(2, 2, 3, 1) RSR_EXTRACT2(2, 4, 5, 2)                             \
-        "ds_read_b32 %[t0], %[s0]\n ds_read_b32 %[t1], %[s1]\n ds_read_b32 %[t2], %[s2]\n ds_read_b32 %[t3], %[s3]\n" \
-        "ds_read_b32 %[t4], %[s4]\n ds_read_b32 %[t5], %[s5]\n"                                                \
-        RSR_ROW(0, 5, RSR_SUM1(0, ADD)) RSR_ROW(1, 4, RSR_SUM1(1, ADD)) RSR_ROW(2, 3, RSR_SUM1(2, ADD))        \
-        RSR_ROW(3, 2, RSR_SUM1(3, ADD)) RSR_ROW(4, 1, RSR_SUM1(4, ADD)) RSR_ROW(5, 0, RSR_SUM1(5, ADD)) "s_branch .Lrsr_end_%=\n" \
-        RSR_HEAD(0, RSR_STORE1(0)) RSR_HEAD(1, RSR_STORE1(1)) RSR_HEAD(2, RSR_STORE1(2)) RSR_HEAD(3, RSR_STORE1(3)) \
-        RSR_HEAD(4, RSR_STORE1(4)) RSR_HEAD(5, RSR_STORE1(5) "s_waitcnt lgkmcnt(1)\n")                         \
-        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
-        : [a] "+v"(acc[0]), [x] "=&v"(x), RSR_S6, [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5) \
-        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), RSR_CTL                                                    \
-        : RSR_CLOBBER);                                                                                        \
+  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t null_row, Sums& acc, uint32_t heads, const Steps& s) { \
+    asm volatile(RSR_FIND RSR_EXTRACT2(shift, v0, v1, 0) RSR_EXTRACT2(shift, v2, v3, 1) RSR_EXTRACT2(shift, v4, v5, 2)  \
+                 "v_mov_b32 v" #v6 ", %[null]\n v_mov_b32 v" #v7 ", %[null]\n" RSR_CALL                \
+                 : "+{" sums "}"(acc)                                                                          \
+                 : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [null] "s"(uniform(null_row)), RSR_CTL(heads & 0x3fu) \
+                 : RSR_CLOBBER __VA_OPT__(,) __VA_ARGS__);                                                     \
   }
 
-// Several vectors per row.  A gather fills neighbouring registers, which have to be named: v[96:111].
-#define RSR_T16 "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", "v108", "v109", "v110", "v111"
-// two registers of sums: two floats, or four 16-bit sums
-#define RSR_SUM2(x, y, ADD) ADD " %[a], %[a], v" #x "\n" ADD " %[b], %[b], v" #y "\n"
-#define RSR_STORE2(q)                                                                                          \
-  "v_add_u32 %[s" #q "], %[ub], %[s" #q "]\n ds_write2_b32 %[s" #q "], %[a], %[b] offset1:1\n v_mov_b32 %[a], 0\n v_mov_b32 %[b], 0\n"
-#define RSR_LANES2_F(x) "v_add_f32_dpp %[a], %[a], %[a] " x "\n v_add_f32_dpp %[b], %[b], %[b] " x "\n"
-#define RSR_LANES2_P(x)                                                                                        \
-  "v_mov_b32_dpp %[x], %[a] " x "\n v_mov_b32_dpp %[y], %[b] " x "\n v_pk_add_u16 %[a], %[a], %[x]\n v_pk_add_u16 %[b], %[b], %[y]\n"
-#define RSR_STEPS2(AT, ADD, LANES)                                                                             \
-  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, AT (&acc)[2], uint32_t hm, \
-                                               uint32_t wd, uint32_t ub) {                                     \
-    uint32_t s0, s1, s2, s3, s4, s5, s6, s7;                                                                   \
-    AT x, y;                                                                                                   \
-    asm volatile(                                                                                              \
-        RSR_EXTRACT8(3)                                                                                        \
-        "ds_read_b64 v[96:97], %[s0]\n ds_read_b64 v[98:99], %[s1]\n ds_read_b64 v[100:101], %[s2]\n ds_read_b64 v[102:103], %[s3]\n" \
-        "ds_read_b64 v[104:105], %[s4]\n ds_read_b64 v[106:107], %[s5]\n ds_read_b64 v[108:109], %[s6]\n ds_read_b64 v[110:111], %[s7]\n" \
-        RSR_ROW(0, 7, RSR_SUM2(96, 97, ADD)) RSR_ROW(1, 6, RSR_SUM2(98, 99, ADD)) RSR_ROW(2, 5, RSR_SUM2(100, 101, ADD)) \
-        RSR_ROW(3, 4, RSR_SUM2(102, 103, ADD)) RSR_ROW(4, 3, RSR_SUM2(104, 105, ADD)) RSR_ROW(5, 2, RSR_SUM2(106, 107, ADD)) \
-        RSR_ROW(6, 1, RSR_SUM2(108, 109, ADD)) RSR_ROW(7, 0, RSR_SUM2(110, 111, ADD)) "s_branch .Lrsr_end_%=\n" \
-        RSR_HEAD(0, RSR_STORE2(0)) RSR_HEAD(1, RSR_STORE2(1)) RSR_HEAD(2, RSR_STORE2(2)) RSR_HEAD(3, RSR_STORE2(3)) \
-        RSR_HEAD(4, RSR_STORE2(4)) RSR_HEAD(5, RSR_STORE2(5)) RSR_HEAD(6, RSR_STORE2(6)) RSR_HEAD(7, RSR_STORE2(7) "s_waitcnt lgkmcnt(1)\n") \
-        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
-        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [x] "=&v"(x), [y] "=&v"(y), RSR_S8                               \
-        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), RSR_CTL                                      \
-        : RSR_CLOBBER, RSR_T16);                                                                               \
-  }                                                                                                            \
-  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, AT (&acc)[2], uint32_t hm, uint32_t wd, uint32_t ub) { \
-    uint32_t s0, s1, s2, s3, s4, s5;                                                                           \
-    AT x, y;                                                                                                   \
-    asm volatile(                                                                                              \
-        RSR_EXTRACT2(3, 0, 1, 0) RSR_EXTRACT2(3, 2, 3, 1) RSR_EXTRACT2(3, 4, 5, 2)                             \
-        "ds_read_b64 v[96:97], %[s0]\n ds_read_b64 v[98:99], %[s1]\n ds_read_b64 v[100:101], %[s2]\n ds_read_b64 v[102:103], %[s3]\n" \
-        "ds_read_b64 v[104:105], %[s4]\n ds_read_b64 v[106:107], %[s5]\n"                                      \
-        RSR_ROW(0, 5, RSR_SUM2(96, 97, ADD)) RSR_ROW(1, 4, RSR_SUM2(98, 99, ADD)) RSR_ROW(2, 3, RSR_SUM2(100, 101, ADD)) \
-        RSR_ROW(3, 2, RSR_SUM2(102, 103, ADD)) RSR_ROW(4, 1, RSR_SUM2(104, 105, ADD)) RSR_ROW(5, 0, RSR_SUM2(106, 107, ADD)) \
-        "s_branch .Lrsr_end_%=\n"                                                                              \
-        RSR_HEAD(0, RSR_STORE2(0)) RSR_HEAD(1, RSR_STORE2(1)) RSR_HEAD(2, RSR_STORE2(2)) RSR_HEAD(3, RSR_STORE2(3)) \
-        RSR_HEAD(4, RSR_STORE2(4)) RSR_HEAD(5, RSR_STORE2(5) "s_waitcnt lgkmcnt(1)\n")                         \
-        RSR_LANES(LANES) ".Lrsr_end_%=:\n"                                                                     \
-        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [x] "=&v"(x), [y] "=&v"(y), RSR_S6                               \
-        : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), RSR_CTL                                                    \
-        : RSR_CLOBBER, RSR_T16);                                                                               \
-  }
-// four floats
-#define RSR_SUM4(x, y, z, w)                                                                                   \
-  "v_add_f32 %[a], %[a], v" #x "\n v_add_f32 %[b], %[b], v" #y "\n v_add_f32 %[c], %[c], v" #z "\n v_add_f32 %[d], %[d], v" #w "\n"
-#define RSR_CLEAR4 "v_mov_b32 %[a], 0\n v_mov_b32 %[b], 0\n v_mov_b32 %[c], 0\n v_mov_b32 %[d], 0\n"
-#define RSR_STORE4(q)                                                                                          \
-  "v_add_u32 %[s" #q "], %[ub], %[s" #q "]\n ds_write2_b32 %[s" #q "], %[a], %[b] offset1:1\n"                 \
-  "ds_write2_b32 %[s" #q "], %[c], %[d] offset0:2 offset1:3\n" RSR_CLEAR4
-#define RSR_LANES4(x)                                                                                          \
-  "v_add_f32_dpp %[a], %[a], %[a] " x "\n v_add_f32_dpp %[b], %[b], %[b] " x "\n"                              \
-  "v_add_f32_dpp %[c], %[c], %[c] " x "\n v_add_f32_dpp %[d], %[d], %[d] " x "\n"
+// One 32-bit word per row and slot.
+#define RSR_READ1 " ds_read_b32 v[96+rsr_q], v[96+rsr_q]\n"
+#define RSR_STORE1 " v_add_u32 v[96+rsr_q], s91, v[96+rsr_q]\n ds_write_b32 v[96+rsr_q], v112\n"
+#define RSR_ZERO1 " v_mov_b32 v112, 0\n"
+#define RSR_ADD_F1 " v_add_f32 v112, v112, v[96+rsr_q]\n"
+#define RSR_FIRST_F1 " v_add_f32 v112, 0, v[96+rsr_q]\n"
+#define RSR_LANES_F1(x) " v_add_f32_dpp v112, v112, v112 " x "\n"
+#define RSR_ADD_I1 " v_add_u32 v112, v112, v[96+rsr_q]\n"
+#define RSR_FIRST_I1 " v_mov_b32 v112, v[96+rsr_q]\n"
+#define RSR_LANES_I1(x) " v_add_u32_dpp v112, v112, v112 " x "\n"
+#define RSR_ADD_P2 " v_pk_add_u16 v112, v112, v[96+rsr_q]\n"
+#define RSR_LANES_P2(x) " v_mov_b32_dpp v114, v112 " x "\n v_pk_add_u16 v112, v112, v114\n"
+// Two words: two floats, or four 16-bit sums.
+#define RSR_READ2 " ds_read_b64 v[96+2*rsr_q:97+2*rsr_q], v[96+2*rsr_q]\n"
+#define RSR_STORE2 " v_add_u32 v[96+2*rsr_q], s91, v[96+2*rsr_q]\n ds_write_b64 v[96+2*rsr_q], v[112:113]\n"
+#define RSR_ZERO2 " v_mov_b32 v112, 0\n v_mov_b32 v113, 0\n"
+#define RSR_ADD_F2 " v_add_f32 v112, v112, v[96+2*rsr_q]\n v_add_f32 v113, v113, v[97+2*rsr_q]\n"
+#define RSR_FIRST_F2 " v_add_f32 v112, 0, v[96+2*rsr_q]\n v_add_f32 v113, 0, v[97+2*rsr_q]\n"
+#define RSR_LANES_F2(x) " v_add_f32_dpp v112, v112, v112 " x "\n v_add_f32_dpp v113, v113, v113 " x "\n"
+#define RSR_ADD_P4 " v_pk_add_u16 v112, v112, v[96+2*rsr_q]\n v_pk_add_u16 v113, v113, v[97+2*rsr_q]\n"
+#define RSR_FIRST_P4 " v_mov_b32 v112, v[96+2*rsr_q]\n v_mov_b32 v113, v[97+2*rsr_q]\n"
+#define RSR_LANES_P4(x) " v_mov_b32_dpp v114, v112 " x "\n v_mov_b32_dpp v115, v113 " x "\n v_pk_add_u16 v112, v112, v114\n v_pk_add_u16 v113, v113, v115\n"
+// Four floats.  (One ds_write_b128: 14 LDS clocks; two ds_write2_b32 would take 25.)
+#define RSR_READ4 " ds_read_b128 v[96+4*rsr_q:99+4*rsr_q], v[96+4*rsr_q]\n"
+#define RSR_STORE4 " v_add_u32 v[96+4*rsr_q], s91, v[96+4*rsr_q]\n ds_write_b128 v[96+4*rsr_q], v[112:115]\n s_nop 0\n"
+#define RSR_ZERO4 " v_mov_b32 v112, 0\n v_mov_b32 v113, 0\n v_mov_b32 v114, 0\n v_mov_b32 v115, 0\n"
+#define RSR_ADD_F4                                                                                             \
+  " v_add_f32 v112, v112, v[96+4*rsr_q]\n v_add_f32 v113, v113, v[97+4*rsr_q]\n v_add_f32 v114, v114, v[98+4*rsr_q]\n v_add_f32 v115, v115, v[99+4*rsr_q]\n"
+#define RSR_FIRST_F4                                                                                           \
+  " v_add_f32 v112, 0, v[96+4*rsr_q]\n v_add_f32 v113, 0, v[97+4*rsr_q]\n v_add_f32 v114, 0, v[98+4*rsr_q]\n v_add_f32 v115, 0, v[99+4*rsr_q]\n"
+#define RSR_LANES_F4(x)                                                                                        \
+  " v_add_f32_dpp v112, v112, v112 " x "\n v_add_f32_dpp v113, v113, v113 " x "\n v_add_f32_dpp v114, v114, v114 " x "\n v_add_f32_dpp v115, v115, v115 " x "\n"
 // int8 activations of several vectors are widened to 16 bits when they are staged, two vectors to a dword, and
 // summed two at a time (v_pk_add_u16).  Nothing is lost: no lane and no slot sums more than kWideRows = 256 rows (the builder cuts
 // longer segments), so a sum lies in -128 * 256 .. 127 * 256, which 16 bits hold (rsr_layout.h asserts it); from the
 // slots on, and between pieces, panels and parts, sums are 32 bits wide.
+// (kStride: bytes of the longest pattern; kWide: where the branches of wide units are.)
 struct F1 {  // one float vector
   using In = float;
   using Acc = float;
-  using Run = float;  // the running sums
+  using Sums = float;  // the running sums
   static constexpr rsr::Pass pass = rsr::kF1;
-  static constexpr int V = pass.V, R = 1, shift = pass.shift, slot_bytes = pass.slot_bytes;  // (R: registers of running sums)
+  static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr uint32_t kStride = 132, kWide = 256 * kStride;
   using Slot = float;  // the sums of a slot
   __device__ static __forceinline__ float get(float x, int) { return x; }
-  RSR_STEPS1(float, "v_add_f32", RSR_LANES1_F)
+  RSR_STEPS(RSR_TABLE(8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_STORE1, RSR_ZERO1),
+            RSR_WIDE8(RSR_READ1, RSR_ADD_F1, RSR_LANES_F1, RSR_STORE1, RSR_ZERO1))
+  RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103)
 };
 struct I1 {  // one int8 vector
   using In = int8_t;
   using Acc = int32_t;
-  using Run = int32_t;
+  using Sums = int32_t;
   static constexpr rsr::Pass pass = rsr::kI1;
-  static constexpr int V = pass.V, R = 1, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr uint32_t kStride = 132, kWide = 256 * kStride;
   using Slot = int32_t;
   __device__ static __forceinline__ int32_t get(int32_t x, int) { return x; }
-  RSR_STEPS1(int32_t, "v_add_u32", RSR_LANES1_I)
+  RSR_STEPS(RSR_TABLE(8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1),
+            RSR_WIDE8(RSR_READ1, RSR_ADD_I1, RSR_LANES_I1, RSR_STORE1, RSR_ZERO1))
+  RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103)
 };
 struct F2 {  // two float vectors
   using In = float;
   using Acc = float;
-  using Run = float;
+  typedef float Sums __attribute__((ext_vector_type(2)));
   static constexpr rsr::Pass pass = rsr::kF2;
-  static constexpr int V = pass.V, R = 2, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr uint32_t kStride = 164, kWide = 256 * kStride;
   typedef float Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
-  RSR_STEPS2(float, "v_add_f32", RSR_LANES2_F)
+  RSR_STEPS(RSR_TABLE(8, 164, 20, 20, 12, 8, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_STORE2, RSR_ZERO2),
+            RSR_WIDE8(RSR_READ2, RSR_ADD_F2, RSR_LANES_F2, RSR_STORE2, RSR_ZERO2))
+  RSR_STEP8(3, "v[112:113]", 96, 98, 100, 102, 104, 106, 108, 110)
 };
 struct P2 {  // two int8 vectors
   using In = int8_t;
   using Acc = int32_t;
-  using Run = uint32_t;
+  using Sums = uint32_t;
   static constexpr rsr::Pass pass = rsr::kP2;
-  static constexpr int V = pass.V, R = 1, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr uint32_t kStride = 164, kWide = 256 * kStride;
   typedef int16_t Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
-  RSR_STEPS1(uint32_t, "v_pk_add_u16", RSR_LANES1_P)
+  RSR_STEPS(RSR_TABLE(8, 164, 20, 16, 12, 4, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1),
+            RSR_WIDE8(RSR_READ1, RSR_ADD_P2, RSR_LANES_P2, RSR_STORE1, RSR_ZERO1))
+  RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103, "v114")
 };
 struct P4 {  // four int8 vectors
   using In = int8_t;
   using Acc = int32_t;
-  using Run = uint32_t;
+  typedef uint32_t Sums __attribute__((ext_vector_type(2)));
   static constexpr rsr::Pass pass = rsr::kP4;
-  static constexpr int V = pass.V, R = 2, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr uint32_t kStride = 228, kWide = 256 * kStride;
   typedef int16_t Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
-  RSR_STEPS2(uint32_t, "v_pk_add_u16", RSR_LANES2_P)
+  RSR_STEPS(RSR_TABLE(8, 228, 28, 20, 12, 8, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_STORE2, RSR_ZERO2),
+            RSR_WIDE8(RSR_READ2, RSR_ADD_P4, RSR_LANES_P4, RSR_STORE2, RSR_ZERO2))
+  RSR_STEP8(3, "v[112:113]", 96, 98, 100, 102, 104, 106, 108, 110, "v114", "v115")
 };
-struct F4 {  // four float vectors; four positions per step (16 registers of gathered sums)
+struct F4 {  // four float vectors; four positions per step (16 registers of gathered activations)
   using In = float;
   using Acc = float;
-  using Run = float;
+  typedef float Sums __attribute__((ext_vector_type(4)));
   static constexpr rsr::Pass pass = rsr::kF4;
-  static constexpr int V = pass.V, R = 4, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
+  static constexpr uint32_t kStride = 132, kWide = 16 * kStride;
   typedef float Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
-  __device__ static __forceinline__ void step4(uint32_t w0, uint32_t w1, float (&acc)[4], uint32_t hm, uint32_t wd, uint32_t ub) {
-    uint32_t s0, s1, s2, s3;
-    asm volatile(
-        RSR_EXTRACT2(4, 0, 1, 0) RSR_EXTRACT2(4, 2, 3, 1)
-        "ds_read_b128 v[96:99], %[s0]\n ds_read_b128 v[100:103], %[s1]\n ds_read_b128 v[104:107], %[s2]\n ds_read_b128 v[108:111], %[s3]\n"
-        RSR_ROW(0, 3, RSR_SUM4(96, 97, 98, 99)) RSR_ROW(1, 2, RSR_SUM4(100, 101, 102, 103))
-        RSR_ROW(2, 1, RSR_SUM4(104, 105, 106, 107)) RSR_ROW(3, 0, RSR_SUM4(108, 109, 110, 111))
-        "s_branch .Lrsr_end_%=\n"
-        RSR_HEAD(0, RSR_STORE4(0)) RSR_HEAD(1, RSR_STORE4(1)) RSR_HEAD(2, RSR_STORE4(2)) RSR_HEAD(3, RSR_STORE4(3) "s_waitcnt lgkmcnt(2)\n")
-        RSR_LANES(RSR_LANES4) ".Lrsr_end_%=:\n"
-        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [c] "+v"(acc[2]), [d] "+v"(acc[3]), [s0] "=&v"(s0), [s1] "=&v"(s1), [s2] "=&v"(s2), [s3] "=&v"(s3)
-        : [w0] "v"(w0), [w1] "v"(w1), RSR_CTL
-        : RSR_CLOBBER, RSR_T16);
+  RSR_STEPS(RSR_TABLE(4, 132, 28, 28, 16, 16, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_STORE4, RSR_ZERO4),
+            RSR_WIDE4(RSR_READ4, RSR_ADD_F4, RSR_LANES_F4, RSR_STORE4, RSR_ZERO4))
+  __device__ static __forceinline__ void step4(uint32_t w0, uint32_t w1, Sums& acc, uint32_t heads, const Steps& s) {
+    asm volatile(RSR_FIND RSR_EXTRACT2(4, 96, 100, 0) RSR_EXTRACT2(4, 104, 108, 1) RSR_CALL
+                 : "+{v[112:115]}"(acc)
+                 : [w0] "v"(w0), [w1] "v"(w1), RSR_CTL(heads & 0xfu)
+                 : RSR_CLOBBER);
   }
-  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, float (&acc)[4], uint32_t hm,
-                                               uint32_t wd, uint32_t ub) {
-    step4(w0, w1, acc, hm, wd, ub);
-    step4(w2, w3, acc, hm >> 4, wd, ub);
+  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, Sums& acc, uint32_t heads, const Steps& s) {
+    step4(w0, w1, acc, heads, s);
+    step4(w2, w3, acc, heads >> 4, s);
   }
-  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, float (&acc)[4], uint32_t hm, uint32_t wd, uint32_t ub) {
-    step4(w0, w1, acc, hm, wd, ub);
-    uint32_t s0, s1;
-    asm volatile(
-        RSR_EXTRACT2(4, 0, 1, 0) "ds_read_b128 v[96:99], %[s0]\n ds_read_b128 v[100:103], %[s1]\n"
-        RSR_ROW(0, 1, RSR_SUM4(96, 97, 98, 99)) RSR_ROW(1, 0, RSR_SUM4(100, 101, 102, 103)) "s_branch .Lrsr_end_%=\n"
-        RSR_HEAD(0, RSR_STORE4(0)) RSR_HEAD(1, RSR_STORE4(1) "s_waitcnt lgkmcnt(2)\n")
-        RSR_LANES(RSR_LANES4) ".Lrsr_end_%=:\n"
-        : [a] "+v"(acc[0]), [b] "+v"(acc[1]), [c] "+v"(acc[2]), [d] "+v"(acc[3]), [s0] "=&v"(s0), [s1] "=&v"(s1)
-        : [w0] "v"(w2), [hm] "s"(uniform(hm >> 4)), [wd] "s"(uniform(wd)), [ub] "s"(uniform(ub))
-        : RSR_CLOBBER, "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103");
+  __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t null_row, Sums& acc, uint32_t heads, const Steps& s) {
+    step4(w0, w1, acc, heads, s);
+    asm volatile(RSR_FIND RSR_EXTRACT2(4, 96, 100, 0) "v_mov_b32 v104, %[null]\n v_mov_b32 v108, %[null]\n" RSR_CALL
+                 : "+{v[112:115]}"(acc)
+                 : [w0] "v"(w2), [null] "s"(uniform(null_row)), RSR_CTL((heads >> 4) & 0x3u)
+                 : RSR_CLOBBER);
   }
 };
 // The scalar fields of a unit descriptor.  The unit number is wavefront-uniform, so the descriptor is
@@ -513,7 +507,8 @@ constexpr int kExtraAhead = 128;  // extra sums of a panel whose slots are fetch
 typedef uint32_t u32x4a __attribute__((ext_vector_type(4)));
 template <class M>
 struct SlotRead {
-  static constexpr int kPieces = M::slot_bytes / 4;  // of 16 bytes
+  using AT = typename M::Acc;
+  static constexpr int kPieces = M::slot_bytes / 4;                    // of 16 bytes
   u32x4a piece[kPieces];
   __device__ static __forceinline__ int turn(int lane) { return kPieces == 1 ? 0 : kPieces == 2 ? (lane >> 4) & 1 : (lane >> 3) & 3; }
   __device__ __forceinline__ void read(const unsigned char* quad, int turn) {  // quad: the lane's first slot
@@ -521,17 +516,30 @@ struct SlotRead {
     for (int c = 0; c < kPieces; ++c) piece[c] = *reinterpret_cast<const u32x4a*>(quad + ((c ^ turn) * 16));
   }
   __device__ static __forceinline__ void clear(unsigned char* quad) {
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));  // (a zero of this place: four registers of zeros would be kept from the start of the kernel)
 #pragma unroll
-    for (int c = 0; c < kPieces; ++c) *reinterpret_cast<u32x4a*>(quad + c * 16) = u32x4a{0, 0, 0, 0};
+    for (int c = 0; c < kPieces; ++c) *reinterpret_cast<u32x4a*>(quad + c * 16) = u32x4a{zero, zero, zero, zero};
   }
   // vector j's sum in slot i of the lane's four, in the order of the pieces: slot i ^ (turn << shift)
-  __device__ __forceinline__ typename M::Acc get(int i, int j) const {
+  __device__ __forceinline__ AT get(int i, int j) const {
     constexpr int per = 16 / M::slot_bytes, words = M::slot_bytes / 4;  // slots per piece, words per slot
     // (element by element: __builtin_bit_cast of a vector's element was compiled as one of its first element)
     struct { uint32_t w[words]; } x;
 #pragma unroll
     for (int k = 0; k < words; ++k) x.w[k] = piece[i / per][(i % per) * words + k];
     return M::get(__builtin_bit_cast(typename M::Slot, x), j);
+  }
+  // Differences in place, where a sum fills its word.
+  __device__ __forceinline__ void subtract(const SlotRead& m) {
+    static_assert(sizeof(typename M::Slot) == 4 * M::V);
+#pragma unroll
+    for (int c = 0; c < kPieces; ++c)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t a = piece[c][k], b = m.piece[c][k];
+        piece[c][k] = __builtin_bit_cast(uint32_t, (AT)(__builtin_bit_cast(AT, a) - __builtin_bit_cast(AT, b)));
+      }
   }
 };
 // What the fold needs of four neighbouring sums: those with value bit 0, those with bit 1, all.
@@ -782,6 +790,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     for (int j = 0; j < 3; ++j) issue_pair(rs, lane4 + (D.npos >> 3) * 1024u, j, tA);
   }
 
+  const uint64_t code = M::table();
   const uint32_t panel_begin = (uint32_t)blk_begin * (uint32_t)p.panels;
   uint32_t open_panel = ~0u;  // the panel (counted from panel_begin) that is known to have room
 
@@ -817,51 +826,69 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     using Read = SlotRead<M>;
     const int turn = Read::turn(lane);
     // G steps together, P of them read at a time: reads that are in flight together share the wait (behind the gathers of
-    // fifteen other wavefronts the LDS answers after several hundred clocks).
+    // fifteen other wavefronts the LDS answers after several hundred clocks).  The slots of the second part are read kPart
+    // steps at a time (registers).
     auto fold_steps = [&]<int G>(int i0) {
-      constexpr int P = V < 4 ? G : M::slot_bytes == 16 ? 1 : G < 2 ? G : 2;
+      constexpr int P = M::slot_bytes == 16 ? 1 : V < 4 ? G : G < 2 ? G : 2;
+      constexpr int kPart = M::slot_bytes == 4 ? (P < 4 ? P : 4) : 1;
       AT x[G][V];
+      unsigned char* const rows = first_quad + i0 * kRowBytes;
 #pragma unroll
       for (int r0 = 0; r0 < G; r0 += P) {
-        unsigned char* const row = first_quad + (i0 + r0) * kRowBytes;
         Read q[P];
-#pragma unroll
-        for (int r = 0; r < P; ++r) q[r].read(row + r * kRowBytes, turn);
-        auto sums = [&](int r, int j, const AT (&d)[4]) {
+        auto add = [&](int r, int j, const AT (&d)[4]) {
           const Quad<AT> s = quad_of<M>(d, turn);
           hi[j][0] += s.odd;
           hi[j][1] += s.high;
           x[r0 + r][j] = s.all;
           if constexpr (PLAIN) plain_sums(pl[j], i0 + r0 + r, lane, s);
         };
-        if (both) {  // Proposition 2.1, v.B(1) - v.B(2): the fold is linear in u
-          unsigned char* const row1 = row + (uint32_t)pslots * M::slot_bytes;
-          Read m[P];
-#pragma unroll
-          for (int r = 0; r < P; ++r) m[r].read(row1 + r * kRowBytes, turn);
-          if (!fill)
-#pragma unroll
-            for (int r = 0; r < P; ++r) Read::clear(row1 + r * kRowBytes);
+        auto add_all = [&](const Read* m) {
 #pragma unroll
           for (int r = 0; r < P; ++r)
 #pragma unroll
             for (int j = 0; j < V; ++j) {
-              const AT d[4] = {q[r].get(0, j) - m[r].get(0, j), q[r].get(1, j) - m[r].get(1, j), q[r].get(2, j) - m[r].get(2, j), q[r].get(3, j) - m[r].get(3, j)};
-              sums(r, j, d);
-            }
-        } else {
+              AT d[4];
 #pragma unroll
-          for (int r = 0; r < P; ++r)
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-              const AT d[4] = {q[r].get(0, j), q[r].get(1, j), q[r].get(2, j), q[r].get(3, j)};
-              sums(r, j, d);
+              for (int c = 0; c < 4; ++c) d[c] = m ? q[r].get(c, j) - m[r].get(c, j) : q[r].get(c, j);
+              add(r, j, d);
             }
+        };
+#pragma unroll
+        for (int r = 0; r < P; ++r) q[r].read(rows + (r0 + r) * kRowBytes, turn);
+        // Proposition 2.1, v.B(1) - v.B(2): the fold is linear in u
+        unsigned char* const rows1 = rows + (uint32_t)pslots * M::slot_bytes;
+        if constexpr (sizeof(Slot) < 4 * V) {  // 16-bit sums, whose differences take 17
+          if (both) {
+            Read m[P];
+#pragma unroll
+            for (int r = 0; r < P; ++r) m[r].read(rows1 + (r0 + r) * kRowBytes, turn);
+            if (!fill)
+#pragma unroll
+              for (int r = 0; r < P; ++r) Read::clear(rows1 + (r0 + r) * kRowBytes);
+            add_all(m);
+          } else {
+            add_all(nullptr);
+          }
+        } else if (both) {
+#pragma unroll
+          for (int r1 = 0; r1 < P; r1 += kPart) {
+            Read m[kPart];
+#pragma unroll
+            for (int r = 0; r < kPart; ++r) m[r].read(rows1 + (r0 + r1 + r) * kRowBytes, turn);
+            if (!fill)
+#pragma unroll
+              for (int r = 0; r < kPart; ++r) Read::clear(rows1 + (r0 + r1 + r) * kRowBytes);
+#pragma unroll
+            for (int r = 0; r < kPart; ++r) q[r1 + r].subtract(m[r]);
+            if constexpr (kPart < P) asm volatile("" ::: "memory");  // (the next reads stay behind)
+          }
         }
         if (!fill)
 #pragma unroll
-          for (int r = 0; r < P; ++r) Read::clear(row + r * kRowBytes);
-        if constexpr (P < G) asm volatile("" ::: "memory");  // (the next steps' reads stay behind: registers)
+          for (int r = 0; r < P; ++r) Read::clear(rows + (r0 + r) * kRowBytes);
+        if constexpr (sizeof(Slot) == 4 * V) add_all(nullptr);
+        if constexpr (P < G) asm volatile("" ::: "memory");
       }
       // (two steps at a time, in this order, for every G: the sums do not depend on how many vectors share a pass)
 #pragma unroll
@@ -881,7 +908,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
         }
       }
     };
-    constexpr int kTogether = PLAIN || M::slot_bytes == 16 ? 2 : V > 1 ? 4 : 8;
+    constexpr int kTogether = PLAIN || M::slot_bytes > 4 ? 2 : V > 1 ? 4 : 8;
     if (frows % kTogether == 0)
 #pragma unroll 1
       for (int i = 0; i < frows; i += kTogether) fold_steps.template operator()<kTogether>(i);
@@ -1019,13 +1046,12 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(extra_list), 0, (int)((min(D.extras, (uint32_t)kExtraAhead) + 1u) / 2u * 4u), 0x00020000);
     const uint32_t extra_pair = __builtin_amdgcn_raw_buffer_load_b32(rsx, (int)lane4, 0, 0);
     // ---- step 1: segmented sums (Eq. SS2) into the panel's slots (u of Algorithm 2) ----
-    typename M::Run acc[M::R];
-#pragma unroll
-    for (int j = 0; j < M::R; ++j) acc[j] = 0;
+    typename M::Sums acc = {};
+    const Steps steps{code + (D.wide ? M::kWide : 0u), D.wide ? 4u : M::kStride, ubase};
     const uint32_t full = D.npos >> 3;
     auto step = [&](int gq) {
       const uint32_t hm = gq < 4 ? D.heads_lo >> (8 * gq) : D.heads_hi >> (8 * (gq - 4));
-      if ((uint32_t)gq < full) M::step8(e[gq][0], e[gq][1], e[gq][2], e[gq][3], acc, hm, D.wide, ubase);
+      if ((uint32_t)gq < full) M::step8(e[gq][0], e[gq][1], e[gq][2], e[gq][3], acc, hm, steps);
     };
 #pragma unroll
     for (int gq = 0; gq < NG / 2; ++gq) step(gq);
@@ -1045,7 +1071,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       // the positions behind the last full granule, always six: a row that the unit does not have is read as row 0
       // and added to sums that no head stores
       const uint32_t hm = (full < 4 ? D.heads_lo >> (8 * full) : D.heads_hi >> (8 * (full - 4)));
-      if (D.npos & 7) M::step6(et[0], et[1], et[2], acc, hm, D.wide, ubase);
+      if (D.npos & 7) M::step6(et[0], et[1], et[2], (uint32_t)p.rows << M::shift, acc, hm, steps);
 #pragma unroll
       for (int j = 0; j < 3; ++j) issue_pair(rs1, pair_base1, j, etn);
     }
