@@ -227,45 +227,43 @@ __device__ __forceinline__ void lds_count_up(uint32_t addr_a, uint32_t addr_b, u
 // position allows as many LDS operations as follow it (they complete in order; scalar loads that are under way besides only make
 // the wait stricter).  Every gather has been waited for when its step returns.
 // Fixed registers: a position's address, then its gathered activations: v96 + (position of the step) * (16-byte row: 4, 8-byte
-// row: 2, else 1); the running sums from v112 on; s90 pattern, s91 panel base, s92-s95 addresses.
+// row: 2, else 1); the running sums from v112 on; s90 pattern, s91 panel base, s86-s89 and s92-s95 addresses.
 // What an activation mode M defines: vectors V per pass, LDS bytes per row (1 << shift) and per slot, and its sums.
 #define RSR_EXTRACT(sh, v, w, half) "v_lshlrev_b32_sdwa v" #v ", " #sh ", %[w" #w "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:" half "\n"
 #define RSR_EXTRACT2(sh, v0, v1, w) RSR_EXTRACT(sh, v0, w, "WORD_0") RSR_EXTRACT(sh, v1, w, "WORD_1")
-// The code of every pattern: rsr_p the pattern, rsr_q the position, rsr_n LDS operations that may be under way, rsr_z 1 where the
-// running sums have been stored and not restarted yet, rsr_b bytes of code so far.  A pattern takes `stride` bytes.  `row`, `first`
-// and `head` are the bytes of a position: a row, the first row of a group, a head; `zeros` those of ZERO.
-#define RSR_TABLE(positions, stride, row, first, head, zeros, READ, ADD, FIRST, STORE, ZERO)                   \
-  ".set rsr_p, 0\n.rept 1 << " #positions "\n.set rsr_q, 0\n.set rsr_n, 0\n.set rsr_z, 0\n.set rsr_b, 4\n"     \
+// The code of every pattern of `positions` positions, `stride` bytes each: rsr_p the pattern, rsr_q the position, rsr_n LDS operations
+// that may be under way, rsr_z 1 where the running sums have been stored and not restarted yet, rsr_b bytes of code so far.
+// `row`, `first` and `head` are the bytes of a position: a row, the first row of a group, a head; `zeros` those of ZERO.  rsr_v is
+// the register of position 0; `back` holds the return address.
+#define RSR_TABLE(v0, positions, stride, row, first, head, zeros, READ, ADD, FIRST, STORE, ZERO, back)         \
+  ".set rsr_v, " #v0 "\n.set rsr_p, 0\n.rept 1 << " #positions "\n.set rsr_q, 0\n.set rsr_n, 0\n.set rsr_z, 0\n.set rsr_b, 4\n" \
   ".rept " #positions "\n.if ((rsr_p >> rsr_q) & 1) == 0\n" READ ".set rsr_n, rsr_n+1\n.endif\n.set rsr_q, rsr_q+1\n.endr\n" \
   ".set rsr_q, 0\n.rept " #positions "\n.if (rsr_p >> rsr_q) & 1\n.if rsr_z\n" ZERO ".set rsr_b, rsr_b+" #zeros "\n.endif\n" STORE \
   ".set rsr_n, rsr_n+1\n.set rsr_z, 1\n.set rsr_b, rsr_b+" #head "\n"                                          \
   ".else\n.set rsr_n, rsr_n-1\n s_waitcnt lgkmcnt(rsr_n)\n"                                                    \
   ".if rsr_z\n" FIRST ".set rsr_b, rsr_b+" #first "\n.else\n" ADD ".set rsr_b, rsr_b+" #row "\n.endif\n.set rsr_z, 0\n" \
   ".endif\n.set rsr_q, rsr_q+1\n.endr\n"                                                                       \
-  ".if rsr_z\n" ZERO ".set rsr_b, rsr_b+" #zeros "\n.endif\n s_setpc_b64 s[94:95]\n"                           \
+  ".if rsr_z\n" ZERO ".set rsr_b, rsr_b+" #zeros "\n.endif\n s_setpc_b64 " back "\n"                          \
   ".if rsr_b > " #stride "\n.error \"a pattern does not fit\"\n.endif\n"                                       \
   ".rept (" #stride "-rsr_b)/4\n s_nop 0\n.endr\n.set rsr_p, rsr_p+1\n.endr\n"
-// Behind the table, for units whose segments take 8 lanes: branches, 4 bytes per pattern, to the code of a step without heads or, with
-// one (a step in four or five: 32 rows a lane), to the code of any pattern, by a test and a branch per position; at a head the lanes' sums are first added with lane exchanges (the s_nop cover the wait states an exchange needs after a vector write).
-#define RSR_WIDE_READ(q, READ) ".set rsr_q, " #q "\n s_bitcmp1_b32 s90, " #q "\n s_cbranch_scc1 .Lrsr_r" #q "_%=\n" READ ".Lrsr_r" #q "_%=:\n"
-#define RSR_WIDE_SUM(q, ADD, LANES, STORE, ZERO)                                                               \
-  ".set rsr_q, " #q "\n s_bitcmp1_b32 s90, " #q "\n s_cbranch_scc1 .Lrsr_h" #q "_%=\n" ADD " s_branch .Lrsr_n" #q "_%=\n" \
-  ".Lrsr_h" #q "_%=:\n s_nop 1\n" LANES("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")                      \
-  " s_nop 1\n" LANES("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")                                         \
-  " s_nop 1\n" LANES("row_half_mirror row_mask:0xf bank_mask:0xf") STORE ZERO ".Lrsr_n" #q "_%=:\n"
-#define RSR_WIDE_PADS(positions) " s_branch .Lrsr_table_%=\n.rept (1 << " #positions ")-1\n s_branch .Lrsr_any_%=\n.endr\n.Lrsr_any_%=:\n"
-#define RSR_WIDE4(READ, ADD, LANES, STORE, ZERO)                                                               \
-  RSR_WIDE_PADS(4)                                                                                             \
-  RSR_WIDE_READ(0, READ) RSR_WIDE_READ(1, READ) RSR_WIDE_READ(2, READ) RSR_WIDE_READ(3, READ) " s_waitcnt lgkmcnt(0)\n" \
-  RSR_WIDE_SUM(0, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(1, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(2, ADD, LANES, STORE, ZERO) \
-  RSR_WIDE_SUM(3, ADD, LANES, STORE, ZERO) " s_setpc_b64 s[94:95]\n"
-#define RSR_WIDE8(READ, ADD, LANES, STORE, ZERO)                                                               \
-  RSR_WIDE_PADS(8)                                                                                             \
-  RSR_WIDE_READ(0, READ) RSR_WIDE_READ(1, READ) RSR_WIDE_READ(2, READ) RSR_WIDE_READ(3, READ) RSR_WIDE_READ(4, READ) \
-  RSR_WIDE_READ(5, READ) RSR_WIDE_READ(6, READ) RSR_WIDE_READ(7, READ) " s_waitcnt lgkmcnt(0)\n"               \
-  RSR_WIDE_SUM(0, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(1, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(2, ADD, LANES, STORE, ZERO) \
-  RSR_WIDE_SUM(3, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(4, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(5, ADD, LANES, STORE, ZERO) \
-  RSR_WIDE_SUM(6, ADD, LANES, STORE, ZERO) RSR_WIDE_SUM(7, ADD, LANES, STORE, ZERO) " s_setpc_b64 s[94:95]\n"
+// Behind the table, for units whose segments take 8 lanes: the lanes' sums are first added at a head with lane exchanges (the s_nop
+// cover the wait states an exchange needs after a vector write), which is more code: tables of four positions, for either half of a step.
+// Branches, 4 bytes per pattern, lead to the step without heads or to the calls of the two halves.  (With a test and
+// a branch per position in their place the units of long segments, which a panel begins with, took half as long again as the others and
+// the launch waited for them: transformer block 29.5 us, 27.1 with the tables; sixteen vectors 85.8 and 80.9; ternary 4096^2 5.92 and
+// 5.35.)
+#define RSR_WIDE_LANES(LANES)                                                                                  \
+  " s_nop 1\n" LANES("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf") " s_nop 1\n" LANES("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf") \
+  " s_nop 1\n" LANES("row_half_mirror row_mask:0xf bank_mask:0xf")
+#define RSR_WIDE(v_low, v_high, stride, row, first, head, zeros, READ, ADD, FIRST, LANES, STORE, ZERO)         \
+  " s_branch .Lrsr_table_%=\n.rept 255\n s_branch .Lrsr_halves_%=\n.endr\n"                                    \
+  ".Lrsr_halves_%=:\n s_getpc_b64 s[88:89]\n.Lrsr_at_%=:\n"                                                    \
+  " s_and_b32 s92, s90, 15\n s_mul_i32 s92, s92, " #stride "\n s_add_u32 s92, s92, .Lrsr_low_%=-.Lrsr_at_%=\n" \
+  " s_add_u32 s92, s88, s92\n s_addc_u32 s93, s89, 0\n s_swappc_b64 s[86:87], s[92:93]\n"                      \
+  " s_lshr_b32 s92, s90, 4\n s_mul_i32 s92, s92, " #stride "\n s_add_u32 s92, s92, .Lrsr_high_%=-.Lrsr_at_%=\n" \
+  " s_add_u32 s92, s88, s92\n s_addc_u32 s93, s89, 0\n s_setpc_b64 s[92:93]\n"                                 \
+  ".Lrsr_low_%=:\n" RSR_TABLE(v_low, 4, stride, row, first, head, zeros, READ, ADD, FIRST, RSR_WIDE_LANES(LANES) STORE, ZERO, "s[86:87]") \
+  ".Lrsr_high_%=:\n" RSR_TABLE(v_high, 4, stride, row, first, head, zeros, READ, ADD, FIRST, RSR_WIDE_LANES(LANES) STORE, ZERO, "s[94:95]")
 // How a unit's steps find their code: pattern 0 at `code`, every further one `stride` bytes on.
 struct Steps {
   uint64_t code;
@@ -285,7 +283,7 @@ struct Steps {
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }  // (into a scalar register)
 #define RSR_CTL(pattern) "{s90}"(uniform(pattern)), "{s91}"(uniform(s.base)), [stride] "s"(uniform(s.stride)), [lo] "s"(uniform((uint32_t)s.code)), [hi] "s"(uniform((uint32_t)(s.code >> 32)))
 #define RSR_CLOBBER                                                                                            \
-  "s92", "s93", "s94", "s95", "scc", "memory", "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", \
+  "s86", "s87", "s88", "s89", "s92", "s93", "s94", "s95", "scc", "memory", "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", \
       "v108", "v109", "v110", "v111"
 // A step of eight positions from four dwords; the last one of a unit, of up to six positions, from three dwords and the null row.
 #define RSR_STEP8(shift, sums, v0, v1, v2, v3, v4, v5, v6, v7, ...)                                    \
@@ -305,53 +303,53 @@ __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__bui
   }
 
 // One 32-bit word per row and slot.
-#define RSR_READ1 " ds_read_b32 v[96+rsr_q], v[96+rsr_q]\n"
-#define RSR_STORE1 " v_add_u32 v[96+rsr_q], s91, v[96+rsr_q]\n ds_write_b32 v[96+rsr_q], v112\n"
+#define RSR_READ1 " ds_read_b32 v[rsr_v+rsr_q], v[rsr_v+rsr_q]\n"
+#define RSR_STORE1 " v_add_u32 v[rsr_v+rsr_q], s91, v[rsr_v+rsr_q]\n ds_write_b32 v[rsr_v+rsr_q], v112\n"
 #define RSR_ZERO1 " v_mov_b32 v112, 0\n"
-#define RSR_ADD_F1 " v_add_f32 v112, v112, v[96+rsr_q]\n"
-#define RSR_FIRST_F1 " v_add_f32 v112, 0, v[96+rsr_q]\n"
+#define RSR_ADD_F1 " v_add_f32 v112, v112, v[rsr_v+rsr_q]\n"
+#define RSR_FIRST_F1 " v_add_f32 v112, 0, v[rsr_v+rsr_q]\n"
 #define RSR_LANES_F1(x) " v_add_f32_dpp v112, v112, v112 " x "\n"
-#define RSR_ADD_I1 " v_add_u32 v112, v112, v[96+rsr_q]\n"
-#define RSR_FIRST_I1 " v_mov_b32 v112, v[96+rsr_q]\n"
+#define RSR_ADD_I1 " v_add_u32 v112, v112, v[rsr_v+rsr_q]\n"
+#define RSR_FIRST_I1 " v_mov_b32 v112, v[rsr_v+rsr_q]\n"
 #define RSR_LANES_I1(x) " v_add_u32_dpp v112, v112, v112 " x "\n"
-#define RSR_ADD_P2 " v_pk_add_u16 v112, v112, v[96+rsr_q]\n"
+#define RSR_ADD_P2 " v_pk_add_u16 v112, v112, v[rsr_v+rsr_q]\n"
 #define RSR_LANES_P2(x) " v_mov_b32_dpp v114, v112 " x "\n v_pk_add_u16 v112, v112, v114\n"
 // Two words: two floats, or four 16-bit sums.
-#define RSR_READ2 " ds_read_b64 v[96+2*rsr_q:97+2*rsr_q], v[96+2*rsr_q]\n"
-#define RSR_STORE2 " v_add_u32 v[96+2*rsr_q], s91, v[96+2*rsr_q]\n ds_write_b64 v[96+2*rsr_q], v[112:113]\n"
+#define RSR_READ2 " ds_read_b64 v[rsr_v+2*rsr_q:rsr_v+2*rsr_q+1], v[rsr_v+2*rsr_q]\n"
+#define RSR_STORE2 " v_add_u32 v[rsr_v+2*rsr_q], s91, v[rsr_v+2*rsr_q]\n ds_write_b64 v[rsr_v+2*rsr_q], v[112:113]\n"
 #define RSR_ZERO2 " v_mov_b32 v112, 0\n v_mov_b32 v113, 0\n"
-#define RSR_ADD_F2 " v_add_f32 v112, v112, v[96+2*rsr_q]\n v_add_f32 v113, v113, v[97+2*rsr_q]\n"
-#define RSR_FIRST_F2 " v_add_f32 v112, 0, v[96+2*rsr_q]\n v_add_f32 v113, 0, v[97+2*rsr_q]\n"
+#define RSR_ADD_F2 " v_add_f32 v112, v112, v[rsr_v+2*rsr_q]\n v_add_f32 v113, v113, v[rsr_v+2*rsr_q+1]\n"
+#define RSR_FIRST_F2 " v_add_f32 v112, 0, v[rsr_v+2*rsr_q]\n v_add_f32 v113, 0, v[rsr_v+2*rsr_q+1]\n"
 #define RSR_LANES_F2(x) " v_add_f32_dpp v112, v112, v112 " x "\n v_add_f32_dpp v113, v113, v113 " x "\n"
-#define RSR_ADD_P4 " v_pk_add_u16 v112, v112, v[96+2*rsr_q]\n v_pk_add_u16 v113, v113, v[97+2*rsr_q]\n"
-#define RSR_FIRST_P4 " v_mov_b32 v112, v[96+2*rsr_q]\n v_mov_b32 v113, v[97+2*rsr_q]\n"
+#define RSR_ADD_P4 " v_pk_add_u16 v112, v112, v[rsr_v+2*rsr_q]\n v_pk_add_u16 v113, v113, v[rsr_v+2*rsr_q+1]\n"
+#define RSR_FIRST_P4 " v_mov_b32 v112, v[rsr_v+2*rsr_q]\n v_mov_b32 v113, v[rsr_v+2*rsr_q+1]\n"
 #define RSR_LANES_P4(x) " v_mov_b32_dpp v114, v112 " x "\n v_mov_b32_dpp v115, v113 " x "\n v_pk_add_u16 v112, v112, v114\n v_pk_add_u16 v113, v113, v115\n"
 // Four floats.  (One ds_write_b128: 14 LDS clocks; two ds_write2_b32 would take 25.)
-#define RSR_READ4 " ds_read_b128 v[96+4*rsr_q:99+4*rsr_q], v[96+4*rsr_q]\n"
-#define RSR_STORE4 " v_add_u32 v[96+4*rsr_q], s91, v[96+4*rsr_q]\n ds_write_b128 v[96+4*rsr_q], v[112:115]\n s_nop 0\n"
+#define RSR_READ4 " ds_read_b128 v[rsr_v+4*rsr_q:rsr_v+4*rsr_q+3], v[rsr_v+4*rsr_q]\n"
+#define RSR_STORE4 " v_add_u32 v[rsr_v+4*rsr_q], s91, v[rsr_v+4*rsr_q]\n ds_write_b128 v[rsr_v+4*rsr_q], v[112:115]\n s_nop 0\n"
 #define RSR_ZERO4 " v_mov_b32 v112, 0\n v_mov_b32 v113, 0\n v_mov_b32 v114, 0\n v_mov_b32 v115, 0\n"
 #define RSR_ADD_F4                                                                                             \
-  " v_add_f32 v112, v112, v[96+4*rsr_q]\n v_add_f32 v113, v113, v[97+4*rsr_q]\n v_add_f32 v114, v114, v[98+4*rsr_q]\n v_add_f32 v115, v115, v[99+4*rsr_q]\n"
+  " v_add_f32 v112, v112, v[rsr_v+4*rsr_q]\n v_add_f32 v113, v113, v[rsr_v+4*rsr_q+1]\n v_add_f32 v114, v114, v[rsr_v+4*rsr_q+2]\n v_add_f32 v115, v115, v[rsr_v+4*rsr_q+3]\n"
 #define RSR_FIRST_F4                                                                                           \
-  " v_add_f32 v112, 0, v[96+4*rsr_q]\n v_add_f32 v113, 0, v[97+4*rsr_q]\n v_add_f32 v114, 0, v[98+4*rsr_q]\n v_add_f32 v115, 0, v[99+4*rsr_q]\n"
+  " v_add_f32 v112, 0, v[rsr_v+4*rsr_q]\n v_add_f32 v113, 0, v[rsr_v+4*rsr_q+1]\n v_add_f32 v114, 0, v[rsr_v+4*rsr_q+2]\n v_add_f32 v115, 0, v[rsr_v+4*rsr_q+3]\n"
 #define RSR_LANES_F4(x)                                                                                        \
   " v_add_f32_dpp v112, v112, v112 " x "\n v_add_f32_dpp v113, v113, v113 " x "\n v_add_f32_dpp v114, v114, v114 " x "\n v_add_f32_dpp v115, v115, v115 " x "\n"
 // int8 activations of several vectors are widened to 16 bits when they are staged, two vectors to a dword, and
 // summed two at a time (v_pk_add_u16).  Nothing is lost: no lane and no slot sums more than kWideRows = 256 rows (the builder cuts
 // longer segments), so a sum lies in -128 * 256 .. 127 * 256, which 16 bits hold (rsr_layout.h asserts it); from the
 // slots on, and between pieces, panels and parts, sums are 32 bits wide.
-// (kStride: bytes of the longest pattern; kWide: where the branches of wide units are.)
+// (kStride: bytes of the longest pattern; kWide: where the branches of wide units are, kWideStride bytes each.)
 struct F1 {  // one float vector
   using In = float;
   using Acc = float;
   using Sums = float;  // the running sums
   static constexpr rsr::Pass pass = rsr::kF1;
   static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
-  static constexpr uint32_t kStride = 132, kWide = 256 * kStride;
+  static constexpr uint32_t kStride = 132, kWide = 256 * kStride, kWideStride = 4;
   using Slot = float;  // the sums of a slot
   __device__ static __forceinline__ float get(float x, int) { return x; }
-  RSR_STEPS(RSR_TABLE(8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_STORE1, RSR_ZERO1),
-            RSR_WIDE8(RSR_READ1, RSR_ADD_F1, RSR_LANES_F1, RSR_STORE1, RSR_ZERO1))
+  RSR_STEPS(RSR_TABLE(96, 8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
+            RSR_WIDE(96, 100, 212, 16, 16, 48, 4, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_LANES_F1, RSR_STORE1, RSR_ZERO1))
   RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103)
 };
 struct I1 {  // one int8 vector
@@ -360,11 +358,11 @@ struct I1 {  // one int8 vector
   using Sums = int32_t;
   static constexpr rsr::Pass pass = rsr::kI1;
   static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
-  static constexpr uint32_t kStride = 132, kWide = 256 * kStride;
+  static constexpr uint32_t kStride = 132, kWide = 256 * kStride, kWideStride = 4;
   using Slot = int32_t;
   __device__ static __forceinline__ int32_t get(int32_t x, int) { return x; }
-  RSR_STEPS(RSR_TABLE(8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1),
-            RSR_WIDE8(RSR_READ1, RSR_ADD_I1, RSR_LANES_I1, RSR_STORE1, RSR_ZERO1))
+  RSR_STEPS(RSR_TABLE(96, 8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
+            RSR_WIDE(96, 100, 212, 16, 16, 48, 4, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_LANES_I1, RSR_STORE1, RSR_ZERO1))
   RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103)
 };
 struct F2 {  // two float vectors
@@ -373,11 +371,11 @@ struct F2 {  // two float vectors
   typedef float Sums __attribute__((ext_vector_type(2)));
   static constexpr rsr::Pass pass = rsr::kF2;
   static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
-  static constexpr uint32_t kStride = 164, kWide = 256 * kStride;
+  static constexpr uint32_t kStride = 164, kWide = 256 * kStride, kWideStride = 4;
   typedef float Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(8, 164, 20, 20, 12, 8, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_STORE2, RSR_ZERO2),
-            RSR_WIDE8(RSR_READ2, RSR_ADD_F2, RSR_LANES_F2, RSR_STORE2, RSR_ZERO2))
+  RSR_STEPS(RSR_TABLE(96, 8, 164, 20, 20, 12, 8, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_STORE2, RSR_ZERO2, "s[94:95]"),
+            RSR_WIDE(96, 104, 324, 20, 20, 72, 8, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_LANES_F2, RSR_STORE2, RSR_ZERO2))
   RSR_STEP8(3, "v[112:113]", 96, 98, 100, 102, 104, 106, 108, 110)
 };
 struct P2 {  // two int8 vectors
@@ -386,11 +384,11 @@ struct P2 {  // two int8 vectors
   using Sums = uint32_t;
   static constexpr rsr::Pass pass = rsr::kP2;
   static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
-  static constexpr uint32_t kStride = 164, kWide = 256 * kStride;
+  static constexpr uint32_t kStride = 164, kWide = 256 * kStride, kWideStride = 4;
   typedef int16_t Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(8, 164, 20, 16, 12, 4, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1),
-            RSR_WIDE8(RSR_READ1, RSR_ADD_P2, RSR_LANES_P2, RSR_STORE1, RSR_ZERO1))
+  RSR_STEPS(RSR_TABLE(96, 8, 164, 20, 16, 12, 4, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
+            RSR_WIDE(96, 100, 308, 20, 16, 72, 4, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_LANES_P2, RSR_STORE1, RSR_ZERO1))
   RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103, "v114")
 };
 struct P4 {  // four int8 vectors
@@ -399,11 +397,11 @@ struct P4 {  // four int8 vectors
   typedef uint32_t Sums __attribute__((ext_vector_type(2)));
   static constexpr rsr::Pass pass = rsr::kP4;
   static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
-  static constexpr uint32_t kStride = 228, kWide = 256 * kStride;
+  static constexpr uint32_t kStride = 228, kWide = 256 * kStride, kWideStride = 4;
   typedef int16_t Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(8, 228, 28, 20, 12, 8, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_STORE2, RSR_ZERO2),
-            RSR_WIDE8(RSR_READ2, RSR_ADD_P4, RSR_LANES_P4, RSR_STORE2, RSR_ZERO2))
+  RSR_STEPS(RSR_TABLE(96, 8, 228, 28, 20, 12, 8, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_STORE2, RSR_ZERO2, "s[94:95]"),
+            RSR_WIDE(96, 104, 516, 28, 20, 120, 8, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_LANES_P4, RSR_STORE2, RSR_ZERO2))
   RSR_STEP8(3, "v[112:113]", 96, 98, 100, 102, 104, 106, 108, 110, "v114", "v115")
 };
 struct F4 {  // four float vectors; four positions per step (16 registers of gathered activations)
@@ -412,11 +410,11 @@ struct F4 {  // four float vectors; four positions per step (16 registers of gat
   typedef float Sums __attribute__((ext_vector_type(4)));
   static constexpr rsr::Pass pass = rsr::kF4;
   static constexpr int V = pass.V, shift = pass.shift, slot_bytes = pass.slot_bytes;
-  static constexpr uint32_t kStride = 132, kWide = 16 * kStride;
+  static constexpr uint32_t kStride = 132, kWide = 16 * kStride, kWideStride = 564;
   typedef float Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(4, 132, 28, 28, 16, 16, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_STORE4, RSR_ZERO4),
-            RSR_WIDE4(RSR_READ4, RSR_ADD_F4, RSR_LANES_F4, RSR_STORE4, RSR_ZERO4))
+  RSR_STEPS(RSR_TABLE(96, 4, 132, 28, 28, 16, 16, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_STORE4, RSR_ZERO4, "s[94:95]"),
+            RSR_TABLE(96, 4, 564, 28, 28, 124, 16, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_WIDE_LANES(RSR_LANES_F4) RSR_STORE4, RSR_ZERO4, "s[94:95]"))
   __device__ static __forceinline__ void step4(uint32_t w0, uint32_t w1, Sums& acc, uint32_t heads, const Steps& s) {
     asm volatile(RSR_FIND RSR_EXTRACT2(4, 96, 100, 0) RSR_EXTRACT2(4, 104, 108, 1) RSR_CALL
                  : "+{v[112:115]}"(acc)
@@ -1047,7 +1045,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     const uint32_t extra_pair = __builtin_amdgcn_raw_buffer_load_b32(rsx, (int)lane4, 0, 0);
     // ---- step 1: segmented sums (Eq. SS2) into the panel's slots (u of Algorithm 2) ----
     typename M::Sums acc = {};
-    const Steps steps{code + (D.wide ? M::kWide : 0u), D.wide ? 4u : M::kStride, ubase};
+    const Steps steps{code + (D.wide ? M::kWide : 0u), D.wide ? M::kWideStride : M::kStride, ubase};
     const uint32_t full = D.npos >> 3;
     auto step = [&](int gq) {
       const uint32_t hm = gq < 4 ? D.heads_lo >> (8 * gq) : D.heads_hi >> (8 * (gq - 4));
