@@ -493,6 +493,7 @@ __device__ __forceinline__ AT sums_of_sixteen(const AT (&v)[16], int lane) {
 }
 
 constexpr int NG = rsr::kMaxGranules;
+constexpr int kLongStaging = 48 * 1024;  // bytes of activations (rsr_body)
 constexpr int kTotal = 12;      // where a record (kItems words) holds its panel's total
 constexpr int kExtraAhead = 128;  // extra sums of a panel whose slots are fetched ahead of the fold
 
@@ -579,8 +580,8 @@ __device__ __forceinline__ void plain_sums(AT (&sums)[12], int step, int lane, c
 // The activations of a workgroup's V vectors go to LDS, row by row, the vectors of a row next to each other (int8:
 // widened to 32 bits, or to 16 where there are several).  Vectors past the batch are zeros.
 template <class M>
-__device__ __forceinline__ void stage(unsigned char* lds, const typename M::In* __restrict__ v, int64_t vstride, int nv, int rows, int first) {
-  const int tid = threadIdx.x, nt = blockDim.x;
+__device__ __forceinline__ void stage(unsigned char* lds, const typename M::In* __restrict__ v, int64_t vstride, int nv, int rows, int first, int nt) {
+  const int tid = threadIdx.x;
   if constexpr (M::V == 1 && sizeof(typename M::In) == 1) {
     const int n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? rows / 16 : 0;
     const uint4* v16 = reinterpret_cast<const uint4*>(v);
@@ -739,7 +740,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? p.rows / 4 : 0;
 #pragma unroll
     for (int j = 0; j < kEarly; ++j) {
-      const int i = tid + j * (int)blockDim.x;
+      const int i = tid + j * p.threads;
       sv[j] = make_uint4(0, 0, 0, 0);
       if (i < n16) sv[j] = reinterpret_cast<const uint4*>(v)[i];
     }
@@ -752,14 +753,14 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   Desc D = load_desc(unit_words, u_first < (uint32_t)p.nunits ? u_first : 0u);
   uint32_t ix = worker ? (uint32_t)wave : n_tot, ix1 = ix + (uint32_t)p.waves;
   if (ix >= n_tot) D.npos = 0;  // (its loads then fall outside the buffer descriptor and read nothing)
-  {
-    const __amdgpu_buffer_rsrc_t rs = unit_rsrc(D.stream_off, D.npos);
-    issue_granule(rs, 0, eA);
-  }
+  const __amdgpu_buffer_rsrc_t rs0 = unit_rsrc(D.stream_off, D.npos);
+  issue_granule(rs0, 0, eA);
+  issue_granule(rs0, 1, eA);
+  __builtin_amdgcn_sched_barrier(0);  // (they would be moved behind the staging)
   // Slots start from zero.  Where every panel stores all its values (`fill`) only slots that are no value's have to be: those
   // of panels of fewer values than a step of the fold reads.  (The slot of value 0 is not stored, but counts under no bit.)
   if (!p.fill || (1 << p.kc) < rsr::kFoldRow)
-    for (uint32_t i = (uint32_t)tid * 16u; i < (uint32_t)p.nbuf * p.ubytes; i += blockDim.x * 16u)
+    for (uint32_t i = (uint32_t)tid * 16u; i < (uint32_t)p.nbuf * p.ubytes; i += (uint32_t)p.threads * 16u)
       *reinterpret_cast<uint4*>(lds + p.off_u + i) = make_uint4(0, 0, 0, 0);
   if (tid < p.nbuf) {
     reinterpret_cast<uint32_t*>(lds + p.off_cnt)[tid] = 0;
@@ -773,19 +774,32 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   if constexpr (kEarly > 0) {
 #pragma unroll
     for (int j = 0; j < kEarly; ++j) {
-      const int i = tid + j * (int)blockDim.x;
+      const int i = tid + j * p.threads;
       if (i < n16) reinterpret_cast<uint4*>(lds)[i] = sv[j];
     }
   }
-  stage<M>(lds, v, p.vstride, nv, p.rows, kEarly * (int)blockDim.x);
+  stage<M>(lds, v, p.vstride, nv, p.rows, kEarly * p.threads, p.threads);
   if (tid < (1 << M::shift) / 4) reinterpret_cast<uint32_t*>(lds + ((size_t)p.rows << M::shift))[tid] = 0;  // the null row
-  __syncthreads();
-  {
-    const __amdgpu_buffer_rsrc_t rs = unit_rsrc(D.stream_off, D.npos);
+  // The first unit's loads.  A load of 16 bytes per lane holds the compute unit's memory pipeline for 16 clocks, all of sixteen
+  // wavefronts' first units for a microsecond: requested together before the barrier they hold up the activations and the
+  // barrier, requested together behind it the first sums.  Two granules with the descriptor, one behind the staging where that is
+  // long, the rest behind the barrier (granules before the staging + before the barrier, us: binary 16384^2 1+0 13.7, 2+0 13.2, 2+1 12.9,
+  // 3+0 13.1, 6+0 13.7; transformer block 1+0 27.0, 2+0 26.1, 2+1 26.5, 3+0 26.5, 6+0 28.3).
+  auto first_loads = [&](int from) {
 #pragma unroll
-    for (int gq = 1; gq < NG; ++gq) issue_granule(rs, gq, eA);
+    for (int gq = 2; gq < NG; ++gq)
+      if (gq >= from) issue_granule(rs0, gq, eA);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) issue_pair(rs, lane4 + (D.npos >> 3) * 1024u, j, tA);
+    for (int j = 0; j < 3; ++j) issue_pair(rs0, lane4 + (D.npos >> 3) * 1024u, j, tA);
+  };
+  if (p.rows << M::shift >= kLongStaging) {
+    issue_granule(rs0, 2, eA);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    first_loads(3);
+  } else {
+    __syncthreads();
+    first_loads(2);
   }
 
   const uint64_t code = M::table();
@@ -1196,6 +1210,7 @@ int enqueue_multi(const rsr_job* jobs, int njobs, const LaunchPlan* plans, void*
     lds = std::max(lds, plans[j].lds);
     if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
   }
+  for (int j = 0; j < njobs; ++j) m.job[j].p.threads = waves * 64;
   hipLaunchKernelGGL(rsr_multi_kernel<M>, dim3((unsigned)grid), dim3((unsigned)(waves * 64)), lds, static_cast<hipStream_t>(stream), m);
   RSR_HIP_TRY(hipGetLastError());
   return RSR_OK;

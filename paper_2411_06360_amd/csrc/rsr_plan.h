@@ -59,6 +59,7 @@ struct KArgs {
   uint32_t sets_magic;       // x / sets as the high half of a product
   uint32_t share, share_more;  // column blocks of a workgroup; so many workgroups have one more
   int waves;     // wavefronts that take units
+  int threads;   // of a workgroup (a launch of several products: of its largest)
   int nunits;    // unit descriptors in the index
   int nbuf;      // panels in flight per workgroup
   int nrec;      // blocks whose panel records are kept (panels > 1)
@@ -179,7 +180,7 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
   plan->lds = total(nbuf);
   plan->grid = grid;
   plan->waves = waves;
-  p.waves = waves;
+  p.waves = waves; p.threads = waves * 64;
   p.nbuf = nbuf; p.buf_magic = magic((uint32_t)nbuf);
   p.nrec = recs(nbuf); p.rec_magic = magic((uint32_t)p.nrec);
   p.off_u = (uint32_t)vbytes;
