@@ -42,8 +42,10 @@ using rsr::PUnit;
     }                                                                         \
   } while (0)
 
-// bit 0: some entry is -1, bit 1: some entry lies outside {-1,0,1}.  Bound by the reading of A: 16 bytes per load
-// where A is aligned.
+// flags[workgroup], bit 0: some entry is -1, bit 1: some entry lies outside {-1,0,1}.  Bound by the reading of A: 16 bytes per load
+// where A is aligned.  A word per workgroup, added up by the host: with one word for all, most wavefronts of a ternary matrix
+// reached their atomic before the first of them was seen (ternary 4096^2: 58 us, 6.4 now).
+constexpr int kKindGroups = 1024;
 __global__ void kind_kernel(const int8_t* __restrict__ A, int64_t count, unsigned* __restrict__ flags) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
   unsigned f = 0;
@@ -61,9 +63,13 @@ __global__ void kind_kernel(const int8_t* __restrict__ A, int64_t count, unsigne
       for (int b = 0; b < 4; ++b) look((int)(d[j] << (24 - 8 * b)) >> 24);
   }
   for (int64_t i = n16 * 16 + id; i < count; i += step) look(A[i]);
-  // one atomic per wavefront that has something new to say (one per thread took 190 us at 4096^2)
+  __shared__ unsigned seen;
+  if (threadIdx.x == 0) seen = 0;
+  __syncthreads();
   const unsigned all = (__any((int)(f & 1u)) ? 1u : 0u) | (__any((int)(f & 2u)) ? 2u : 0u);
-  if ((threadIdx.x & 63) == 0 && (all & ~*const_cast<volatile unsigned*>(flags))) atomicOr(flags, all);
+  if ((threadIdx.x & 63) == 0 && all) atomicOr(&seen, all);
+  __syncthreads();
+  if (threadIdx.x == 0) flags[blockIdx.x] = seen;
 }
 
 // val[(block * parts + part) * rows + r].  A workgroup takes 64 rows of kValueBlocks column blocks through LDS, so that
@@ -434,14 +440,19 @@ units_kernel(Geometry g, const uint8_t* __restrict__ group_all, const PanelInfo*
              });
 }
 
-// One wavefront per unit.
+// One wavefront per unit: its rows and heads are collected in LDS (ent), the rows of every segment trade places, and the granules are
+// written out.  Bound by the latency of chains - list, offsets, rows from memory; entries, bank loads, exchange in LDS - so
+// four groups go through the first together, and through the second four quarters of the lanes, each elsewhere in the unit.
 constexpr int kEmitWaves = 4;
+constexpr int kGroupsAtOnce = 4;
+constexpr int kReach = 3;        // positions a row may move per trade
+constexpr int kTradeRounds = 2;  // times every lane looks at every row of its segments
 __global__ void __launch_bounds__(64 * kEmitWaves)
 emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const PanelInfo* __restrict__ info, const uint16_t* __restrict__ list_all,
             const uint32_t* __restrict__ extra_all, const uint32_t* __restrict__ off, const uint16_t* __restrict__ sigma,
             unsigned char* __restrict__ stream) {
   __shared__ uint16_t ent_all[kEmitWaves][rsr::kMaxPositions][64];
-  __shared__ uint32_t load_all[kEmitWaves][2][rsr::kMaxPositions][8];  // rows per LDS bank (a byte each), half wavefront and position
+  __shared__ uint32_t load_all[kEmitWaves][rsr::kMaxPositions][2][8];  // rows per LDS bank (a byte each), position and half wavefront
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t ui = blockIdx.x * kEmitWaves + wave;
   if (ui >= nunits) return;  // (no barriers below: the wavefronts are independent)
@@ -449,8 +460,11 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   const int npos = U.npos;
   if (npos == 0) return;
   volatile uint16_t (*ent)[64] = ent_all[wave];
-  volatile uint32_t (*load)[8] = load_all[wave][lane >> 5];
   uint32_t* load_words = &load_all[wave][0][0][0];
+  const volatile uint8_t* load_bytes = reinterpret_cast<const volatile uint8_t*>(load_words);
+  const int half = lane >> 5;
+  auto load_at = [&](int p, int b) { return (p * 2 + half) * 32 + b; };
+  auto add_load = [&](int p, int b, uint32_t x) { atomicAdd(&load_words[load_at(p, b) >> 2], x << (8 * (b & 3))); };
   const uint32_t panel = U.panel - g.panel0;
   const PanelInfo I = info[panel];
   const uint64_t heads = (uint64_t)U.heads_lo | ((uint64_t)U.heads_hi << 32);
@@ -460,75 +474,115 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   const bool owner = sub == 0;
   const uint16_t* list = list_all + (int64_t)panel * g.list_stride;
   const uint16_t null_index = (uint16_t)g.rows;
-  for (int i = lane; i < 2 * rsr::kMaxPositions * 8; i += 64) load_words[i] = 0;
+  for (int i = lane; i < rsr::kMaxPositions * 2 * 8; i += 64) load_words[i] = 0;
   uint32_t entry = U.first + ((uint32_t)lane >> wbits);
   for (int p0 = 0; p0 < npos;) {
-    const uint64_t rest = heads >> p0;
-    if (rest == 0) {  // the position that makes the count even
-      for (; p0 < npos; ++p0) ent[p0][lane] = null_index;
-      break;
-    }
-    const int m = __ffsll((long long)rest) - 1;
-    uint32_t n = 0, slot = (uint32_t)g.s.nslots + (lane & (rsr::kDummySlots - 1));
-    const uint16_t* rows = sigma;
-    if (entry < end) {
-      const uint32_t s = list[entry];
-      uint32_t of = s, piece = 0;
-      if (s >= (uint32_t)g.s.nslots) {
-        const uint32_t x = extra_all[(int64_t)panel * g.extra_stride + (s - g.s.nslots - rsr::kDummySlots)];
-        of = x & 0xffffu; piece = x >> 16;
+    // the next groups: where they begin and how many rows a lane has
+    int at[kGroupsAtOnce], m[kGroupsAtOnce];
+    uint32_t s[kGroupsAtOnce], n[kGroupsAtOnce], slot[kGroupsAtOnce];
+    const uint16_t* rows[kGroupsAtOnce];
+#pragma unroll
+    for (int i = 0; i < kGroupsAtOnce; ++i) {
+      const uint64_t rest = p0 < npos ? heads >> p0 : 0;
+      at[i] = p0; m[i] = -1; s[i] = 0xffffffffu;
+      if (rest == 0) {
+        if (p0 < npos) {  // the position that makes the count even
+          for (; p0 < npos; ++p0) ent[p0][lane] = null_index;
+        }
+        continue;
       }
-      uint32_t bp, value;
-      slot_value(g, panel, of, &bp, &value);
-      const uint32_t* o = off + (int64_t)bp * ((1 << g.k) + 1) + value;
-      const uint32_t o0 = o[0], all = o[1] - o0, np = pieces_of(all);
-      const uint32_t a = all * piece / np, b = all * (piece + 1) / np;
-      rows = sigma + (int64_t)bp * g.rows + o0 + a;
-      n = b - a;
-      if (owner) slot = s;
+      m[i] = __ffsll((long long)rest) - 1;
+      if (entry < end) s[i] = list[entry];
+      p0 += m[i] + 1;
+      entry += 64u >> wbits;
     }
-    for (int j = 0; j < m; ++j) {
+    uint32_t o0[kGroupsAtOnce], o1[kGroupsAtOnce], piece[kGroupsAtOnce], bp[kGroupsAtOnce];
+#pragma unroll
+    for (int i = 0; i < kGroupsAtOnce; ++i) {
+      o0[i] = o1[i] = piece[i] = bp[i] = 0;
+      slot[i] = (uint32_t)g.s.nslots + (lane & (rsr::kDummySlots - 1));
+      if (s[i] == 0xffffffffu) continue;
+      uint32_t of = s[i];
+      if (of >= (uint32_t)g.s.nslots) {
+        const uint32_t x = extra_all[(int64_t)panel * g.extra_stride + (of - g.s.nslots - rsr::kDummySlots)];
+        of = x & 0xffffu; piece[i] = x >> 16;
+      }
+      uint32_t value;
+      slot_value(g, panel, of, &bp[i], &value);
+      const uint32_t* o = off + (int64_t)bp[i] * ((1 << g.k) + 1) + value;
+      o0[i] = o[0]; o1[i] = o[1];
+      if (owner) slot[i] = s[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kGroupsAtOnce; ++i) {
+      const uint32_t all = o1[i] - o0[i], np = pieces_of(all);
+      const uint32_t a = all * piece[i] / np, b = all * (piece[i] + 1) / np;
+      rows[i] = sigma + (int64_t)bp[i] * g.rows + o0[i] + a;
+      n[i] = b - a;
+    }
+    int most = 0;
+#pragma unroll
+    for (int i = 0; i < kGroupsAtOnce; ++i) most = max(most, m[i]);
+    for (int j = 0; j < most; ++j) {
       const uint32_t r = ((uint32_t)j << wbits) + sub;
-      const uint16_t row = r < n ? rows[r] : null_index;
-      ent[p0 + j][lane] = row;
-      if (row != null_index) atomicAdd(const_cast<uint32_t*>(&load[p0 + j][(row & 31) >> 2]), 1u << (8 * (row & 3)));
+      uint16_t row[kGroupsAtOnce];
+#pragma unroll
+      for (int i = 0; i < kGroupsAtOnce; ++i) row[i] = j < m[i] && r < n[i] ? rows[i][r] : null_index;
+#pragma unroll
+      for (int i = 0; i < kGroupsAtOnce; ++i)
+        if (j < m[i]) {
+          ent[at[i] + j][lane] = row[i];
+          if (row[i] != null_index) add_load(at[i] + j, row[i] & 31, 1u);
+        }
     }
-    ent[p0 + m][lane] = (uint16_t)slot;
-    p0 += m + 1;
-    entry += 64u >> wbits;
+#pragma unroll
+    for (int i = 0; i < kGroupsAtOnce; ++i)
+      if (m[i] >= 0) ent[at[i] + m[i]][lane] = (uint16_t)slot[i];
   }
   // The order of the rows inside a segment is free (a segment is a sum).  The LDS has 32 banks of 4 bytes and
   // serves the two halves of a wavefront one after the other; a half costs as many clocks as its fullest bank has
-  // distinct addresses.  Two rows of a lane's segment trade places while that lowers the squared loads of the banks
-  // (row mod 32) at their two positions: the gathers of the product then meet in fewer banks.  The loads
-  // are kept with atomics; a decision may see a neighbour's move late, which only costs quality.
-  auto bank_load = [&](int p, int b) { return (int)((load[p][b >> 2] >> (8 * (b & 3))) & 0xffu); };
-  auto add_load = [&](int p, int b, uint32_t x) { atomicAdd(const_cast<uint32_t*>(&load[p][b >> 2]), x << (8 * (b & 3))); };
-  // A quarter of the lanes at a time: the lanes of a group stand at the same position, and would all leave a crowded bank
-  // at once.
-  constexpr int kReach = 6;  // positions a row may move per trade
-  for (int pass = 0; pass < 8; ++pass) {
-    if (((lane + pass) & 3) != 0) continue;
-    for (int p0 = 0; p0 < npos;) {
-      const uint64_t rest = heads >> p0;
-      if (rest == 0) break;
-      const int p1 = p0 + __ffsll((long long)rest) - 1;
-      for (int p = p0; p < p1; ++p)
-        for (int q = p + 1; q < min(p1, p + 1 + kReach); ++q) {
-          const uint16_t rp = ent[p][lane], rq = ent[q][lane];
-          if (rp == null_index || rq == null_index) continue;
-          const int bp = rp & 31, bq = rq & 31;
-          if (bp == bq) continue;
-          const int delta = (bank_load(p, bq) - bank_load(p, bp) + 1) + (bank_load(q, bp) - bank_load(q, bq) + 1);
-          if (delta < 0) {
-            add_load(p, bp, (uint32_t)-1); add_load(p, bq, 1u);
-            add_load(q, bq, (uint32_t)-1); add_load(q, bp, 1u);
-            ent[p][lane] = rq; ent[q][lane] = rp;
-          }
+  // distinct addresses.  Two rows of a lane's segment trade places where that lowers the squared loads of the banks
+  // (row mod 32) at their two positions most: the gathers of the product then meet in fewer banks.
+  // A quarter of the lanes at a time at a position: the lanes of a group stand at the same one, and would all leave a crowded bank at
+  // once.  The four quarters go round the unit's positions a quarter of the way apart.  (Fullest bank of a half wavefront for 4096 segments of 4
+  // rows on average, by simulation: 3.45 deep without trades, 2.44 and 2.28 after one and two rounds, 2.24 after three; trades over
+  // five positions instead of three 2.27.  One quarter after the other through every group, first improvement first: 2.24, and 655 us
+  // instead of 101 at ternary 4096^2, k = 10, where the units with a long group took longest.)
+  const int start = (lane & 3) * npos / 4;
+  for (int round = 0; round < kTradeRounds; ++round)
+    for (int t = 0; t < npos; ++t) {
+      const int p = t + start < npos ? t + start : t + start - npos;
+      const uint64_t rest = heads >> p;
+      const int p1 = rest ? p + __ffsll((long long)rest) - 1 : 0;  // the group's head
+      if (p + 1 < p1) {
+        const uint32_t row = ent[p][lane];
+        uint32_t other[kReach];
+#pragma unroll
+        for (int i = 0; i < kReach; ++i) other[i] = ent[min(p + 1 + i, p1 - 1)][lane];
+        const int b = row & 31, here = load_bytes[load_at(p, b)];
+        int best = 0, with = 0;
+        int there_b[kReach], here_o[kReach], there_o[kReach];
+#pragma unroll
+        for (int i = 0; i < kReach; ++i) {
+          const int q = min(p + 1 + i, p1 - 1), o = other[i] & 31;
+          there_b[i] = load_bytes[load_at(q, b)]; here_o[i] = load_bytes[load_at(p, o)]; there_o[i] = load_bytes[load_at(q, o)];
         }
-      p0 = p1 + 1;
+#pragma unroll
+        for (int i = 0; i < kReach; ++i) {
+          const int delta = (here_o[i] - here + 1) + (there_b[i] - there_o[i] + 1);
+          if (p + 1 + i < p1 && other[i] != null_index && (int)(other[i] & 31) != b && delta < best) { best = delta; with = i; }
+        }
+        if (best < 0 && row != null_index) {
+          uint32_t o = other[0];
+#pragma unroll
+          for (int i = 1; i < kReach; ++i) o = with == i ? other[i] : o;
+          const int q = p + 1 + with;
+          add_load(p, b, (uint32_t)-1); add_load(p, o & 31, 1u);
+          add_load(q, o & 31, (uint32_t)-1); add_load(q, b, 1u);
+          ent[p][lane] = (uint16_t)o; ent[q][lane] = (uint16_t)row;
+        }
+      }
     }
-  }
   unsigned char* to = stream + (int64_t)U.stream_off * rsr::kStreamAlign;
   const int full = npos / rsr::kGranulePositions;
   for (int gq = 0; gq < full; ++gq) {
@@ -553,13 +607,13 @@ namespace rsr_internal {
 
 int device_matrix_kind(const int8_t* dA, int64_t count, int* kind, std::string* err) {
   DevBuf flags;
-  PREP_TRY(hipMalloc(&flags.p, 4));
-  PREP_TRY(hipMemset(flags.p, 0, 4));
-  const int grid = (int)std::min<int64_t>(4096, (count + 4095) / 4096);
+  const int grid = (int)std::min<int64_t>(kKindGroups, (count + 4095) / 4096);
+  PREP_TRY(hipMalloc(&flags.p, (size_t)grid * sizeof(unsigned)));
   hipLaunchKernelGGL(kind_kernel, dim3((unsigned)grid), dim3(256), 0, nullptr, dA, count, static_cast<unsigned*>(flags.p));
   PREP_TRY(hipGetLastError());
-  unsigned f = 0;
-  PREP_TRY(hipMemcpy(&f, flags.p, 4, hipMemcpyDeviceToHost));
+  unsigned seen[kKindGroups], f = 0;
+  PREP_TRY(hipMemcpy(seen, flags.p, (size_t)grid * sizeof(unsigned), hipMemcpyDeviceToHost));
+  for (int i = 0; i < grid; ++i) f |= seen[i];
   *kind = (f & 2u) ? 0 : ((f & 1u) ? 2 : 1);
   return 0;
 }
