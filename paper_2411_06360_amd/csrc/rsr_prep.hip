@@ -223,12 +223,24 @@ __device__ __forceinline__ int rows_of_key(int key) {  // positions a group of t
   return key < kKeys8 ? kKeys8 - key : kKeys8 + kKeys1 - 1 - key;
 }
 
+// Rows per group of a panel, in LDS, for a wavefront that walks them together: 64 at a time in a register.
+struct GroupRows {
+  const uint8_t* rows;
+  int lane;
+  uint32_t base = 0xffffffffu;
+  int held = 0;
+  __device__ __forceinline__ uint32_t operator()(uint32_t i) {  // i: the same for all lanes
+    i = (uint32_t)__builtin_amdgcn_readfirstlane((int)i);
+    if ((i & ~63u) != base) { base = i & ~63u; held = rows[base + lane]; }
+    return (uint32_t)__builtin_amdgcn_readlane(held, (int)(i & 63));
+  }
+};
 // The units of a panel: whole groups of one width, in order, at most kMaxPositions positions and about equally many
-// each.  f(wide, first list entry, first group, groups, positions) for every unit.
-template <typename G, typename F>
-__device__ __forceinline__ void walk_units(const PanelInfo& I, G group_rows, F f) {
+// each.  By a whole wavefront.  f(wide, first list entry, first group, groups, positions) for every unit.
+template <typename F>
+__device__ __forceinline__ void walk_units(const PanelInfo& I, GroupRows group_rows, F f) {
   uint32_t group = 0, entry = 0;
-#pragma unroll
+#pragma unroll 1
   for (int wide = 1; wide >= 0; --wide) {
     const uint32_t per = wide ? 8u : 64u, count = wide ? I.n8 : I.n1;
     const uint32_t ng = (count + per - 1) / per;
@@ -263,13 +275,14 @@ __device__ __forceinline__ bool slot_value(const Geometry& g, uint32_t panel, ui
 }
 
 // One workgroup per panel.  A chain of short steps on LDS counters: bound by their latency; several workgroups share a
-// compute unit.
+// compute unit.  (With the limits' costs, the classes' sums and the walk over the groups each by single lanes: 59 us at ternary
+// 4096^2, k = 10; 47 now, most of it the ranking by one wavefront and the places in the list.)
 __global__ void __launch_bounds__(256)
 plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__ list_all, uint8_t* __restrict__ group_all,
             uint32_t* __restrict__ extra_all, PanelInfo* __restrict__ info) {
   __shared__ uint16_t len[rsr::kMaxPanelSlots], rank[rsr::kMaxPanelSlots], list[rsr::kMaxPanelSlots + rsr::kMaxExtras];
   __shared__ uint16_t cnt[kKeys][64];
-  __shared__ uint32_t hist[rsr::kWideRows + 1], start[kKeys + 1], ex_slot[rsr::kMaxExtras];
+  __shared__ uint32_t hist[rsr::kWideRows + 1], above[rsr::kWideRows + 2], start[kKeys + 1], ex_slot[rsr::kMaxExtras];
   __shared__ uint16_t ex_rank[rsr::kMaxExtras];
   __shared__ uint8_t ex_key[rsr::kMaxExtras], groups[1024];
   __shared__ uint32_t cost[8], tot_rows, tot_segments, n_extra, best_cap;
@@ -279,6 +292,7 @@ plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__
   for (int i = tid; i < kKeys * 64; i += 256) (&cnt[0][0])[i] = 0;
   for (int i = tid; i <= rsr::kWideRows; i += 256) hist[i] = 0;
   if (tid == 0) { tot_rows = 0; tot_segments = 0; n_extra = 0; }
+  if (tid < 7) cost[tid] = 0;
   __syncthreads();
   {
     uint32_t my_rows = 0, my_segments = 0;
@@ -299,23 +313,40 @@ plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__
     atomicAdd(&tot_segments, my_segments);
   }
   __syncthreads();
-  // Up to how many rows a segment takes one lane: the limit that gives the fewest positions.
-  if (tid < 7) {
-    const uint32_t cap = (uint32_t)caps[tid];
-    uint32_t c = 0, seen = 0, m = 0;
-    for (uint32_t n = rsr::kWideRows; n > cap; --n) {
-      const uint32_t h = hist[n];
-      if (h) m = (n + 7) / 8;
-      c += ((seen + h + 7) / 8 - (seen + 7) / 8) * (m + 1);
-      seen += h;
+  // Up to how many rows a segment takes one lane: the limit that gives the fewest positions.  Thread t stands for the segments of
+  // n = t + 1 rows: with `more` longer ones (above[n]: those of n rows and more) they begin ceil(..) further groups of n rows.
+  {
+    const int n = tid + 1;
+    uint32_t sum = 0;
+    if (tid < 64) {  // suffix sums of the histogram, four lengths per lane
+      uint32_t part[4];
+#pragma unroll
+      for (int i = 3; i >= 0; --i) { sum += hist[4 * lane + i + 1]; part[i] = sum; }
+      uint32_t after = sum;
+#pragma unroll
+      for (int d = 1; d < 64; d *= 2) {
+        const uint32_t t = __shfl_down(after, d);
+        if (lane + d < 64) after += t;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) above[4 * lane + i + 1] = part[i] + after - sum;
+      if (lane == 0) above[rsr::kWideRows + 1] = 0;
     }
-    seen = 0;
-    for (uint32_t n = cap; n > 0; --n) {
-      const uint32_t h = hist[n];
-      c += ((seen + h + 63) / 64 - (seen + 63) / 64) * (n + 1);
-      seen += h;
+    __syncthreads();
+    const uint32_t with = above[n], more = above[n + 1];
+#pragma unroll
+    for (int c = 0; c < 7; ++c) {
+      uint32_t mine = 0;
+      if (n > caps[c]) {
+        mine = ((with + 7) / 8 - (more + 7) / 8) * (uint32_t)((n + 7) / 8 + 1);
+      } else {
+        const uint32_t wide = above[caps[c] + 1];
+        mine = ((with - wide + 63) / 64 - (more - wide + 63) / 64) * (uint32_t)(n + 1);
+      }
+#pragma unroll
+      for (int d = 32; d > 0; d /= 2) mine += __shfl_xor(mine, d);
+      if (lane == 0) atomicAdd(&cost[c], mine);
     }
-    cost[tid] = c;
   }
   __syncthreads();
   if (tid == 0) {
@@ -357,20 +388,30 @@ plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__
     if (lane == 0) n_extra = min(extras, (uint32_t)g.extra_stride);
   }
   __syncthreads();
-  if (tid < kKeys) {
-    uint32_t s = 0;
-    for (int c = 0; c < 64; ++c) s += cnt[tid][(c + tid) & 63];
-    start[tid + 1] = s;
+  for (int key = tid >> 6; key < kKeys; key += 4) {  // a wavefront per class, lane = residue
+    uint32_t s = cnt[key][lane];
+#pragma unroll
+    for (int d = 32; d > 0; d /= 2) s += __shfl_xor(s, d);
+    if (lane == 0) start[key + 1] = s;
   }
   __syncthreads();
-  if (tid == 0) {
-    uint32_t s = 0;
-    start[0] = 0;
-    for (int i = 1; i <= kKeys; ++i) { s += start[i]; start[i] = s; }
+  if (tid < 64) {  // prefix sums over the classes, two per lane
+    static_assert(kKeys <= 128 && kKeys % 2 == 0, "two classes per lane");
+    const bool in = 2 * lane < kKeys;
+    const uint32_t a = in ? start[2 * lane + 1] : 0u, b = in ? start[2 * lane + 2] : 0u;
+    uint32_t incl = a + b;
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const uint32_t t = __shfl_up(incl, d);
+      if (lane >= d) incl += t;
+    }
+    if (in) { start[2 * lane + 1] = incl - b; start[2 * lane + 2] = incl; }
+    if (lane == 0) start[0] = 0;
   }
   __syncthreads();
   auto place = [&](int key, uint32_t r, int residue) {
     uint32_t at = start[key];
+#pragma unroll 8
     for (int i = 0; i < 64; ++i) {
       const int c = (i + lane) & 63;
       at += min((uint32_t)cnt[key][c], r + (c < residue ? 1u : 0u));
@@ -394,19 +435,19 @@ plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__
   for (uint32_t i = tid; i < start[kKeys]; i += 256) list_out[i] = list[i];
   if (tid < (int)n_extra) extra_all[(int64_t)panel * g.extra_stride + tid] = ex_slot[tid];
   __syncthreads();
-  if (tid == 0) {
+  if (tid < 64) {
     PanelInfo I;
     I.n8 = n8; I.n1 = n1;
     I.units = 0; I.stream = 0;
     I.extras = n_extra; I.rows = tot_rows; I.segments = tot_segments;
-    walk_units(I, [&](uint32_t i) { return (uint32_t)groups[i]; },
+    walk_units(I, GroupRows{groups, lane},
                [&](int, uint32_t, uint32_t, uint32_t, uint32_t npos) { ++I.units; I.stream += (npos + 1) & ~1u; });
     if (I.units == 0) I.units = 1;  // a panel without entries still has to count for its block
-    info[panel] = I;
+    if (lane == 0) info[panel] = I;
   }
 }
 
-// One wavefront per panel; lane 0 walks the groups.
+// One wavefront per panel.
 __global__ void __launch_bounds__(64)
 units_kernel(Geometry g, const uint8_t* __restrict__ group_all, const PanelInfo* __restrict__ info, const PanelBase* __restrict__ base,
              PUnit* __restrict__ units) {
@@ -416,26 +457,28 @@ units_kernel(Geometry g, const uint8_t* __restrict__ group_all, const PanelInfo*
   const uint32_t ng = (I.n8 + 7) / 8 + (I.n1 + 63) / 64;
   for (uint32_t i = threadIdx.x; i < ng; i += 64) groups[i] = group_all[(int64_t)panel * g.group_stride + i];
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  const int lane = threadIdx.x;
   PUnit u;
   u.block = g.block0 + panel / g.s.panels; u.panel = g.panel0 + panel;
   u.units_in_panel = (uint16_t)I.units; u.extras = (uint16_t)I.extras; u.reserved = 0;
   uint32_t at = base[panel].unit, stream = base[panel].stream;
   if (ng == 0) {
     u.stream_off = stream; u.heads_lo = 0; u.heads_hi = 0; u.npos = 0; u.wide = 0; u.first = 0;
-    units[at] = u;
+    if (lane == 0) units[at] = u;
     return;
   }
-  walk_units(I, [&](uint32_t i) { return (uint32_t)groups[i]; },
+  GroupRows rows{groups, lane};
+  walk_units(I, rows,
              [&](int wide, uint32_t first, uint32_t group, uint32_t n, uint32_t npos) {
                uint64_t heads = 0;
                uint32_t p = 0;
-               for (uint32_t i = 0; i < n; ++i) { p += groups[group + i]; heads |= 1ull << p; ++p; }
+               for (uint32_t i = 0; i < n; ++i) { p += rows(group + i); heads |= 1ull << p; ++p; }
                u.stream_off = stream;
                u.heads_lo = (uint32_t)heads; u.heads_hi = (uint16_t)(heads >> 32);
                u.npos = (uint8_t)((npos + 1) & ~1u); u.wide = (uint8_t)wide;
                u.first = first;
-               units[at++] = u;
+               if (lane == 0) units[at] = u;
+               ++at;
                stream += (npos + 1) & ~1u;
              });
 }
