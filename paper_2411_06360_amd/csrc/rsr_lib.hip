@@ -173,13 +173,13 @@ __device__ __forceinline__ Swapped swap16(uint32_t v) {  // .x: rows 0,0,2,2 of 
 // this are in place before the counter moves.
 __device__ __forceinline__ uint32_t lds_count_up(uint32_t lds_byte_addr) {
   uint32_t old;
-  uint64_t saved;
   asm volatile(
-      "s_mov_b64 %[sv], exec\n s_mov_b64 exec, 1\n ds_add_rtn_u32 %[o], %[ad], %[one]\n s_mov_b64 exec, %[sv]\n s_waitcnt lgkmcnt(0)\n"
-      : [o] "=&v"(old), [sv] "=&s"(saved)
-      : [ad] "v"(lds_byte_addr), [one] "v"(1u)
-      : "memory");
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)old);
+      "v_mov_b32 v116, %[ad]\n v_mov_b32 v117, 1\n s_mov_b64 s[88:89], exec\n s_mov_b64 exec, 1\n ds_add_rtn_u32 v116, v116, v117\n"
+      " s_mov_b64 exec, s[88:89]\n s_waitcnt lgkmcnt(0)\n v_readfirstlane_b32 %[o], v116\n"
+      : [o] "=&s"(old)
+      : [ad] "s"(__builtin_amdgcn_readfirstlane((int)lds_byte_addr))
+      : "v116", "v117", "s88", "s89", "memory");
+  return old;
 }
 
 // LDS words of the workgroup's bookkeeping, in assembly: through generic pointers a volatile access becomes a flat
@@ -197,20 +197,6 @@ __device__ __forceinline__ void lds_bump(uint32_t lds_byte_addr) {
 }
 __device__ __forceinline__ void lds_clear(uint32_t lds_byte_addr) {
   asm volatile("ds_write_b32 %0, %1" ::"v"(lds_byte_addr), "v"(0u) : "memory");
-}
-
-// Two counters at once: one wait behind the gathers of the other wavefronts instead of two.
-__device__ __forceinline__ void lds_count_up(uint32_t addr_a, uint32_t addr_b, uint32_t& a, uint32_t& b) {
-  uint32_t x, y;
-  uint64_t saved;
-  asm volatile(
-      "s_mov_b64 %[sv], exec\n s_mov_b64 exec, 1\n ds_add_rtn_u32 %[x], %[aa], %[one]\n ds_add_rtn_u32 %[y], %[ab], %[one]\n"
-      "s_mov_b64 exec, %[sv]\n s_waitcnt lgkmcnt(0)\n"
-      : [x] "=&v"(x), [y] "=&v"(y), [sv] "=&s"(saved)
-      : [aa] "v"(addr_a), [ab] "v"(addr_b), [one] "v"(1u)
-      : "memory");
-  a = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
-  b = (uint32_t)__builtin_amdgcn_readfirstlane((int)y);
 }
 
 // ---- the positions of a unit, eight (one granule) at a time, four in the pass over four float vectors ----
@@ -286,13 +272,33 @@ __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__bui
   "s86", "s87", "s88", "s89", "s92", "s93", "s94", "s95", "scc", "memory", "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", \
       "v108", "v109", "v110", "v111"
 // A step of eight positions from four dwords; the last one of a unit, of up to six positions, from three dwords and the null row.
-#define RSR_STEP8(shift, sums, v0, v1, v2, v3, v4, v5, v6, v7, ...)                                    \
-  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, Sums& acc, uint32_t heads, const Steps& s) { \
-    asm volatile(RSR_FIND RSR_EXTRACT2(shift, v0, v1, 0) RSR_EXTRACT2(shift, v2, v3, 1) RSR_EXTRACT2(shift, v4, v5, 2) RSR_EXTRACT2(shift, v6, v7, 3) \
-                 RSR_CALL                                                                              \
-                 : "+{" sums "}"(acc)                                                                          \
-                 : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), RSR_CTL(heads & 0xffu)              \
-                 : RSR_CLOBBER __VA_OPT__(,) __VA_ARGS__);                                                     \
+// With TICKET a counter in LDS (byte address `counter`) goes up by one besides; returns its old value.  It is one LDS operation ahead of the
+// gathers, whose wait is longer.
+// (Registers of its own, v116 and v117: the compiler would take ones that a load of the stream may still write, as it sees it, and wait.)
+#define RSR_TICKET                                                                                             \
+  "v_mov_b32 v116, %[counter]\n v_mov_b32 v117, 1\n s_mov_b64 s[88:89], exec\n s_mov_b64 exec, 1\n ds_add_rtn_u32 v116, v116, v117\n" \
+  " s_mov_b64 exec, s[88:89]\n"
+#define RSR_TAKEN " s_waitcnt lgkmcnt(0)\n v_readfirstlane_b32 %[ticket], v116\n"
+#define RSR_STEP8(shift, sums, v0, v1, v2, v3, v4, v5, v6, v7, ...)                                            \
+  template <bool TICKET>                                                                                       \
+  __device__ static __forceinline__ uint32_t step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, Sums& acc, uint32_t heads, const Steps& s, \
+                                                   uint32_t counter) {                                         \
+    if constexpr (TICKET) {                                                                                    \
+      uint32_t ticket;                                                                                         \
+      asm volatile(RSR_TICKET RSR_FIND RSR_EXTRACT2(shift, v0, v1, 0) RSR_EXTRACT2(shift, v2, v3, 1) RSR_EXTRACT2(shift, v4, v5, 2) \
+                   RSR_EXTRACT2(shift, v6, v7, 3) RSR_CALL RSR_TAKEN                                           \
+                   : "+{" sums "}"(acc), [ticket] "=&s"(ticket)                                                \
+                   : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), [counter] "s"(uniform(counter)), RSR_CTL(heads & 0xffu) \
+                   : RSR_CLOBBER, "v116", "v117" __VA_OPT__(,) __VA_ARGS__);                                   \
+      return ticket;                                                                                           \
+    } else {                                                                                                   \
+      asm volatile(RSR_FIND RSR_EXTRACT2(shift, v0, v1, 0) RSR_EXTRACT2(shift, v2, v3, 1) RSR_EXTRACT2(shift, v4, v5, 2) \
+                   RSR_EXTRACT2(shift, v6, v7, 3) RSR_CALL                                                     \
+                   : "+{" sums "}"(acc)                                                                        \
+                   : [w0] "v"(w0), [w1] "v"(w1), [w2] "v"(w2), [w3] "v"(w3), RSR_CTL(heads & 0xffu)            \
+                   : RSR_CLOBBER __VA_OPT__(,) __VA_ARGS__);                                                   \
+      return 0;                                                                                                \
+    }                                                                                                          \
   }                                                                                                            \
   __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t null_row, Sums& acc, uint32_t heads, const Steps& s) { \
     asm volatile(RSR_FIND RSR_EXTRACT2(shift, v0, v1, 0) RSR_EXTRACT2(shift, v2, v3, 1) RSR_EXTRACT2(shift, v4, v5, 2)  \
@@ -421,9 +427,20 @@ struct F4 {  // four float vectors; four positions per step (16 registers of gat
                  : [w0] "v"(w0), [w1] "v"(w1), RSR_CTL(heads & 0xfu)
                  : RSR_CLOBBER);
   }
-  __device__ static __forceinline__ void step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, Sums& acc, uint32_t heads, const Steps& s) {
-    step4(w0, w1, acc, heads, s);
+  template <bool TICKET>
+  __device__ static __forceinline__ uint32_t step8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, Sums& acc, uint32_t heads, const Steps& s,
+                                                   uint32_t counter) {
+    uint32_t ticket = 0;
+    if constexpr (TICKET) {
+      asm volatile(RSR_TICKET RSR_FIND RSR_EXTRACT2(4, 96, 100, 0) RSR_EXTRACT2(4, 104, 108, 1) RSR_CALL RSR_TAKEN
+                   : "+{v[112:115]}"(acc), [ticket] "=&s"(ticket)
+                   : [w0] "v"(w0), [w1] "v"(w1), [counter] "s"(uniform(counter)), RSR_CTL(heads & 0xfu)
+                   : RSR_CLOBBER, "v116", "v117");
+    } else {
+      step4(w0, w1, acc, heads, s);
+    }
     step4(w2, w3, acc, heads >> 4, s);
+    return ticket;
   }
   __device__ static __forceinline__ void step6(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t null_row, Sums& acc, uint32_t heads, const Steps& s) {
     step4(w0, w1, acc, heads, s);
@@ -747,11 +764,11 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   }
   const uint32_t u_begin = blk_unit[blk_begin];
   const uint32_t n_tot = blk_unit[blk_end] - u_begin;  // units of this workgroup, numbered 0 .. n_tot-1
-  // The first two units of every wavefront are fixed (its own number and that plus the number of wavefronts); the first
-  // one's descriptor and the beginning of its stream are requested before the barrier.  Later units come from a counter.
+  // The first unit of every wavefront is fixed (its own number); its descriptor and the beginning of its stream are requested before the
+  // barrier.  Later units come from a counter.
   const uint32_t u_first = u_begin + (uint32_t)wave;
   Desc D = load_desc(unit_words, u_first < (uint32_t)p.nunits ? u_first : 0u);
-  uint32_t ix = worker ? (uint32_t)wave : n_tot, ix1 = ix + (uint32_t)p.waves;
+  uint32_t ix = worker ? (uint32_t)wave : n_tot;
   if (ix >= n_tot) D.npos = 0;  // (its loads then fall outside the buffer descriptor and read nothing)
   const __amdgpu_buffer_rsrc_t rs0 = unit_rsrc(D.stream_off, D.npos);
   issue_granule(rs0, 0, eA);
@@ -770,7 +787,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     reinterpret_cast<uint32_t*>(lds + p.off_done)[tid] = 0;
     reinterpret_cast<uint32_t*>(lds + p.off_blocks)[tid] = 0;
   }
-  if (tid == 0) *reinterpret_cast<uint32_t*>(lds + p.off_ctr) = 2u * (uint32_t)p.waves;
+  if (tid == 0) *reinterpret_cast<uint32_t*>(lds + p.off_ctr) = (uint32_t)p.waves;
   if constexpr (kEarly > 0) {
 #pragma unroll
     for (int j = 0; j < kEarly; ++j) {
@@ -1046,7 +1063,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     const uint32_t turn = p.nbuf == 1 ? 0u : __umulhi(panel, p.buf_magic);
     const uint32_t buf = panel - turn * (uint32_t)p.nbuf;
     const uint32_t ubase = p.off_u + buf * p.ubytes;
-    if (turn != 0 && panel != open_panel) {
+    if (__builtin_expect(turn != 0 && panel != open_panel, 0)) {
       while (uniform(lds_load(p.off_epoch + buf * 4u)) < turn) __builtin_amdgcn_s_sleep(1);
       open_panel = panel;
     }
@@ -1063,10 +1080,19 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     const uint32_t full = D.npos >> 3;
     auto step = [&](int gq) {
       const uint32_t hm = gq < 4 ? D.heads_lo >> (8 * gq) : D.heads_hi >> (8 * (gq - 4));
-      if ((uint32_t)gq < full) M::step8(e[gq][0], e[gq][1], e[gq][2], e[gq][3], acc, hm, steps);
+      if (__builtin_expect((uint32_t)gq < full, 1)) M::template step8<false>(e[gq][0], e[gq][1], e[gq][2], e[gq][3], acc, hm, steps, 0u);
     };
+    // The wavefront takes its next unit only here, behind the fold of a panel that it may have had to do and the wait for room: while it
+    // folds it holds back one unit of another panel, not two (binary 16384^2, eight vectors: 44.1 us with
+    // the next unit taken ahead of the fold, 41.6 so; eight int8 vectors 34.6 and 31.4; transformer block, sixteen vectors 79.2 and 73.8).
+    uint32_t ix1;
+    if (__builtin_expect(full != 0, 1)) {
+      ix1 = M::template step8<true>(e[0][0], e[0][1], e[0][2], e[0][3], acc, D.heads_lo, steps, p.off_ctr);
+    } else {
+      ix1 = lds_count_up(p.off_ctr);
+    }
 #pragma unroll
-    for (int gq = 0; gq < NG / 2; ++gq) step(gq);
+    for (int gq = 1; gq < NG / 2; ++gq) step(gq);
     // The next unit's loads go out one by one between the later steps: a wavefront that issues a whole unit at once waits
     // for room in the memory pipeline while it could be summing.
     Desc D1 = load_desc(unit_words, ix1 < n_tot ? u_begin + ix1 : 0u);  // past the end it reads unit 0 (unused)
@@ -1083,16 +1109,13 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       // the positions behind the last full granule, always six: a row that the unit does not have is read as row 0
       // and added to sums that no head stores
       const uint32_t hm = (full < 4 ? D.heads_lo >> (8 * full) : D.heads_hi >> (8 * (full - 4)));
-      if (D.npos & 7) M::step6(et[0], et[1], et[2], (uint32_t)p.rows << M::shift, acc, hm, steps);
+      if (__builtin_expect(D.npos & 7, 1)) M::step6(et[0], et[1], et[2], (uint32_t)p.rows << M::shift, acc, hm, steps);
 #pragma unroll
       for (int j = 0; j < 3; ++j) issue_pair(rs1, pair_base1, j, etn);
     }
-    // The wavefront reserves the unit after the next only now: the last units then go to the wavefronts that get there
-    // first.
-    uint32_t before, ix2;
-    lds_count_up(p.off_cnt + buf * 4u, p.off_ctr, before, ix2);
+    const uint32_t before = lds_count_up(p.off_cnt + buf * 4u);
     if (before + 1 == D.units_in_panel) fold(D, buf, ubase, extra_pair);
-    ix = ix1; ix1 = ix2; D = D1;
+    ix = ix1; D = D1;
   };
 
   while (ix < n_tot) {
