@@ -206,45 +206,46 @@ struct Load {
     folds += (double)h.nblocks * T.shape.panels * (T.shape.nslots / kFoldRow);
   }
 };
-// A unit of the stream keeps its share of a panel's sums in LDS from its start until the panel is folded, about one and a half
-// times as long as it is summed: with room for the sums of fewer units in flight (kRoom: float, kRoom8: int8, whose sums
-// take half the LDS) wavefronts stand still.  Returns the sums of how many units a workgroup has room for, 1e9 if the LDS does not limit
-// the panels in flight, 0 if the pass does not fit.
+// A unit of the stream keeps its share of a panel's sums in LDS from its start until the panel is folded, longer than
+// it is summed: with room for the sums of fewer units in flight (kRoom: float, kRoom8: int8) wavefronts stand still.  Returns the
+// sums of how many units a workgroup has room for, 1e9 if the LDS does not limit the panels in flight, 0 if the pass does not fit.
 // `cus`: the compute units that the product has, the device's or its share of a launch (fewer: more blocks per workgroup,
 // which need a second panel in flight).
-constexpr double kRoom = 32, kRoom8 = 24;
+constexpr double kRoom = 28, kRoom8 = 50;
 inline double room_for(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch, int cus) {
   LaunchPlan plan;
   if (plan_tile(M, h, T, false, batch, cus, 1, &plan) != RSR_OK) return 0;
   const int64_t panels = h.nblocks * T.shape.panels, per_wg = (h.nblocks + plan.p.g1 - 1) / plan.p.g1 * T.shape.panels;
   return plan.p.nbuf >= std::min<int64_t>(kMostBuffers, per_wg) ? 1e9 : (double)plan.p.nbuf * (double)T.nunits / (double)panels;
 }
-// Which pass.  A pass over V vectors takes as many times less units and folds, each of which costs more, and a launch with less
-// than a unit per wavefront of the device takes as long as one unit does: few units are better spread out, a vector per
-// pass.  The constants, in the time of a full round of units with one vector (1.65 us), are fitted to 500 matrices of 1024 to
-// 32768 rows (binary, ternary, correlated; k from 8 to 13), 2 to 16 vectors, in all three passes: on average the choice is 0.7 %
-// (float) and 0.9 % (int8) slower than the best of the three.  Float without the folds, the staging and the waiting for room: 5.4 %
-// (1472 x 30464, k = 8, eleven vectors: 53 us with one vector per pass, 24 with four).
+// Which pass.  A pass over V vectors takes as many times less units and folds, each of which costs more, and more rows to
+// stage; a launch with less than a unit per wavefront of the device takes as long as one unit does (and a device nearly full of units
+// somewhat longer than one half full): few units are better spread out, a vector per pass.  The constants, in the time of a full round
+// of units with one vector, are fitted to 170 matrices of 1024 to 32768 rows (binary, ternary, correlated; k from 8 to
+// 13), 2 to 16 vectors, in all three passes: on average the choice is 1.1 % (float) and 1.2 % (int8) slower than the best of the three; fitted to
+// every other product 1.1 and 1.1 % on the rest.  (With the constants of the kernels that tested and branched at every position: 1.7 and 1.8 %;
+// ternary 6703 x 13056, k = 11, five int8 vectors: 27.2 us with four per pass, 20.7 with two.)
+struct PassCosts {
+  double full, busy;                   // a round of units: 1, or full + busy * rounds where that is more
+  double start, unit, fold, rows;      // once, per round of units, per round of folds, per 16384 rows
+};
+constexpr PassCosts kCosts[2][3] = {  // [int8][one, two, four vectors]
+    {{0.45, 0.85, 0, 1, 0.2, 0}, {0.45, 0.85, 0, 1.2, 0.5, 0.9}, {0.45, 0.85, 0.25, 2.35, 0.65, 1.7}},
+    {{0.35, 0.9, 0, 1, 0, 0}, {0.35, 0.9, 0, 1.1, 0.05, 0}, {0.35, 0.9, 0, 1.3, 0.4, 2.2}}};
 inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, const Load& load, int cus) {
   if (h.step2_plain || batch < 2) return Mode::one;
   const double device = (double)h.num_cu * h.waves;
-  auto rounds = [&](int V) { return std::max(1.0, load.units * ((batch + V - 1) / V) / device); };
-  if (!i8) {
-    const double rows = 0.4 * (double)T.rows / 16384;  // a wider pass has more to stage
-    auto cost = [&](Mode m, double start, double unit, double fold) {
-      const Pass& M = pass_of(false, m);
-      const double room = room_for(M, h, T, batch, cus);
-      return room == 0 ? 1e30 : start + unit * rounds(M.V) * std::max(1.0, kRoom / room) + fold * load.folds * ((batch + M.V - 1) / M.V) / device;
-    };
-    const double c1 = cost(Mode::one, 0, 1, 0.25), c2 = cost(Mode::two, rows, 1.1, 0.4), c4 = cost(Mode::four, 0.6 + rows, 2.0, 0.6);
-    return c4 < c2 && c4 < c1 ? Mode::four : c2 < c1 ? Mode::two : Mode::one;
-  }
-  // (a device that is nearly full of units is slower than one that is half full: 2048 x 2888, four vectors, 0.96 units per
-  // wavefront: 7.6 us with one vector per pass, 6.8 with two; 3584 x 2432, 0.57 units: 5.7 and 6.5)
-  const double c1 = std::max(0.55 + 0.6 * load.units * batch / device, rounds(1)), c2 = 1.1 * rounds(2), c4 = 1.5 * rounds(4);
-  if (c4 < c2 && c4 < c1 && room_for(kP4, h, T, batch, cus) >= kRoom8) return Mode::four;
-  // (two have a vector's rows and slots in the bytes of one, but twice its records: 16 KB a block at 128 panels)
-  return c2 < c1 && room_for(kP2, h, T, batch, cus) > 0 ? Mode::two : Mode::one;
+  auto cost = [&](Mode m) {
+    const Pass& M = pass_of(i8, m);
+    const double room = room_for(M, h, T, batch, cus);
+    if (room == 0) return 1e30;
+    const PassCosts& c = kCosts[i8][(int)m];
+    const double sets = (double)((batch + M.V - 1) / M.V) / device, units = load.units * sets;
+    const double rounds = std::max({1.0, units, c.full + c.busy * units});
+    return c.start + c.unit * rounds * std::max(1.0, (i8 ? kRoom8 : kRoom) / room) + c.fold * load.folds * sets + c.rows * (double)T.rows / 16384;
+  };
+  const double c1 = cost(Mode::one), c2 = cost(Mode::two), c4 = cost(Mode::four);
+  return c4 < c2 && c4 < c1 ? Mode::four : c2 < c1 ? Mode::two : Mode::one;
 }
 
 // The launch of one row tile's product.
