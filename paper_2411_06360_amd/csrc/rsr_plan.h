@@ -223,7 +223,7 @@ inline double room_for(const Pass& M, const PlanMatrix& h, const PlanTile& T, in
 // somewhat longer than one half full): few units are better spread out, a vector per pass.  The constants, in the time of a full round
 // of units with one vector, are fitted to 170 matrices of 1024 to 32768 rows (binary, ternary, correlated; k from 8 to
 // 13), 2 to 16 vectors, in all three passes: on average the choice is 1.1 % (float) and 1.2 % (int8) slower than the best of the three; fitted to
-// every other product 1.1 and 1.1 % on the rest.  (With the constants of the kernels that tested and branched at every position: 1.7 and 1.8 %;
+// every other product 1.1 and 1.1 % on the rest; 1.0 and 1.3 % on 2478 other matrices.  (With the constants of the kernels that tested and branched at every position: 1.7 and 1.8 %;
 // ternary 6703 x 13056, k = 11, five int8 vectors: 27.2 us with four per pass, 20.7 with two.)
 struct PassCosts {
   double full, busy;                   // a round of units: 1, or full + busy * rounds where that is more
