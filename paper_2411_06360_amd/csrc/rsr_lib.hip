@@ -217,21 +217,19 @@ __device__ __forceinline__ void lds_clear(uint32_t lds_byte_addr) {
 // What an activation mode M defines: vectors V per pass, LDS bytes per row (1 << shift) and per slot, and its sums.
 #define RSR_EXTRACT(sh, v, w, half) "v_lshlrev_b32_sdwa v" #v ", " #sh ", %[w" #w "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:" half "\n"
 #define RSR_EXTRACT2(sh, v0, v1, w) RSR_EXTRACT(sh, v0, w, "WORD_0") RSR_EXTRACT(sh, v1, w, "WORD_1")
-// The code of every pattern of `positions` positions, `stride` bytes each: rsr_p the pattern, rsr_q the position, rsr_n LDS operations
-// that may be under way, rsr_z 1 where the running sums have been stored and not restarted yet, rsr_b bytes of code so far.
-// `row`, `first` and `head` are the bytes of a position: a row, the first row of a group, a head; `zeros` those of ZERO.  rsr_v is
-// the register of position 0; `back` holds the return address.
-#define RSR_TABLE(v0, positions, stride, row, first, head, zeros, READ, ADD, FIRST, STORE, ZERO, back)         \
-  ".set rsr_v, " #v0 "\n.set rsr_p, 0\n.rept 1 << " #positions "\n.set rsr_q, 0\n.set rsr_n, 0\n.set rsr_z, 0\n.set rsr_b, 4\n" \
+// The code of every pattern of `positions` positions, `stride` bytes each, at the label `name`: rsr_p the pattern, rsr_q the position,
+// rsr_n LDS operations that may be under way, rsr_z 1 where the running sums have been stored and not restarted yet.  rsr_v is the
+// register of position 0; `back` holds the return address.  The assembler places the patterns itself (.org), `stride` bytes apart
+// whatever their instructions take, and refuses one that is longer.
+#define RSR_TABLE(name, v0, positions, stride, READ, ADD, FIRST, STORE, ZERO, back)                            \
+  ".Lrsr_" name "_%=:\n.set rsr_v, " #v0 "\n.set rsr_p, 0\n.rept 1 << " #positions "\n.set rsr_q, 0\n.set rsr_n, 0\n.set rsr_z, 0\n" \
   ".rept " #positions "\n.if ((rsr_p >> rsr_q) & 1) == 0\n" READ ".set rsr_n, rsr_n+1\n.endif\n.set rsr_q, rsr_q+1\n.endr\n" \
-  ".set rsr_q, 0\n.rept " #positions "\n.if (rsr_p >> rsr_q) & 1\n.if rsr_z\n" ZERO ".set rsr_b, rsr_b+" #zeros "\n.endif\n" STORE \
-  ".set rsr_n, rsr_n+1\n.set rsr_z, 1\n.set rsr_b, rsr_b+" #head "\n"                                          \
-  ".else\n.set rsr_n, rsr_n-1\n s_waitcnt lgkmcnt(rsr_n)\n"                                                    \
-  ".if rsr_z\n" FIRST ".set rsr_b, rsr_b+" #first "\n.else\n" ADD ".set rsr_b, rsr_b+" #row "\n.endif\n.set rsr_z, 0\n" \
+  ".set rsr_q, 0\n.rept " #positions "\n.if (rsr_p >> rsr_q) & 1\n.if rsr_z\n" ZERO ".endif\n" STORE            \
+  ".set rsr_n, rsr_n+1\n.set rsr_z, 1\n"                                                                      \
+  ".else\n.set rsr_n, rsr_n-1\n s_waitcnt lgkmcnt(rsr_n)\n.if rsr_z\n" FIRST ".else\n" ADD ".endif\n.set rsr_z, 0\n" \
   ".endif\n.set rsr_q, rsr_q+1\n.endr\n"                                                                       \
-  ".if rsr_z\n" ZERO ".set rsr_b, rsr_b+" #zeros "\n.endif\n s_setpc_b64 " back "\n"                          \
-  ".if rsr_b > " #stride "\n.error \"a pattern does not fit\"\n.endif\n"                                       \
-  ".rept (" #stride "-rsr_b)/4\n s_nop 0\n.endr\n.set rsr_p, rsr_p+1\n.endr\n"
+  ".if rsr_z\n" ZERO ".endif\n s_setpc_b64 " back "\n"                                                        \
+  ".set rsr_p, rsr_p+1\n.org .Lrsr_" name "_%=+" #stride "*rsr_p\n.endr\n"
 // Behind the table, for units whose segments take 8 lanes: the lanes' sums are first added at a head with lane exchanges (the s_nop
 // cover the wait states an exchange needs after a vector write), which is more code: tables of four positions, for either half of a step.
 // Branches, 4 bytes per pattern, lead to the step without heads or to the calls of the two halves.  (With a test and
@@ -241,15 +239,15 @@ __device__ __forceinline__ void lds_clear(uint32_t lds_byte_addr) {
 #define RSR_WIDE_LANES(LANES)                                                                                  \
   " s_nop 1\n" LANES("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf") " s_nop 1\n" LANES("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf") \
   " s_nop 1\n" LANES("row_half_mirror row_mask:0xf bank_mask:0xf")
-#define RSR_WIDE(v_low, v_high, stride, row, first, head, zeros, READ, ADD, FIRST, LANES, STORE, ZERO)         \
+#define RSR_WIDE(v_low, v_high, stride, READ, ADD, FIRST, LANES, STORE, ZERO)         \
   " s_branch .Lrsr_table_%=\n.rept 255\n s_branch .Lrsr_halves_%=\n.endr\n"                                    \
   ".Lrsr_halves_%=:\n s_getpc_b64 s[88:89]\n.Lrsr_at_%=:\n"                                                    \
   " s_and_b32 s92, s90, 15\n s_mul_i32 s92, s92, " #stride "\n s_add_u32 s92, s92, .Lrsr_low_%=-.Lrsr_at_%=\n" \
   " s_add_u32 s92, s88, s92\n s_addc_u32 s93, s89, 0\n s_swappc_b64 s[86:87], s[92:93]\n"                      \
   " s_lshr_b32 s92, s90, 4\n s_mul_i32 s92, s92, " #stride "\n s_add_u32 s92, s92, .Lrsr_high_%=-.Lrsr_at_%=\n" \
   " s_add_u32 s92, s88, s92\n s_addc_u32 s93, s89, 0\n s_setpc_b64 s[92:93]\n"                                 \
-  ".Lrsr_low_%=:\n" RSR_TABLE(v_low, 4, stride, row, first, head, zeros, READ, ADD, FIRST, RSR_WIDE_LANES(LANES) STORE, ZERO, "s[86:87]") \
-  ".Lrsr_high_%=:\n" RSR_TABLE(v_high, 4, stride, row, first, head, zeros, READ, ADD, FIRST, RSR_WIDE_LANES(LANES) STORE, ZERO, "s[94:95]")
+  RSR_TABLE("low", v_low, 4, stride, READ, ADD, FIRST, RSR_WIDE_LANES(LANES) STORE, ZERO, "s[86:87]") \
+  RSR_TABLE("high", v_high, 4, stride, READ, ADD, FIRST, RSR_WIDE_LANES(LANES) STORE, ZERO, "s[94:95]")
 // How a unit's steps find their code: pattern 0 at `code`, every further one `stride` bytes on.
 struct Steps {
   uint64_t code;
@@ -260,7 +258,7 @@ struct Steps {
   __device__ static __forceinline__ uint64_t table() {                                                         \
     uint32_t lo, hi;                                                                                           \
     asm volatile("s_getpc_b64 s[92:93]\n.Lrsr_here_%=:\n s_add_u32 %[lo], s92, .Lrsr_table_%=-.Lrsr_here_%=\n" \
-                 " s_addc_u32 %[hi], s93, 0\n s_branch .Lrsr_over_%=\n.p2align 6\n.Lrsr_table_%=:\n" TABLE WIDE ".Lrsr_over_%=:\n" \
+                 " s_addc_u32 %[hi], s93, 0\n s_branch .Lrsr_over_%=\n.p2align 6\n" TABLE WIDE ".Lrsr_over_%=:\n" \
                  : [lo] "=&s"(lo), [hi] "=&s"(hi)::"s92", "s93", "scc");                                       \
     return (uint64_t)hi << 32 | lo;                                                                            \
   }
@@ -354,8 +352,8 @@ struct F1 {  // one float vector
   static constexpr uint32_t kStride = 132, kWide = 256 * kStride, kWideStride = 4;
   using Slot = float;  // the sums of a slot
   __device__ static __forceinline__ float get(float x, int) { return x; }
-  RSR_STEPS(RSR_TABLE(96, 8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
-            RSR_WIDE(96, 100, 212, 16, 16, 48, 4, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_LANES_F1, RSR_STORE1, RSR_ZERO1))
+  RSR_STEPS(RSR_TABLE("table", 96, 8, 132, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
+            RSR_WIDE(96, 100, 212, RSR_READ1, RSR_ADD_F1, RSR_FIRST_F1, RSR_LANES_F1, RSR_STORE1, RSR_ZERO1))
   RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103)
 };
 struct I1 {  // one int8 vector
@@ -367,8 +365,8 @@ struct I1 {  // one int8 vector
   static constexpr uint32_t kStride = 132, kWide = 256 * kStride, kWideStride = 4;
   using Slot = int32_t;
   __device__ static __forceinline__ int32_t get(int32_t x, int) { return x; }
-  RSR_STEPS(RSR_TABLE(96, 8, 132, 16, 16, 12, 4, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
-            RSR_WIDE(96, 100, 212, 16, 16, 48, 4, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_LANES_I1, RSR_STORE1, RSR_ZERO1))
+  RSR_STEPS(RSR_TABLE("table", 96, 8, 132, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
+            RSR_WIDE(96, 100, 212, RSR_READ1, RSR_ADD_I1, RSR_FIRST_I1, RSR_LANES_I1, RSR_STORE1, RSR_ZERO1))
   RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103)
 };
 struct F2 {  // two float vectors
@@ -380,8 +378,8 @@ struct F2 {  // two float vectors
   static constexpr uint32_t kStride = 164, kWide = 256 * kStride, kWideStride = 4;
   typedef float Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(96, 8, 164, 20, 20, 12, 8, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_STORE2, RSR_ZERO2, "s[94:95]"),
-            RSR_WIDE(96, 104, 324, 20, 20, 72, 8, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_LANES_F2, RSR_STORE2, RSR_ZERO2))
+  RSR_STEPS(RSR_TABLE("table", 96, 8, 164, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_STORE2, RSR_ZERO2, "s[94:95]"),
+            RSR_WIDE(96, 104, 324, RSR_READ2, RSR_ADD_F2, RSR_FIRST_F2, RSR_LANES_F2, RSR_STORE2, RSR_ZERO2))
   RSR_STEP8(3, "v[112:113]", 96, 98, 100, 102, 104, 106, 108, 110)
 };
 struct P2 {  // two int8 vectors
@@ -393,8 +391,8 @@ struct P2 {  // two int8 vectors
   static constexpr uint32_t kStride = 164, kWide = 256 * kStride, kWideStride = 4;
   typedef int16_t Slot __attribute__((ext_vector_type(2)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(96, 8, 164, 20, 16, 12, 4, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
-            RSR_WIDE(96, 100, 308, 20, 16, 72, 4, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_LANES_P2, RSR_STORE1, RSR_ZERO1))
+  RSR_STEPS(RSR_TABLE("table", 96, 8, 164, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_STORE1, RSR_ZERO1, "s[94:95]"),
+            RSR_WIDE(96, 100, 308, RSR_READ1, RSR_ADD_P2, RSR_FIRST_I1, RSR_LANES_P2, RSR_STORE1, RSR_ZERO1))
   RSR_STEP8(2, "v112", 96, 97, 98, 99, 100, 101, 102, 103, "v114")
 };
 struct P4 {  // four int8 vectors
@@ -406,8 +404,8 @@ struct P4 {  // four int8 vectors
   static constexpr uint32_t kStride = 228, kWide = 256 * kStride, kWideStride = 4;
   typedef int16_t Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ int32_t get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(96, 8, 228, 28, 20, 12, 8, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_STORE2, RSR_ZERO2, "s[94:95]"),
-            RSR_WIDE(96, 104, 516, 28, 20, 120, 8, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_LANES_P4, RSR_STORE2, RSR_ZERO2))
+  RSR_STEPS(RSR_TABLE("table", 96, 8, 228, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_STORE2, RSR_ZERO2, "s[94:95]"),
+            RSR_WIDE(96, 104, 516, RSR_READ2, RSR_ADD_P4, RSR_FIRST_P4, RSR_LANES_P4, RSR_STORE2, RSR_ZERO2))
   RSR_STEP8(3, "v[112:113]", 96, 98, 100, 102, 104, 106, 108, 110, "v114", "v115")
 };
 struct F4 {  // four float vectors; four positions per step (16 registers of gathered activations)
@@ -419,8 +417,8 @@ struct F4 {  // four float vectors; four positions per step (16 registers of gat
   static constexpr uint32_t kStride = 132, kWide = 16 * kStride, kWideStride = 564;
   typedef float Slot __attribute__((ext_vector_type(4)));
   __device__ static __forceinline__ float get(Slot x, int j) { return x[j]; }
-  RSR_STEPS(RSR_TABLE(96, 4, 132, 28, 28, 16, 16, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_STORE4, RSR_ZERO4, "s[94:95]"),
-            RSR_TABLE(96, 4, 564, 28, 28, 124, 16, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_WIDE_LANES(RSR_LANES_F4) RSR_STORE4, RSR_ZERO4, "s[94:95]"))
+  RSR_STEPS(RSR_TABLE("table", 96, 4, 132, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_STORE4, RSR_ZERO4, "s[94:95]"),
+            RSR_TABLE("wide", 96, 4, 564, RSR_READ4, RSR_ADD_F4, RSR_FIRST_F4, RSR_WIDE_LANES(RSR_LANES_F4) RSR_STORE4, RSR_ZERO4, "s[94:95]"))
   __device__ static __forceinline__ void step4(uint32_t w0, uint32_t w1, Sums& acc, uint32_t heads, const Steps& s) {
     asm volatile(RSR_FIND RSR_EXTRACT2(4, 96, 100, 0) RSR_EXTRACT2(4, 104, 108, 1) RSR_CALL
                  : "+{v[112:115]}"(acc)
