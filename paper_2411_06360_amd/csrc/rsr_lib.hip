@@ -866,7 +866,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     // steps at a time (registers).
     auto fold_steps = [&]<int G>(int i0) {
       constexpr int P = M::slot_bytes == 16 ? 1 : V < 4 ? G : G < 2 ? G : 2;
-      constexpr int kPart = M::slot_bytes == 4 ? (P < 4 ? P : 4) : 1;
+      constexpr int kPart = M::slot_bytes == 4 ? (P < 4 ? P : 4) : M::slot_bytes == 8 ? P : 1;
       AT x[G][V];
       unsigned char* const rows = first_quad + i0 * kRowBytes;
 #pragma unroll
@@ -944,7 +944,10 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
         }
       }
     };
-    constexpr int kTogether = PLAIN || M::slot_bytes > 4 ? 2 : V > 1 ? 4 : 8;
+    // (Slots of 8 bytes: two steps together, and the second part's slots one step at a time, are three waits where one does.  Ternary
+    // 7388 x 5593, k = 11, two float vectors: 11.05 us so, 10.24 with four steps and their second part at once; 5215 x 1990, sixteen int8
+    // vectors, four per pass: 12.8 and 12.1.)
+    constexpr int kTogether = PLAIN || M::slot_bytes > 8 ? 2 : V > 1 ? 4 : 8;
     if (frows % kTogether == 0)
 #pragma unroll 1
       for (int i = 0; i < frows; i += kTogether) fold_steps.template operator()<kTogether>(i);
