@@ -1095,14 +1095,21 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     // The wavefront takes its next unit only here, behind the fold of a panel that it may have had to do and the wait for room: while it
     // folds it holds back one unit of another panel, not two (binary 16384^2, eight vectors: 44.1 us with
     // the next unit taken ahead of the fold, 41.6 so; eight int8 vectors 34.6 and 31.4; transformer block, sixteen vectors 79.2 and 73.8).
+    // Several vectors per pass, whose fold is long: in the last step ahead of that unit's loads, so that the last units go to the
+    // wavefronts that are furthest on.  In the first step they went to whichever had started first, units of long segments among them, which
+    // end last and whose wavefronts then fold: ternary 7672 x 2776, k = 9, two vectors, 9.2 us and 8.6 so.  One vector: in the first step;
+    // later, the compiler has the first sums wait for one load more (ternary 4096^2: 5.4 us and 5.6).
+    constexpr int kTake = V > 1 ? NG / 2 - 1 : 0;
     uint32_t ix1;
-    if (__builtin_expect(full != 0, 1)) {
-      ix1 = M::template step8<true>(e[0][0], e[0][1], e[0][2], e[0][3], acc, D.heads_lo, steps, p.off_ctr);
+#pragma unroll
+    for (int gq = 0; gq < kTake; ++gq) step(gq);
+    if (__builtin_expect(full > (uint32_t)kTake, 1)) {
+      ix1 = M::template step8<true>(e[kTake][0], e[kTake][1], e[kTake][2], e[kTake][3], acc, D.heads_lo >> (8 * kTake), steps, p.off_ctr);
     } else {
       ix1 = lds_count_up(p.off_ctr);
     }
 #pragma unroll
-    for (int gq = 1; gq < NG / 2; ++gq) step(gq);
+    for (int gq = kTake + 1; gq < NG / 2; ++gq) step(gq);
     // The next unit's loads go out one by one between the later steps: a wavefront that issues a whole unit at once waits
     // for room in the memory pipeline while it could be summing.
     Desc D1 = load_desc(unit_words, ix1 < n_tot ? u_begin + ix1 : 0u);  // past the end it reads unit 0 (unused)
