@@ -97,10 +97,14 @@ struct LaunchPlan {
 constexpr int kManyPanels = 16;  // panels per block from which the records of one block may do
 constexpr int kMostBuffers = 8;  // panels in flight per workgroup at most
 
-inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // x / d for small x as the high half of a product (d >= 2)
 inline uint32_t magic(uint32_t d) { return d < 2 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+
+// How many workgroups of so many bytes share a compute unit's LDS, which is given out in pieces of 1280 bytes (binary 4713 x 1264, k = 11,
+// eleven vectors, two per pass: three workgroups of 54 000 bytes, 690 in all, were planned where two fit, and took two rounds).
+constexpr int groups_in_lds(size_t bytes, size_t lds_max) { return (int)(lds_max / align_up(bytes, 1280)); }
 
 // Launch shape of one row tile for `batch` vectors on `num_cu` compute units in mode M.
 // `max_wg_per_cu`: how many workgroups of this product may share a compute unit (a launch that carries
@@ -155,7 +159,7 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
     const int most = (int)std::min<int64_t>(kMostBuffers, panels_per_wg), least = (int)std::min<int64_t>(2, panels_per_wg);
     auto most_that_fit = [&]() {
       int n = most;
-      while (n > least && (total(n) > h.lds_max || (wg > 1 && (size_t)wg * total(n) > h.lds_max))) --n;
+      while (n > least && (total(n) > h.lds_max || (wg > 1 && groups_in_lds(total(n), h.lds_max) < wg))) --n;
       return n;
     };
     one_block = false;
@@ -169,7 +173,7 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
     }
     // (of five wavefronts only two workgroups share a compute unit, all other sizes fill its sixteen: timed with kernels that spin,
     // 256 * wg workgroups of n wavefronts at this register count, n = 1 .. 16; ternary 2902 x 6720, k = 9: 9.4 -> 6.7 us)
-    if (wg == 1 || (wg * waves <= 16 && !(wg == 3 && waves == 5) && (size_t)wg * total(nbuf) <= h.lds_max)) break;
+    if (wg == 1 || (wg * waves <= 16 && !(wg == 3 && waves == 5) && groups_in_lds(total(nbuf), h.lds_max) >= wg)) break;
   }
   p.g1 = (int)g1;
   p.sets = (int)sets; p.sets_magic = magic((uint32_t)sets);

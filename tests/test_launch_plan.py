@@ -124,3 +124,13 @@ def test_small_panels_do_not_count_as_lack_of_room(shim, i8):
     """Eight panels in flight are the most there can be: with a unit per panel that is no reason to take narrow passes."""
     assert product(shim, 1472, 30464, 8, 1, 0, 11, i8, 1).vectors == 4
     assert product(shim, 1024, 9881, 9, 1, 0, 2, i8, 1).vectors == 1  # (few units: a vector per pass)
+
+
+@pytest.mark.parametrize("i8", [0, 1])
+def test_workgroups_share_the_lds_in_pieces_of_1280_bytes(shim, i8):
+    """Three workgroups of just under a third of the LDS do not fit: those that are planned would wait for a second round."""
+    for rows in range(1000, 30000, 13):
+        for k, batch in ((9, 8), (11, 11), (11, 2), (12, 3)):
+            a = product(shim, rows, 115 * k, k, 1, 0, batch, i8, 4)
+            per_cu = min(16 // a.waves, LDS // (-(-a.lds // 1280) * 1280))
+            assert a.grid <= CUS * per_cu, (rows, k, batch, a.lds, a.grid)
