@@ -70,7 +70,7 @@ constexpr uint64_t kMagic = 0x5253522b2b763031ull;  // "RSR++v01"
 
 // One row tile of the index on the device (a matrix of up to rsr::kTileRows rows has one).
 struct DeviceTile : rsr::PlanTile {
-  size_t stream_bytes = 0, unit_bytes = 0, blk_bytes = 0, extra_bytes = 0;
+  size_t unit_bytes = 0, blk_bytes = 0, extra_bytes = 0;
   void* d_tables = nullptr;  // the allocation that holds them all
   void* d_stream = nullptr;
   void* d_units = nullptr;

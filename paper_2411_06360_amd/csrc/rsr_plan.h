@@ -4,6 +4,7 @@
 #define RSR_PLAN_H_
 
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <cstring>
@@ -30,6 +31,7 @@ struct PlanTile {
   bool fill = false;  // absent values are stored as zeros: a panel's slots need no clearing
   uint32_t max_units_per_block = 0;
   int64_t nunits = 0;
+  size_t stream_bytes = 0;  // of all units: kPositionBytes per position
 };
 struct PlanMatrix {
   int num_cu = 0;
@@ -202,62 +204,69 @@ enum class Mode { one, two, four };
 inline const Pass& pass_of(bool i8, Mode m) {
   return m == Mode::four ? (i8 ? kP4 : kF4) : m == Mode::two ? (i8 ? kP2 : kF2) : (i8 ? kI1 : kF1);
 }
-// What a launch has to do per vector, over all products that share it: units, and steps of the fold (kFoldRow slots).
-struct Load {
-  double units = 0, folds = 0;
-  void add(const PlanMatrix& h, const PlanTile& T) {
-    units += (double)T.nunits;
-    folds += (double)h.nblocks * T.shape.panels * (T.shape.nslots / kFoldRow);
-  }
-};
-// A unit of the stream keeps its share of a panel's sums in LDS from its start until the panel is folded, longer than
-// it is summed: with room for the sums of fewer units in flight (kRoom: float, kRoom8: int8) wavefronts stand still.  Returns the
-// sums of how many units a workgroup has room for, 1e9 if the LDS does not limit the panels in flight, 0 if the pass does not fit.
-// `cus`: the compute units that the product has, the device's or its share of a launch (fewer: more blocks per workgroup,
-// which need a second panel in flight).
-constexpr double kRoom = 28, kRoom8 = 50;
-inline double room_for(const Pass& M, const PlanMatrix& h, const PlanTile& T, int batch, int cus) {
-  LaunchPlan plan;
-  if (plan_tile(M, h, T, false, batch, cus, 1, &plan) != RSR_OK) return 0;
-  const int64_t panels = h.nblocks * T.shape.panels, per_wg = (h.nblocks + plan.p.g1 - 1) / plan.p.g1 * T.shape.panels;
-  return plan.p.nbuf >= std::min<int64_t>(kMostBuffers, per_wg) ? 1e9 : (double)plan.p.nbuf * (double)T.nunits / (double)panels;
-}
-// Which pass.  A pass over V vectors takes as many times less units and folds, each of which costs more, and more rows to
-// stage; a launch with less than a unit per wavefront of the device takes as long as one unit does (and a device nearly full of units
-// somewhat longer than one half full): few units are better spread out, a vector per pass.  The constants, in the time of a full round
-// of units with one vector, are fitted to 170 matrices of 1024 to 32768 rows (binary, ternary, correlated; k from 8 to
-// 13), 2 to 16 vectors, in all three passes: on average the choice is 1.1 % (float) and 1.2 % (int8) slower than the best of the three; fitted to
-// every other product 1.1 and 1.1 % on the rest; 1.0 and 1.3 % on 2478 other matrices.  (With the constants of the kernels that tested and branched at every position: 1.7 and 1.8 %;
-// ternary 6703 x 13056, k = 11, five int8 vectors: 27.2 us with four per pass, 20.7 with two.)
+// Which pass.  A pass over V vectors takes as many times less units and folds, each of which costs more, and stages more rows.  A launch
+// is estimated from its plan: how many rounds of workgroups an XCD goes through (the siblings of a block range share one: with fewer
+// than eight block ranges some XCDs stay idle), and how long a round takes: the start and the rows staged, and then the longest of what
+// keeps the compute unit busy, of a wavefront's units and a fold one after the other, and of the panels that wait for room, where
+// there are more than fit (the root of the sum of the squares: none hides the others entirely).  In microseconds, fitted to the times of all
+// three passes of 2227 matrices on an MI355X: 1585 of 1024 to 32768 rows with k from 8 to 13 and 642 of 16 to 32768 rows with k from 1 to
+// 16 (binary, ternary, correlated; 2 to 300 vectors).  On average the choice is 0.3 (float) and 0.7 % (int8) slower than the best of the
+// three; 0.4 and 0.7 % on one half of the matrices with the constants fitted to the other half.  The rule before (rounds of units of the whole
+// device, and a count of the units that have room; fitted to 170 matrices of the first kind and up to sixteen vectors): 1.2 and 1.5 %,
+// and up to twice the time (ternary 16867 x 47, k = 8, 64 float vectors: 20.0 us with one per pass, 10.4 with two; binary 4868 x 19245,
+// k = 11, eleven: 41 and 27).
 struct PassCosts {
-  double full, busy;                   // a round of units: 1, or full + busy * rounds where that is more
-  double start, unit, fold, rows;      // once, per round of units, per round of folds, per 16384 rows
+  double once, round;         // of a launch, of a round of workgroups
+  double stage, odd;          // per 64 KB staged, and on top where the rows are no multiple of four (narrow loads)
+  double share;               // staging per further workgroup on the compute unit
+  double unit, second;        // latency of a unit of 48 positions; on top for a wavefront with more than one
+  double sum, positions;      // the compute unit busy with 16 units, and with their positions
+  double fold, panel, busy;   // latency of a fold of 2048 slots; busy with 16 panels, and with 2048 slots of each
+  double wait;                // panels that wait for room
+  double crowd;               // exponent of the workgroups that share a compute unit
 };
 constexpr PassCosts kCosts[2][3] = {  // [int8][one, two, four vectors]
-    {{0.45, 0.85, 0, 1, 0.2, 0}, {0.45, 0.85, 0, 1.2, 0.5, 0.9}, {0.45, 0.85, 0.25, 2.35, 0.65, 1.7}},
-    {{0.35, 0.9, 0, 1, 0, 0}, {0.35, 0.9, 0, 1.1, 0.05, 0}, {0.35, 0.9, 0, 1.3, 0.4, 2.2}}};
-inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, const Load& load, int cus) {
+    {{1.764, 2.260, 0.532, 2.716, 0.543, 1.168, 1.104, 1.099, 0.007, 0.589, 0.968, 0.495, 1.133, 0.973},
+     {2.390, 2.697, 1.085, 0.213, 0.420, 0.827, 0.736, 0.926, 0.666, 0.934, 1.147, 2.188, 1.259, 0.853},
+     {2.055, 3.303, 2.265, 0.090, 0.000, 0.580, 1.828, 0.454, 2.303, 2.437, 1.230, 7.893, 1.681, 1.131}},
+    {{1.896, 1.799, 1.295, 0.862, 0.750, 1.035, 1.730, 1.048, 0.039, 0.508, 0.928, 0.785, 1.431, 0.916},
+     {1.899, 2.131, 1.123, 1.290, 1.580, 1.094, 1.760, 1.124, 0.122, 0.775, 1.693, 1.448, 1.467, 0.928},
+     {2.361, 2.728, 1.370, 1.386, 0.486, 1.444, 0.000, 0.888, 1.562, 0.405, 1.692, 6.280, 1.476, 0.924}}};
+// Estimated microseconds of a launch on `cus` compute units, 1e30 if there is none.
+inline double pass_time(bool i8, Mode m, const PlanMatrix& h, const PlanTile& T, int batch, int cus, int max_wg_per_cu) {
+  const Pass& M = pass_of(i8, m);
+  const PassCosts& c = kCosts[i8][(int)m];
+  LaunchPlan plan;
+  if (plan_tile(M, h, T, false, batch, cus, max_wg_per_cu, &plan) != RSR_OK) return 1e30;
+  const KArgs& p = plan.p;
+  const double on_xcd = std::max(1.0, cus / 8.0), groups = (double)((p.g1 + 7) / 8) * p.sets;
+  const double fit = std::max(1.0, std::min(plan.waves == 5 ? 2.0 : (double)(16 / plan.waves), (double)groups_in_lds(plan.lds, h.lds_max)));
+  const double rounds = std::max(1.0, std::ceil(groups / (on_xcd * fit))), together = std::min(fit, std::ceil(groups / on_xcd));
+  const double blocks = (double)((h.nblocks + p.g1 - 1) / p.g1);  // of the largest share
+  const double units = blocks * (double)T.nunits / (double)h.nblocks, per_wave = units / plan.waves;
+  const double panels = blocks * T.shape.panels, slots = T.shape.nslots / 2048.0;
+  const double positions = (double)T.stream_bytes / (48.0 * kPositionBytes * (double)std::max<int64_t>(1, T.nunits));
+  const double staged = (double)(T.rows << M.shift) / 65536;
+  const double unit = c.unit * positions, fold = c.fold * slots;
+  const double busy = std::pow(together, c.crowd) * (units * (c.sum + c.positions * positions) + panels * (c.panel + c.busy * slots)) / 16;
+  const double chain = std::max(1.0, per_wave) * unit + (per_wave > 1 ? c.second : 0.0) + fold;
+  const double room = c.wait * std::max(0.0, panels / p.nbuf - 1) * (unit + fold);
+  return c.once + rounds * (c.round + (c.stage + (T.rows % 4 ? c.odd : 0.0)) * staged * (1 + c.share * (together - 1)) +
+                            std::sqrt(busy * busy + chain * chain + room * room));
+}
+inline Mode shortest(const double (&time)[3]) { return time[2] < time[1] && time[2] < time[0] ? Mode::four : time[1] < time[0] ? Mode::two : Mode::one; }
+inline Mode pick_mode(bool i8, const PlanMatrix& h, const PlanTile& T, int batch, int cus, int max_wg_per_cu) {
   if (h.step2_plain || batch < 2) return Mode::one;
-  const double device = (double)h.num_cu * h.waves;
-  auto cost = [&](Mode m) {
-    const Pass& M = pass_of(i8, m);
-    const double room = room_for(M, h, T, batch, cus);
-    if (room == 0) return 1e30;
-    const PassCosts& c = kCosts[i8][(int)m];
-    const double sets = (double)((batch + M.V - 1) / M.V) / device, units = load.units * sets;
-    const double rounds = std::max({1.0, units, c.full + c.busy * units});
-    return c.start + c.unit * rounds * std::max(1.0, (i8 ? kRoom8 : kRoom) / room) + c.fold * load.folds * sets + c.rows * (double)T.rows / 16384;
-  };
-  const double c1 = cost(Mode::one), c2 = cost(Mode::two), c4 = cost(Mode::four);
-  return c4 < c2 && c4 < c1 ? Mode::four : c2 < c1 ? Mode::two : Mode::one;
+  double time[3];
+  for (const Mode m : {Mode::one, Mode::two, Mode::four}) time[(int)m] = pass_time(i8, m, h, T, batch, cus, max_wg_per_cu);
+  return shortest(time);
 }
 
 // The launch of one row tile's product.
 inline int plan_product(bool i8, const PlanMatrix& h, const PlanTile& T, bool accumulate, int batch, Mode* mode, LaunchPlan* plan) {
-  Load load;
-  load.add(h, T);
-  *mode = pick_mode(i8, h, T, batch, load, h.num_cu);
-  return plan_tile(pass_of(i8, *mode), h, T, accumulate, batch, h.num_cu, 4, plan);
+  constexpr int most = 4;  // workgroups per compute unit
+  *mode = pick_mode(i8, h, T, batch, h.num_cu, most);
+  return plan_tile(pass_of(i8, *mode), h, T, accumulate, batch, h.num_cu, most, plan);
 }
 
 // The compute units of several products that share a launch, in proportion to the bytes of their tables: multiples of 8
@@ -292,20 +301,23 @@ struct SharedJob {
   int64_t bytes;  // of its tables
 };
 constexpr int kMaxJobs = 8;
-// The widest pass that every product takes on its own share, or narrower until all of them fit (a narrower pass has more sets
-// of vectors, so fewer workgroups a set and more blocks a workgroup: that one product fits does not say that all do).  On
+// The pass in which the product that takes longest on its share takes least, or narrower until all of them fit (a narrower pass has
+// more sets of vectors, so fewer workgroups a set and more blocks a workgroup: that one product fits does not say that all do).  On
 // failure *failed is the product that has no launch.
 inline int plan_shared(bool i8, const SharedJob* jobs, int njobs, int num_cu, int batch, Mode* mode, LaunchPlan* plans, int* failed) {
   int64_t bytes[kMaxJobs];
-  Load load;
   int share[kMaxJobs];
-  for (int j = 0; j < njobs; ++j) { bytes[j] = jobs[j].bytes; load.add(*jobs[j].h, *jobs[j].T); }
+  for (int j = 0; j < njobs; ++j) bytes[j] = jobs[j].bytes;
   split_device(bytes, njobs, num_cu, share);
-  Mode most = Mode::four;
+  double time[3] = {0, 0, 0};
+  bool one = batch < 2;
   for (int j = 0; j < njobs; ++j) {
     share[j] = std::min(share[j], jobs[j].h->num_cu);
-    most = std::min(most, pick_mode(i8, *jobs[j].h, *jobs[j].T, batch, load, share[j]));
+    one = one || jobs[j].h->step2_plain;
   }
+  for (const Mode m : {Mode::one, Mode::two, Mode::four})
+    for (int j = 0; j < njobs && !one; ++j) time[(int)m] = std::max(time[(int)m], pass_time(i8, m, *jobs[j].h, *jobs[j].T, batch, share[j], 1));
+  const Mode most = one ? Mode::one : shortest(time);
   int rc = RSR_OK;
   for (const Mode m : {Mode::four, Mode::two, Mode::one}) {
     if (m > most) continue;

@@ -23,7 +23,7 @@ PlanMatrix matrix_of(const Request& r, int num_cu, int64_t lds_max) {
 PlanTile tile_of(const Request& r, const PlanMatrix& h) {
   PlanTile t;
   t.rows = r.rows; t.shape = panel_shape(r.rows, r.k, r.planes ? r.planes : r.parts, r.planes == 0);
-  t.max_extras = r.max_extras; t.nunits = r.units;
+  t.max_extras = r.max_extras; t.nunits = r.units; t.stream_bytes = (size_t)r.units * 40 * kPositionBytes;
   t.max_units_per_block = (uint32_t)((r.units + h.nblocks - 1) / h.nblocks);
   return t;
 }

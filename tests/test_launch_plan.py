@@ -134,3 +134,24 @@ def test_workgroups_share_the_lds_in_pieces_of_1280_bytes(shim, i8):
             a = product(shim, rows, 115 * k, k, 1, 0, batch, i8, 4)
             per_cu = min(16 // a.waves, LDS // (-(-a.lds // 1280) * 1280))
             assert a.grid <= CUS * per_cu, (rows, k, batch, a.lds, a.grid)
+
+
+@pytest.mark.parametrize("rows,cols,k,parts,units,batch,i8,vectors", [
+    (4868, 19245, 11, 1, 5618, 11, 0, 2),    # 41 us with one vector per pass, 27 with two
+    (4608, 14028, 11, 1, 3932, 11, 0, 2),    # 31 and 21
+    (4901, 21824, 11, 2, 13891, 11, 0, 2),   # 94 and 68
+    (5056, 26112, 10, 2, 13878, 64, 1, 4),   # 215 with two, 154 with four
+    (10402, 70, 6, 2, 120, 64, 0, 2),        # 13.6 with one, 8.7 with two
+    (16867, 47, 8, 2, 100, 64, 0, 2),        # 20.0 and 10.4
+    (12587, 1596, 11, 1, 881, 300, 0, 2),    # 167 and 116
+    (72, 9720, 11, 1, 884, 300, 0, 2),       # 215 and 161
+    (23987, 3427, 13, 1, 3634, 11, 1, 2),    # 33.0 and 23.6
+    (4744, 249, 14, 1, 72, 64, 1, 2),        # 16.3 and 11.6
+    (3912, 71, 16, 1, 80, 64, 1, 2),         # 16.1 and 11.3
+])
+def test_the_pass_that_was_measured_to_be_shortest(shim, rows, cols, k, parts, units, batch, i8, vectors):
+    """Units as the builder gives them; workgroups of several rounds, of few block ranges, of panels that wait for room."""
+    r, a = Request(rows, cols, units, k, parts, 0, 64, batch, i8), Answer()
+    assert shim.shim_product(ctypes.byref(r), CUS, LDS, ctypes.byref(a)) == 0
+    check(a, (rows, cols, k))
+    assert a.vectors == vectors
