@@ -4,6 +4,7 @@ from __future__ import annotations
 import numpy as np
 
 import paper_2411_06360_amd as R
+from tests.launch_plan import vectors_per_pass
 
 
 class DeviceIndex:
@@ -57,3 +58,13 @@ def assert_f32_close(got: np.ndarray, exact64: np.ndarray, v: np.ndarray, rel: f
     worst = float((err / bound).max())
     assert worst <= 1.0, f"max error is {worst:.3g} x the allowed 1e-5*sum|v|"
     return worst
+
+
+def batch_per_pass(planner, info, i8: bool, max_extras: int = 0) -> dict:
+    """{1: .., 2: .., 4: ..}: the smallest of some batches (most of them leave a last set with fewer vectors) whose product takes a pass
+    over so many vectors.  All three have to be reached."""
+    found = {}
+    for batch in (1, 2, 3, 5, 7, 9, 11, 13, 17, 23, 33, 49, 65, 97, 131, 195, 263, 390, 521, 1043):
+        found.setdefault(vectors_per_pass(planner, info, batch, i8, max_extras), batch)
+    assert set(found) == {1, 2, 4}, (found, info.rows, info.cols, info.k, info.work_units)
+    return found

@@ -1,4 +1,4 @@
-// The launch planner (csrc/rsr_plan.h) behind plain C functions, for tests/test_launch_plan.py.
+// The launch planner (csrc/rsr_plan.h) behind plain C functions, for tests/launch_plan.py.
 #include "rsr_plan.h"
 
 using namespace rsr;
@@ -8,6 +8,7 @@ struct Request {  // an index as the builder would make it, and the call
   int64_t rows, cols, units;  // units: of the whole tile
   int32_t k, parts, planes;   // planes > 0: bit planes in place of parts
   int32_t max_extras, batch, i8;
+  int64_t stream;  // bytes of the units; 0: 40 positions each
 };
 struct Answer {
   int64_t grid, lds, vectors, waves, buffers, workgroups, end_of_lds;
@@ -23,7 +24,7 @@ PlanMatrix matrix_of(const Request& r, int num_cu, int64_t lds_max) {
 PlanTile tile_of(const Request& r, const PlanMatrix& h) {
   PlanTile t;
   t.rows = r.rows; t.shape = panel_shape(r.rows, r.k, r.planes ? r.planes : r.parts, r.planes == 0);
-  t.max_extras = r.max_extras; t.nunits = r.units; t.stream_bytes = (size_t)r.units * 40 * kPositionBytes;
+  t.max_extras = r.max_extras; t.nunits = r.units; t.stream_bytes = (size_t)(r.stream ? r.stream : r.units * 40 * kPositionBytes);
   t.max_units_per_block = (uint32_t)((r.units + h.nblocks - 1) / h.nblocks);
   return t;
 }

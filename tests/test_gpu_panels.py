@@ -1,14 +1,15 @@
 """The index in panels of ranked segments (csrc/rsr_layout.h) and the passes over one, two and four vectors, at the sizes
 where they change course: panels of fewer values than a fold step reads, both parts in one panel or in several, row
 counts on either side of the widths a segment may take (one lane, eight lanes, several pieces, more pieces than are fetched ahead
-of the fold), odd rows and batches.  Which pass a call takes depends on how many units the launch has: large batches of
-small matrices reach those over two and four vectors."""
+of the fold), odd rows and batches.  Which pass a call takes depends on how many units the launch has: the segment lengths are
+repeated over so many column blocks that all three are taken, which is asserted."""
 import numpy as np
 import pytest
 
 import paper_2411_06360_amd as R
 from oracle import dense, steps
-from tests.gpu_util import DeviceIndex, assert_f32_close
+from tests.gpu_util import DeviceIndex, assert_f32_close, batch_per_pass
+from tests.launch_plan import build
 
 pytestmark = pytest.mark.gpu
 
@@ -58,10 +59,16 @@ def test_panel_shapes(k):
             check_products(d, A, (1, 3, 1201), 310 + k)
 
 
-@pytest.mark.parametrize("lengths", [
-    [1, 1, 1], [5, 6, 7, 8, 9], [47, 48, 49], [46, 46, 47, 47, 48, 95, 96], [255, 256, 257], [256] * 9, [511, 512, 513, 3],
-    [3000, 1, 1, 700], [1] * 63 + [64], [1] * 65, list(range(1, 70)),
-])
+LENGTHS = [[1, 1, 1], [5, 6, 7, 8, 9], [47, 48, 49], [46, 46, 47, 47, 48, 95, 96], [255, 256, 257], [256] * 9, [511, 512, 513, 3],
+           [3000, 1, 1, 700], [1] * 63 + [64], [1] * 65, list(range(1, 70))]
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    return build(str(tmp_path_factory.mktemp("plan")))
+
+
+@pytest.mark.parametrize("lengths", LENGTHS)
 def test_segment_lengths(lengths):
     A = with_segments(lengths, 9, sum(lengths))
     print(f"segments of {lengths[:8]}.. rows: {A.shape}", flush=True)
@@ -71,6 +78,27 @@ def test_segment_lengths(lengths):
     A = np.tile(A, (1, 16))  # more blocks: more units, other passes
     with DeviceIndex(A, 9) as d:
         check_products(d, A, (301, 602), 18)
+
+
+@pytest.mark.parametrize("lengths", LENGTHS)
+def test_segment_lengths_in_every_pass(planner, lengths):
+    A = with_segments(lengths, 9, sum(lengths))
+    times = 200
+    print(f"segments of {lengths[:8]}.. rows in every pass: {A.shape} x {times}", flush=True)
+    g = np.random.default_rng(27)
+    with DeviceIndex(np.tile(A, (1, times)), 9) as d:
+        for i8 in (True, False):
+            for vectors, batch in batch_per_pass(planner, d.info, i8, 2 * sum((n - 1) // 256 for n in lengths)).items():
+                if i8:
+                    v = g.integers(-128, 128, size=(batch, A.shape[0]), dtype=np.int8)
+                    v[: batch // 2] = -128  # (a segment of 256 such rows sums to the lowest 16-bit number)
+                    assert np.array_equal(d.matvec(v).astype(np.int64), np.tile(dense.matvec_i8(A, v), (1, times))), (vectors, batch)
+                else:
+                    v = g.standard_normal((batch, A.shape[0])).astype(np.float32)
+                    got = d.matvec(v)
+                    assert_f32_close(got, np.tile(dense.matvec_f32(A, v), (1, times)), v)
+                    for j in (0, batch // 2, batch - 1):
+                        assert np.array_equal(got[j], d.matvec(v[j])), (vectors, batch, j)
 
 
 def test_more_pieces_than_are_fetched_ahead_of_the_fold():

@@ -2,34 +2,15 @@
 fits, whatever the planner takes for its pass.  The planner is compiled here as it stands; the indexes are made up, with as
 many units and extra slots as the builder can give them."""
 import ctypes
-import os
-import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CUS, LDS = 256, 160 * 1024  # of an MI355X
-
-
-class Request(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int64) for n in ("rows", "cols", "units")] + [(n, ctypes.c_int32) for n in ("k", "parts", "planes", "max_extras", "batch", "i8")]
-
-
-class Answer(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int64) for n in ("grid", "lds", "vectors", "waves", "buffers", "workgroups", "end_of_lds")]
+from tests.launch_plan import CUS, LDS, Answer, Request, build
 
 
 @pytest.fixture(scope="module")
 def shim(tmp_path_factory):
-    so = str(tmp_path_factory.mktemp("plan") / "plan_shim.so")
-    subprocess.run(["g++", "-O2", "-std=c++20", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2411_06360_amd", "csrc"),
-                    os.path.join(ROOT, "tests", "plan_shim.cpp"), "-o", so], check=True)
-    lib = ctypes.CDLL(so)
-    lib.shim_panels.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
-    lib.shim_planes_per_handle.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 2
-    lib.shim_product.argtypes = [ctypes.POINTER(Request), ctypes.c_int, ctypes.c_int64, ctypes.POINTER(Answer)]
-    lib.shim_shared.argtypes = [ctypes.POINTER(Request), ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.POINTER(Answer)]
-    return lib
+    return build(str(tmp_path_factory.mktemp("plan")))
 
 
 def request(shim, rows, cols, k, parts=2, planes=0, batch=1, i8=0, units_per_panel=2):
