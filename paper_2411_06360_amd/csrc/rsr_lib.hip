@@ -804,7 +804,9 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   // wavefronts' first units for a microsecond: requested together before the barrier they hold up the activations and the
   // barrier, requested together behind it the first sums.  Two granules with the descriptor, one behind the staging where that is
   // long, the rest behind the barrier (granules before the staging + before the barrier, us: binary 16384^2 1+0 13.7, 2+0 13.2, 2+1 12.9,
-  // 3+0 13.1, 6+0 13.7; transformer block 1+0 27.0, 2+0 26.1, 2+1 26.5, 3+0 26.5, 6+0 28.3).
+  // 3+0 13.1, 6+0 13.7; transformer block 1+0 27.0, 2+0 26.1, 2+1 26.5, 3+0 26.5, 6+0 28.3).  Where the line lies, 2+1 against 2+0 at 16 row counts,
+  // two matrices each: one float vector +0.6 % up to 48 KB of activations, -0.6 % from 52 to 64 KB, equal above; two and four -0.5 to -2 % from 54 KB; one
+  // int8 vector -1 % throughout; two and four, whose staging widens what it reads and waits for it, +1.5 % and +2 % from 80 KB: not there.
   auto first_loads = [&](int from) {
 #pragma unroll
     for (int gq = 2; gq < NG; ++gq)
@@ -816,7 +818,8 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     issue_granule(rs0, 0, eA);
     issue_granule(rs0, 1, eA);
   }
-  if (p.rows << M::shift >= kLongStaging) {
+  constexpr bool kThird = V == 1 || sizeof(typename M::In) == 4;
+  if (kThird && p.rows << M::shift >= kLongStaging) {
     issue_granule(rs0, 2, eA);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
