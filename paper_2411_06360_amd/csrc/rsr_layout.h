@@ -14,7 +14,7 @@
 //     to the 64 lanes of a wavefront in rank order: a GROUP is 64 consecutive segments, one per lane, walked for as
 //     many positions as its longest segment has rows.  Ranking makes the 64 segments of a group almost equally long,
 //     so that no lane needs a flag of its own: where a group ends is the same position for all lanes, a bit of a mask
-//     in the unit's descriptor (a scalar branch), and the position behind it, the HEAD, holds the lanes' slots.
+//     in the unit's descriptor (which picks the code of a step), and the position behind it, the HEAD, holds the lanes' slots.
 //     Among segments of equal length the order is such that the slots of neighbouring lanes lie in different LDS
 //     banks.  Shorter segments in a group, and the lanes of a group that is not full, read the null row index `rows`
 //     (a zero kept behind the activations in LDS); lanes without a segment store to a dummy slot.

@@ -205,10 +205,13 @@ __device__ __forceinline__ void lds_clear(uint32_t lds_byte_addr) {
 // vector; a head stores the running sums to the panel's slot (byte address s91 + slot) and restarts them.  Which positions of a
 // step are heads is one of 2^8 (2^4) patterns, the same for all lanes, and every pattern has straight code of its own
 // in a table that the assembler expands: the step's addresses are extracted to fixed registers and the code of its pattern is called.
-// With a bit test and a branch per position in their place a wavefront issued 90 branches per unit (26 now), and gathered at the
+// With a bit test and a branch per position in their place a wavefront issued 90 branches per unit (24 now), and gathered at the
 // heads too (one position in five, an LDS read of 3 clocks each): binary 16384^2, k = 12, eight vectors 49.8 -> 44.5 us, eight int8
 // vectors 37.3 -> 35.2, transformer block with sixteen vectors 90.0 -> 85.7; one vector, bound by the stream: 13.6 -> 13.7.
-// A table takes 33 to 58 KB, of which an index uses the patterns of its groups' lengths (some sixty).
+// Tables, in KB, and those of wide units: F1 and I1 33 + 8, F2 and P2 41 + 11, P4 57 + 17, F4 (four positions) 2 + 9; an index uses the
+// patterns of its groups' lengths (some sixty).  P4 by four positions too (10 KB): of a million instruction fetches of a launch 3.4 thousand
+// miss instead of 7.0 (ternary 5215 x 1990, k = 11, sixteen vectors), which is not what that launch waits for (12.7 us, 12.5 so); over 520 matrices
+// with 2 to 64 vectors 0.2 to 1.5 % more time, from 8 % more (2112 x 2112, eleven vectors: 7.8 us, 8.5 so) to 2 % less.
 // All gathers of a step are issued before the first sum so that their latencies overlap; the wait before the add of a
 // position allows as many LDS operations as follow it (they complete in order; scalar loads that are under way besides only make
 // the wait stricter).  Every gather has been waited for when its step returns.
@@ -253,7 +256,9 @@ struct Steps {
   uint64_t code;
   uint32_t stride, base;  // base: LDS byte address of the panel's slots
 };
-// Emits a mode's table into the kernel (once per kernel: the wavefronts jump over it) and returns its address.
+// Emits a mode's table into the kernel (once per kernel: the wavefronts jump over it) and returns its address.  The compiler takes a .rept for
+// a few instructions and plans short branches: they reach 128 KB, the largest kernel (P4) has 109; beyond that the assembler refuses
+// the branches over the table.
 #define RSR_STEPS(TABLE, WIDE)                                                                                 \
   __device__ static __forceinline__ uint64_t table() {                                                         \
     uint32_t lo, hi;                                                                                           \
@@ -835,7 +840,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
 
   // ---- the fold of a panel, and the completion of its block, by the wavefront that has summed its last unit ----
   auto fold = [&](const Desc& D, uint32_t buf, uint32_t ubase, uint32_t extra_pair) {
-    // (so are the lane masks below, for which the lane's number has to look new)
+    // (the lane's number has to look new, or the masks made of it below would be kept in scalar registers from the start of the kernel)
     int lane = tid & 63;
     asm volatile("" : "+v"(lane));
     // (The sums in LDS need no fence: LDS operations of a wavefront execute in order, so those of every unit of the panel were

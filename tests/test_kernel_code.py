@@ -1,5 +1,5 @@
 """The code of the product kernels as the compiler leaves it: where the assembler puts the entries of a table of patterns
-(csrc/rsr_lib.hip, RSR_TABLE)."""
+(csrc/rsr_lib.hip, RSR_TABLE), and how large the kernels are."""
 import os
 import re
 import struct
@@ -74,3 +74,11 @@ def test_patterns_lie_a_stride_apart_whatever_their_instructions_take(tmp_path, 
 def test_a_pattern_longer_than_the_stride_is_an_error(tmp_path):
     run, _ = table_of(tmp_path, 32, 2)
     assert run.returncode != 0 and ".org" in run.stdout, run.stdout
+
+
+def test_every_kernel_is_within_reach_of_a_branch():
+    """A short branch reaches 128 KB, and the compiler, which takes a .rept for a few instructions, plans no others."""
+    if not os.path.exists(build.LIB):
+        build.build()
+    sizes = {name: len(code) for name, code in functions(build.LIB).items()}
+    assert len(sizes) > 14 and max(sizes.values()) < 120 * 1024, sizes
