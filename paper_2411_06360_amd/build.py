@@ -17,10 +17,11 @@ SOURCES = ["rsr_lib.hip", "rsr_dense.hip", "rsr_prep.hip", "rsr_pack.cpp", "rsr_
 ARCH = "gfx950"
 
 # -packed-fp32-ops off: the compiler must not form packed fp32 instructions from the float adds.
+# -amdgpu-kernarg-preload-count: the leading arguments of a kernel are in scalar registers when it starts.
 FLAGS = [
     "-O3", "-std=c++20", f"--offload-arch={ARCH}", "-fPIC", "-shared", "-fno-strict-aliasing",
     "-fno-gpu-rdc", "-Wall", "-Wno-unused-command-line-argument",
-    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16",
 ]
 
 

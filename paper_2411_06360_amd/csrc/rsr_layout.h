@@ -30,7 +30,7 @@
 //
 // Streams on the device:
 //   stream    bytes   unit streams, back to back, each on a 128-byte boundary
-//   units     PUnit   32-byte descriptors, in panel order
+//   units     PUnit   32-byte descriptors, in panel order, and room for kUnitsBehind more (read ahead by wavefronts that have no unit)
 //   blk_unit  uint32  nblocks+1 offsets into `units`
 #ifndef RSR_LAYOUT_H_
 #define RSR_LAYOUT_H_
@@ -49,6 +49,8 @@ constexpr int kWideRows = 256;                       // rows of a piece of a seg
 // Passes over several int8 vectors keep a slot's sum in 16 bits: kWideRows entries of -128 .. 127 are what these hold.
 static_assert(kWideRows * 128 <= 32768 && kWideRows * 127 <= 32767, "the sum of a slot has to fit 16 bits");
 constexpr int kMaxExtras = 2 * 32768 / kWideRows;    // extra slots of a panel at most (both parts of 32768 rows)
+
+constexpr int kUnitsBehind = 16;                     // as many as a workgroup has wavefronts
 
 struct alignas(16) PUnit {
   uint32_t stream_off;   // in multiples of kStreamAlign bytes

@@ -126,17 +126,25 @@ using rsr::kItems;
 using rsr::LaunchPlan;
 using rsr::Mode;
 
-// A kernel's own arguments, in the memory they were passed in.
+// The leading arguments of a kernel, fourteen words (four pointers and rsr::Start), are in scalar registers when a wavefront starts
+// (-amdgpu-kernarg-preload-count, build.py); the rest it reads from the memory they were passed in.
+struct KMore {
+  const uint16_t* extra_slots;
+  void* out;
+  KArgs p;
+};
 #ifdef __HIP_DEVICE_COMPILE__
-typedef const __attribute__((address_space(4))) KArgs* KArgsPtr;
-__device__ __forceinline__ KArgsPtr args_at(size_t offset) {
-  return (KArgsPtr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + offset);
-}
+#define RSR_CONSTANT const __attribute__((address_space(4)))
+#define RSR_GLOBAL __attribute__((address_space(1)))
+__device__ __forceinline__ RSR_CONSTANT char* argument_memory() { return (RSR_CONSTANT char*)__builtin_amdgcn_kernarg_segment_ptr(); }
 #else
-typedef const KArgs* KArgsPtr;
-__device__ inline KArgsPtr args_at(size_t) { return nullptr; }  // (the host pass only has to parse the kernels)
+#define RSR_CONSTANT const
+#define RSR_GLOBAL
+__device__ inline const char* argument_memory() { return nullptr; }  // (the host pass only has to parse the kernels)
 #endif
-__device__ __forceinline__ KArgsPtr launder(KArgsPtr p) {
+typedef RSR_CONSTANT KMore* KMorePtr;
+typedef RSR_CONSTANT uint32_t* TablePtr;  // a table that is read with scalar loads
+__device__ __forceinline__ KMorePtr launder(KMorePtr p) {
   asm volatile("" : "+s"(p));
   return p;
 }
@@ -476,8 +484,8 @@ __device__ __forceinline__ Desc make_desc(uint32_t w0, uint32_t w1, uint32_t w2,
   d.extras = w5 >> 16;
   return d;
 }
-__device__ __forceinline__ Desc load_desc(const uint32_t* __restrict__ unit_words, uint32_t u) {
-  const uint32_t* w = unit_words + (size_t)__builtin_amdgcn_readfirstlane((int)u) * 8;
+__device__ __forceinline__ Desc load_desc(TablePtr unit_words, uint32_t u) {
+  const TablePtr w = unit_words + (size_t)__builtin_amdgcn_readfirstlane((int)u) * 8;
   return make_desc(w[0], w[1], w[2], w[3], w[4], w[5]);
 }
 
@@ -599,106 +607,97 @@ __device__ __forceinline__ void plain_sums(AT (&sums)[12], int step, int lane, c
 
 // The activations of a workgroup's V vectors go to LDS, row by row, the vectors of a row next to each other (int8:
 // widened to 32 bits, or to 16 where there are several).  Vectors past the batch are zeros.
+// A piece is 16 bytes of one float vector (four rows), 16 bytes of one int8 vector, 4 bytes each of several.  A thread
+// fetches kAtOnce pieces of every vector together; the caller fetches the first ones before anything else.  Pieces lie wherever the vectors
+// begin: the loads take any address (floats are on four bytes, int8 vectors of an odd number of rows are not).
 template <class M>
-__device__ __forceinline__ void stage(unsigned char* lds, const typename M::In* __restrict__ v, int64_t vstride, int nv, int rows, int first, int nt) {
-  const int tid = threadIdx.x;
-  if constexpr (M::V == 1 && sizeof(typename M::In) == 1) {
-    const int n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? rows / 16 : 0;
-    const uint4* v16 = reinterpret_cast<const uint4*>(v);
-    for (int i = tid; i < n16; i += nt) {
-      const uint4 x = v16[i];
-      const uint32_t d[4] = {x.x, x.y, x.z, x.w};
+struct Staging {
+  using In = typename M::In;
+  static constexpr bool kFloat = sizeof(In) == 4;
+  static constexpr int kAtOnce = M::V == 1 ? (kFloat ? 4 : 1) : M::V == 2 || !kFloat ? 4 : 2;
+  static constexpr int kRows = !kFloat && M::V == 1 ? 16 : 4;    // rows of a piece
+  static constexpr int kWords = !kFloat && M::V > 1 ? 1 : 4;
+  uint32_t x[kAtOnce][M::V][kWords];
+
+  // pieces i, i + nt, ... of `n`; vectors from `nv` on are zeros
+  __device__ __forceinline__ void fetch(const In* __restrict__ v, int vstride, int nv, int i, int n, int nt) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        reinterpret_cast<int4*>(lds)[4 * i + j] =
-            make_int4((int32_t)(d[j] << 24) >> 24, (int32_t)(d[j] << 16) >> 24, (int32_t)(d[j] << 8) >> 24, (int32_t)d[j] >> 24);
-    }
-    for (int i = n16 * 16 + tid; i < rows; i += nt) reinterpret_cast<int32_t*>(lds)[i] = v[i];
-  } else if constexpr (M::V == 1) {  // rows from `first` on (the caller has staged the ones before)
-    const int n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? rows / 4 : 0;
-    for (int i = first + tid; i < n16; i += nt) reinterpret_cast<uint4*>(lds)[i] = reinterpret_cast<const uint4*>(v)[i];
-    for (int i = n16 * 4 + tid; i < rows; i += nt) reinterpret_cast<float*>(lds)[i] = v[i];
-  } else if constexpr (sizeof(typename M::In) == 4) {
-    // four rows at a time where every vector starts on 16 bytes; kAtOnce of them so that the loads wait together
-    const int n4 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0 && (vstride & 3) == 0) ? rows / 4 : 0;
-    constexpr int kAtOnce = M::V == 2 ? 4 : 2;
-    for (int i0 = tid; i0 < n4; i0 += kAtOnce * nt) {
-      float x[kAtOnce][M::V][4];
-#pragma unroll
-      for (int a = 0; a < kAtOnce; ++a)
-#pragma unroll
-        for (int j = 0; j < M::V; ++j) {
-          float4 y = make_float4(0, 0, 0, 0);
-          if (j < nv) y = reinterpret_cast<const float4*>(v + j * vstride)[min(i0 + a * nt, n4 - 1)];
-          x[a][j][0] = y.x; x[a][j][1] = y.y; x[a][j][2] = y.z; x[a][j][3] = y.w;
-        }
+    for (int j = 0; j < M::V; ++j) {
+      const In* from = v + (j < nv ? (int64_t)j * vstride : 0);
 #pragma unroll
       for (int a = 0; a < kAtOnce; ++a) {
-        const int i = i0 + a * nt;
-        if (i >= n4) break;
-        float4* to = reinterpret_cast<float4*>(lds + ((size_t)i * 4 << M::shift));
-        if constexpr (M::V == 2) {
-          to[0] = make_float4(x[a][0][0], x[a][1][0], x[a][0][1], x[a][1][1]);
-          to[1] = make_float4(x[a][0][2], x[a][1][2], x[a][0][3], x[a][1][3]);
-        } else {
+        uint32_t w[kWords];
+        const uint32_t at = (uint32_t)min(i + a * nt, n - 1);
+        __builtin_memcpy(w, reinterpret_cast<const unsigned char*>(from) + at * (kWords * 4), sizeof(w));
 #pragma unroll
-          for (int r = 0; r < 4; ++r) to[r] = make_float4(x[a][0][r], x[a][1][r], x[a][2][r], x[a][3][r]);
-        }
+        for (int c = 0; c < kWords; ++c) x[a][j][c] = w[c];
       }
     }
-    for (int i0 = n4 * 4 + tid; i0 < rows; i0 += 4 * nt) {
-      float x[4][M::V];
+  }
+  __device__ __forceinline__ void put(unsigned char* lds, int nv, int i, int n, int nt) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+    for (int j = 1; j < M::V; ++j)
+      if (j >= nv)
 #pragma unroll
-        for (int j = 0; j < M::V; ++j) x[a][j] = j < nv ? v[j * vstride + min(i0 + a * nt, rows - 1)] : 0.0f;
+        for (int a = 0; a < kAtOnce; ++a)
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
-        if (i0 + a * nt < rows)
+          for (int c = 0; c < kWords; ++c) x[a][j][c] = 0;
+    // (all of them are there ahead of the first store: the compiler would move every load to its store, one wait each)
 #pragma unroll
-          for (int j = 0; j < M::V; ++j) reinterpret_cast<float*>(lds)[(i0 + a * nt) * M::V + j] = x[a][j];
-    }
-  } else {
-    const int n4 = ((reinterpret_cast<uintptr_t>(v) & 3) == 0 && (vstride & 3) == 0) ? rows / 4 : 0;
-    constexpr int kAtOnce = 4;
-    for (int i0 = tid; i0 < n4; i0 += kAtOnce * nt) {
-      uint32_t x[kAtOnce][M::V];
+    for (int a = 0; a < kAtOnce; ++a)
 #pragma unroll
-      for (int a = 0; a < kAtOnce; ++a)
+      for (int j = 0; j < M::V; ++j)
 #pragma unroll
-        for (int j = 0; j < M::V; ++j) x[a][j] = j < nv ? reinterpret_cast<const uint32_t*>(v + j * vstride)[min(i0 + a * nt, n4 - 1)] : 0u;
+        for (int c = 0; c < kWords; ++c) asm volatile("" : "+v"(x[a][j][c]));
 #pragma unroll
-      for (int a = 0; a < kAtOnce; ++a) {
-        const int i = i0 + a * nt;
-        if (i >= n4) break;
+    for (int a = 0; a < kAtOnce; ++a) {
+      const int at = i + a * nt;
+      if (at >= n) break;
+      uint4* to = reinterpret_cast<uint4*>(lds + ((size_t)at * kRows << M::shift));
+      if constexpr (kFloat && M::V == 1) {
+        to[0] = make_uint4(x[a][0][0], x[a][0][1], x[a][0][2], x[a][0][3]);
+      } else if constexpr (kFloat && M::V == 2) {
+        to[0] = make_uint4(x[a][0][0], x[a][1][0], x[a][0][1], x[a][1][1]);
+        to[1] = make_uint4(x[a][0][2], x[a][1][2], x[a][0][3], x[a][1][3]);
+      } else if constexpr (kFloat) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) to[r] = make_uint4(x[a][0][r], x[a][1][r], x[a][2][r], x[a][3][r]);
+      } else if constexpr (M::V == 1) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const uint32_t d = x[a][0][c];
+          to[c] = make_uint4((uint32_t)((int32_t)(d << 24) >> 24), (uint32_t)((int32_t)(d << 16) >> 24), (uint32_t)((int32_t)(d << 8) >> 24),
+                             (uint32_t)((int32_t)d >> 24));
+        }
+      } else {
         uint32_t w[4][M::V / 2];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int j = 0; j < M::V / 2; ++j)
-            w[r][j] = ((uint32_t)((int32_t)(x[a][2 * j] << (24 - 8 * r)) >> 24) & 0xffffu) | ((uint32_t)((int32_t)(x[a][2 * j + 1] << (24 - 8 * r)) >> 24) << 16);
+            w[r][j] = ((uint32_t)((int32_t)(x[a][2 * j][0] << (24 - 8 * r)) >> 24) & 0xffffu) | ((uint32_t)((int32_t)(x[a][2 * j + 1][0] << (24 - 8 * r)) >> 24) << 16);
         if constexpr (M::V == 2) {
-          reinterpret_cast<uint4*>(lds)[i] = make_uint4(w[0][0], w[1][0], w[2][0], w[3][0]);
+          to[0] = make_uint4(w[0][0], w[1][0], w[2][0], w[3][0]);
         } else {
-          reinterpret_cast<uint4*>(lds)[2 * i] = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
-          reinterpret_cast<uint4*>(lds)[2 * i + 1] = make_uint4(w[2][0], w[2][1], w[3][0], w[3][1]);
+          to[0] = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
+          to[1] = make_uint4(w[2][0], w[2][1], w[3][0], w[3][1]);
         }
       }
     }
-    for (int i0 = n4 * 4 + tid; i0 < rows; i0 += kAtOnce * nt) {
-      int16_t x[kAtOnce][M::V];
+  }
+  // the rows behind the last piece (fewer than kRows)
+  __device__ static __forceinline__ void put_rest(unsigned char* lds, const In* __restrict__ v, int vstride, int nv, int first, int rows, int tid) {
+    if (first + tid >= rows) return;
+    const int r = first + tid;
 #pragma unroll
-      for (int a = 0; a < kAtOnce; ++a)
-#pragma unroll
-        for (int j = 0; j < M::V; ++j) x[a][j] = j < nv ? (int16_t)v[j * vstride + min(i0 + a * nt, rows - 1)] : (int16_t)0;
-#pragma unroll
-      for (int a = 0; a < kAtOnce; ++a)
-        if (i0 + a * nt < rows)
-#pragma unroll
-          for (int j = 0; j < M::V; ++j) reinterpret_cast<int16_t*>(lds)[(i0 + a * nt) * M::V + j] = x[a][j];
+    for (int j = 0; j < M::V; ++j) {
+      const In y = j < nv ? v[(int64_t)j * vstride + r] : (In)0;
+      if constexpr (kFloat) reinterpret_cast<float*>(lds)[r * M::V + j] = y;
+      else if constexpr (M::V == 1) reinterpret_cast<int32_t*>(lds)[r] = y;
+      else reinterpret_cast<int16_t*>(lds)[r * M::V + j] = y;
     }
   }
-}
+};
 
 // The work of one workgroup: `wg` is its number among the workgroups of this product (a launch may
 // carry several products, see rsr_multi_kernel).  The workgroup may have more wavefronts than the
@@ -706,23 +705,22 @@ __device__ __forceinline__ void stage(unsigned char* lds, const typename M::In* 
 // PLAIN selects step 2 of Algorithm 2 as printed there (the product u . Bin_[k] term by term,
 // O(k 2^k)) instead of the RSR++ fold of Algorithm 3: kept for the comparison of Appendix F.2.
 template <class M, bool PLAIN>
-__device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ stream, const uint32_t* __restrict__ unit_words,
-                                         const uint32_t* __restrict__ blk_unit, const uint16_t* __restrict__ extra_slots,
-                                         const typename M::In* __restrict__ vin, typename M::Acc* __restrict__ out, const KArgsPtr pa,
-                                         const int wg) {
-  const KArgs p = *pa;
+__device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ stream, const TablePtr unit_words, const TablePtr blk_unit,
+                                         const typename M::In* __restrict__ vin, const rsr::Start st,
+                                         const KMorePtr more, const int wg) {
   using AT = typename M::Acc;
   constexpr int V = M::V;
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool worker = wave < p.waves;
+  const bool worker = wave < (int)(st.shape & 0xffu);
+  const int threads = (int)(st.shape >> 8 & 0xffu) * 64, rows = (int)(st.rows_stride & 0xffffu), vstride = (int)(st.rows_stride >> 16);
 
-  const rsr::Share mine = rsr::share_of(p, (uint32_t)wg);
+  const rsr::Share mine = rsr::share_of(st.sets_more & 0xffffu, st.sets_magic, st.row0_g1 >> 16, st.share, st.sets_more >> 16, (uint32_t)wg);
   if (mine.first == mine.last) return;
   const int b = (int)mine.set * V, blk_begin = (int)mine.first, blk_end = (int)mine.last;
-  const int nv = min(V, p.batch - b);
+  const int nv = min(V, (int)(st.shape >> 16) - b);
   const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
 
   // Two register buffers: while one unit is summed from one, the next unit's stream arrives in the
@@ -750,61 +748,45 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     et[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)pair_base + j * 256, 0, kNonTemporal);
   };
 
-  // The activations are staged first: their loads go out before anything else so that they do
-  // not queue behind the (much larger) first stream loads of the other wavefronts.
-  const typename M::In* __restrict__ v = vin + (int64_t)b * p.vstride + p.row0;
-  constexpr int kEarly = (V == 1 && sizeof(typename M::In) == 4) ? 4 : 0;  // 16-byte pieces per thread fetched before the descriptors
-  uint4 sv[kEarly ? kEarly : 1];
-  int n16 = 0;
-  if constexpr (kEarly > 0) {
-    n16 = ((reinterpret_cast<uintptr_t>(v) & 15) == 0) ? p.rows / 4 : 0;
-#pragma unroll
-    for (int j = 0; j < kEarly; ++j) {
-      const int i = tid + j * p.threads;
-      sv[j] = make_uint4(0, 0, 0, 0);
-      if (i < n16) sv[j] = reinterpret_cast<const uint4*>(v)[i];
-    }
-  }
-  const uint32_t u_begin = blk_unit[blk_begin];
-  const uint32_t n_tot = blk_unit[blk_end] - u_begin;  // units of this workgroup, numbered 0 .. n_tot-1
+  // The start of a launch is a chain of waits for memory - block offsets, descriptor, stream, sums - that every workgroup goes through
+  // at the same time, so nothing waits that need not.  The activations go first, so that their loads do not queue behind the (much larger)
+  // first stream loads of the other wavefronts; what names them, and the block offsets, is in registers from the start.  The other
+  // arguments are asked for together, with the block offsets.  (Stamps of ternary 4096^2, one float vector, before: 0.9 us until the
+  // activations were requested, in four waits for arguments, and the staging waited behind the first stream loads.  5.25 us a product then,
+  // 4.74 so; binary 1024^2, int8: 4.04 and 3.54; a transformer block 26.6 and 24.3.)
+  const typename M::In* __restrict__ v = vin + (int64_t)b * vstride + (st.row0_g1 & 0xffffu);
+  using Stage = Staging<M>;
+  const int pieces = rows / Stage::kRows;
+  Stage staged;
+  if (pieces > 0) staged.fetch(v, vstride, nv, tid, pieces, threads);
+  uint32_t u_begin = blk_unit[blk_begin], u_end = blk_unit[blk_end];
+  const KArgs p = more->p;
+  const uint16_t* const extra_slots = (const uint16_t*)(const RSR_GLOBAL uint16_t*)more->extra_slots;
+  asm volatile("" : "+s"(u_begin), "+s"(u_end) : "s"(p.nbuf), "s"(p.ubytes), "s"(p.off_u), "s"(p.off_done), "s"(p.off_cnt), "s"(p.off_epoch), "s"(p.off_ctr),
+               "s"(p.buf_magic), "s"(p.panels), "s"(p.extra_stride), "s"(p.clear), "s"(extra_slots));
+  const uint32_t n_tot = u_end - u_begin;  // units of this workgroup, numbered 0 .. n_tot-1
   // The first unit of every wavefront is fixed (its own number); its descriptor and the beginning of its stream are requested before the
-  // barrier.  Later units come from a counter.
-  const uint32_t u_first = u_begin + (uint32_t)wave;
-  Desc D = load_desc(unit_words, u_first < (uint32_t)p.nunits ? u_first : 0u);
+  // barrier.  Later units come from a counter.  (Behind the last descriptor there is room for as many as a workgroup has wavefronts.)
+  Desc D = load_desc(unit_words, u_begin + (uint32_t)wave);
   uint32_t ix = worker ? (uint32_t)wave : n_tot;
+  if (p.clear)  // slots start from zero
+    for (uint32_t i = (uint32_t)tid * 16u; i < (uint32_t)p.nbuf * p.ubytes; i += (uint32_t)threads * 16u)
+      *reinterpret_cast<uint4*>(lds + p.off_u + i) = make_uint4(0, 0, 0, 0);
+  // the counters of records and buffers, and behind them the one that hands out units
+  const uint32_t counters = (p.off_ctr - p.off_done) / 4;
+  if ((uint32_t)tid <= counters) reinterpret_cast<uint32_t*>(lds + p.off_done)[tid] = (uint32_t)tid == counters ? st.shape & 0xffu : 0u;
+  if (tid < (1 << M::shift) / 4) reinterpret_cast<uint32_t*>(lds + ((size_t)rows << M::shift))[tid] = 0;  // the null row
   if (ix >= n_tot) D.npos = 0;  // (its loads then fall outside the buffer descriptor and read nothing)
   const __amdgpu_buffer_rsrc_t rs0 = unit_rsrc(D.stream_off, D.npos);
-  // (One int8 vector: its loads go out during the staging, which would wait for the stream ahead of them; behind it 4096^2 takes
-  // 5.39 instead of 5.67 us, a transformer block 26.5 instead of 27.1.  Several vectors: no clear gain, 73.7 against 74.4 us for sixteen.)
-  constexpr bool kAhead = !(V == 1 && sizeof(typename M::In) == 1);
-  if constexpr (kAhead) {
-    issue_granule(rs0, 0, eA);
-    issue_granule(rs0, 1, eA);
-  }
+  issue_granule(rs0, 0, eA);
+  issue_granule(rs0, 1, eA);
   __builtin_amdgcn_sched_barrier(0);  // (they would be moved behind the staging)
-  // Slots start from zero.  Where every panel stores all its values (`fill`) only slots that are no value's have to be: those
-  // of panels of fewer values than a step of the fold reads.  (The slot of value 0 is not stored, but counts under no bit.)
-  if (!p.fill || (1 << p.kc) < rsr::kFoldRow)
-    for (uint32_t i = (uint32_t)tid * 16u; i < (uint32_t)p.nbuf * p.ubytes; i += (uint32_t)p.threads * 16u)
-      *reinterpret_cast<uint4*>(lds + p.off_u + i) = make_uint4(0, 0, 0, 0);
-  if (tid < p.nbuf) {
-    reinterpret_cast<uint32_t*>(lds + p.off_cnt)[tid] = 0;
-    reinterpret_cast<uint32_t*>(lds + p.off_epoch)[tid] = 0;
+  if (pieces > 0) staged.put(lds, nv, tid, pieces, threads);
+  for (int i = Stage::kAtOnce * threads; i < pieces; i += Stage::kAtOnce * threads) {
+    staged.fetch(v, vstride, nv, i + tid, pieces, threads);
+    staged.put(lds, nv, i + tid, pieces, threads);
   }
-  if (tid < p.nrec) {
-    reinterpret_cast<uint32_t*>(lds + p.off_done)[tid] = 0;
-    reinterpret_cast<uint32_t*>(lds + p.off_blocks)[tid] = 0;
-  }
-  if (tid == 0) *reinterpret_cast<uint32_t*>(lds + p.off_ctr) = (uint32_t)p.waves;
-  if constexpr (kEarly > 0) {
-#pragma unroll
-    for (int j = 0; j < kEarly; ++j) {
-      const int i = tid + j * p.threads;
-      if (i < n16) reinterpret_cast<uint4*>(lds)[i] = sv[j];
-    }
-  }
-  stage<M>(lds, v, p.vstride, nv, p.rows, kEarly * p.threads, p.threads);
-  if (tid < (1 << M::shift) / 4) reinterpret_cast<uint32_t*>(lds + ((size_t)p.rows << M::shift))[tid] = 0;  // the null row
+  Stage::put_rest(lds, v, vstride, nv, pieces * Stage::kRows, rows, tid);
   // The first unit's loads.  A load of 16 bytes per lane holds the compute unit's memory pipeline for 16 clocks, all of sixteen
   // wavefronts' first units for a microsecond: requested together before the barrier they hold up the activations and the
   // barrier, requested together behind it the first sums.  Two granules with the descriptor, one behind the staging where that is
@@ -819,12 +801,8 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
 #pragma unroll
     for (int j = 0; j < 3; ++j) issue_pair(rs0, lane4 + (D.npos >> 3) * 1024u, j, tA);
   };
-  if constexpr (!kAhead) {
-    issue_granule(rs0, 0, eA);
-    issue_granule(rs0, 1, eA);
-  }
   constexpr bool kThird = V == 1 || sizeof(typename M::In) == 4;
-  if (kThird && p.rows << M::shift >= kLongStaging) {
+  if (kThird && rows << M::shift >= kLongStaging) {
     issue_granule(rs0, 2, eA);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
@@ -847,8 +825,9 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     // stored before its count, and the last count has returned.  A fence would also wait for the stream of the next unit.)
     // (most arguments are fetched again: kept in scalar registers from the start of the kernel they would crowd out what
     // the units need; what the reads of the sums depend on is one word that stays)
-    const KArgsPtr again = launder(pa);
-    const KArgs f = *again;
+    const KMorePtr again = launder(more);
+    const KArgs f = again->p;
+    AT* const out = (AT*)(RSR_GLOBAL AT*)again->out;
     const int pslots = f.pslots; const bool both = f.both, fill = f.fill;
     unsigned char* const u = lds + ubase;
     // Lane l holds the slots 256 i + 4 l + c: value bits 0 and 1 (c) and 8 and up (i) are folded inside the lane: "sum the
@@ -1134,7 +1113,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       // the positions behind the last full granule, always six: a row that the unit does not have is read as row 0
       // and added to sums that no head stores
       const uint32_t hm = (full < 4 ? D.heads_lo >> (8 * full) : D.heads_hi >> (8 * (full - 4)));
-      if (__builtin_expect(D.npos & 7, 1)) M::step6(et[0], et[1], et[2], (uint32_t)p.rows << M::shift, acc, hm, steps);
+      if (__builtin_expect(D.npos & 7, 1)) M::step6(et[0], et[1], et[2], (uint32_t)rows << M::shift, acc, hm, steps);
 #pragma unroll
       for (int j = 0; j < 3; ++j) issue_pair(rs1, pair_base1, j, etn);
     }
@@ -1152,43 +1131,53 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
 
 template <class M, bool PLAIN>
 __global__ void __launch_bounds__(1024)
-rsr_matvec_kernel(const unsigned char* __restrict__ stream, const uint32_t* __restrict__ unit_words,
-                  const uint32_t* __restrict__ blk_unit, const uint16_t* __restrict__ extra_slots, const typename M::In* __restrict__ vin,
-                  typename M::Acc* __restrict__ out, const KArgs) {
-  rsr_body<M, PLAIN>(stream, unit_words, blk_unit, extra_slots, vin, out, args_at(6 * sizeof(void*)), (int)blockIdx.x);
+rsr_matvec_kernel(const unsigned char* __restrict__ stream, const uint32_t* __restrict__ unit_words, const uint32_t* __restrict__ blk_unit,
+                  const typename M::In* __restrict__ vin, const uint32_t sets_more, const uint32_t sets_magic, const uint32_t share, const uint32_t rows_stride,
+                  const uint32_t row0_g1, const uint32_t shape, const KMore) {
+  constexpr size_t at = 4 * sizeof(void*) + sizeof(rsr::Start);  // of the KMore
+  static_assert(at == 56);
+  rsr_body<M, PLAIN>(stream, (TablePtr)unit_words, (TablePtr)blk_unit, vin, rsr::Start{sets_more, sets_magic, share, rows_stride, row0_g1, shape},
+                     (KMorePtr)(argument_memory() + at), (int)blockIdx.x);
 }
 
 // Several products in one launch (rsr_matvec_multi): every product owns a range of workgroups and
-// brings its own tables, activations, results and LDS layout.
+// brings its own tables, activations, results and LDS layout.  A workgroup finds its product among the first workgroups of the second
+// and later ones (there are at most eight products; those that are not there begin behind the grid), which are its leading arguments.
 using rsr::kMaxJobs;
 struct KJob {
   const unsigned char* stream;
   const uint32_t* unit_words;
   const uint32_t* blk_unit;
-  const uint16_t* extra_slots;
   const void* vin;
-  void* out;
-  int wg_begin;  // first workgroup of this product
-  int pad;
-  KArgs p;
+  rsr::Start start;
+  uint32_t wg_begin;  // first workgroup of this product
+  KMore more;
 };
 struct MultiArgs {
-  int njobs;
-  int pad;
   KJob job[kMaxJobs];
 };
+typedef RSR_CONSTANT KJob* KJobPtr;
+static_assert(kMaxJobs == 8);
 
 template <class M>
-__global__ void __launch_bounds__(1024) rsr_multi_kernel(const MultiArgs m) {
-  int j = 0;
-#pragma unroll
-  for (int i = 1; i < kMaxJobs; ++i)
-    if (i < m.njobs && (int)blockIdx.x >= m.job[i].wg_begin) j = i;
-  // (selected with a wavefront-uniform index: the arguments stay in scalar registers)
-  const KJob& J = m.job[j];
-  rsr_body<M, false>(J.stream, J.unit_words, J.blk_unit, J.extra_slots, static_cast<const typename M::In*>(J.vin),
-                     static_cast<typename M::Acc*>(J.out), args_at(offsetof(MultiArgs, job) + (size_t)uniform((uint32_t)j) * sizeof(KJob) + offsetof(KJob, p)),
-                     (int)blockIdx.x - J.wg_begin);
+__global__ void __launch_bounds__(1024) rsr_multi_kernel(const uint32_t b1, const uint32_t b2, const uint32_t b3, const uint32_t b4, const uint32_t b5,
+                                                         const uint32_t b6, const uint32_t b7, const uint32_t, const MultiArgs) {
+  constexpr size_t at = 8 * sizeof(uint32_t);  // of the MultiArgs
+  const uint32_t wg = blockIdx.x;
+  uint32_t j = 0;  // (in assembly: the compiler adds up comparisons in vector registers)
+#define RSR_BEHIND(b) "s_cmp_ge_u32 %1, " b "\n s_addc_u32 %0, %0, 0\n"
+  asm(RSR_BEHIND("%2") RSR_BEHIND("%3") RSR_BEHIND("%4") RSR_BEHIND("%5") RSR_BEHIND("%6") RSR_BEHIND("%7") RSR_BEHIND("%8")
+      : "+&s"(j) : "s"(wg), "s"(b1), "s"(b2), "s"(b3), "s"(b4), "s"(b5), "s"(b6), "s"(b7) : "scc");
+  const KJobPtr J = (KJobPtr)(argument_memory() + at + (size_t)j * sizeof(KJob));
+  // what takes fourteen registers from the start in rsr_matvec_kernel, read together
+  typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+  u32x8 pointers, words;
+  static_assert(offsetof(KJob, start) == 32 && offsetof(KJob, wg_begin) == 56);
+  asm volatile("s_load_dwordx8 %0, %2, 0x0\n s_load_dwordx8 %1, %2, 0x20\n s_waitcnt lgkmcnt(0)" : "=&s"(pointers), "=&s"(words) : "s"(J));
+  auto pointer = [&](int i) { return (uint64_t)pointers[2 * i + 1] << 32 | pointers[2 * i]; };
+  rsr_body<M, false>((const unsigned char*)(const RSR_GLOBAL unsigned char*)pointer(0), (TablePtr)pointer(1), (TablePtr)pointer(2),
+                     (const typename M::In*)(const RSR_GLOBAL typename M::In*)pointer(3),
+                     rsr::Start{words[0], words[1], words[2], words[3], words[4], words[5]}, &J->more, (int)(wg - words[6]));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1196,10 +1185,11 @@ __global__ void __launch_bounds__(1024) rsr_multi_kernel(const MultiArgs m) {
 // ---------------------------------------------------------------------------------------------
 template <class M, bool PLAIN>
 int enqueue(const DeviceTile& T, const LaunchPlan& plan, const typename M::In* v, void* out, void* stream) {
+  const rsr::Start st = rsr::start_of(plan.p);
   hipLaunchKernelGGL((rsr_matvec_kernel<M, PLAIN>), dim3((unsigned)plan.grid), dim3((unsigned)(plan.waves * 64)), plan.lds,
                      static_cast<hipStream_t>(stream), static_cast<const unsigned char*>(T.d_stream), static_cast<const uint32_t*>(T.d_units),
-                     static_cast<const uint32_t*>(T.d_blk_unit), static_cast<const uint16_t*>(T.d_extras), v,
-                     static_cast<typename M::Acc*>(out), plan.p);
+                     static_cast<const uint32_t*>(T.d_blk_unit), v, st.sets_more, st.sets_magic, st.share, st.rows_stride, st.row0_g1, st.shape,
+                     KMore{static_cast<const uint16_t*>(T.d_extras), out, plan.p});
   RSR_HIP_TRY(hipGetLastError());
   return RSR_OK;
 }
@@ -1239,27 +1229,30 @@ template <class M>
 int enqueue_multi(const rsr_job* jobs, int njobs, const LaunchPlan* plans, void* stream) {
   MultiArgs m;
   std::memset(&m, 0, sizeof(m));
-  m.njobs = njobs;
+  uint32_t begin[kMaxJobs];
   int64_t grid = 0;
   int waves = 1;
   size_t lds = 0;
-  for (int j = 0; j < njobs; ++j) {
+  for (int j = 0; j < njobs; ++j) waves = std::max(waves, plans[j].waves);
+  for (int j = 0; j < kMaxJobs; ++j) {
+    begin[j] = 0xffffffffu;
+    if (j >= njobs) continue;
     const DeviceTile& T = jobs[j].h->tiles[0];
     KJob& J = m.job[j];
     J.stream = static_cast<const unsigned char*>(T.d_stream);
     J.unit_words = static_cast<const uint32_t*>(T.d_units);
     J.blk_unit = static_cast<const uint32_t*>(T.d_blk_unit);
-    J.extra_slots = static_cast<const uint16_t*>(T.d_extras);
-    J.vin = jobs[j].v; J.out = jobs[j].out;
-    J.wg_begin = (int)grid;
-    J.p = plans[j].p;
+    J.vin = jobs[j].v;
+    J.more = {static_cast<const uint16_t*>(T.d_extras), jobs[j].out, plans[j].p};
+    J.more.p.threads = waves * 64;
+    J.start = rsr::start_of(J.more.p);
+    begin[j] = J.wg_begin = (uint32_t)grid;
     grid += plans[j].grid;  // (a multiple of 8: every product starts on the first XCD of the round-robin)
-    waves = std::max(waves, plans[j].waves);
     lds = std::max(lds, plans[j].lds);
     if (grid > 0x7fffffff) return fail(RSR_ERR_INVALID_ARGUMENT, "batch too large");
   }
-  for (int j = 0; j < njobs; ++j) m.job[j].p.threads = waves * 64;
-  hipLaunchKernelGGL(rsr_multi_kernel<M>, dim3((unsigned)grid), dim3((unsigned)(waves * 64)), lds, static_cast<hipStream_t>(stream), m);
+  hipLaunchKernelGGL(rsr_multi_kernel<M>, dim3((unsigned)grid), dim3((unsigned)(waves * 64)), lds, static_cast<hipStream_t>(stream), begin[1], begin[2],
+                     begin[3], begin[4], begin[5], begin[6], begin[7], 0u, m);
   RSR_HIP_TRY(hipGetLastError());
   return RSR_OK;
 }

@@ -46,14 +46,24 @@ struct PlanMatrix {
 
 // Kernel arguments.
 struct KArgs {
+  // what the start of a kernel and its units need, together (a scalar load takes neighbouring words)
+  int nbuf;      // panels in flight per workgroup
+  uint32_t ubytes;  // bytes of a panel's sums in LDS
+  uint32_t off_u, off_rec, off_done, off_blocks, off_cnt, off_epoch, off_ctr;  // LDS byte offsets
+  uint32_t buf_magic, rec_magic;  // x / nbuf and x / nrec as high halves of products
+  int panels;       // of a block (rsr_layout.h)
+  int extra_stride; // entries per panel in the list of extra slots
+  // Slots have to be cleared ahead of the first panels.  Where every panel stores all its values (`fill`) only slots that are no
+  // value's are: those of panels of fewer values than a step of the fold reads.  (The slot of value 0 is not stored, but counts under no bit.)
+  int clear;
   int rows, cols, k, nblocks, last_width, batch;
   int vstride;   // elements between the activation vectors of consecutive batch lanes (the matrix's row count)
   int row0;      // first row of this row tile
   int accumulate;  // add to `out` instead of overwriting it (second and later row tiles, rsr_matvec_acc)
   int scaled;      // multiply the product by `scale` first (rsr_matvec_acc)
   uint32_t scale;  // bits of a float (float activations) or of an int (int8 activations)
-  int kc, both, pslots, panels;  // panels of a block (rsr_layout.h)
-  int fill, extra_stride;        // absent values are stored as zeros; entries per panel in the list of extra slots
+  int kc, both, pslots;  // panels of a block (rsr_layout.h)
+  int fill;              // absent values are stored as zeros
   // a part's weight: 1 << (part * wshift + wfirst), negative for part `wneg` (-1: none)
   int wshift, wfirst, wneg;
   int g1;        // workgroups per set of vectors
@@ -62,12 +72,7 @@ struct KArgs {
   uint32_t share, share_more;  // column blocks of a workgroup; so many workgroups have one more
   int waves;     // wavefronts that take units
   int threads;   // of a workgroup (a launch of several products: of its largest)
-  int nunits;    // unit descriptors in the index
-  int nbuf;      // panels in flight per workgroup
   int nrec;      // blocks whose panel records are kept (panels > 1)
-  uint32_t buf_magic, rec_magic;  // x / nbuf and x / nrec as high halves of products
-  uint32_t ubytes;  // bytes of a panel's sums in LDS
-  uint32_t off_u, off_rec, off_done, off_blocks, off_cnt, off_epoch, off_ctr;  // LDS byte offsets
 };
 
 // A workgroup's set of vectors and column blocks.  The siblings of a block range, one per set, sit 8 workgroup ids apart so that
@@ -77,16 +82,35 @@ struct KArgs {
 struct Share {
   uint32_t set, first, last;  // blocks first .. last - 1
 };
-constexpr Share share_of(const KArgs& p, uint32_t wg) {
+constexpr Share share_of(uint32_t sets, uint32_t sets_magic, uint32_t g1, uint32_t share, uint32_t share_more, uint32_t wg) {
   const uint32_t eights = wg >> 3;
-  const uint32_t grp = p.sets == 1 ? eights : (uint32_t)(((uint64_t)eights * p.sets_magic) >> 32);
+  const uint32_t grp = sets == 1 ? eights : (uint32_t)(((uint64_t)eights * sets_magic) >> 32);
   const uint32_t g = grp * 8 + (wg & 7);
-  Share s{eights - grp * (uint32_t)p.sets, 0, 0};
-  if (g < (uint32_t)p.g1) {
-    s.first = g * p.share + (g < p.share_more ? g : p.share_more);
-    s.last = s.first + p.share + (g < p.share_more ? 1u : 0u);
+  Share s{eights - grp * sets, 0, 0};
+  if (g < g1) {
+    s.first = g * share + (g < share_more ? g : share_more);
+    s.last = s.first + share + (g < share_more ? 1u : 0u);
   }
   return s;
+}
+constexpr Share share_of(const KArgs& p, uint32_t wg) {
+  return share_of((uint32_t)p.sets, p.sets_magic, (uint32_t)p.g1, p.share, p.share_more, wg);
+}
+
+// What a workgroup needs to know before it can ask for anything: its share of the blocks, and where its activations are.  Six words, which
+// go ahead of the other arguments with four pointers: the fourteen words that a wavefront finds in its scalar registers when it
+// starts (rsr_lib.hip).
+struct Start {
+  uint32_t sets_more;   // sets | share_more << 16
+  uint32_t sets_magic, share;
+  uint32_t rows_stride; // rows | vstride << 16
+  uint32_t row0_g1;     // row0 | g1 << 16
+  uint32_t shape;       // waves | wavefronts of the workgroup << 8 | batch << 16
+};
+static_assert(kTileRows < 65536 && kMaxRows < 65536, "rows and strides fit 16 bits");
+inline Start start_of(const KArgs& p) {
+  return {(uint32_t)p.sets | p.share_more << 16, p.sets_magic, p.share, (uint32_t)p.rows | (uint32_t)p.vstride << 16,
+          (uint32_t)p.row0 | (uint32_t)p.g1 << 16, (uint32_t)p.waves | (uint32_t)(p.threads / 64) << 8 | (uint32_t)p.batch << 16};
 }
 
 struct LaunchPlan {
@@ -121,8 +145,8 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
   p.vstride = (int)h.rows; p.row0 = (int)T.row0; p.accumulate = accumulate ? 1 : 0;
   p.kc = S.kc; p.both = S.both; p.pslots = S.pslots; p.panels = S.panels;
   p.fill = T.fill ? 1 : 0; p.extra_stride = T.extra_stride;
+  p.clear = !T.fill || (1 << S.kc) < kFoldRow;
   p.wshift = h.qbit ? 1 : 0; p.wfirst = h.first_plane; p.wneg = h.negative_part;
-  p.nunits = (int)T.nunits;
 
   // LDS: activations, panels in flight, records of the blocks in flight, counters
   const size_t vbytes = align_up((size_t)(T.rows + 1) << M.shift, 16);

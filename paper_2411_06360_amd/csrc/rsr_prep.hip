@@ -774,7 +774,7 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
   out->unit_bytes = (size_t)nunits * sizeof(PUnit);
   out->blk_bytes = blk_unit.size() * 4;
   out->extra_bytes = extras ? (size_t)npanels * g.extra_stride * 2 : 0;
-  const size_t at_stream = take(out->stream_bytes + 1024), at_units = take(out->unit_bytes + 32), at_blk = take(out->blk_bytes + 16);
+  const size_t at_stream = take(out->stream_bytes + 1024), at_units = take(out->unit_bytes + rsr::kUnitsBehind * sizeof(PUnit)), at_blk = take(out->blk_bytes + 16);
   const size_t at_slots = take(out->extra_bytes);
   PREP_TRY(hipMalloc(&tables.p, bytes));
   unsigned char* const t = static_cast<unsigned char*>(tables.p);

@@ -102,3 +102,38 @@ def test_shared_launches_with_several_vectors(shapes, batches):
         torch.cuda.synchronize()
         for h in hs:
             R.rsr_destroy(h)
+
+
+@pytest.mark.parametrize("rows", [1, 3, 4, 5, 15, 16, 17, 1023, 4097, 5003, 9001, 16384])
+def test_activations_at_any_address(rows):
+    """Staging: the last piece and the rows behind it, vectors that begin at every remainder of 16 bytes (an odd number of int8
+    rows, base pointers off by an element), sets that are not full, from single and shared launches."""
+    import torch
+
+    g = np.random.default_rng(405)
+    A = g.integers(-1, 2, size=(rows, 90)).astype(np.int8)
+    print(f"activations at any address, {rows} rows", flush=True)
+    h = R.rsr_preprocess(A, 6)
+    try:
+        for batch in (1, 2, 3, 5, 140):
+            for off in (0, 1, 2, 3):
+                vf = g.standard_normal((batch, rows)).astype(np.float32)
+                v8 = g.integers(-128, 128, size=(batch, rows), dtype=np.int8)
+                for v, dtype, one, many, exact in ((vf, torch.float32, R.rsr_matvec, R.rsr_matvec_multi, dense.matvec_f32),
+                                                   (v8, torch.int32, R.rsr_matvec_i8, R.rsr_matvec_multi_i8, dense.matvec_i8)):
+                    room = torch.full((off + v.size,), 77, dtype=torch.from_numpy(v).dtype, device="cuda")  # (it ends with the vectors)
+                    room[off:] = torch.from_numpy(v.ravel()).cuda()
+                    x = room[off:]
+                    out = torch.full((2, batch, 90), -7, dtype=dtype, device="cuda")
+                    one(h, x, out[0], batch, stream())
+                    many([(h, x, out[1])], batch, stream())
+                    torch.cuda.synchronize()
+                    got, want = out.cpu().numpy(), exact(A, v)
+                    assert np.array_equal(got[0], got[1]), (batch, off)
+                    if dtype is torch.int32:
+                        assert np.array_equal(got[0].astype(np.int64), want), (batch, off)
+                    else:
+                        assert_f32_close(got[0], want, v)
+    finally:
+        torch.cuda.synchronize()
+        R.rsr_destroy(h)
