@@ -619,15 +619,17 @@ struct Staging {
   static constexpr int kWords = !kFloat && M::V > 1 ? 1 : 4;
   uint32_t x[kAtOnce][M::V][kWords];
 
-  // pieces i, i + nt, ... of `n`; vectors from `nv` on are zeros
-  __device__ __forceinline__ void fetch(const In* __restrict__ v, int vstride, int nv, int i, int n, int nt) {
+  // Pieces first + lane, first + lane + nt, ... of `n`; vectors from `nv` on are zeros.  Nothing is requested for a wavefront's turn that lies
+  // behind the last piece: a load of 16 bytes per lane holds the compute unit's memory pipeline for 16 clocks wherever it reads.
+  __device__ __forceinline__ void fetch(const In* __restrict__ v, int vstride, int nv, int first, int lane, int n, int nt) {
 #pragma unroll
-    for (int j = 0; j < M::V; ++j) {
-      const In* from = v + (j < nv ? (int64_t)j * vstride : 0);
+    for (int a = 0; a < kAtOnce; ++a) {
+      if (first + a * nt >= n) break;
+      const uint32_t at = (uint32_t)min(first + lane + a * nt, n - 1);
 #pragma unroll
-      for (int a = 0; a < kAtOnce; ++a) {
+      for (int j = 0; j < M::V; ++j) {
+        const In* from = v + (j < nv ? (int64_t)j * vstride : 0);
         uint32_t w[kWords];
-        const uint32_t at = (uint32_t)min(i + a * nt, n - 1);
         __builtin_memcpy(w, reinterpret_cast<const unsigned char*>(from) + at * (kWords * 4), sizeof(w));
 #pragma unroll
         for (int c = 0; c < kWords; ++c) x[a][j][c] = w[c];
@@ -758,7 +760,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   using Stage = Staging<M>;
   const int pieces = rows / Stage::kRows;
   Stage staged;
-  if (pieces > 0) staged.fetch(v, vstride, nv, tid, pieces, threads);
+  staged.fetch(v, vstride, nv, wave * 64, lane, pieces, threads);
   uint32_t u_begin = blk_unit[blk_begin], u_end = blk_unit[blk_end];
   const KArgs p = more->p;
   const uint16_t* const extra_slots = (const uint16_t*)(const RSR_GLOBAL uint16_t*)more->extra_slots;
@@ -781,9 +783,9 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   issue_granule(rs0, 0, eA);
   issue_granule(rs0, 1, eA);
   __builtin_amdgcn_sched_barrier(0);  // (they would be moved behind the staging)
-  if (pieces > 0) staged.put(lds, nv, tid, pieces, threads);
+  staged.put(lds, nv, tid, pieces, threads);
   for (int i = Stage::kAtOnce * threads; i < pieces; i += Stage::kAtOnce * threads) {
-    staged.fetch(v, vstride, nv, i + tid, pieces, threads);
+    staged.fetch(v, vstride, nv, i + wave * 64, lane, pieces, threads);
     staged.put(lds, nv, i + tid, pieces, threads);
   }
   Stage::put_rest(lds, v, vstride, nv, pieces * Stage::kRows, rows, tid);
