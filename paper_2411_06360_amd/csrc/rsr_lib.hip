@@ -151,15 +151,6 @@ __device__ __forceinline__ KMorePtr launder(KMorePtr p) {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// ---- wavefront sums with DPP (no LDS traffic).  The total ends up in lane 63. ----
-template <int CTRL, int ROW_MASK, int BANK_MASK>
-__device__ __forceinline__ float dpp_get(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROW_MASK, BANK_MASK, false));
-}
-template <int CTRL, int ROW_MASK, int BANK_MASK>
-__device__ __forceinline__ int dpp_get(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, BANK_MASK, false);
-}
 // Lane swaps of a value with itself, in assembly: the compiler takes the two results of the swap
 // builtins for equal when they are combined as floats.  (The s_nop covers the wait states a lane
 // swap needs after a vector write of its operands.)
@@ -489,35 +480,48 @@ __device__ __forceinline__ Desc load_desc(TablePtr unit_words, uint32_t u) {
   return make_desc(w[0], w[1], w[2], w[3], w[4], w[5]);
 }
 
+// Sums of sixteen values over the 64 lanes, all at once.  In each of four exchanges a lane keeps half of its values and gives the other half
+// to its partner, so that they cost 8 + 4 + 2 + 1 additions instead of 16 each: over lane bits 5 and 4 with lane swaps of two values (what was one
+// value's upper half and the other's lower half change places; the sum of the two is the exchange), over bits 3 and 2 with additions that
+// write a part of the banks.  Two plain additions over bits 1 and 0 follow.  On return every lane holds the sum of v[lane >> 2].
+// Bound by the instructions of one wavefront, four clocks each: 34, and no masks.  (With an exchange inside the quads first, which takes two
+// selections a pair, 65, and masks: transformer block with sixteen vectors
+// 65.7 us, 64.0 so; binary 16384^2, eight int8 vectors 30.5 and 30.0.)  In assembly: the compiler takes the two results of the swap
+// builtins for equal when they are combined as floats.  (The s_nop cover the wait states a swap and a lane exchange need after
+// a vector write of their operands.)
+#define RSR_REST_OF_SIXTEEN(ADD)                                                                               \
+  "s_nop 1\n " ADD " %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n " ADD " %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n " \
+  ADD " %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n " ADD " %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n s_nop 1\n " \
+  ADD " %0, %0, %0 row_shl:4 row_mask:0xf bank_mask:0x5\n " ADD " %0, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xa\n s_nop 1\n " \
+  ADD " %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n s_nop 1\n " ADD " %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
 template <typename AT>
-__device__ __forceinline__ AT exchange_add(AT even, AT odd, bool take_odd, int step) {
-  const AT keep = take_odd ? odd : even, give = take_odd ? even : odd;
-  switch (step) {
-    case 0: return keep + dpp_get<0xB1, 0xf, 0xf>(give);  // quad_perm [1,0,3,2]: lane xor 1
-    case 1: return keep + dpp_get<0x4E, 0xf, 0xf>(give);  // quad_perm [2,3,0,1]: lane xor 2
-    // lane xor 4: lanes 0-3 and 8-11 of a row read 4 lanes up, lanes 4-7 and 12-15 read 4 lanes down
-    case 2: return keep + (dpp_get<0x104, 0xf, 0x5>(give) + dpp_get<0x114, 0xf, 0xa>(give));
-    default: return keep + dpp_get<0x128, 0xf, 0xf>(give);  // row_ror:8 is lane xor 8 inside a row
-  }
+__device__ __forceinline__ AT sums_of_sixteen(const AT (&v)[16]) {
+  AT a[16], w[8], x[4];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) a[i] = v[i];
+  asm("s_nop 1\n v_permlane32_swap_b32 %0, %8\n v_permlane32_swap_b32 %1, %9\n v_permlane32_swap_b32 %2, %10\n v_permlane32_swap_b32 %3, %11\n"
+      " v_permlane32_swap_b32 %4, %12\n v_permlane32_swap_b32 %5, %13\n v_permlane32_swap_b32 %6, %14\n v_permlane32_swap_b32 %7, %15"
+      : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]),
+        "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15]));
+#pragma unroll
+  for (int i = 0; i < 8; ++i) w[i] = a[i] + a[i + 8];
+  asm("s_nop 1\n v_permlane16_swap_b32 %0, %4\n v_permlane16_swap_b32 %1, %5\n v_permlane16_swap_b32 %2, %6\n v_permlane16_swap_b32 %3, %7"
+      : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x[i] = w[i] + w[i + 4];
+  if constexpr (sizeof(AT) == 4 && (AT)0.5 != (AT)0)
+    asm(RSR_REST_OF_SIXTEEN("v_add_f32_dpp") : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+  else
+    asm(RSR_REST_OF_SIXTEEN("v_add_u32_dpp") : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+  return x[0];
 }
-// Sums of sixteen values over the 64 lanes, all at once: after every exchange a lane keeps half of its values and
-// hands the other half to its partner, so the four halving exchanges (lane xor 1, 2, 4, 8) cost 8 + 4 + 2 + 1
-// additions instead of 16 each; the four rows of 16 lanes follow with lane swaps.  On return every lane holds the
-// sum of v[lane & 15].
+// x where the lane's bit 2, 3, 4 or 5 is set, 0 elsewhere, for all four bits.
 template <typename AT>
-__device__ __forceinline__ AT sums_of_sixteen(const AT (&v)[16], int lane) {
-  AT w[8], x[4], y[2];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) w[i] = exchange_add(v[2 * i], v[2 * i + 1], lane & 1, 0);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) x[i] = exchange_add(w[2 * i], w[2 * i + 1], lane & 2, 1);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) y[i] = exchange_add(x[2 * i], x[2 * i + 1], lane & 4, 2);
-  const AT row = exchange_add(y[0], y[1], lane & 8, 3);
-  const Swapped h = swap32(__builtin_bit_cast(uint32_t, row));
-  const AT two = __builtin_bit_cast(AT, h.x) + __builtin_bit_cast(AT, h.y);
-  const Swapped q = swap16(__builtin_bit_cast(uint32_t, two));
-  return __builtin_bit_cast(AT, q.x) + __builtin_bit_cast(AT, q.y);
+__device__ __forceinline__ void by_lane_bits(AT x, AT& b2, AT& b3, AT& b4, AT& b5) {
+  b2 = b3 = b4 = b5 = (AT)0;
+  asm("s_nop 1\n v_mov_b32_dpp %0, %4 quad_perm:[0,1,2,3] row_mask:0xf bank_mask:0xa\n v_mov_b32_dpp %1, %4 quad_perm:[0,1,2,3] row_mask:0xf bank_mask:0xc\n"
+      " v_mov_b32_dpp %2, %4 quad_perm:[0,1,2,3] row_mask:0xa bank_mask:0xf\n v_mov_b32_dpp %3, %4 quad_perm:[0,1,2,3] row_mask:0xc bank_mask:0xf"
+      : "+v"(b2), "+v"(b3), "+v"(b4), "+v"(b5) : "v"(x));
 }
 
 constexpr int NG = rsr::kMaxGranules;
@@ -829,7 +833,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     // the units need; what the reads of the sums depend on is one word that stays)
     const KMorePtr again = launder(more);
     const KArgs f = again->p;
-    AT* const out = (AT*)(RSR_GLOBAL AT*)again->out;
+    RSR_GLOBAL AT* const out = (RSR_GLOBAL AT*)again->out;
     const int pslots = f.pslots; const bool both = f.both, fill = f.fill;
     unsigned char* const u = lds + ubase;
     // Lane l holds the slots 256 i + 4 l + c: value bits 0 and 1 (c) and 8 and up (i) are folded inside the lane: "sum the
@@ -967,14 +971,15 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
 #pragma unroll
     for (int j = 0; j < V; ++j) {
       AT items[kItems];
+      if constexpr (PLAIN) {
 #pragma unroll
-      for (int i = 0; i < 6; ++i) {
-        if constexpr (PLAIN) {
-          items[i] = pl[j][i]; items[6 + i] = pl[j][6 + i];
-        } else {
-          items[2 + i] = ((lane >> i) & 1) ? tot[j] : (AT)0;
-          items[i < 2 ? i : 6 + i] = hi[j][i];
-        }
+        for (int i = 0; i < 12; ++i) items[i] = pl[j][i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) items[i < 2 ? i : 6 + i] = hi[j][i];
+        items[2] = (lane & 1) ? tot[j] : (AT)0;
+        items[3] = (lane & 2) ? tot[j] : (AT)0;
+        by_lane_bits(tot[j], items[4], items[5], items[6], items[7]);
       }
       items[kTotal] = tot[j];
       items[13] = items[14] = items[15] = (AT)0;
@@ -993,24 +998,24 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
           for (uint32_t e = (uint32_t)kExtraAhead + (uint32_t)lane; e < D.extras; e += 64)
             add_extra(extra_slots[(size_t)D.panel * f.extra_stride + e], M::get(reinterpret_cast<const Slot*>(u)[first_extra + e], j));
       }
-      sum[j] = sums_of_sixteen<AT>(items, lane);
+      sum[j] = sums_of_sixteen<AT>(items);
     }
     if (more) release();
     // ---- the block: its panels' sums, the parts with their weights, k outputs ----
     const int blk = (int)D.block;
-    auto put = [&](int bit, int j, AT res) {
+    auto put = [&](int bit, bool here, int j, AT res) {
       // value bit `bit` belongs to column k-1-bit of the block (first column most significant)
       const int width = (blk == f.nblocks - 1) ? f.last_width : f.k;
       const int col = f.k - 1 - bit;
-      if (lane < 16 && bit < f.k && col < width && j < nv) {
-        AT* dst = out + (int64_t)(b + j) * f.cols + (int64_t)blk * f.k + col;
+      if (here && bit < f.k && col < width && j < nv) {
+        RSR_GLOBAL AT* dst = out + (int64_t)(b + j) * f.cols + (int64_t)blk * f.k + col;
         const AT term = f.scaled ? res * __builtin_bit_cast(AT, f.scale) : res;
         *dst = f.accumulate ? *dst + term : term;  // row tiles add up: the product is linear in the rows
       }
     };
     if (f.nrec == 0) {
 #pragma unroll
-      for (int j = 0; j < V; ++j) put(lane & 15, j, sum[j]);
+      for (int j = 0; j < V; ++j) put(lane >> 2, (lane & 3) == 0, j, sum[j]);
     } else {
       const uint32_t bl = (uint32_t)(blk - blk_begin);
       const uint32_t earlier = f.nrec == 1 ? bl : __umulhi(bl, f.rec_magic);  // blocks that have used these records before
@@ -1018,9 +1023,9 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       while (uniform(lds_load(f.off_blocks + ring * 4u)) < earlier) __builtin_amdgcn_s_sleep(1);
       AT* rec = reinterpret_cast<AT*>(lds + f.off_rec) + (size_t)ring * f.panels * V * kItems;
       const int mine = (int)(D.panel - D.block * (uint32_t)f.panels);
-      if (lane < kItems)
+      if ((lane & 3) == 0)
 #pragma unroll
-        for (int j = 0; j < V; ++j) rec[(mine * V + j) * kItems + lane] = sum[j];
+        for (int j = 0; j < V; ++j) rec[(mine * V + j) * kItems + (lane >> 2)] = sum[j];
       const uint32_t before = lds_count_up(f.off_done + ring * 4u);
       if ((int)before + 1 == f.panels) {  // (the other panels' records were stored before their counts)
         // The four rows of 16 lanes take every fourth panel.  Bits below kc are in the records; a higher bit sees
@@ -1045,7 +1050,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
           const Swapped hs = swap32(__builtin_bit_cast(uint32_t, acc[j]));
           const AT two = __builtin_bit_cast(AT, hs.x) + __builtin_bit_cast(AT, hs.y);
           const Swapped qs = swap16(__builtin_bit_cast(uint32_t, two));
-          put(bit, j, __builtin_bit_cast(AT, qs.x) + __builtin_bit_cast(AT, qs.y));
+          put(bit, lane < 16, j, __builtin_bit_cast(AT, qs.x) + __builtin_bit_cast(AT, qs.y));
         }
         lds_clear(f.off_done + ring * 4u);
         lds_bump(f.off_blocks + ring * 4u);
