@@ -135,7 +135,7 @@ __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, i
   if (bp >= nbp) return;  // (no barriers below: the wavefronts are independent)
   const int nvals = 1 << k;
   const int ndw = max(1, nvals >> 1);
-  volatile uint32_t* h = lds_hist + (size_t)wave * ndw;
+  uint32_t* const h = lds_hist + (size_t)wave * ndw;  // (counted up with atomics: what other lanes have counted is read behind a barrier to the compiler)
   const uint16_t* v = val + (int64_t)bp * rows;
   for (int i = lane; i < ndw; i += 64) h[i] = 0;
   constexpr int kAhead = 8;  // chunks of 64 rows whose values are fetched together
@@ -145,8 +145,9 @@ __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, i
     for (int j = 0; j < kAhead; ++j) x[j] = v[min(r0 + 64 * j + lane, rows - 1)];
 #pragma unroll
     for (int j = 0; j < kAhead; ++j)
-      if (r0 + 64 * j + lane < rows) atomicAdd(const_cast<uint32_t*>(&h[x[j] >> 1]), 1u << (16 * (x[j] & 1)));
+      if (r0 + 64 * j + lane < rows) atomicAdd(&h[x[j] >> 1], 1u << (16 * (x[j] & 1)));
   }
+  asm volatile("" ::: "memory");
   // exclusive prefix: the full segmentation (kept in LDS as the next free position of every value)
   uint32_t carry = 0;
   uint32_t* o = off + (int64_t)bp * (nvals + 1);
@@ -169,6 +170,7 @@ __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, i
     }
     carry += __shfl(incl, 63);
   }
+  asm volatile("" ::: "memory");
   if (lane == 0) o[nvals] = (uint32_t)rows;
   uint16_t* sg = sigma + (int64_t)bp * rows;
   for (int r0 = 0; r0 < rows; r0 += 64 * kAhead) {
@@ -180,7 +182,7 @@ __global__ void sort_kernel(const uint16_t* __restrict__ val, int rows, int k, i
       const int r = r0 + 64 * j + lane;
       if (r < rows) {
         const uint32_t sh = 16 * (x[j] & 1);
-        const uint32_t at = (atomicAdd(const_cast<uint32_t*>(&h[x[j] >> 1]), 1u << sh) >> sh) & 0xffffu;
+        const uint32_t at = (atomicAdd(&h[x[j] >> 1], 1u << sh) >> sh) & 0xffffu;
         sg[at] = (uint16_t)r;
       }
     }
@@ -502,9 +504,12 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   const PUnit U = units[ui];
   const int npos = U.npos;
   if (npos == 0) return;
-  volatile uint16_t (*ent)[64] = ent_all[wave];
-  uint32_t* load_words = &load_all[wave][0][0][0];
-  const volatile uint8_t* load_bytes = reinterpret_cast<const volatile uint8_t*>(load_words);
+  // (Plain accesses, and a barrier to the compiler where other lanes' atomics have to be seen: volatile ones through these pointers are
+  // flat instructions, each with a wait of its own - 2000 clocks for every position of a trade round.)
+  uint16_t (*const ent)[64] = ent_all[wave];
+  uint32_t* const load_words = &load_all[wave][0][0][0];
+  const uint8_t* const load_bytes = reinterpret_cast<const uint8_t*>(load_words);
+  auto settle = []() { asm volatile("" ::: "memory"); };
   const int half = lane >> 5;
   auto load_at = [&](int p, int b) { return (p * 2 + half) * 32 + b; };
   auto add_load = [&](int p, int b, uint32_t x) { atomicAdd(&load_words[load_at(p, b) >> 2], x << (8 * (b & 3))); };
@@ -594,6 +599,7 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   const int start = (lane & 3) * npos / 4;
   for (int round = 0; round < kTradeRounds; ++round)
     for (int t = 0; t < npos; ++t) {
+      settle();
       const int p = t + start < npos ? t + start : t + start - npos;
       const uint64_t rest = heads >> p;
       const int p1 = rest ? p + __ffsll((long long)rest) - 1 : 0;  // the group's head
