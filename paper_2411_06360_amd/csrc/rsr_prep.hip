@@ -496,8 +496,9 @@ __global__ void __launch_bounds__(64 * kEmitWaves)
 emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const PanelInfo* __restrict__ info, const uint16_t* __restrict__ list_all,
             const uint32_t* __restrict__ extra_all, const uint32_t* __restrict__ off, const uint16_t* __restrict__ sigma,
             unsigned char* __restrict__ stream) {
-  __shared__ uint16_t ent_all[kEmitWaves][rsr::kMaxPositions][64];
-  __shared__ uint32_t load_all[kEmitWaves][rsr::kMaxPositions][2][8];  // rows per LDS bank (a byte each), position and half wavefront
+  __shared__ uint16_t ent_all[kEmitWaves][rsr::kMaxPositions + kReach][64];
+  __shared__ uint32_t load_all[kEmitWaves][rsr::kMaxPositions + kReach][2][8];  // rows per LDS bank (a byte each), position and half wavefront
+  __shared__ uint8_t ends_all[kEmitWaves][rsr::kMaxPositions];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t ui = blockIdx.x * kEmitWaves + wave;
   if (ui >= nunits) return;  // (no barriers below: the wavefronts are independent)
@@ -508,7 +509,7 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   // flat instructions, each with a wait of its own - 2000 clocks for every position of a trade round.)
   uint16_t (*const ent)[64] = ent_all[wave];
   uint32_t* const load_words = &load_all[wave][0][0][0];
-  const uint8_t* const load_bytes = reinterpret_cast<const uint8_t*>(load_words);
+  uint8_t* const ends = ends_all[wave];
   auto settle = []() { asm volatile("" ::: "memory"); };
   const int half = lane >> 5;
   auto load_at = [&](int p, int b) { return (p * 2 + half) * 32 + b; };
@@ -596,40 +597,54 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
   // rows on average, by simulation: 3.45 deep without trades, 2.44 and 2.28 after one and two rounds, 2.24 after three; trades over
   // five positions instead of three 2.27.  One quarter after the other through every group, first improvement first: 2.24, and 655 us
   // instead of 101 at ternary 4096^2, k = 10, where the units with a long group took longest.)
+  // Bound by the instructions of one wavefront and two waits for the LDS per position: the end of a position's group comes from a table, what is
+  // kReach positions on has the same address plus a constant (up to kReach rows behind a unit may be read, and are not used), and a row
+  // that would trade places with one of its own bank needs no test (the loads do not change: a difference of 2).
+  if (lane < npos) {
+    const uint64_t rest = heads >> lane;
+    ends[lane] = (uint8_t)(rest ? lane + __ffsll((long long)rest) - 1 : 0);  // the group's head
+  }
+  settle();
   const int start = (lane & 3) * npos / 4;
+  uint16_t* const column = &ent[0][lane];
+  uint8_t* const banks = reinterpret_cast<uint8_t*>(load_words) + half * 32;
   for (int round = 0; round < kTradeRounds; ++round)
     for (int t = 0; t < npos; ++t) {
       settle();
       const int p = t + start < npos ? t + start : t + start - npos;
-      const uint64_t rest = heads >> p;
-      const int p1 = rest ? p + __ffsll((long long)rest) - 1 : 0;  // the group's head
-      if (p + 1 < p1) {
-        const uint32_t row = ent[p][lane];
-        uint32_t other[kReach];
+      const int others = (int)ends[p] - p - 1;  // rows of the group behind this one
+      uint16_t* const at = column + p * 64;
+      uint8_t* const load = banks + p * 64;
+      const uint32_t row = at[0];
+      uint32_t other[kReach];
 #pragma unroll
-        for (int i = 0; i < kReach; ++i) other[i] = ent[min(p + 1 + i, p1 - 1)][lane];
-        const int b = row & 31, here = load_bytes[load_at(p, b)];
-        int best = 0, with = 0;
-        int there_b[kReach], here_o[kReach], there_o[kReach];
+      for (int i = 0; i < kReach; ++i) other[i] = at[(i + 1) * 64];
+      const uint32_t b = row & 31;
+      const int here = load[b];
+      int best = 0, with = 0;
+      int there_b[kReach], here_o[kReach], there_o[kReach];
 #pragma unroll
-        for (int i = 0; i < kReach; ++i) {
-          const int q = min(p + 1 + i, p1 - 1), o = other[i] & 31;
-          there_b[i] = load_bytes[load_at(q, b)]; here_o[i] = load_bytes[load_at(p, o)]; there_o[i] = load_bytes[load_at(q, o)];
-        }
+      for (int i = 0; i < kReach; ++i) {
+        const uint32_t o = other[i] & 31;
+        there_b[i] = load[b + (i + 1) * 64]; here_o[i] = load[o]; there_o[i] = load[o + (i + 1) * 64];
+      }
 #pragma unroll
-        for (int i = 0; i < kReach; ++i) {
-          const int delta = (here_o[i] - here + 1) + (there_b[i] - there_o[i] + 1);
-          if (p + 1 + i < p1 && other[i] != null_index && (int)(other[i] & 31) != b && delta < best) { best = delta; with = i; }
-        }
-        if (best < 0 && row != null_index) {
-          uint32_t o = other[0];
+      for (int i = 0; i < kReach; ++i) {
+        const int delta = (here_o[i] - here + 1) + (there_b[i] - there_o[i] + 1);
+        if (i < others && other[i] != null_index && delta < best) { best = delta; with = i; }
+      }
+      if (best < 0 && row != null_index) {
+        uint32_t o = other[0];
 #pragma unroll
-          for (int i = 1; i < kReach; ++i) o = with == i ? other[i] : o;
-          const int q = p + 1 + with;
-          add_load(p, b, (uint32_t)-1); add_load(p, o & 31, 1u);
-          add_load(q, o & 31, (uint32_t)-1); add_load(q, b, 1u);
-          ent[p][lane] = (uint16_t)o; ent[q][lane] = (uint16_t)row;
-        }
+        for (int i = 1; i < kReach; ++i) o = with == i ? other[i] : o;
+        // (rows of a byte per bank: a bank's counter is a byte of a word)
+        uint32_t* const lb = load_words + (load - banks + half * 32) / 4 + b / 4;
+        uint32_t* const lo = load_words + (load - banks + half * 32) / 4 + (o & 31) / 4;
+        const uint32_t one_b = 1u << (8 * (b & 3)), one_o = 1u << (8 * (o & 3));
+        const int q = (with + 1) * 16;
+        atomicAdd(lb, 0u - one_b); atomicAdd(lo, one_o);
+        atomicAdd(lo + q, 0u - one_o); atomicAdd(lb + q, one_b);
+        at[0] = (uint16_t)o; at[(with + 1) * 64] = (uint16_t)row;
       }
     }
   unsigned char* to = stream + (int64_t)U.stream_off * rsr::kStreamAlign;
