@@ -8,8 +8,9 @@
 //                        ("bucket sort" in the proof of Theorem 3.6).
 //   3. plan_kernel       per panel: the segments ranked by their number of rows, the groups they form, how many
 //                        units and stream bytes those take.
-//   (host)               where every panel's units and streams begin: O(panels), no row data.
-//   4. units_kernel      per panel: the unit descriptors.
+//      begin_kernel      where every panel's units and streams begin, and what there is in all (which the host reads to
+//                        allocate the tables).
+//   4. units_kernel      per panel: the unit descriptors, the block offsets, the slots of cut segments.
 //   5. emit_kernel       per unit: the rows dealt out to the 64 lanes, the rows of a lane's segment spread over the
 //                        LDS banks, granule order.
 //
@@ -449,13 +450,94 @@ plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__
   }
 }
 
-// One wavefront per panel.
+// What the panels of a tile come to: read by the host when the last of them is planned.
+struct Totals {
+  unsigned long long units, stream, rows, segments, groups;  // stream in multiples of kStreamAlign
+  uint32_t block_units, extras;                              // of a block, of a panel, at most
+};
+
+// One workgroup: prefix sums over the panels of a run (`totals` holds those of the runs before; `first`: there are none).  A panel is a thread.
+// Bound by a chain: a read of memory, lane exchanges, the wavefronts' sums, a second read for the units of whole blocks.  (The sizes of all panels used
+// to be copied to the host, added up there and copied back, the slots of cut segments as well: five copies of 13 to 30 us.  Ternary 4096^2 with
+// product and release 324 us, 303 so.)
+constexpr int kBeginThreads = 1024;
+__global__ void __launch_bounds__(kBeginThreads)
+begin_kernel(int panels_per_block, uint32_t panels, bool first, const PanelInfo* __restrict__ info, PanelBase* base, Totals* __restrict__ totals) {
+  typedef unsigned long long u64;
+  // (a turn's sums fit 32 bits: a panel's units fit 16)
+  static_assert((u64)kBeginThreads * 0xffffu * rsr::kMaxPositions < (1ull << 32));
+  constexpr int kWaves = kBeginThreads / 64;
+  __shared__ uint32_t wave_units[kWaves], wave_stream[kWaves], block_units, extras;
+  __shared__ u64 rows, segments, groups;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  if (tid == 0) { rows = segments = groups = 0; block_units = extras = 0; }
+  u64 units = first ? 0 : totals->units, stream = first ? 0 : totals->stream;  // of the panels ahead of this turn
+  u64 my_rows = 0, my_segments = 0, my_groups = 0;
+  uint32_t my_extras = 0;
+  for (uint32_t p0 = 0; p0 < panels; p0 += nt) {
+    const uint32_t p = p0 + tid;
+    PanelInfo I{};
+    if (p < panels) I = info[p];
+    uint32_t u = I.units, st = I.stream;
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const uint32_t x = __shfl_up(u, d), y = __shfl_up(st, d);
+      if (lane >= d) { u += x; st += y; }
+    }
+    if (lane == 63) { wave_units[wave] = u; wave_stream[wave] = st; }
+    __syncthreads();
+    uint32_t all_units = 0, all_stream = 0;
+    for (int w = 0; w < nt / 64; ++w) {
+      if (w == wave) { u += all_units; st += all_stream; }
+      all_units += wave_units[w]; all_stream += wave_stream[w];
+    }
+    if (p < panels) base[p] = PanelBase{(uint32_t)units + u - I.units, (uint32_t)stream + st - I.stream};
+    units += all_units; stream += all_stream;
+    my_rows += I.rows; my_segments += I.segments; my_groups += (I.n8 + 7) / 8 + (I.n1 + 63) / 64;
+    my_extras = max(my_extras, I.extras);
+    __syncthreads();  // (the wavefronts' sums are read; and behind it the panels' beginnings are there for the whole workgroup)
+  }
+  uint32_t my_units = 0;
+  for (uint32_t b = tid; b < panels / panels_per_block; b += nt) {
+    const uint32_t next = (b + 1) * panels_per_block;
+    my_units = max(my_units, (next < panels ? base[next].unit : (uint32_t)units) - base[b * panels_per_block].unit);
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d /= 2) {
+    my_rows += __shfl_xor(my_rows, d); my_segments += __shfl_xor(my_segments, d); my_groups += __shfl_xor(my_groups, d);
+    my_units = max(my_units, (uint32_t)__shfl_xor(my_units, d)); my_extras = max(my_extras, (uint32_t)__shfl_xor(my_extras, d));
+  }
+  if (lane == 0) {
+    atomicAdd(&rows, my_rows); atomicAdd(&segments, my_segments); atomicAdd(&groups, my_groups);
+    atomicMax(&block_units, my_units); atomicMax(&extras, my_extras);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    Totals t{};
+    if (!first) t = *totals;
+    t.units = units; t.stream = stream;
+    t.rows += rows; t.segments += segments; t.groups += groups;
+    t.block_units = max(t.block_units, block_units); t.extras = max(t.extras, extras);
+    *totals = t;
+  }
+}
+
+// One wavefront per panel.  `extra_slots`: null if no segment of the tile is cut.
 __global__ void __launch_bounds__(64)
-units_kernel(Geometry g, const uint8_t* __restrict__ group_all, const PanelInfo* __restrict__ info, const PanelBase* __restrict__ base,
-             PUnit* __restrict__ units) {
+units_kernel(Geometry g, int nblocks, uint32_t nunits, const uint8_t* __restrict__ group_all, const PanelInfo* __restrict__ info,
+             const PanelBase* __restrict__ base, const uint32_t* __restrict__ extra_all, PUnit* __restrict__ units, uint32_t* __restrict__ blk_unit,
+             uint16_t* __restrict__ extra_slots) {
   __shared__ uint8_t groups[1024];
   const uint32_t panel = blockIdx.x;
   const PanelInfo I = info[panel];
+  if (panel % g.s.panels == 0 && threadIdx.x == 0) {
+    const uint32_t block = g.block0 + panel / g.s.panels;
+    blk_unit[block] = base[panel].unit;
+    if (block + 1 == (uint32_t)nblocks) blk_unit[nblocks] = nunits;
+  }
+  if (extra_slots)
+    for (uint32_t i = threadIdx.x; i < (uint32_t)g.extra_stride; i += 64)
+      extra_slots[(size_t)(g.panel0 + panel) * g.extra_stride + i] = i < I.extras ? (uint16_t)(extra_all[(int64_t)panel * g.extra_stride + i] & 0xffffu) : (uint16_t)0;
   const uint32_t ng = (I.n8 + 7) / 8 + (I.n1 + 63) / 64;
   for (uint32_t i = threadIdx.x; i < ng; i += 64) groups[i] = group_all[(int64_t)panel * g.group_stride + i];
   __syncthreads();
@@ -711,13 +793,13 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
   DevBuf work;
   size_t most = 0;  // bytes; 0: not asked yet
   constexpr size_t kMuch = (size_t)4 << 30;
-  size_t at_val, at_sigma, at_off, at_list, at_group, at_extra, at_info, at_base;
+  size_t at_val, at_sigma, at_off, at_list, at_group, at_extra, at_info, at_base, at_totals;
   for (;;) {
     const size_t nbp = (size_t)at_once * parts, np = (size_t)at_once * g.s.panels;
     bytes = 0;
     at_val = take(nbp * rows * 2); at_sigma = take(nbp * rows * 2); at_off = take(nbp * (nvals + 1) * 4);
     at_list = take(np * g.list_stride * 2); at_group = take(np * g.group_stride); at_extra = take(np * g.extra_stride * 4);
-    at_info = take(np * sizeof(PanelInfo)); at_base = take(np * sizeof(PanelBase));
+    at_info = take(np * sizeof(PanelInfo)); at_base = take((size_t)npanels * sizeof(PanelBase)); at_totals = take(sizeof(Totals));
     if (bytes > kMuch && most == 0) {
       size_t total = 0;
       PREP_TRY(hipMemGetInfo(&most, &total));
@@ -735,7 +817,8 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
   uint8_t* const group = w + at_group;
   uint32_t* const extra = reinterpret_cast<uint32_t*>(w + at_extra);
   PanelInfo* const info = reinterpret_cast<PanelInfo*>(w + at_info);
-  PanelBase* const base = reinterpret_cast<PanelBase*>(w + at_base);
+  PanelBase* const base = reinterpret_cast<PanelBase*>(w + at_base);  // of all panels
+  Totals* const totals = reinterpret_cast<Totals*>(w + at_totals);
 
   // Steps 1 to 3 for the blocks b0 .. b0 + nb - 1.
   auto plan = [&](int64_t b0, int64_t nb) -> int {
@@ -756,61 +839,47 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
     PREP_TRY(hipGetLastError());
     return 0;
   };
-  std::vector<PanelInfo> hinfo((size_t)npanels);
+  Totals sums{};
+  std::vector<uint32_t> first_unit;  // of every run
   for (int64_t b0 = 0; b0 < nblocks; b0 += at_once) {
     const int64_t nb = std::min(at_once, nblocks - b0);
     const int rc = plan(b0, nb);
     if (rc != 0) return rc;
-    PREP_TRY(hipMemcpy(&hinfo[(size_t)(b0 * g.s.panels)], info, (size_t)(nb * g.s.panels) * sizeof(PanelInfo), hipMemcpyDeviceToHost));
+    first_unit.push_back((uint32_t)sums.units);
+    hipLaunchKernelGGL(begin_kernel, dim3(1), dim3((unsigned)std::min<int64_t>(kBeginThreads, (nb * g.s.panels + 63) / 64 * 64)), 0, nullptr, g.s.panels, (uint32_t)(nb * g.s.panels), b0 == 0,
+                       static_cast<const PanelInfo*>(info), base + b0 * g.s.panels, totals);
+    PREP_TRY(hipGetLastError());
+    PREP_TRY(hipMemcpy(&sums, totals, sizeof(Totals), hipMemcpyDeviceToHost));
+    if (sums.units > 0x7fffffffull || sums.stream > 0xffffffffull) { *err = "index too large"; return RSR_ERR_UNSUPPORTED; }
   }
-
-  // ---- where every panel's units and streams begin (host; no row data involved) ----
-  std::vector<PanelBase> hbase((size_t)npanels);
-  std::vector<uint32_t> blk_unit((size_t)nblocks + 1);
-  uint64_t nunits = 0, nstream = 0;
-  uint32_t max_units = 0;
-  uint32_t extras = 0;
-  out->stored_rows = 0; out->segments = 0; out->head_bytes = 0;
-  for (int64_t b = 0; b < nblocks; ++b) {
-    blk_unit[(size_t)b] = (uint32_t)nunits;
-    const uint64_t first = nunits;
-    for (int i = 0; i < g.s.panels; ++i) {
-      const size_t at = (size_t)(b * g.s.panels + i);
-      const PanelInfo& I = hinfo[at];
-      hbase[at] = PanelBase{(uint32_t)nunits, (uint32_t)nstream};
-      nunits += I.units; nstream += I.stream;
-      extras = std::max(extras, I.extras);
-      out->stored_rows += I.rows; out->segments += I.segments;
-      out->head_bytes += ((int64_t)(I.n8 + 7) / 8 + (I.n1 + 63) / 64) * rsr::kPositionBytes;
-      if (nunits > 0x7fffffffull || nstream > 0xffffffffull) { *err = "index too large"; return RSR_ERR_UNSUPPORTED; }
-    }
-    max_units = std::max<uint32_t>(max_units, (uint32_t)(nunits - first));
-  }
-  blk_unit[(size_t)nblocks] = (uint32_t)nunits;
+  const uint64_t nunits = sums.units, nstream = sums.stream;
+  const uint32_t extras = sums.extras;
+  first_unit.push_back((uint32_t)nunits);
+  out->stored_rows = (int64_t)sums.rows; out->segments = (int64_t)sums.segments; out->head_bytes = (int64_t)sums.groups * rsr::kPositionBytes;
 
   // One allocation for the tables: streams, descriptors, block offsets, slots of cut segments.
   DevBuf tables;
   bytes = 0;
   out->stream_bytes = (size_t)nstream * rsr::kStreamAlign;
   out->unit_bytes = (size_t)nunits * sizeof(PUnit);
-  out->blk_bytes = blk_unit.size() * 4;
+  out->blk_bytes = (size_t)(nblocks + 1) * 4;
   out->extra_bytes = extras ? (size_t)npanels * g.extra_stride * 2 : 0;
   const size_t at_stream = take(out->stream_bytes + 1024), at_units = take(out->unit_bytes + rsr::kUnitsBehind * sizeof(PUnit)), at_blk = take(out->blk_bytes + 16);
   const size_t at_slots = take(out->extra_bytes);
   PREP_TRY(hipMalloc(&tables.p, bytes));
   unsigned char* const t = static_cast<unsigned char*>(tables.p);
-  PREP_TRY(hipMemcpy(t + at_blk, blk_unit.data(), out->blk_bytes, hipMemcpyHostToDevice));
   PUnit* const units = reinterpret_cast<PUnit*>(t + at_units);
-  for (int64_t b0 = 0; b0 < nblocks; b0 += at_once) {
+  uint16_t* const slots = extras ? reinterpret_cast<uint16_t*>(t + at_slots) : nullptr;
+  for (int64_t b0 = 0, run = 0; b0 < nblocks; b0 += at_once, ++run) {
     const int64_t nb = std::min(at_once, nblocks - b0), p0 = b0 * g.s.panels, np = nb * g.s.panels;
     if (at_once < nblocks) {
       const int rc = plan(b0, nb);
       if (rc != 0) return rc;
     }
-    const uint32_t u0 = blk_unit[(size_t)b0], nu = blk_unit[(size_t)(b0 + nb)] - u0;
-    PREP_TRY(hipMemcpy(base, hbase.data() + p0, (size_t)np * sizeof(PanelBase), hipMemcpyHostToDevice));
-    hipLaunchKernelGGL(units_kernel, dim3((unsigned)np), dim3(64), 0, nullptr, g, static_cast<const uint8_t*>(group),
-                       static_cast<const PanelInfo*>(info), static_cast<const PanelBase*>(base), units);
+    const uint32_t u0 = first_unit[(size_t)run], nu = first_unit[(size_t)run + 1] - u0;
+    hipLaunchKernelGGL(units_kernel, dim3((unsigned)np), dim3(64), 0, nullptr, g, (int)nblocks, (uint32_t)nunits, static_cast<const uint8_t*>(group),
+                       static_cast<const PanelInfo*>(info), static_cast<const PanelBase*>(base + p0), static_cast<const uint32_t*>(extra), units,
+                       reinterpret_cast<uint32_t*>(t + at_blk), slots);
     PREP_TRY(hipGetLastError());
     // (a grid holds 2^32 threads)
     constexpr uint32_t kUnitsAtOnce = 1u << 25;
@@ -821,24 +890,16 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
                          static_cast<const uint32_t*>(extra), static_cast<const uint32_t*>(off), static_cast<const uint16_t*>(sigma), t + at_stream);
       PREP_TRY(hipGetLastError());
     }
-    if (extras) {
-      std::vector<uint32_t> x((size_t)np * g.extra_stride);
-      std::vector<uint16_t> slots(x.size(), 0);
-      PREP_TRY(hipMemcpy(x.data(), extra, x.size() * 4, hipMemcpyDeviceToHost));
-      for (size_t i = 0; i < x.size(); ++i)
-        if (i % g.extra_stride < hinfo[(size_t)p0 + i / g.extra_stride].extras) slots[i] = (uint16_t)(x[i] & 0xffffu);
-      PREP_TRY(hipMemcpy(t + at_slots + (size_t)p0 * g.extra_stride * 2, slots.data(), slots.size() * 2, hipMemcpyHostToDevice));
-    }
   }
   PREP_TRY(hipStreamSynchronize(nullptr));
   out->shape = g.s;
   out->extra_stride = g.extra_stride; out->max_extras = (int)extras; out->fill = g.fill != 0;
   out->nunits = (int64_t)nunits;
-  out->max_units_per_block = max_units;
+  out->max_units_per_block = sums.block_units;
   out->d_stream = t + at_stream;
   out->d_units = units;
   out->d_blk_unit = t + at_blk;
-  out->d_extras = extras ? t + at_slots : nullptr;
+  out->d_extras = slots;
   out->d_tables = tables.release();
   return 0;
 }
