@@ -941,7 +941,56 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     // 7388 x 5593, k = 11, two float vectors: 11.05 us so, 10.24 with four steps and their second part at once; 5215 x 1990, sixteen int8
     // vectors, four per pass: 12.8 and 12.1.)
     constexpr int kTogether = PLAIN || M::slot_bytes > 8 ? 2 : V > 1 ? 4 : 8;
-    if (frows % kTogether == 0)
+    // Two int8 vectors, panels of one part with several groups of four steps: a group is read while the one before is added up, in the same
+    // order, so that the LDS is waited for once.  (Four waits in a panel of 4096 slots are a fifth of its fold, and panels wait for the
+    // room that it takes: binary 16384^2, eight vectors, 29.9 us without, 28.9 so.  One float vector, with two groups of eight steps: 41.0 us and
+    // 42.1 for eight, and slower where no panel takes this path, too; it keeps them.)
+    constexpr bool kAhead = M::slot_bytes == 4 && V > 1;
+    if (kAhead && !both && frows % 8 == 0) {
+      if constexpr (kAhead) {
+        Read even[4], odd[4];
+        auto read = [&](Read (&q)[4], int i) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) q[r].read(first_quad + (i + r) * kRowBytes, turn);
+        };
+        auto add = [&](const Read (&q)[4], int i) {
+          if (!fill)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Read::clear(first_quad + (i + r) * kRowBytes);
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            AT x[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              AT d[4];
+#pragma unroll
+              for (int c = 0; c < 4; ++c) d[c] = q[r].get(c, j);
+              const Quad<AT> t = quad_of<M>(d, turn);
+              hi[j][0] += t.odd;
+              hi[j][1] += t.high;
+              x[r] = t.all;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; r += 2) {
+              const AT g = x[r] + x[r + 1];
+              hi[j][2] += x[r + 1];
+              if (r) hi[j][3] += g;
+              if ((i >> 2) & 1) hi[j][4] += g;
+              if ((i >> 3) & 1) hi[j][5] += g;
+              tot[j] += g;
+            }
+          }
+        };
+        read(even, 0);
+#pragma unroll 1
+        for (int i = 0; i < frows; i += 8) {
+          read(odd, i + 4);
+          add(even, i);
+          if (i + 8 < frows) read(even, i + 8);
+          add(odd, i + 4);
+        }
+      }
+    } else if (frows % kTogether == 0)
 #pragma unroll 1
       for (int i = 0; i < frows; i += kTogether) fold_steps.template operator()<kTogether>(i);
     else if (frows == 1)
