@@ -11,7 +11,7 @@
 //      begin_kernel      where every panel's units and streams begin, and what there is in all (which the host reads to
 //                        allocate the tables).
 //   4. units_kernel      per panel: the unit descriptors, the block offsets, the slots of cut segments.
-//   5. emit_kernel       per unit: the rows dealt out to the 64 lanes, the rows of a lane's segment spread over the
+//   5. emit_kernel       per half of a unit: the rows dealt out to the lanes, the rows of a lane's segment spread over the
 //                        LDS banks, granule order.
 //
 // Steps 1 to 3 and 4 to 5 run over all column blocks at once where a grid can hold their panels and the device has the
@@ -567,9 +567,11 @@ units_kernel(Geometry g, int nblocks, uint32_t nunits, const uint8_t* __restrict
              });
 }
 
-// One wavefront per unit: its rows and heads are collected in LDS (ent), the rows of every segment trade places, and the granules are
-// written out.  Bound by the latency of chains - list, offsets, rows from memory; entries, bank loads, exchange in LDS - so
-// four groups go through the first together, and through the second four quarters of the lanes, each elsewhere in the unit.
+// One wavefront per half of a unit (lanes 0 to 31 or 32 to 63 of those that will sum it: the LDS serves the halves one after the other, so
+// that their banks have nothing to do with each other).  Two lanes work on every column of rows: they collect every other group's rows and
+// heads in LDS (ent), let the rows of every segment trade places in two halves of the unit, and write every other granule.  Bound by the latency
+// of chains - list, offsets, rows from memory; entries, bank loads, exchange in LDS - so four groups go through the first together, and
+// there are twice as many and half as long chains as with a wavefront per unit (ternary 4096^2, k = 10: 60 us so, 45 now).
 constexpr int kEmitWaves = 4;
 constexpr int kGroupsAtOnce = 4;
 constexpr int kReach = 3;        // positions a row may move per trade
@@ -578,35 +580,36 @@ __global__ void __launch_bounds__(64 * kEmitWaves)
 emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const PanelInfo* __restrict__ info, const uint16_t* __restrict__ list_all,
             const uint32_t* __restrict__ extra_all, const uint32_t* __restrict__ off, const uint16_t* __restrict__ sigma,
             unsigned char* __restrict__ stream) {
-  __shared__ uint16_t ent_all[kEmitWaves][rsr::kMaxPositions + kReach][64];
-  __shared__ uint32_t load_all[kEmitWaves][rsr::kMaxPositions + kReach][2][8];  // rows per LDS bank (a byte each), position and half wavefront
+  __shared__ uint16_t ent_all[kEmitWaves][rsr::kMaxPositions + kReach][32];
+  __shared__ uint32_t load_all[kEmitWaves][rsr::kMaxPositions + kReach][8];  // rows per LDS bank (a byte each) and position
   __shared__ uint8_t ends_all[kEmitWaves][rsr::kMaxPositions];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t ui = blockIdx.x * kEmitWaves + wave;
+  const uint32_t ui = (blockIdx.x * kEmitWaves + wave) / 2;
   if (ui >= nunits) return;  // (no barriers below: the wavefronts are independent)
+  const int half = wave & 1, c = lane & 31, turn = lane >> 5;  // the lane's column of the half, and which of its two lanes it is
+  const uint32_t column_lane = (uint32_t)(half * 32 + c);      // the lane that will sum it
   const PUnit U = units[ui];
   const int npos = U.npos;
   if (npos == 0) return;
   // (Plain accesses, and a barrier to the compiler where other lanes' atomics have to be seen: volatile ones through these pointers are
   // flat instructions, each with a wait of its own - 2000 clocks for every position of a trade round.)
-  uint16_t (*const ent)[64] = ent_all[wave];
-  uint32_t* const load_words = &load_all[wave][0][0][0];
+  uint16_t (*const ent)[32] = ent_all[wave];
+  uint32_t* const load_words = &load_all[wave][0][0];
   uint8_t* const ends = ends_all[wave];
   auto settle = []() { asm volatile("" ::: "memory"); };
-  const int half = lane >> 5;
-  auto load_at = [&](int p, int b) { return (p * 2 + half) * 32 + b; };
-  auto add_load = [&](int p, int b, uint32_t x) { atomicAdd(&load_words[load_at(p, b) >> 2], x << (8 * (b & 3))); };
+  auto add_load = [&](int p, int b) { atomicAdd(&load_words[p * 8 + (b >> 2)], 1u << (8 * (b & 3))); };
   const uint32_t panel = U.panel - g.panel0;
   const PanelInfo I = info[panel];
   const uint64_t heads = (uint64_t)U.heads_lo | ((uint64_t)U.heads_hi << 32);
   const int wbits = U.wide ? 3 : 0;
   const uint32_t end = U.wide ? I.n8 : I.n8 + I.n1;
-  const uint32_t sub = (uint32_t)lane & ((1u << wbits) - 1);
+  const uint32_t sub = column_lane & ((1u << wbits) - 1);
   const bool owner = sub == 0;
   const uint16_t* list = list_all + (int64_t)panel * g.list_stride;
   const uint16_t null_index = (uint16_t)g.rows;
-  for (int i = lane; i < rsr::kMaxPositions * 2 * 8; i += 64) load_words[i] = 0;
-  uint32_t entry = U.first + ((uint32_t)lane >> wbits);
+  for (int i = lane; i < rsr::kMaxPositions * 8; i += 64) load_words[i] = 0;
+  const uint32_t step = 64u >> wbits;
+  uint32_t entry = U.first + (column_lane >> wbits) + (turn ? step : 0u);
   for (int p0 = 0; p0 < npos;) {
     // the next groups: where they begin and how many rows a lane has
     int at[kGroupsAtOnce], m[kGroupsAtOnce];
@@ -614,24 +617,26 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
     const uint16_t* rows[kGroupsAtOnce];
 #pragma unroll
     for (int i = 0; i < kGroupsAtOnce; ++i) {
-      const uint64_t rest = p0 < npos ? heads >> p0 : 0;
-      at[i] = p0; m[i] = -1; s[i] = 0xffffffffu;
-      if (rest == 0) {
-        if (p0 < npos) {  // the position that makes the count even
-          for (; p0 < npos; ++p0) ent[p0][lane] = null_index;
+      at[i] = 0; m[i] = -1; s[i] = 0xffffffffu;
+#pragma unroll
+      for (int which = 0; which < 2; ++which) {  // the next two groups, one for either lane of a column
+        const uint64_t rest = p0 < npos ? heads >> p0 : 0;
+        if (rest == 0) {
+          for (; p0 < npos; ++p0) ent[p0][c] = null_index;  // the position that makes the count even
+          continue;
         }
-        continue;
+        const int length = __ffsll((long long)rest) - 1;
+        if (which == turn) { at[i] = p0; m[i] = length; }
+        p0 += length + 1;
       }
-      m[i] = __ffsll((long long)rest) - 1;
-      if (entry < end) s[i] = list[entry];
-      p0 += m[i] + 1;
-      entry += 64u >> wbits;
+      if (m[i] >= 0 && entry < end) s[i] = list[entry];
+      entry += 2 * step;
     }
     uint32_t o0[kGroupsAtOnce], o1[kGroupsAtOnce], piece[kGroupsAtOnce], bp[kGroupsAtOnce];
 #pragma unroll
     for (int i = 0; i < kGroupsAtOnce; ++i) {
       o0[i] = o1[i] = piece[i] = bp[i] = 0;
-      slot[i] = (uint32_t)g.s.nslots + (lane & (rsr::kDummySlots - 1));
+      slot[i] = (uint32_t)g.s.nslots + (column_lane & (rsr::kDummySlots - 1));
       if (s[i] == 0xffffffffu) continue;
       uint32_t of = s[i];
       if (of >= (uint32_t)g.s.nslots) {
@@ -662,23 +667,23 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
 #pragma unroll
       for (int i = 0; i < kGroupsAtOnce; ++i)
         if (j < m[i]) {
-          ent[at[i] + j][lane] = row[i];
-          if (row[i] != null_index) add_load(at[i] + j, row[i] & 31, 1u);
+          ent[at[i] + j][c] = row[i];
+          if (row[i] != null_index) add_load(at[i] + j, row[i] & 31);
         }
     }
 #pragma unroll
     for (int i = 0; i < kGroupsAtOnce; ++i)
-      if (m[i] >= 0) ent[at[i] + m[i]][lane] = (uint16_t)slot[i];
+      if (m[i] >= 0) ent[at[i] + m[i]][c] = (uint16_t)slot[i];
   }
   // The order of the rows inside a segment is free (a segment is a sum).  The LDS has 32 banks of 4 bytes and
   // serves the two halves of a wavefront one after the other; a half costs as many clocks as its fullest bank has
   // distinct addresses.  Two rows of a lane's segment trade places where that lowers the squared loads of the banks
   // (row mod 32) at their two positions most: the gathers of the product then meet in fewer banks.
-  // A quarter of the lanes at a time at a position: the lanes of a group stand at the same one, and would all leave a crowded bank at
-  // once.  The four quarters go round the unit's positions a quarter of the way apart.  (Fullest bank of a half wavefront for 4096 segments of 4
-  // rows on average, by simulation: 3.45 deep without trades, 2.44 and 2.28 after one and two rounds, 2.24 after three; trades over
-  // five positions instead of three 2.27.  One quarter after the other through every group, first improvement first: 2.24, and 655 us
-  // instead of 101 at ternary 4096^2, k = 10, where the units with a long group took longest.)
+  // A quarter of the columns at a time at a position: the lanes of a group stand at the same one, and would all leave a crowded bank at
+  // once.  The four quarters, and the two lanes of a column, go round the unit's positions apart from each other.  (Fullest bank of a half wavefront
+  // for 4096 segments of 4 rows on average, by simulation: 3.45 deep without trades, 2.44 and 2.28 after one and two rounds, 2.24 after
+  // three; trades over five positions instead of three 2.27.  One quarter after the other through every group, first improvement first: 2.24.)
+  // The two lanes of a column stay half a unit apart, further than a trade reaches; in units too short for that one of them does it all.
   // Bound by the instructions of one wavefront and two waits for the LDS per position: the end of a position's group comes from a table, what is
   // kReach positions on has the same address plus a constant (up to kReach rows behind a unit may be read, and are not used), and a row
   // that would trade places with one of its own bank needs no test (the loads do not change: a difference of 2).
@@ -687,20 +692,22 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
     ends[lane] = (uint8_t)(rest ? lane + __ffsll((long long)rest) - 1 : 0);  // the group's head
   }
   settle();
-  const int start = (lane & 3) * npos / 4;
-  uint16_t* const column = &ent[0][lane];
-  uint8_t* const banks = reinterpret_cast<uint8_t*>(load_words) + half * 32;
-  for (int round = 0; round < kTradeRounds; ++round)
-    for (int t = 0; t < npos; ++t) {
+  const bool two = npos / 2 > kReach;
+  const int places = two ? npos / 2 : npos;  // (npos is even)
+  const int start = two ? (c & 3) * npos / 8 + turn * places : (c & 3) * npos / 4;
+  uint16_t* const column = &ent[0][c];
+  uint8_t* const banks = reinterpret_cast<uint8_t*>(load_words);
+  for (int round = 0; round < kTradeRounds && (two || turn == 0); ++round)
+    for (int t = 0; t < places; ++t) {
       settle();
       const int p = t + start < npos ? t + start : t + start - npos;
       const int others = (int)ends[p] - p - 1;  // rows of the group behind this one
-      uint16_t* const at = column + p * 64;
-      uint8_t* const load = banks + p * 64;
+      uint16_t* const at = column + p * 32;
+      uint8_t* const load = banks + p * 32;
       const uint32_t row = at[0];
       uint32_t other[kReach];
 #pragma unroll
-      for (int i = 0; i < kReach; ++i) other[i] = at[(i + 1) * 64];
+      for (int i = 0; i < kReach; ++i) other[i] = at[(i + 1) * 32];
       const uint32_t b = row & 31;
       const int here = load[b];
       int best = 0, with = 0;
@@ -708,7 +715,7 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
 #pragma unroll
       for (int i = 0; i < kReach; ++i) {
         const uint32_t o = other[i] & 31;
-        there_b[i] = load[b + (i + 1) * 64]; here_o[i] = load[o]; there_o[i] = load[o + (i + 1) * 64];
+        there_b[i] = load[b + (i + 1) * 32]; here_o[i] = load[o]; there_o[i] = load[o + (i + 1) * 32];
       }
 #pragma unroll
       for (int i = 0; i < kReach; ++i) {
@@ -720,25 +727,26 @@ emit_kernel(Geometry g, uint32_t nunits, const PUnit* __restrict__ units, const 
 #pragma unroll
         for (int i = 1; i < kReach; ++i) o = with == i ? other[i] : o;
         // (rows of a byte per bank: a bank's counter is a byte of a word)
-        uint32_t* const lb = load_words + (load - banks + half * 32) / 4 + b / 4;
-        uint32_t* const lo = load_words + (load - banks + half * 32) / 4 + (o & 31) / 4;
+        uint32_t* const lb = load_words + p * 8 + b / 4;
+        uint32_t* const lo = load_words + p * 8 + (o & 31) / 4;
         const uint32_t one_b = 1u << (8 * (b & 3)), one_o = 1u << (8 * (o & 3));
-        const int q = (with + 1) * 16;
+        const int q = (with + 1) * 8;
         atomicAdd(lb, 0u - one_b); atomicAdd(lo, one_o);
         atomicAdd(lo + q, 0u - one_o); atomicAdd(lb + q, one_b);
-        at[0] = (uint16_t)o; at[(with + 1) * 64] = (uint16_t)row;
+        at[0] = (uint16_t)o; at[(with + 1) * 32] = (uint16_t)row;
       }
     }
   unsigned char* to = stream + (int64_t)U.stream_off * rsr::kStreamAlign;
+  settle();  // (what the other lane of the column has left)
   const int full = npos / rsr::kGranulePositions;
-  for (int gq = 0; gq < full; ++gq) {
+  for (int gq = turn; gq < full; gq += 2) {
     uint32_t w[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)ent[gq * 8 + 2 * j][lane] | ((uint32_t)ent[gq * 8 + 2 * j + 1][lane] << 16);
-    reinterpret_cast<uint4*>(to)[gq * 64 + lane] = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)ent[gq * 8 + 2 * j][c] | ((uint32_t)ent[gq * 8 + 2 * j + 1][c] << 16);
+    reinterpret_cast<uint4*>(to)[gq * 64 + column_lane] = make_uint4(w[0], w[1], w[2], w[3]);
   }
-  for (int p = full * 8; p < npos; p += 2)
-    reinterpret_cast<uint32_t*>(to)[p * 32 + lane] = (uint32_t)ent[p][lane] | ((uint32_t)ent[p + 1][lane] << 16);
+  for (int p = full * 8 + 2 * turn; p < npos; p += 4)
+    reinterpret_cast<uint32_t*>(to)[p * 32 + column_lane] = (uint32_t)ent[p][c] | ((uint32_t)ent[p + 1][c] << 16);
 }
 
 struct DevBuf {  // frees on scope exit
@@ -881,11 +889,11 @@ int device_build_tile(const int8_t* dA, int64_t rows, int64_t cols, int64_t ld, 
                        static_cast<const PanelInfo*>(info), static_cast<const PanelBase*>(base + p0), static_cast<const uint32_t*>(extra), units,
                        reinterpret_cast<uint32_t*>(t + at_blk), slots);
     PREP_TRY(hipGetLastError());
-    // (a grid holds 2^32 threads)
-    constexpr uint32_t kUnitsAtOnce = 1u << 25;
+    // (a grid holds 2^32 threads, a unit takes 128)
+    constexpr uint32_t kUnitsAtOnce = 1u << 24;
     for (uint32_t u = 0; u < nu; u += kUnitsAtOnce) {
       const uint32_t n = std::min(kUnitsAtOnce, nu - u);
-      hipLaunchKernelGGL(emit_kernel, dim3((n + kEmitWaves - 1) / kEmitWaves), dim3(64 * kEmitWaves), 0, nullptr, g, n,
+      hipLaunchKernelGGL(emit_kernel, dim3((2 * n + kEmitWaves - 1) / kEmitWaves), dim3(64 * kEmitWaves), 0, nullptr, g, n,
                          static_cast<const PUnit*>(units) + u0 + u, static_cast<const PanelInfo*>(info), static_cast<const uint16_t*>(list),
                          static_cast<const uint32_t*>(extra), static_cast<const uint32_t*>(off), static_cast<const uint16_t*>(sigma), t + at_stream);
       PREP_TRY(hipGetLastError());
