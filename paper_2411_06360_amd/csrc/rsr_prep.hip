@@ -248,7 +248,10 @@ __device__ __forceinline__ void walk_units(const PanelInfo& I, GroupRows group_r
     const uint32_t per = wide ? 8u : 64u, count = wide ? I.n8 : I.n1;
     const uint32_t ng = (count + per - 1) / per;
     uint32_t all = 0;
-    for (uint32_t i = 0; i < ng; ++i) all += group_rows(group + i) + 1;
+    for (uint32_t i = (uint32_t)group_rows.lane; i < ng; i += 64) all += group_rows.rows[group + i] + 1u;
+#pragma unroll
+    for (int d = 32; d > 0; d /= 2) all += __shfl_xor(all, d);
+    all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
     const uint32_t nu = (all + rsr::kMaxPositions - 5) / (rsr::kMaxPositions - 4);
     const uint32_t target = nu ? (all + nu - 1) / nu : 0;
     uint32_t first = 0, cur = 0;
@@ -284,7 +287,7 @@ __global__ void __launch_bounds__(256)
 plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__ list_all, uint8_t* __restrict__ group_all,
             uint32_t* __restrict__ extra_all, PanelInfo* __restrict__ info) {
   __shared__ uint16_t len[rsr::kMaxPanelSlots], rank[rsr::kMaxPanelSlots], list[rsr::kMaxPanelSlots + rsr::kMaxExtras];
-  __shared__ uint16_t cnt[kKeys][64];
+  __shared__ __align__(4) uint16_t cnt[kKeys][64];
   __shared__ uint32_t hist[rsr::kWideRows + 1], above[rsr::kWideRows + 2], start[kKeys + 1], ex_slot[rsr::kMaxExtras];
   __shared__ uint16_t ex_rank[rsr::kMaxExtras];
   __shared__ uint8_t ex_key[rsr::kMaxExtras], groups[1024];
@@ -299,17 +302,28 @@ plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__
   __syncthreads();
   {
     uint32_t my_rows = 0, my_segments = 0;
-    for (int s = tid; s < g.s.nslots; s += 256) {
-      uint32_t bp, value, n = 0;
-      const bool real = slot_value(g, panel, (uint32_t)s, &bp, &value);
-      if (real) {
-        const uint32_t* o = off + (int64_t)bp * ((1 << g.k) + 1) + value;
-        n = o[1] - o[0];
+    constexpr int kTogether = 4;  // slots of a thread whose offsets are fetched together
+    for (int s0 = tid; s0 < g.s.nslots; s0 += 256 * kTogether) {
+      uint32_t o0[kTogether], o1[kTogether];
+      bool real[kTogether];
+#pragma unroll
+      for (int j = 0; j < kTogether; ++j) {
+        const uint32_t s = (uint32_t)min(s0 + 256 * j, g.s.nslots - 1);
+        uint32_t bp, value;
+        real[j] = slot_value(g, panel, s, &bp, &value);
+        const uint32_t* o = off + (int64_t)bp * ((1 << g.k) + 1) + (real[j] ? value : 0u);
+        o0[j] = o[0]; o1[j] = o[1];
       }
-      len[s] = n || (real && g.fill) ? (uint16_t)n : kNoSegment;
-      if (n) {
-        my_rows += n; ++my_segments;
-        if (n <= (uint32_t)rsr::kWideRows) atomicAdd(&hist[n], 1u);
+#pragma unroll
+      for (int j = 0; j < kTogether; ++j) {
+        const int s = s0 + 256 * j;
+        if (s >= g.s.nslots) break;
+        const uint32_t n = real[j] ? o1[j] - o0[j] : 0u;
+        len[s] = n || (real[j] && g.fill) ? (uint16_t)n : kNoSegment;
+        if (n) {
+          my_rows += n; ++my_segments;
+          if (n <= (uint32_t)rsr::kWideRows) atomicAdd(&hist[n], 1u);
+        }
       }
     }
     atomicAdd(&tot_rows, my_rows);
@@ -391,11 +405,15 @@ plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__
     if (lane == 0) n_extra = min(extras, (uint32_t)g.extra_stride);
   }
   __syncthreads();
-  for (int key = tid >> 6; key < kKeys; key += 4) {  // a wavefront per class, lane = residue
-    uint32_t s = cnt[key][lane];
-#pragma unroll
-    for (int d = 32; d > 0; d /= 2) s += __shfl_xor(s, d);
-    if (lane == 0) start[key + 1] = s;
+  if (tid < kKeys) {  // a thread per class, two residues at a time, every thread from another bank on
+    const uint32_t* const pairs = reinterpret_cast<const uint32_t*>(cnt[tid]);
+    uint32_t s = 0;
+#pragma unroll 8
+    for (int i = 0; i < 32; ++i) {
+      const uint32_t two = pairs[(i + tid) & 31];
+      s += (two & 0xffffu) + (two >> 16);
+    }
+    start[tid + 1] = s;
   }
   __syncthreads();
   if (tid < 64) {  // prefix sums over the classes, two per lane
