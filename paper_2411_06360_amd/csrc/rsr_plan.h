@@ -232,11 +232,13 @@ inline const Pass& pass_of(bool i8, Mode m) {
 // is estimated from its plan: how many rounds of workgroups an XCD goes through (the siblings of a block range share one: with fewer
 // than eight block ranges some XCDs stay idle), and how long a round takes: the start and the rows staged, and then the longest of what
 // keeps the compute unit busy, of a wavefront's units and a fold one after the other, and of the panels that wait for room, where
-// there are more than fit (the root of the sum of the squares: none hides the others entirely).  In microseconds, fitted to the times of all
-// three passes of 2227 matrices on an MI355X: 1585 of 1024 to 32768 rows with k from 8 to 13 and 642 of 16 to 32768 rows with k from 1 to
-// 16 (binary, ternary, correlated; 2 to 300 vectors).  On average the choice is 0.3 (float) and 0.7 % (int8) slower than the best of the
-// three; 0.4 and 0.7 % on one half of the matrices with the constants fitted to the other half.  The rule before (rounds of units of the whole
-// device, and a count of the units that have room; fitted to 170 matrices of the first kind and up to sixteen vectors): 1.2 and 1.5 %,
+// there are more than fit (the root of the sum of the squares: none hides the others entirely).  In microseconds.  Float: fitted to the times
+// of all three passes of 3222 matrices of 1024 to 32768 rows with k from 8 to 13 and 2 to 16 vectors, and 290 of 16 to 32768 rows with k from 3 to
+// 16 and 2 to 300 vectors.  On average the choice is 0.4 % slower than the best of the three on the former and 0.3 % on the latter, one product in
+// 35 more than 5 % (with the constants fitted to the kernels whose staging requested four pieces per thread and vector whatever the row count: 1.1 and
+// 0.2 %, one in eleven).  int8: fitted earlier, to 2227 matrices of both kinds; 0.8 and 0.4 % (fitting them again gained nothing).  The
+// rule before (rounds of units of the whole device, and a count of the units that have room; fitted to 170 matrices of the first kind and
+// up to sixteen vectors): 1.2 and 1.5 %,
 // and up to twice the time (ternary 16867 x 47, k = 8, 64 float vectors: 20.0 us with one per pass, 10.4 with two; binary 4868 x 19245,
 // k = 11, eleven: 41 and 27).
 struct PassCosts {
@@ -250,9 +252,9 @@ struct PassCosts {
   double crowd;               // exponent of the workgroups that share a compute unit
 };
 constexpr PassCosts kCosts[2][3] = {  // [int8][one, two, four vectors]
-    {{1.764, 2.260, 0.532, 2.716, 0.543, 1.168, 1.104, 1.099, 0.007, 0.589, 0.968, 0.495, 1.133, 0.973},
-     {2.390, 2.697, 1.085, 0.213, 0.420, 0.827, 0.736, 0.926, 0.666, 0.934, 1.147, 2.188, 1.259, 0.853},
-     {2.055, 3.303, 2.265, 0.090, 0.000, 0.580, 1.828, 0.454, 2.303, 2.437, 1.230, 7.893, 1.681, 1.131}},
+    {{0.766, 2.774, 0.694, 0.158, 0.352, 0.727, 1.507, 1.253, 0.000, 0.097, 0.364, 1.036, 2.005, 0.860},
+     {1.577, 2.220, 0.613, 0.225, 1.018, 0.455, 1.729, 0.991, 0.650, 0.597, 0.781, 2.085, 1.909, 0.776},
+     {1.062, 3.340, 1.171, 0.477, 0.663, 0.239, 2.039, 0.569, 2.469, 1.300, 1.357, 6.309, 1.828, 0.842}},
     {{1.896, 1.799, 1.295, 0.862, 0.750, 1.035, 1.730, 1.048, 0.039, 0.508, 0.928, 0.785, 1.431, 0.916},
      {1.899, 2.131, 1.123, 1.290, 1.580, 1.094, 1.760, 1.124, 0.122, 0.775, 1.693, 1.448, 1.467, 0.928},
      {2.361, 2.728, 1.370, 1.386, 0.486, 1.444, 0.000, 0.888, 1.562, 0.405, 1.692, 6.280, 1.476, 0.924}}};
