@@ -190,3 +190,36 @@ def test_more_panels_than_one_grid_of_the_builder_holds():
         vf = g.standard_normal((1, 2)).astype(np.float32)
         assert_f32_close(d.matvec(vf), vf.astype(np.float64) @ A, vf)
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("blocks", [63, 1024, 1025, 2049])
+def test_beginnings_of_panels(blocks):
+    """More panels than begin_kernel has threads, and one more or less: sizes, and the products of a matrix whose first blocks hold segments
+    that are cut (extra slots) and whose others are short."""
+    g = np.random.default_rng(601)
+    rows, k = 300, 3
+    A = g.integers(-1, 2, size=(rows, blocks * k)).astype(np.int8)
+    A[:, :2 * k] = g.integers(0, 2, size=(1, 2 * k))  # segments of 300 rows
+    print(f"{blocks} panels of {rows} rows, k={k}", flush=True)
+    with DeviceIndex(A, k) as d:
+        seen = [((A.reshape(rows, blocks, k) == part) * np.array([4, 2, 1])).sum(axis=2) for part in (1, -1)]
+        assert d.info.stored_rows == sum(int((x != 0).sum()) for x in seen)
+        assert d.info.segments == sum(len(np.unique((x + 8 * np.arange(blocks))[x != 0])) for x in seen)
+        for batch in (1, 3):
+            v8 = g.integers(-128, 128, size=(batch, rows), dtype=np.int8)
+            assert np.array_equal(d.matvec(v8).astype(np.int64), dense.matvec_i8(A, v8)), batch
+
+
+@pytest.mark.parametrize("rows", [700, 5000])  # slots that are cleared, absent values that are stored
+@pytest.mark.parametrize("k", [11, 12, 13])    # eight and sixteen steps of a fold, and panels of half a block
+@pytest.mark.parametrize("cols", [13, 300])
+def test_folds_of_two_int8_vectors(rows, k, cols):
+    g = np.random.default_rng(602)
+    A = g.integers(0, 2, size=(rows, cols)).astype(np.int8)
+    print(f"two int8 vectors, binary {rows}x{cols} k={k}", flush=True)
+    with DeviceIndex(A, k) as d:
+        v8 = g.integers(-128, 128, size=(8, rows), dtype=np.int8)
+        v8[0] = -128
+        want = dense.matvec_i8(A, v8)
+        for batch in (2, 3, 8, 8):
+            assert np.array_equal(d.matvec(v8[:batch]).astype(np.int64), want[:batch]), batch
