@@ -233,17 +233,19 @@ inline const Pass& pass_of(bool i8, Mode m) {
 // than eight block ranges some XCDs stay idle), and how long a round takes: the start and the rows staged, and then the longest of what
 // keeps the compute unit busy, of a wavefront's units and a fold one after the other, and of the panels that wait for room, where
 // there are more than fit (the root of the sum of the squares: none hides the others entirely).  In microseconds.  Float: fitted to the times
-// of all three passes of 3222 matrices of 1024 to 32768 rows with k from 8 to 13 and 2 to 16 vectors, and 290 of 16 to 32768 rows with k from 3 to
-// 16 and 2 to 300 vectors.  On average the choice is 0.4 % slower than the best of the three on the former and 0.3 % on the latter, one product in
-// 35 more than 5 % (with the constants fitted to the kernels whose staging requested four pieces per thread and vector whatever the row count: 1.1 and
-// 0.2 %, one in eleven).  int8: fitted earlier, to 2227 matrices of both kinds; 0.8 and 0.4 % (fitting them again gained nothing).  The
-// rule before (rounds of units of the whole device, and a count of the units that have room; fitted to 170 matrices of the first kind and
-// up to sixteen vectors): 1.2 and 1.5 %,
+// of all three passes of 3222 products with 1024 to 32768 rows, k from 8 to 13 and 2 to 16 vectors, and 290 with 16 to 32768 rows, k from 3 to
+// 16 and 2 to 300 vectors.  On 6535 of the former kind and 421 of the latter that nothing was fitted to, the choice is 0.24 and 0.21 % slower than the best of
+// the three on average, one in 60 more than 5 % (with the constants before, fitted to kernels whose staging requested four pieces per thread and vector
+// whatever the row count: 1.0 and 0.3 %, one in thirteen).  int8: fitted earlier, to 2227 products of both kinds; on 9943 and 661 others 0.7 %, one in 18 more than 5 %.
+// `odd` for int8 was fitted by itself to 7245 products with rows that are no multiple of four, as a part of what it was when such rows were staged byte by byte (0.862,
+// 1.290, 1.386): a quarter to a half does best on either half of them, and on the other half takes the choice from 0.71 to 0.59 % off the best
+// (ternary 9645 x 9664, k = 10, seven vectors: 21.4 us with two per pass, 17.7 with four).  The rule before (rounds of units of the whole device, and a count
+// of the units that have room; fitted to 170 products of the first kind): 1.2 and 1.5 %,
 // and up to twice the time (ternary 16867 x 47, k = 8, 64 float vectors: 20.0 us with one per pass, 10.4 with two; binary 4868 x 19245,
 // k = 11, eleven: 41 and 27).
 struct PassCosts {
   double once, round;         // of a launch, of a round of workgroups
-  double stage, odd;          // per 64 KB staged, and on top where the rows are no multiple of four (narrow loads)
+  double stage, odd;          // per 64 KB staged, and on top where the rows are no multiple of four (a load and a wait more behind the last piece)
   double share;               // staging per further workgroup on the compute unit
   double unit, second;        // latency of a unit of 48 positions; on top for a wavefront with more than one
   double sum, positions;      // the compute unit busy with 16 units, and with their positions
@@ -255,9 +257,9 @@ constexpr PassCosts kCosts[2][3] = {  // [int8][one, two, four vectors]
     {{0.766, 2.774, 0.694, 0.158, 0.352, 0.727, 1.507, 1.253, 0.000, 0.097, 0.364, 1.036, 2.005, 0.860},
      {1.577, 2.220, 0.613, 0.225, 1.018, 0.455, 1.729, 0.991, 0.650, 0.597, 0.781, 2.085, 1.909, 0.776},
      {1.062, 3.340, 1.171, 0.477, 0.663, 0.239, 2.039, 0.569, 2.469, 1.300, 1.357, 6.309, 1.828, 0.842}},
-    {{1.896, 1.799, 1.295, 0.862, 0.750, 1.035, 1.730, 1.048, 0.039, 0.508, 0.928, 0.785, 1.431, 0.916},
-     {1.899, 2.131, 1.123, 1.290, 1.580, 1.094, 1.760, 1.124, 0.122, 0.775, 1.693, 1.448, 1.467, 0.928},
-     {2.361, 2.728, 1.370, 1.386, 0.486, 1.444, 0.000, 0.888, 1.562, 0.405, 1.692, 6.280, 1.476, 0.924}}};
+    {{1.896, 1.799, 1.295, 0.215, 0.750, 1.035, 1.730, 1.048, 0.039, 0.508, 0.928, 0.785, 1.431, 0.916},
+     {1.899, 2.131, 1.123, 0.323, 1.580, 1.094, 1.760, 1.124, 0.122, 0.775, 1.693, 1.448, 1.467, 0.928},
+     {2.361, 2.728, 1.370, 0.346, 0.486, 1.444, 0.000, 0.888, 1.562, 0.405, 1.692, 6.280, 1.476, 0.924}}};
 // Estimated microseconds of a launch on `cus` compute units, 1e30 if there is none.
 inline double pass_time(bool i8, Mode m, const PlanMatrix& h, const PlanTile& T, int batch, int cus, int max_wg_per_cu) {
   const Pass& M = pass_of(i8, m);

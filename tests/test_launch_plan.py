@@ -136,3 +136,21 @@ def test_the_pass_that_was_measured_to_be_shortest(shim, rows, cols, k, parts, u
     assert shim.shim_product(ctypes.byref(r), CUS, LDS, ctypes.byref(a)) == 0
     check(a, (rows, cols, k))
     assert a.vectors == vectors
+
+
+@pytest.mark.parametrize("rows,cols,k,parts,units,stream,batch,vectors", [
+    (9645, 9664, 10, 2, 8821, 45894400, 7, 4),    # 21.4 us with two vectors per pass, 17.7 with four
+    (8754, 5219, 9, 2, 5043, 24705024, 12, 4),    # 19.0 and 16.1
+    (12358, 7360, 10, 2, 9489, 43555072, 7, 4),   # 20.7 and 17.7
+    (2558, 2560, 10, 2, 993, 4136448, 12, 4),     # 9.1 and 7.8
+    (2559, 2560, 11, 2, 700, 3267072, 7, 2),      # 8.5 with one, 7.2 with two
+    (3133, 8872, 9, 2, 3944, 18285568, 2, 2),     # 8.8 and 7.6
+    (4537, 1472, 9, 1, 451, 1890048, 11, 2),      # 7.3 and 6.3
+    (5374, 1624, 10, 1, 514, 2267648, 2, 1),      # 4.6 with one, 5.3 with two
+])
+def test_int8_rows_that_are_no_multiple_of_four(shim, rows, cols, k, parts, units, stream, batch, vectors):
+    """Such rows are staged as wide as others: they do not make several vectors per pass dear."""
+    r, a = Request(rows, cols, units, k, parts, 0, 64, batch, 1, stream), Answer()
+    assert shim.shim_product(ctypes.byref(r), CUS, LDS, ctypes.byref(a)) == 0
+    check(a, (rows, cols, k))
+    assert a.vectors == vectors
