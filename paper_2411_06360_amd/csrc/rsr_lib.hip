@@ -707,7 +707,7 @@ struct Staging {
 
 // The work of one workgroup: `wg` is its number among the workgroups of this product (a launch may
 // carry several products, see rsr_multi_kernel).  The workgroup may have more wavefronts than the
-// product has use for (p.waves): the others help to stage the activations and take no units.
+// product has use for (Start::waves): the others help to stage the activations and take no units.
 // PLAIN selects step 2 of Algorithm 2 as printed there (the product u . Bin_[k] term by term,
 // O(k 2^k)) instead of the RSR++ fold of Algorithm 3: kept for the comparison of Appendix F.2.
 template <class M, bool PLAIN>
@@ -720,13 +720,13 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool worker = wave < (int)(st.shape & 0xffu);
-  const int threads = (int)(st.shape >> 8 & 0xffu) * 64, rows = (int)(st.rows_stride & 0xffffu), vstride = (int)(st.rows_stride >> 16);
+  const bool worker = wave < (int)st.waves();
+  const int threads = st.threads(), rows = st.rows(), vstride = st.vstride();
 
-  const rsr::Share mine = rsr::share_of(st.sets_more & 0xffffu, st.sets_magic, st.row0_g1 >> 16, st.share, st.sets_more >> 16, (uint32_t)wg);
+  const rsr::Share mine = rsr::share_of(st, (uint32_t)wg);
   if (mine.first == mine.last) return;
   const int b = (int)mine.set * V, blk_begin = (int)mine.first, blk_end = (int)mine.last;
-  const int nv = min(V, (int)(st.shape >> 16) - b);
+  const int nv = min(V, st.batch() - b);
   const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
 
   // Two register buffers: while one unit is summed from one, the next unit's stream arrives in the
@@ -760,7 +760,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   // arguments are asked for together, with the block offsets.  (Stamps of ternary 4096^2, one float vector, before: 0.9 us until the
   // activations were requested, in four waits for arguments, and the staging waited behind the first stream loads.  5.25 us a product then,
   // 4.74 so; binary 1024^2, int8: 4.04 and 3.54; a transformer block 26.6 and 24.3.)
-  const typename M::In* __restrict__ v = vin + (int64_t)b * vstride + (st.row0_g1 & 0xffffu);
+  const typename M::In* __restrict__ v = vin + (int64_t)b * vstride + st.row0();
   using Stage = Staging<M>;
   const int pieces = rows / Stage::kRows;
   Stage staged;
@@ -780,7 +780,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
       *reinterpret_cast<uint4*>(lds + p.off_u + i) = make_uint4(0, 0, 0, 0);
   // the counters of records and buffers, and behind them the one that hands out units
   const uint32_t counters = (p.off_ctr - p.off_done) / 4;
-  if ((uint32_t)tid <= counters) reinterpret_cast<uint32_t*>(lds + p.off_done)[tid] = (uint32_t)tid == counters ? st.shape & 0xffu : 0u;
+  if ((uint32_t)tid <= counters) reinterpret_cast<uint32_t*>(lds + p.off_done)[tid] = (uint32_t)tid == counters ? st.waves() : 0u;
   if (tid < (1 << M::shift) / 4) reinterpret_cast<uint32_t*>(lds + ((size_t)rows << M::shift))[tid] = 0;  // the null row
   if (ix >= n_tot) D.npos = 0;  // (its loads then fall outside the buffer descriptor and read nothing)
   const __amdgpu_buffer_rsrc_t rs0 = unit_rsrc(D.stream_off, D.npos);
@@ -1241,7 +1241,7 @@ __global__ void __launch_bounds__(1024) rsr_multi_kernel(const uint32_t b1, cons
 // ---------------------------------------------------------------------------------------------
 template <class M, bool PLAIN>
 int enqueue(const DeviceTile& T, const LaunchPlan& plan, const typename M::In* v, void* out, void* stream) {
-  const rsr::Start st = rsr::start_of(plan.p);
+  const rsr::Start st = rsr::start_of(plan, plan.waves);
   hipLaunchKernelGGL((rsr_matvec_kernel<M, PLAIN>), dim3((unsigned)plan.grid), dim3((unsigned)(plan.waves * 64)), plan.lds,
                      static_cast<hipStream_t>(stream), static_cast<const unsigned char*>(T.d_stream), static_cast<const uint32_t*>(T.d_units),
                      static_cast<const uint32_t*>(T.d_blk_unit), v, st.sets_more, st.sets_magic, st.share, st.rows_stride, st.row0_g1, st.shape,
@@ -1300,8 +1300,7 @@ int enqueue_multi(const rsr_job* jobs, int njobs, const LaunchPlan* plans, void*
     J.blk_unit = static_cast<const uint32_t*>(T.d_blk_unit);
     J.vin = jobs[j].v;
     J.more = {static_cast<const uint16_t*>(T.d_extras), jobs[j].out, plans[j].p};
-    J.more.p.threads = waves * 64;
-    J.start = rsr::start_of(J.more.p);
+    J.start = rsr::start_of(plans[j], waves);
     begin[j] = J.wg_begin = (uint32_t)grid;
     grid += plans[j].grid;  // (a multiple of 8: every product starts on the first XCD of the round-robin)
     lds = std::max(lds, plans[j].lds);

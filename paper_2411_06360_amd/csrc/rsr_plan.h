@@ -56,24 +56,38 @@ struct KArgs {
   // Slots have to be cleared ahead of the first panels.  Where every panel stores all its values (`fill`) only slots that are no
   // value's are: those of panels of fewer values than a step of the fold reads.  (The slot of value 0 is not stored, but counts under no bit.)
   int clear;
-  int rows, cols, k, nblocks, last_width, batch;
-  int vstride;   // elements between the activation vectors of consecutive batch lanes (the matrix's row count)
-  int row0;      // first row of this row tile
+  int cols, k, nblocks, last_width;
   int accumulate;  // add to `out` instead of overwriting it (second and later row tiles, rsr_matvec_acc)
   int scaled;      // multiply the product by `scale` first (rsr_matvec_acc)
   uint32_t scale;  // bits of a float (float activations) or of an int (int8 activations)
-  int kc, both, pslots;  // panels of a block (rsr_layout.h)
+  int kc, both, pslots;  // of a panel (rsr_layout.h)
   int fill;              // absent values are stored as zeros
   // a part's weight: 1 << (part * wshift + wfirst), negative for part `wneg` (-1: none)
   int wshift, wfirst, wneg;
-  int g1;        // workgroups per set of vectors
-  int sets;      // sets of vectors
-  uint32_t sets_magic;       // x / sets as the high half of a product
-  uint32_t share, share_more;  // column blocks of a workgroup; so many workgroups have one more
-  int waves;     // wavefronts that take units
-  int threads;   // of a workgroup (a launch of several products: of its largest)
   int nrec;      // blocks whose panel records are kept (panels > 1)
 };
+
+// What a workgroup needs to know before it can ask for anything: its share of the blocks, and where its activations are.  Six words, which
+// go ahead of the other arguments with four pointers: the fourteen words that a wavefront finds in its scalar registers when it
+// starts (rsr_lib.hip).
+struct Start {
+  uint32_t sets_more;   // sets of vectors | share_more << 16
+  uint32_t sets_magic;  // x / sets as the high half of a product
+  uint32_t share;       // column blocks of a workgroup; the first share_more workgroups have one more
+  uint32_t rows_stride; // rows | vstride << 16 (elements between consecutive vectors: the matrix's row count)
+  uint32_t row0_g1;     // first row of the row tile | g1 << 16 (workgroups per set of vectors)
+  uint32_t shape;       // wavefronts that take units | wavefronts of the workgroup << 8 | vectors << 16
+  constexpr uint32_t sets() const { return sets_more & 0xffffu; }
+  constexpr uint32_t share_more() const { return sets_more >> 16; }
+  constexpr int rows() const { return (int)(rows_stride & 0xffffu); }
+  constexpr int vstride() const { return (int)(rows_stride >> 16); }
+  constexpr uint32_t row0() const { return row0_g1 & 0xffffu; }
+  constexpr uint32_t g1() const { return row0_g1 >> 16; }
+  constexpr uint32_t waves() const { return shape & 0xffu; }
+  constexpr int threads() const { return (int)(shape >> 8 & 0xffu) * 64; }
+  constexpr int batch() const { return (int)(shape >> 16); }
+};
+static_assert(kTileRows < 65536 && kMaxRows < 65536, "rows and strides fit 16 bits");
 
 // A workgroup's set of vectors and column blocks.  The siblings of a block range, one per set, sit 8 workgroup ids apart so that
 // round-robin dispatch puts them on the same XCD (shared L2).  Without a division: in the kernel three of them (two in 64 bits) took 0.2 to
@@ -82,41 +96,25 @@ struct KArgs {
 struct Share {
   uint32_t set, first, last;  // blocks first .. last - 1
 };
-constexpr Share share_of(uint32_t sets, uint32_t sets_magic, uint32_t g1, uint32_t share, uint32_t share_more, uint32_t wg) {
-  const uint32_t eights = wg >> 3;
-  const uint32_t grp = sets == 1 ? eights : (uint32_t)(((uint64_t)eights * sets_magic) >> 32);
+constexpr Share share_of(const Start& st, uint32_t wg) {
+  const uint32_t sets = st.sets(), more = st.share_more(), eights = wg >> 3;
+  const uint32_t grp = sets == 1 ? eights : (uint32_t)(((uint64_t)eights * st.sets_magic) >> 32);
   const uint32_t g = grp * 8 + (wg & 7);
   Share s{eights - grp * sets, 0, 0};
-  if (g < g1) {
-    s.first = g * share + (g < share_more ? g : share_more);
-    s.last = s.first + share + (g < share_more ? 1u : 0u);
+  if (g < st.g1()) {
+    s.first = g * st.share + (g < more ? g : more);
+    s.last = s.first + st.share + (g < more ? 1u : 0u);
   }
   return s;
-}
-constexpr Share share_of(const KArgs& p, uint32_t wg) {
-  return share_of((uint32_t)p.sets, p.sets_magic, (uint32_t)p.g1, p.share, p.share_more, wg);
-}
-
-// What a workgroup needs to know before it can ask for anything: its share of the blocks, and where its activations are.  Six words, which
-// go ahead of the other arguments with four pointers: the fourteen words that a wavefront finds in its scalar registers when it
-// starts (rsr_lib.hip).
-struct Start {
-  uint32_t sets_more;   // sets | share_more << 16
-  uint32_t sets_magic, share;
-  uint32_t rows_stride; // rows | vstride << 16
-  uint32_t row0_g1;     // row0 | g1 << 16
-  uint32_t shape;       // waves | wavefronts of the workgroup << 8 | batch << 16
-};
-static_assert(kTileRows < 65536 && kMaxRows < 65536, "rows and strides fit 16 bits");
-inline Start start_of(const KArgs& p) {
-  return {(uint32_t)p.sets | p.share_more << 16, p.sets_magic, p.share, (uint32_t)p.rows | (uint32_t)p.vstride << 16,
-          (uint32_t)p.row0 | (uint32_t)p.g1 << 16, (uint32_t)p.waves | (uint32_t)(p.threads / 64) << 8 | (uint32_t)p.batch << 16};
 }
 
 struct LaunchPlan {
   KArgs p;
+  int rows = 0, vstride = 0, row0 = 0, batch = 0;
+  int sets = 0, g1 = 0;  // sets of vectors, workgroups for each
+  uint32_t share = 0, share_more = 0;
   int64_t grid = 0;
-  int waves = 0;
+  int waves = 0;  // wavefronts that take units; of the workgroup, too, unless it shares the launch with larger ones
   size_t lds = 0;
 };
 
@@ -140,9 +138,8 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
   KArgs& p = plan->p;
   std::memset(&p, 0, sizeof(p));
   const Shape& S = T.shape;
-  p.rows = (int)T.rows; p.cols = (int)h.cols; p.k = h.k;
-  p.nblocks = (int)h.nblocks; p.last_width = h.last_width; p.batch = batch;
-  p.vstride = (int)h.rows; p.row0 = (int)T.row0; p.accumulate = accumulate ? 1 : 0;
+  p.cols = (int)h.cols; p.k = h.k;
+  p.nblocks = (int)h.nblocks; p.last_width = h.last_width; p.accumulate = accumulate ? 1 : 0;
   p.kc = S.kc; p.both = S.both; p.pslots = S.pslots; p.panels = S.panels;
   p.fill = T.fill ? 1 : 0; p.extra_stride = T.extra_stride;
   p.clear = !T.fill || (1 << S.kc) < kFoldRow;
@@ -201,16 +198,15 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
     // 256 * wg workgroups of n wavefronts at this register count, n = 1 .. 16; ternary 2902 x 6720, k = 9: 9.4 -> 6.7 us)
     if (wg == 1 || (wg * waves <= 16 && !(wg == 3 && waves == 5) && groups_in_lds(total(nbuf), h.lds_max) >= wg)) break;
   }
-  p.g1 = (int)g1;
-  p.sets = (int)sets; p.sets_magic = magic((uint32_t)sets);
-  p.share = (uint32_t)(h.nblocks / g1); p.share_more = (uint32_t)(h.nblocks % g1);
   const int64_t grid = (g1 + 7) / 8 * 8 * sets;
-  if (grid > 0x7fffffff) return RSR_ERR_INVALID_ARGUMENT;
+  if (grid > 0x7fffffff || batch > 65535 || g1 > 65535) return RSR_ERR_INVALID_ARGUMENT;  // (16 bits each in a Start)
 
-  plan->lds = total(nbuf);
+  plan->rows = (int)T.rows; plan->vstride = (int)h.rows; plan->row0 = (int)T.row0; plan->batch = batch;
+  plan->sets = (int)sets; plan->g1 = (int)g1;
+  plan->share = (uint32_t)(h.nblocks / g1); plan->share_more = (uint32_t)(h.nblocks % g1);
   plan->grid = grid;
   plan->waves = waves;
-  p.waves = waves; p.threads = waves * 64;
+  plan->lds = total(nbuf);
   p.nbuf = nbuf; p.buf_magic = magic((uint32_t)nbuf);
   p.nrec = recs(nbuf); p.rec_magic = magic((uint32_t)p.nrec);
   p.off_u = (uint32_t)vbytes;
@@ -221,6 +217,12 @@ inline int plan_tile(const Pass& M, const PlanMatrix& h, const PlanTile& T, bool
   p.off_epoch = p.off_cnt + (uint32_t)nbuf * 4;
   p.off_ctr = p.off_epoch + (uint32_t)nbuf * 4;
   return RSR_OK;
+}
+
+// The words of a planned launch whose workgroups have so many wavefronts.
+inline Start start_of(const LaunchPlan& p, int waves) {
+  return {(uint32_t)p.sets | p.share_more << 16, magic((uint32_t)p.sets), p.share, (uint32_t)p.rows | (uint32_t)p.vstride << 16,
+          (uint32_t)p.row0 | (uint32_t)p.g1 << 16, (uint32_t)p.waves | (uint32_t)waves << 8 | (uint32_t)p.batch << 16};
 }
 
 // ---- how many vectors share a pass ----
@@ -267,10 +269,10 @@ inline double pass_time(bool i8, Mode m, const PlanMatrix& h, const PlanTile& T,
   LaunchPlan plan;
   if (plan_tile(M, h, T, false, batch, cus, max_wg_per_cu, &plan) != RSR_OK) return 1e30;
   const KArgs& p = plan.p;
-  const double on_xcd = std::max(1.0, cus / 8.0), groups = (double)((p.g1 + 7) / 8) * p.sets;
+  const double on_xcd = std::max(1.0, cus / 8.0), groups = (double)((plan.g1 + 7) / 8) * plan.sets;
   const double fit = std::max(1.0, std::min(plan.waves == 5 ? 2.0 : (double)(16 / plan.waves), (double)groups_in_lds(plan.lds, h.lds_max)));
   const double rounds = std::max(1.0, std::ceil(groups / (on_xcd * fit))), together = std::min(fit, std::ceil(groups / on_xcd));
-  const double blocks = (double)((h.nblocks + p.g1 - 1) / p.g1);  // of the largest share
+  const double blocks = (double)((h.nblocks + plan.g1 - 1) / plan.g1);  // of the largest share
   const double units = blocks * (double)T.nunits / (double)h.nblocks, per_wave = units / plan.waves;
   const double panels = blocks * T.shape.panels, slots = T.shape.nslots / 2048.0;
   const double positions = (double)T.stream_bytes / (48.0 * kPositionBytes * (double)std::max<int64_t>(1, T.nunits));

@@ -29,7 +29,7 @@ PlanTile tile_of(const Request& r, const PlanMatrix& h) {
   return t;
 }
 void answer(const LaunchPlan& p, const Pass& pass, Answer* a) {
-  *a = Answer{p.grid, (int64_t)p.lds, pass.V, p.waves, p.p.nbuf, p.p.g1, (int64_t)p.p.off_ctr + 4};
+  *a = Answer{p.grid, (int64_t)p.lds, pass.V, p.waves, p.p.nbuf, p.g1, (int64_t)p.p.off_ctr + 4};
 }
 }  // namespace
 

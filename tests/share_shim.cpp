@@ -15,8 +15,9 @@ int64_t shim_shares(int64_t rows, int64_t nblocks, int batch, int vectors, int n
   t.max_units_per_block = (uint32_t)units_per_block; t.nunits = nblocks * units_per_block;
   LaunchPlan p;
   if (plan_tile(vectors == 4 ? kF4 : vectors == 2 ? kF2 : kF1, h, t, false, batch, num_cu, max_wg_per_cu, &p) != RSR_OK || p.grid > room) return -1;
+  const Start start = start_of(p, p.waves);
   for (int64_t wg = 0; wg < p.grid; ++wg) {
-    const Share s = share_of(p.p, (uint32_t)wg);
+    const Share s = share_of(start, (uint32_t)wg);
     out[3 * wg] = s.set; out[3 * wg + 1] = s.first; out[3 * wg + 2] = s.last;
   }
   return p.grid;

@@ -33,3 +33,12 @@ def test_words_of_a_launch(shim, rows, all_rows, row0, batch, blocks):
                 launched += 1
                 assert rc == 0 and list(planned) == list(unpacked), (vectors, cus, threads)
     assert launched
+
+
+def test_more_than_the_words_hold_is_refused(shim):
+    """Vectors and workgroups have 16 bits each."""
+    planned, unpacked = (ctypes.c_int64 * 9)(), (ctypes.c_int64 * 9)()
+    assert shim(1024, 1024, 0, 40, 8, 65535, 1, 256, 0, planned, unpacked) == 0
+    for vectors in (1, 2, 4):
+        assert shim(1024, 1024, 0, 40, 8, 65536, vectors, 256, 0, planned, unpacked) < 0
+    assert shim(1024, 1024, 0, 3000000, 8, 1, 1, 100000, 0, planned, unpacked) < 0
