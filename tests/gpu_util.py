@@ -68,3 +68,30 @@ def batch_per_pass(planner, info, i8: bool, max_extras: int = 0) -> dict:
         found.setdefault(vectors_per_pass(planner, info, batch, i8, max_extras), batch)
     assert set(found) == {1, 2, 4}, (found, info.rows, info.cols, info.k, info.work_units)
     return found
+
+
+def batches_per_pass(planner, info, i8: bool, passes, max_extras: int = 0, shared: bool = False) -> dict:
+    """{(vectors per pass, vectors of the last set if it is not full, otherwise 0): the smallest such batch}, all of them for every one of `passes`."""
+    want = {(v, left) for v in passes for left in range(v)}
+    found = {}
+    for batch in range(1, 1200):
+        v = vectors_per_pass(planner, info, batch, i8, max_extras, shared)
+        found.setdefault((v, batch % v), batch)
+        if want <= set(found):
+            break
+    assert want <= set(found), (found, info.rows, info.cols, info.k, info.work_units)
+    return {key: found[key] for key in sorted(want)}
+
+
+def extra_slots(planner, A: np.ndarray, k: int) -> int:
+    """Further pieces (of 256 rows) of the segments of a panel, at most."""
+    parts = [A == 1] + ([A == -1] if (A < 0).any() else [])
+    panels = planner.shim_panels(A.shape[0], k, len(parts), 0)  # of a block: all values of both parts, or windows of one part's values
+    together, windows = (len(parts), 1) if panels == 1 else (1, panels // len(parts))
+    most = 0
+    for c in range(0, A.shape[1], k):
+        values = [P[:, c:c + k].astype(np.int64) @ (1 << np.arange(k - 1, -1, -1))[: P[:, c:c + k].shape[1]] for P in parts]
+        pieces = np.array([np.maximum(0, -(-np.bincount(x, minlength=1 << k) // 256) - 1) for x in values])
+        pieces[:, 0] = 0  # (value 0 is not stored)
+        most = max(most, int(pieces.reshape(len(parts) // together, together, windows, -1).sum(axis=(1, 3)).max()))
+    return most

@@ -28,9 +28,12 @@ def build(folder):
     return lib
 
 
-def vectors_per_pass(lib, info, batch, i8, max_extras=0):
-    """How many vectors share a pass in a product of a built index (rsr_info)."""
+def vectors_per_pass(lib, info, batch, i8, max_extras=0, shared=False):
+    """How many vectors share a pass in a product of a built index (rsr_info); shared: from rsr_matvec_multi with this product alone."""
     r = Request(info.rows, info.cols, info.work_units, info.k, info.parts, 0, max_extras, batch, int(i8), info.index_bytes + info.segment_bytes)
     a = Answer()
-    assert lib.shim_product(ctypes.byref(r), info.compute_units, LDS, ctypes.byref(a)) == 0
+    if shared:
+        assert lib.shim_shared(ctypes.byref(r), 1, info.compute_units, LDS, ctypes.byref(a)) == 0
+    else:
+        assert lib.shim_product(ctypes.byref(r), info.compute_units, LDS, ctypes.byref(a)) == 0
     return a.vectors

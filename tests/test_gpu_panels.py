@@ -8,7 +8,7 @@ import pytest
 
 import paper_2411_06360_amd as R
 from oracle import dense, steps
-from tests.gpu_util import DeviceIndex, assert_f32_close, batch_per_pass
+from tests.gpu_util import DeviceIndex, assert_f32_close, batch_per_pass, batches_per_pass, extra_slots
 from tests.launch_plan import build
 
 pytestmark = pytest.mark.gpu
@@ -210,16 +210,30 @@ def test_beginnings_of_panels(blocks):
             assert np.array_equal(d.matvec(v8).astype(np.int64), dense.matvec_i8(A, v8)), batch
 
 
-@pytest.mark.parametrize("rows", [700, 5000])  # slots that are cleared, absent values that are stored
-@pytest.mark.parametrize("k", [11, 12, 13])    # eight and sixteen steps of a fold, and panels of half a block
-@pytest.mark.parametrize("cols", [13, 300])
-def test_folds_of_two_int8_vectors(rows, k, cols):
+@pytest.mark.parametrize("kind,rows,k,steps,fill", [
+    ("binary", 700, 11, 8, False), ("binary", 5000, 11, 8, True),
+    ("binary", 5000, 12, 16, False), ("binary", 9000, 12, 16, True),
+    ("binary", 5000, 13, 16, False), ("binary", 17000, 13, 16, True),  # panels of half a block
+    ("ternary", 5000, 12, 16, False),                                  # panels of one part
+])
+@pytest.mark.parametrize("cut", [False, True])
+def test_folds_of_two_int8_vectors(planner, kind, rows, k, steps, fill, cut):
+    """Panels of one part in passes over two int8 vectors: eight and sixteen steps of a fold, slots that are cleared and absent values that are
+    stored, with and without segments that are cut."""
     g = np.random.default_rng(602)
-    A = g.integers(0, 2, size=(rows, cols)).astype(np.int8)
-    print(f"two int8 vectors, binary {rows}x{cols} k={k}", flush=True)
-    with DeviceIndex(A, k) as d:
-        v8 = g.integers(-128, 128, size=(8, rows), dtype=np.int8)
-        v8[0] = -128
-        want = dense.matvec_i8(A, v8)
-        for batch in (2, 3, 8, 8):
-            assert np.array_equal(d.matvec(v8[:batch]).astype(np.int64), want[:batch]), batch
+    B = (g.integers(0, 2, size=(rows, 3 * k)) if kind == "binary" else g.integers(-1, 2, size=(rows, 3 * k))).astype(np.int8)
+    if cut:
+        B[g.permutation(rows)[:600]] = np.tile(np.array([[1, 0, 1]], np.int8), k)
+    times = 80
+    tiled = lambda x: np.tile(x, (1, times))[:, :-2]  # (a narrow last block)
+    extras = extra_slots(planner, B, k)
+    assert (extras > 0) == cut and fill == (rows >= 2 << k)
+    print(f"two int8 vectors, {kind} {rows} rows, k={k}, {extras} extra slots", flush=True)
+    with DeviceIndex(tiled(B), k) as d:
+        assert 1 << d.info.lo_bits == 256 * steps
+        for batch in batches_per_pass(planner, d.info, True, (2,), extras).values():
+            v8 = g.integers(-128, 128, size=(batch, rows), dtype=np.int8)
+            v8[0], v8[-1] = -128, 127
+            want = tiled(dense.matvec_i8(B, v8))
+            for _ in range(2):
+                assert np.array_equal(d.matvec(v8).astype(np.int64), want), batch

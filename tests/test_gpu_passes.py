@@ -5,7 +5,8 @@ import pytest
 
 import paper_2411_06360_amd as R
 from oracle import dense
-from tests.gpu_util import DeviceIndex, assert_f32_close
+from tests.gpu_util import DeviceIndex, assert_f32_close, batches_per_pass, extra_slots
+from tests.launch_plan import build
 
 pytestmark = pytest.mark.gpu
 
@@ -104,33 +105,47 @@ def test_shared_launches_with_several_vectors(shapes, batches):
             R.rsr_destroy(h)
 
 
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    return build(str(tmp_path_factory.mktemp("plan")))
+
+
 @pytest.mark.parametrize("rows", [1, 3, 4, 5, 15, 16, 17, 1023, 4097, 5003, 9001, 16384])
-def test_activations_at_any_address(rows):
-    """Staging: the last piece and the rows behind it, vectors that begin at every remainder of 16 bytes (an odd number of int8
-    rows, base pointers off by an element), sets that are not full, from single and shared launches."""
+def test_activations_at_any_address(planner, rows):
+    """Staging in every pass: the last piece and the rows behind it, vectors that begin at every remainder of 16 bytes (an odd number of
+    int8 rows, base pointers off by an element), sets of every number of vectors, from single and shared launches."""
     import torch
 
     g = np.random.default_rng(405)
-    A = g.integers(-1, 2, size=(rows, 90)).astype(np.int8)
-    print(f"activations at any address, {rows} rows", flush=True)
-    h = R.rsr_preprocess(A, 6)
+    k, times = 6, 130
+    A = g.integers(-1, 2, size=(rows, 3 * k)).astype(np.int8)
+    A[0] = 1  # (at least one entry of each kind)
+    A[rows - 1, ::2] = -1
+    tiled = lambda x: np.tile(x, (1, times))
+    h = R.rsr_preprocess(tiled(A), k)
     try:
-        for batch in (1, 2, 3, 5, 140):
-            for off in (0, 1, 2, 3):
-                vf = g.standard_normal((batch, rows)).astype(np.float32)
-                v8 = g.integers(-128, 128, size=(batch, rows), dtype=np.int8)
-                for v, dtype, one, many, exact in ((vf, torch.float32, R.rsr_matvec, R.rsr_matvec_multi, dense.matvec_f32),
-                                                   (v8, torch.int32, R.rsr_matvec_i8, R.rsr_matvec_multi_i8, dense.matvec_i8)):
+        info, extras = R.rsr_info(h), extra_slots(planner, A, k)
+        for i8, dtype, one, many, exact in ((False, torch.float32, R.rsr_matvec, R.rsr_matvec_multi, dense.matvec_f32),
+                                            (True, torch.int32, R.rsr_matvec_i8, R.rsr_matvec_multi_i8, dense.matvec_i8)):
+            passes = (1, 2) if not i8 and rows > 9001 else (1, 2, 4)  # (rows of four floats do not fit in LDS beyond)
+            batches = set()
+            for shared in (False, True):
+                batches |= set(batches_per_pass(planner, info, i8, passes, extras, shared).values())
+            print(f"activations at any address, {rows} rows, {'int8' if i8 else 'float'}, batches {sorted(batches)}", flush=True)
+            for batch in sorted(batches):
+                v = g.integers(-128, 128, size=(batch, rows), dtype=np.int8) if i8 else g.standard_normal((batch, rows)).astype(np.float32)
+                want = tiled(exact(A, v))
+                for off in (0, 1, 2, 3):
                     room = torch.full((off + v.size,), 77, dtype=torch.from_numpy(v).dtype, device="cuda")  # (it ends with the vectors)
                     room[off:] = torch.from_numpy(v.ravel()).cuda()
                     x = room[off:]
-                    out = torch.full((2, batch, 90), -7, dtype=dtype, device="cuda")
+                    out = torch.full((2, batch, info.cols), -7, dtype=dtype, device="cuda")
                     one(h, x, out[0], batch, stream())
                     many([(h, x, out[1])], batch, stream())
                     torch.cuda.synchronize()
-                    got, want = out.cpu().numpy(), exact(A, v)
+                    got = out.cpu().numpy()
                     assert np.array_equal(got[0], got[1]), (batch, off)
-                    if dtype is torch.int32:
+                    if i8:
                         assert np.array_equal(got[0].astype(np.int64), want), (batch, off)
                     else:
                         assert_f32_close(got[0], want, v)
