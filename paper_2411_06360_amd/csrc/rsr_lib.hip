@@ -484,7 +484,7 @@ __device__ __forceinline__ Desc load_desc(TablePtr unit_words, uint32_t u) {
 // to its partner, so that they cost 8 + 4 + 2 + 1 additions instead of 16 each: over lane bits 5 and 4 with lane swaps of two values (what was one
 // value's upper half and the other's lower half change places; the sum of the two is the exchange), over bits 3 and 2 with additions that
 // write a part of the banks.  Two plain additions over bits 1 and 0 follow.  On return every lane holds the sum of v[lane >> 2].
-// Bound by the instructions of one wavefront, four clocks each: 34, and no masks.  (With an exchange inside the quads first, which takes two
+// Bound by the instructions of one wavefront, four clocks each: 32 and six waits, and no masks.  (With an exchange inside the quads first, which takes two
 // selections a pair, 65, and masks: transformer block with sixteen vectors
 // 65.7 us, 64.0 so; binary 16384^2, eight int8 vectors 30.5 and 30.0.)  In assembly: the compiler takes the two results of the swap
 // builtins for equal when they are combined as floats.  (The s_nop cover the wait states a swap and a lane exchange need after
@@ -624,7 +624,9 @@ struct Staging {
   uint32_t x[kAtOnce][M::V][kWords];
 
   // Pieces first + lane, first + lane + nt, ... of `n`; vectors from `nv` on are zeros.  Nothing is requested for a wavefront's turn that lies
-  // behind the last piece: a load of 16 bytes per lane holds the compute unit's memory pipeline for 16 clocks wherever it reads.
+  // behind the last piece: a load of 16 bytes per lane holds the compute unit's memory pipeline for 16 clocks wherever it reads.  For a vector that is
+  // not there the first one is read again: a branch ahead of every vector's load costs full sets 2 % with two float vectors (28 products; up to 7, binary
+  // 9001 x 5000, k = 12: 6.53 us and 7.03 for two) and gains sets that are not full nothing, in any pass.
   __device__ __forceinline__ void fetch(const In* __restrict__ v, int vstride, int nv, int first, int lane, int n, int nt) {
 #pragma unroll
     for (int a = 0; a < kAtOnce; ++a) {
@@ -759,7 +761,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
   // first stream loads of the other wavefronts; what names them, and the block offsets, is in registers from the start.  The other
   // arguments are asked for together, with the block offsets.  (Stamps of ternary 4096^2, one float vector, before: 0.9 us until the
   // activations were requested, in four waits for arguments, and the staging waited behind the first stream loads.  5.25 us a product then,
-  // 4.74 so; binary 1024^2, int8: 4.04 and 3.54; a transformer block 26.6 and 24.3.)
+  // 4.74 so; a transformer block 26.6 and 24.3.)
   const typename M::In* __restrict__ v = vin + (int64_t)b * vstride + st.row0();
   using Stage = Staging<M>;
   const int pieces = rows / Stage::kRows;
@@ -854,6 +856,23 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     using Slot = typename M::Slot;
     using Read = SlotRead<M>;
     const int turn = Read::turn(lane);
+    // The sums x(0) .. x(G - 1) of vector j in steps i0 .. i0 + G - 1: two steps at a time, in this order, for every G (the sums do not depend on how many
+    // vectors share a pass).
+    auto add_up = [&]<int G>(auto x, int j, int i0) {
+      if constexpr (G == 1) {  // a panel of one step
+        tot[j] += x(0);
+      } else {
+#pragma unroll
+        for (int r = 0; r < G; r += 2) {
+          const AT g = x(r) + x(r + 1);
+          hi[j][2] += x(r + 1);
+          if (G == 2 ? ((i0 >> 1) & 1) : ((r >> 1) & 1)) hi[j][3] += g;
+          if (G <= 4 ? ((i0 >> 2) & 1) : ((r >> 2) & 1)) hi[j][4] += g;
+          if ((i0 >> 3) & 1) hi[j][5] += g;
+          tot[j] += g;
+        }
+      }
+    };
     // G steps together, P of them read at a time: reads that are in flight together share the wait (behind the gathers of
     // fifteen other wavefronts the LDS answers after several hundred clocks).  The slots of the second part are read kPart
     // steps at a time (registers).
@@ -919,23 +938,8 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
         if constexpr (sizeof(Slot) == 4 * V) add_all(nullptr);
         if constexpr (P < G) asm volatile("" ::: "memory");
       }
-      // (two steps at a time, in this order, for every G: the sums do not depend on how many vectors share a pass)
 #pragma unroll
-      for (int j = 0; j < V; ++j) {
-        if constexpr (G == 1) {  // a panel of one step
-          tot[j] += x[0][j];
-        } else {
-#pragma unroll
-          for (int r = 0; r < G; r += 2) {
-            const AT g = x[r][j] + x[r + 1][j];
-            hi[j][2] += x[r + 1][j];
-            if (G == 2 ? ((i0 >> 1) & 1) : ((r >> 1) & 1)) hi[j][3] += g;
-            if (G <= 4 ? ((i0 >> 2) & 1) : ((r >> 2) & 1)) hi[j][4] += g;
-            if ((i0 >> 3) & 1) hi[j][5] += g;
-            tot[j] += g;
-          }
-        }
-      }
+      for (int j = 0; j < V; ++j) add_up.template operator()<G>([&](int r) { return x[r][j]; }, j, i0);
     };
     // (Slots of 8 bytes: two steps together, and the second part's slots one step at a time, are three waits where one does.  Ternary
     // 7388 x 5593, k = 11, two float vectors: 11.05 us so, 10.24 with four steps and their second part at once; 5215 x 1990, sixteen int8
@@ -943,8 +947,10 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
     constexpr int kTogether = PLAIN || M::slot_bytes > 8 ? 2 : V > 1 ? 4 : 8;
     // Two int8 vectors, panels of one part with several groups of four steps: a group is read while the one before is added up, in the same
     // order, so that the LDS is waited for once.  (Four waits in a panel of 4096 slots are a fifth of its fold, and panels wait for the
-    // room that it takes: binary 16384^2, eight vectors, 29.9 us without, 28.9 so.  One float vector, with two groups of eight steps: 41.0 us and
-    // 42.1 for eight, and slower where no panel takes this path, too; it keeps them.)
+    // room that it takes: binary 16384^2, eight vectors, 29.9 us without, 28.9 so.  The others keep their waits, each timed both ways.  One float
+    // vector, with two groups of eight steps: 41.0 us and 42.1 for eight, and slower where no panel takes this path, too.  Slots of 8 bytes,
+    // whose reads spill registers: two float vectors 7 to 40 % more over 18 products, four int8 21 to 79 % over 15, 14.9 us and 17.4, 14.0 and 18.7
+    // for eight at binary 9001 x 5000, k = 12.  Panels of both parts have twice the reads in flight already and were not timed.)
     constexpr bool kAhead = M::slot_bytes == 4 && V > 1;
     if (kAhead && !both && frows % 8 == 0) {
       if constexpr (kAhead) {
@@ -970,15 +976,7 @@ __device__ __forceinline__ void rsr_body(const unsigned char* __restrict__ strea
               hi[j][1] += t.high;
               x[r] = t.all;
             }
-#pragma unroll
-            for (int r = 0; r < 4; r += 2) {
-              const AT g = x[r] + x[r + 1];
-              hi[j][2] += x[r + 1];
-              if (r) hi[j][3] += g;
-              if ((i >> 2) & 1) hi[j][4] += g;
-              if ((i >> 3) & 1) hi[j][5] += g;
-              tot[j] += g;
-            }
+            add_up.template operator()<4>([&](int r) { return x[r]; }, j, i);
           }
         };
         read(even, 0);

@@ -282,7 +282,8 @@ __device__ __forceinline__ bool slot_value(const Geometry& g, uint32_t panel, ui
 
 // One workgroup per panel.  A chain of short steps on LDS counters: bound by their latency; several workgroups share a
 // compute unit.  (With the limits' costs, the classes' sums and the walk over the groups each by single lanes: 59 us at ternary
-// 4096^2, k = 10; 47 now, most of it the ranking by one wavefront and the places in the list.)
+// 4096^2, k = 10; 47 without; 39 now that offsets are fetched four at a time and a thread adds up a class, most of it the ranking by one wavefront and
+// the places in the list.)
 __global__ void __launch_bounds__(256)
 plan_kernel(Geometry g, const uint32_t* __restrict__ off, uint16_t* __restrict__ list_all, uint8_t* __restrict__ group_all,
             uint32_t* __restrict__ extra_all, PanelInfo* __restrict__ info) {
